@@ -193,6 +193,16 @@ struct TileExtra {
   // alone and scales its tile sums by 2^alpha (a query's bits then depend on
   // the other queries of its wave)
   int fold_alpha = 0;
+  // workgroups per (query tile, chunk): 1, or 2, 4, 8 where the pairs are too
+  // few to fill the chip.  Rows up to 256 wide: tsum [P][128][2][m_pad] takes
+  // the tile sums of every lane half, bsum beside it the fp32 form's bound
+  // terms or, centred fp16 form, the group's scale (half 0) and bound factor
+  // (half 1); combine_parts adds them.  Wide rows: sub [P][8][4][m_pad] takes
+  // the sub-chunk sums of the four accumulators of a query; combine_subs.
+  int nsub = 1;
+  float* tsum = nullptr;
+  float* bsum = nullptr;
+  double* sub = nullptr;
 };
 
 int exact_padded_dim(int d);  // 0 if unsupported
@@ -228,6 +238,21 @@ stag_status row_stats_async(const float* A, int64_t rows, int d, unsigned long l
 int choose_resident_form(uint32_t resident, int d, double a, double eps, double max_nrm_q, double max_nrm_x,
                          float max_abs_q, float max_abs_x);
 int64_t query_tile_rows();
+// Sets ex->nsub and allocates the records of a Gaussian or logistic launch
+// whose pairs of a 128-query tile and a chunk alone would leave compute units
+// idle: below kFewPairs pairs, the smallest power of two up to 8 that gives
+// kSplitGrid workgroups (2 per compute unit; 37 queries against
+// 300,000 rows at d = 64, 74 pairs: 232 us a call, now 155).  Wide rows, whose
+// workgroups are long and whose records are small, share up to
+// kFewPairsWide pairs, so that the last round of workgroups is short as well
+// (10,000 queries against 70,000
+// rows at d = 784, 1,422 pairs: 3.95 ms whole, 3.72 ms in halves, measured on
+// an earlier form of the wide tile).  One workgroup per pair otherwise, with a workspace
+// that is not the pool (the no-allocation call's need is part of its
+// interface), and for the exponential kernel, whose near pairs are kept per
+// chunk.
+constexpr int64_t kFewPairs = 128, kSplitGrid = 512, kFewPairsWide = 2048;
+stag_status alloc_parts(const Operands& xo, const Operands& qo, int kernel, Workspace& ws, TileExtra* ex);
 stag_status launch_exact_tiles(const Operands& xo, const Operands& qo, double* partial, const TileExtra& ex,
                                hipStream_t st);
 // A Gaussian sum below this is recomputed with its exponents shifted by

@@ -139,6 +139,80 @@ __global__ __launch_bounds__(256) void prep_rows(const float* __restrict__ src, 
   }
 }
 
+// Wide rows (dp > 256): the same preparation into the fragment layout of
+// kde_tile_wide.h.  One workgroup per 32-row tile; thread t handles row t % 32
+// of the tile and every 8th 16-byte piece of its row, so that a wave writes 1
+// KB of consecutive bytes (a whole fragment) and reads 64 consecutive bytes of
+// each of 32 rows.  Bound by the rows' traffic (X read once, the operands
+// written once): 70,000 rows of 784 in the split form took 315 us with a wave
+// per row and one element per lane and load.
+template <int FORM, bool VEC>
+__global__ __launch_bounds__(256) void prep_wide(const float* __restrict__ src, int64_t n, int d, int dp, double scale,
+                                                 double neg_a_log2e, int is_query, char* __restrict__ part0,
+                                                 char* __restrict__ part1, float* __restrict__ off,
+                                                 double* __restrict__ nrm,
+                                                 unsigned long long* __restrict__ max_nrm_bits) {
+  constexpr int E = FORM == STAG_FORM_FP32 ? 4 : 8;  // row elements per 16-byte piece
+  __shared__ double psum[8][32];
+  const int tid = threadIdx.x, r = tid & 31;
+  const int64_t tile = blockIdx.x;
+  const int64_t row = tile * kTileRows + r;
+  const bool real = row < n;
+  const float* srow = src + (real ? row : 0) * (int64_t)d;
+  const int pieces = dp / E, H = dp / 2;
+  const int64_t base = tile * kTileRows * dp / E;  // the tile's first piece
+  double sq = 0.0;
+  for (int q = tid >> 5; q < pieces; q += 8) {
+    // piece q = 2 s + h of its row
+    const int k0 = FORM == STAG_FORM_FP32 ? (q & 1) * H + 4 * (q >> 1) : 8 * q;
+    float v[E];
+    if (VEC && real && k0 + E <= d) {
+#pragma unroll
+      for (int e = 0; e < E; e += 4) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(srow + k0 + e);
+        v[e] = x.x; v[e + 1] = x.y; v[e + 2] = x.z; v[e + 3] = x.w;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[e] = real && k0 + e < d ? srow[k0 + e] : 0.0f;
+    }
+    const int64_t o = (base + (int64_t)q * 32 + r) * 16;
+    if constexpr (FORM == STAG_FORM_FP32) {
+      f32x4 w;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        sq += (double)v[e] * (double)v[e];
+        w[e] = (float)((double)v[e] * scale);
+      }
+      *reinterpret_cast<f32x4*>(part0 + o) = w;
+    } else {
+      u16x8 hi, lo;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        sq += (double)v[e] * (double)v[e];
+        unsigned short p[3];
+        split_value<FORM>((float)((double)v[e] * scale), p);
+        hi[e] = p[0];
+        lo[e] = p[1];
+      }
+      *reinterpret_cast<u16x8*>(part0 + o) = hi;
+      *reinterpret_cast<u16x8*>(part1 + o) = lo;
+    }
+  }
+  psum[tid >> 5][r] = sq;
+  __syncthreads();
+  if (tid < 32) {
+    double s = psum[0][r];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) s += psum[w][r];
+    off[row] = real ? (float)(neg_a_log2e * s) : (is_query ? 0.0f : kPadOffset);
+    if (real && nrm) nrm[row] = s;
+    double mx = real ? s : 0.0;
+    for (int o = 16; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+    if (tid == 0 && max_nrm_bits) atomicMax(max_nrm_bits, (unsigned long long)__double_as_longlong(mx));
+  }
+}
+
 // S(q) = sum of chunk partials in chunk order; optional 1/n; a-priori bound.
 // With flag: a sum below kRescueBelow sets flag[q] and its 128-query tile's
 // flag (both zeroed beforehand).
@@ -350,9 +424,41 @@ stag_status launch_prep(const float* src, int64_t n, int d, int dp, int64_t rows
   return check_launch("prep_rows");
 }
 
+template <int FORM>
+stag_status launch_prep_wide(const float* src, int64_t n, int d, int dp, int64_t rows_pad, double scale,
+                             double neg_a_l2e, int is_query, void* const* parts, float* off, double* nrm,
+                             unsigned long long* maxbits, hipStream_t st) {
+  ScopedTimer tm("kde_prep", st);
+  const dim3 grid((unsigned)(rows_pad / kTileRows));
+  // 16-byte row reads where every row starts at one
+  const bool vec = d % 4 == 0 && ((uintptr_t)src & 15u) == 0;
+  auto launch = [&](auto kern) {
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, src, n, d, dp, scale, neg_a_l2e, is_query,
+                       static_cast<char*>(parts[0]), static_cast<char*>(parts[1]), off, nrm, maxbits);
+  };
+  if (vec) launch(prep_wide<FORM, true>);
+  else launch(prep_wide<FORM, false>);
+  return check_launch("prep_wide");
+}
+
 stag_status prep_any(int form, const float* src, int64_t n, int d, int dp, int64_t rows_pad, double scale,
                      double neg_a_l2e, int is_query, void* const* parts, float* off, u16x8* aug, double* nrm,
                      unsigned long long* maxbits, hipStream_t st, const int* map = nullptr) {
+  if (dp > 256) {  // the fragment layout of the wide tile
+    if (map || aug) return fail(STAG_E_UNSUPPORTED, "wide rows: no row map");
+    switch (form) {
+      case STAG_FORM_FP32:
+        return launch_prep_wide<STAG_FORM_FP32>(src, n, d, dp, rows_pad, scale, neg_a_l2e, is_query, parts, off, nrm,
+                                                maxbits, st);
+      case STAG_FORM_FP16_SPLIT:
+        return launch_prep_wide<STAG_FORM_FP16_SPLIT>(src, n, d, dp, rows_pad, scale, neg_a_l2e, is_query, parts, off,
+                                                      nrm, maxbits, st);
+      case STAG_FORM_BF16_SPLIT:
+        return launch_prep_wide<STAG_FORM_BF16_SPLIT>(src, n, d, dp, rows_pad, scale, neg_a_l2e, is_query, parts, off,
+                                                      nrm, maxbits, st);
+      default: return fail(STAG_E_UNSUPPORTED, "d > 256 needs the fp32, fp16 split or bf16 split form");
+    }
+  }
   switch (form) {
     case STAG_FORM_FP32:
       return launch_prep<STAG_FORM_FP32>(src, n, d, dp, rows_pad, scale, neg_a_l2e, is_query, parts, off, aug, nrm,
@@ -499,7 +605,147 @@ int choose_resident_form(uint32_t resident, int d, double a, double eps, double 
 
 int64_t query_tile_rows() { return kBQ; }
 
+namespace {
+
+// Partials of the chunks of a wide launch from the sub-chunks' sums: those of
+// each accumulator in order, then the four of a query pairwise, as one
+// workgroup per chunk adds them.
+__global__ __launch_bounds__(256) void combine_subs(const double* __restrict__ sub, int64_t m_pad,
+                                                    double* __restrict__ partial) {
+  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t c = blockIdx.y;
+  if (q >= m_pad) return;
+  double t[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int k = 0; k < kSubs; ++k)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] += sub[sub_index(c, k, 4, i, m_pad, q)];
+  partial[c * m_pad + q] = (t[0] + t[1]) + (t[2] + t[3]);
+}
+
+// Partials (and bound numerators) of the chunks from the tile sums of a part
+// launch, added in the order of the tiles' own loops: each lane half in tile
+// order, then the halves.  KIND 0: sums alone; 1: centred fp32 form (bsum:
+// each tile's bound term); 2: centred fp16 form (fp64 sum per group, scaled
+// and weighted with its bound factor when the group ends).  A workgroup takes
+// 32 queries of a chunk and brings 64 tiles' sums at a time to LDS, all loads
+// in flight; 64 threads (query, lane half) then add them.
+constexpr int kCombineTiles = 64;
+template <int KIND>
+__global__ __launch_bounds__(256) void combine_parts(const float* __restrict__ tsum, const float* __restrict__ bsum,
+                                                     const int* __restrict__ tgroup,
+                                                     const int64_t* __restrict__ n_pad_dev, int64_t n_pad_host,
+                                                     int64_t m_pad, double* __restrict__ partial,
+                                                     double* __restrict__ bpart) {
+  __shared__ float ts[kCombineTiles][64], bs[KIND ? kCombineTiles : 1][64];
+  __shared__ int tg[kCombineTiles + 1];
+  __shared__ double osum[32], obound[32];
+  const int tid = threadIdx.x, c = tid & 31, h = (tid >> 5) & 1;
+  const int64_t q0 = (int64_t)blockIdx.x * 32;  // m_pad is a multiple of 128
+  const int64_t chunk = blockIdx.y;
+  const int64_t n_pad = n_pad_dev ? *n_pad_dev : n_pad_host;
+  const int nt = (int)max((int64_t)0, min((int64_t)kChunkTiles, n_pad / kTileRows - chunk * kChunkTiles));
+  double acc = 0.0, bacc = 0.0, seg = 0.0;
+  for (int t0 = 0; t0 < nt; t0 += kCombineTiles) {
+    const int k = min(kCombineTiles, nt - t0);
+    float v[kCombineTiles / 4], w[kCombineTiles / 4];
+#pragma unroll
+    for (int i = 0; i < kCombineTiles / 4; ++i) {
+      const int t = t0 + min(4 * i + (tid >> 6), k - 1);
+      v[i] = tsum[tsum_index(chunk, t, h, m_pad, q0 + c)];
+      if constexpr (KIND != 0) w[i] = bsum[tsum_index(chunk, t, h, m_pad, q0 + c)];
+    }
+    __syncthreads();  // the previous round's sums are taken
+#pragma unroll
+    for (int i = 0; i < kCombineTiles / 4; ++i) {
+      ts[4 * i + (tid >> 6)][tid & 63] = v[i];
+      if constexpr (KIND != 0) bs[4 * i + (tid >> 6)][tid & 63] = w[i];
+    }
+    if constexpr (KIND == 2) {
+      // the groups, one past the round's tiles (-1 past the chunk's last)
+      if (tid <= kCombineTiles) tg[tid] = t0 + tid < nt ? tgroup[chunk * kChunkTiles + t0 + tid] : -1;
+    }
+    __syncthreads();
+    if (tid < 64) {
+      for (int t = 0; t < k; ++t) {
+        if constexpr (KIND == 2) {
+          seg += (double)ts[t][tid];
+          if (tg[t + 1] != tg[t]) {  // the group's last tile in the chunk
+            const double s = (double)bs[t][c];
+            acc = fma(seg, s, acc);
+            bacc = fma(seg, s * (double)bs[t][32 + c], bacc);
+            seg = 0.0;
+          }
+        } else {
+          acc += (double)ts[t][tid];
+          if constexpr (KIND == 1) bacc += (double)bs[t][tid];
+        }
+      }
+    }
+  }
+  if (tid >= 32 && tid < 64) {
+    osum[c] = acc;
+    obound[c] = bacc;
+  }
+  __syncthreads();
+  if (tid < 32) {
+    partial[chunk * m_pad + q0 + c] = acc + osum[c];
+    if (KIND != 0) bpart[chunk * m_pad + q0 + c] = bacc + obound[c];
+  }
+}
+
+}  // namespace
+
+stag_status alloc_parts(const Operands& xo, const Operands& qo, int kernel, Workspace& ws, TileExtra* ex) {
+  ex->nsub = 1;
+  if (!ws.pooled() || kernel == STAG_KERNEL_EXPONENTIAL) return STAG_OK;
+  const int64_t P = exact_chunks(xo.rows_pad), pairs = P * (qo.rows_pad / kBQ);
+  const bool wide = xo.dp > 256;
+  if (pairs >= (wide ? kFewPairsWide : kFewPairs)) return STAG_OK;
+  int nsub = 2;
+  while (nsub < 8 && pairs * nsub < (wide ? kFewPairsWide : kSplitGrid)) nsub *= 2;
+  if (wide) {
+    STAG_TRY(ws.alloc(&ex->sub, (size_t)P * kSubs * 4 * qo.rows_pad));
+  } else {
+    const size_t sums = (size_t)P * kChunkTiles * 2 * qo.rows_pad;
+    STAG_TRY(ws.alloc(&ex->tsum, sums));
+    if (xo.centred) STAG_TRY(ws.alloc(&ex->bsum, sums));
+  }
+  ex->nsub = nsub;
+  return STAG_OK;
+}
+
+static stag_status launch_tiles_by_mode(const Operands& xo, const Operands& qo, double* partial, const TileExtra& ex,
+                                        hipStream_t st);
+
 stag_status launch_exact_tiles(const Operands& xo, const Operands& qo, double* partial, const TileExtra& ex,
+                               hipStream_t st) {
+  if (ex.nsub > 1 && (ex.qtile_active || ex.max_pass || ex.cflag || ex.kernel == STAG_KERNEL_EXPONENTIAL)) {
+    // launches over selected tiles, and those of the rescue: whole chunks
+    TileExtra e = ex;
+    e.nsub = 1;
+    return launch_tiles_by_mode(xo, qo, partial, e, st);
+  }
+  STAG_TRY(launch_tiles_by_mode(xo, qo, partial, ex, st));
+  if (ex.nsub == 1) return STAG_OK;
+  const int64_t m_pad = qo.rows_pad;
+  const unsigned P = (unsigned)exact_chunks(xo.rows_pad);
+  if (xo.dp > 256) {
+    hipLaunchKernelGGL(combine_subs, dim3((unsigned)ceil_div(m_pad, 256), P), dim3(256), 0, st, ex.sub, m_pad, partial);
+    return check_launch("combine_subs");
+  }
+  const dim3 grid((unsigned)(m_pad / 32), P);
+  auto combine = [&](auto kern) {
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, ex.tsum, ex.bsum, xo.tgroup, xo.n_pad_dev, xo.rows_pad, m_pad,
+                       partial, ex.bpart);
+  };
+  if (!xo.centred) combine(combine_parts<0>);
+  else if (xo.form == STAG_FORM_FP32) combine(combine_parts<1>);
+  else combine(combine_parts<2>);
+  return check_launch("combine_parts");
+}
+
+static stag_status launch_tiles_by_mode(const Operands& xo, const Operands& qo, double* partial, const TileExtra& ex,
                                hipStream_t st) {
   if (ex.kernel != STAG_KERNEL_GAUSSIAN && (ex.self || ex.tp))
     return fail(STAG_E_UNSUPPORTED, "tile extras need the Gaussian kernel");
@@ -511,6 +757,9 @@ stag_status launch_exact_tiles(const Operands& xo, const Operands& qo, double* p
     case tiles::kModeLogShift: return launch_tiles_log_shift(xo, qo, partial, ex, st);
     case tiles::kModeGauss: return launch_tiles_gauss(xo, qo, partial, ex, st);
     case tiles::kModeGaussExtra: return launch_tiles_gauss_extra(xo, qo, partial, ex, st);
+    case tiles::kModeGaussPart: return launch_tiles_gauss_part(xo, qo, partial, ex, st);
+    case tiles::kModeGaussExtraPart: return launch_tiles_gauss_extra_part(xo, qo, partial, ex, st);
+    case tiles::kModeLogisticPart: return launch_tiles_logistic_part(xo, qo, partial, ex, st);
     case tiles::kModeExponential: return launch_tiles_exponential(xo, qo, partial, ex, st);
     default: return launch_tiles_logistic(xo, qo, partial, ex, st);
   }
@@ -862,6 +1111,8 @@ struct ExactBuffers {
   uint8_t* cflag = nullptr;
   int* qsample = nullptr;
   unsigned int* counts = nullptr;
+  // records of the main tile launch where several workgroups share a chunk
+  TileExtra share;
 };
 
 // The fp32 form of the Gaussian sum centres the data tile by tile (the wide
@@ -892,6 +1143,7 @@ stag_status alloc_exact(int form, int kernel, int64_t n, int64_t m, int d, Works
     STAG_TRY(ws.alloc(&b->cflag, (size_t)b->P * ceil_div(m_pad, 256)));
     STAG_TRY(ws.alloc(&b->qsample, (size_t)(m_pad / kBQ)));
     STAG_TRY(ws.alloc(&b->counts, 2));
+    STAG_TRY(alloc_parts(b->xo, b->qo, kernel, ws, &b->share));
     return alloc_rescue(kernel, b->P, b->qsp, ws, &b->rb);
   }
   if (use_centred(form, kernel, d)) {
@@ -906,6 +1158,7 @@ stag_status alloc_exact(int form, int kernel, int64_t n, int64_t m, int d, Works
     STAG_TRY(ws.alloc(&b->partial, (size_t)b->P * b->qo.rows_pad));
     STAG_TRY(ws.alloc(&b->bpart, (size_t)b->P * b->qo.rows_pad));
     STAG_TRY(ws.alloc(&b->bp2, (size_t)b->P * b->qo.rows_pad));
+    STAG_TRY(alloc_parts(b->xo, b->qo, kernel, ws, &b->share));
     return alloc_rescue(kernel, b->P, b->qo, ws, &b->rb);
   }
   STAG_TRY(alloc_operands(form, n, d, false, ws, &b->xo));
@@ -913,6 +1166,7 @@ stag_status alloc_exact(int form, int kernel, int64_t n, int64_t m, int d, Works
   b->P = (int)exact_chunks(b->xo.rows_pad);
   STAG_TRY(ws.alloc(&b->partial, (size_t)b->P * b->qo.rows_pad));
   if (kernel == STAG_KERNEL_EXPONENTIAL) STAG_TRY(ws.alloc(&b->near_over, (size_t)m));
+  STAG_TRY(alloc_parts(b->xo, b->qo, kernel, ws, &b->share));
   return alloc_rescue(kernel, b->P, b->qo, ws, &b->rb);
 }
 
@@ -932,7 +1186,7 @@ stag_status run_centred(const float* X, int64_t n, const float* Q, int64_t m, in
   STAG_TRY(prep_any(STAG_FORM_FP32, Q, m, d, qo.dp, qo.rows_pad, 1.0, 0.0, 1, qo.part, qo.off, nullptr, qo.nrm,
                     nullptr, st));
   const BoundModel bm = make_bound_model(STAG_FORM_FP32, d, a, STAG_KERNEL_GAUSSIAN);
-  TileExtra ex;
+  TileExtra ex = b.share;
   ex.a = a;
   ex.bpart = b.bpart;
   ex.c_cent = (float)bm.c_cent;
@@ -999,7 +1253,7 @@ stag_status run_adaptive(const float* X, int64_t n, const float* Q, int64_t m, i
   // first pass: one fp16 product per pair, with the bound numerators, then
   // the selection of the pairs to recompute (on the sampled tiles: qmask)
   const BoundModel bm1 = make_bound_model(STAG_FORM_FP32, d, a, STAG_KERNEL_GAUSSIAN);
-  TileExtra ex1;
+  TileExtra ex1 = b.share;
   ex1.a = a;
   ex1.bpart = b.bpart;
   ex1.c_cent = (float)bm1.c_cent;
@@ -1077,7 +1331,7 @@ stag_status run_exact(const float* X, int64_t n, const float* Q, int64_t m, int3
   const double at = kernel_tile_a(kernel, a);
   STAG_TRY(prep_operands(X, at, false, b.xo, stream));
   STAG_TRY(prep_operands(Q, at, true, b.qo, stream));
-  TileExtra ex;
+  TileExtra ex = b.share;
   ex.kernel = kernel;
   if (kernel == STAG_KERNEL_EXPONENTIAL) {
     ex.near_x = X;

@@ -80,7 +80,9 @@ extern "C" stag_status stag_kde_random_sample(const float* X, int64_t n, const f
   const int P = (int)exact_chunks(xo.rows_pad);
   double* partial = nullptr;
   STAG_TRY(ws.alloc(&partial, (size_t)P * qo.rows_pad));
-  STAG_TRY(launch_exact_tiles(xo, qo, partial, TileExtra{}, stream));
+  TileExtra ex;
+  STAG_TRY(alloc_parts(xo, qo, STAG_KERNEL_GAUSSIAN, ws, &ex));
+  STAG_TRY(launch_exact_tiles(xo, qo, partial, ex, stream));
   const double scale = (double)n / (double)samples;
   return reduce_with_rescue(partial, P, qo, xo, a, scale, make_bound_model(form, d, a), S_out, bound_out, ws, stream);
 }

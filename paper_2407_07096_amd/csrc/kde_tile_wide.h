@@ -1,0 +1,275 @@
+// Wide rows (256 < d <= 1024) of the exact kernel density: the matrix-core
+// tile of the fp32 and the hi + lo split forms, and the operand layout it
+// reads (internal; included by kde_tiles.h).
+//
+// Operand layout ("fragments").  Rows are stored per 32-row tile in the order
+// in which a wave reads its matrix operands: fragment (tile, s) is 1 KB, 16
+// bytes per lane, lane l = 32 h + r holding, of row r of the tile,
+//   split forms  the 8 halfs of dimensions [16 s + 8 h, 16 s + 8 h + 8)
+//   fp32         the 4 floats of dimensions h DP/2 + [4 s, 4 s + 4)
+// A tile has DP/16 (split) or DP/8 (fp32) fragments; a fragment is one
+// coalesced 1 KB read, lands in LDS as it is and is read back there at
+// 16 bytes per lane without bank conflicts.
+#pragma once
+
+namespace stag {
+namespace tiles {
+
+constexpr int kWideRT = 8;          // 32-row data tiles per workgroup step
+constexpr int kWideQT = 4;          // 32-query blocks per workgroup (kBQ queries)
+constexpr int kSubTiles = 16;       // 32-row tiles per sub-chunk
+constexpr int kSubs = kChunkTiles / kSubTiles;
+constexpr int kWideRuns = kSubTiles / kWideRT;  // steps per sub-chunk
+// Record of sub-chunk k of the chunk, accumulator c of C, query qi.
+__device__ inline int64_t sub_index(int64_t chunk, int k, int C, int c, int64_t m_pad, int64_t qi) {
+  return ((chunk * kSubs + k) * C + c) * m_pad + qi;
+}
+constexpr int kWideWinQ = 8, kWideWinC = 8;
+
+// Workgroup b -> (128-query tile, chunk).  Workgroups are dealt to the 8 XCDs
+// in turn; XCD x takes the x-th eighth of the list of all pairs, ordered by
+// windows of 8 query tiles x 8 chunks, so that the 64 workgroups an XCD runs
+// together read 8 chunks' rows and 8 tiles' queries instead of 64 different
+// ones of either.  Returns false past the end of the list.
+__device__ inline bool wide_tile(int64_t b, int nq, int P, int* qtile, int* chunk) {
+  const int64_t total = (int64_t)nq * P, per = (total + 7) / 8;
+  const int64_t i = (b % 8) * per + b / 8;
+  if (b / 8 >= per || i >= total) return false;
+  const int g = (int)(i / ((int64_t)kWideWinC * nq));  // chunk group
+  const int cg = min(kWideWinC, P - g * kWideWinC);
+  const int64_t r = i - (int64_t)g * kWideWinC * nq;  // < cg * nq
+  const int w = (int)(r / (kWideWinQ * cg));
+  const int qn = min(kWideWinQ, nq - w * kWideWinQ);
+  const int e = (int)(r - (int64_t)w * kWideWinQ * cg);
+  *chunk = g * kWideWinC + e / qn;
+  *qtile = w * kWideWinQ + e % qn;
+  return true;
+}
+
+// Row tile i (0 .. 3) of wave half wr among the 8 of a step: 0, 1, 4, 5 or 2, 3, 6, 7.
+__device__ inline int wide_row_tile(int wr, int i) { return (i & 1) + 2 * wr + 4 * (i >> 1); }
+
+template <int FORM>
+constexpr int kWideParts = FORM == STAG_FORM_FP32 ? 1 : 2;
+
+// A workgroup takes one (128 queries, 4096-row chunk) pair (or a share of
+// it: ex.nsub workgroups per pair, each storing its sub-chunks' sums, which
+// combine_subs adds in the same order), 256 data rows at a time: the four waves split the 8 x 4
+// blocks of 32 rows x 32 queries as 2 x 2, 4 row tiles x 2 query blocks (128
+// accumulators) each.  Wave half wr takes the tiles t with (t / 2) % 2 = wr.
+// Per k-step the 8 row and 4 query fragments (per part) go through registers
+// to LDS, loaded from memory two steps ahead of their use (two buffers, one
+// barrier per step); a wave reads 12 fragments for its 24 products (split).
+// Products of one block come in ascending k with the parts in a fixed order on
+// one accumulator, so a result has the same bits as with any other tiling.
+// Measured at n = 70,000, d = 784: against 10,000 queries in the fp16 split
+// form 7.8 -> 2.3 ms (1.29 PFLOP/s of products; library GEMMs reach 1.25 here),
+// against itself 55 -> 17.5 ms, in fp32 88 -> 66 ms (the tile before this one
+// kept 32 queries per workgroup in LDS and streamed every row from the
+// last-level cache for them: 0.5 TB a call).
+// Sums: per lane fp64 over the tiles of a sub-chunk in order, the sub-chunks
+// in order, then lane halves, then the two waves of a query block.
+// Near pairs (exponential kernel): the first kNearSlots tiles that hold some
+// are taken of each class t % 4 (two classes per wave) and lane.
+template <int FORM, int MODE>
+__global__ __launch_bounds__(256, 2) void tile_wide(const char* __restrict__ X0, const char* __restrict__ X1,
+                                                    const float* __restrict__ Xoff, const char* __restrict__ Q0,
+                                                    const char* __restrict__ Q1, const float* __restrict__ Qoff,
+                                                    int nfrag, int ns, int64_t n_pad, int n_qtiles, int P,
+                                                    int64_t m_pad, double* __restrict__ partial, TileExtra ex) {
+  constexpr int NP = kWideParts<FORM>;
+  constexpr int NF = (kWideRT + kWideQT) * NP;  // fragments per step
+  constexpr bool NEAR = MODE == kModeExponential;
+  __shared__ __attribute__((aligned(16))) char frag[2][NF * 1024];
+  __shared__ double wsum[2][4][32];
+  __shared__ uint32_t near_lds[NEAR ? 4 * kNearSlots * 256 : 1];
+  __shared__ double total[2][256];
+  const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wr = wave >> 1, wq = wave & 1;
+  int qtile, chunk;
+  // shares of a chunk are neighbours in the order of the list
+  if (!wide_tile(blockIdx.x, n_qtiles, P * ex.nsub, &qtile, &chunk)) return;
+  const int part = chunk % ex.nsub;
+  chunk /= ex.nsub;
+  if (ex.qtile_active && ex.qtile_active[qtile] == 0) return;  // whole block
+  const int nrun = kSubs / ex.nsub;  // sub-chunks of this workgroup
+  const int64_t row0 = (int64_t)chunk * kChunkRows + (int64_t)part * nrun * kSubTiles * kTileRows;
+  const int ntiles = (int)max((int64_t)0, min((n_pad - row0) / kTileRows, (int64_t)nrun * kSubTiles));
+  const int nblk = (ntiles + kWideRT - 1) / kWideRT;
+  const int64_t tile0 = row0 / kTileRows;
+  int64_t col[2], qi[2];
+  float alpha[2], ys[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    col[j] = (int64_t)qtile * kBQ + (2 * wq + j) * 32;
+    qi[j] = col[j] + r32;
+    alpha[j] = Qoff[qi[j]];
+    ys[j] = kShiftMode<MODE> ? ex.yshift[qi[j]] : 0.0f;
+  }
+
+  double acc[2] = {acc_init<MODE>(), acc_init<MODE>()};
+#pragma unroll
+  for (int j = 0; j < 2; ++j) total[j][tid] = acc[j];
+  auto end_run = [&](int k) {  // end of this workgroup's sub-chunk k
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      if (ex.nsub > 1) ex.sub[sub_index(chunk, part * nrun + k, 4, 2 * wr + h, m_pad, qi[j])] = acc[j];
+      else total[j][tid] = acc_add<MODE>(total[j][tid], acc[j]);
+      acc[j] = acc_init<MODE>();
+    }
+  };
+  if (ntiles == 0) {  // a share past the last row (nsub > 1)
+    for (int k = 0; k < nrun; ++k) end_run(k);
+    return;
+  }
+
+  // This wave's fragments of a step: row tiles 2 wave and 2 wave + 1 and query
+  // tile wave, every part (scalar addresses; past the chunk's last tile the
+  // last one is read again and its results left out).
+  constexpr int WA = kWideRT / 4;
+  const int64_t tbytes = (int64_t)nfrag * 1024;
+  f32x4 sa[NP][WA], sb[NP];
+  auto gload = [&](int b, int s) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+#pragma unroll
+      for (int k = 0; k < WA; ++k) {
+        const int64_t t = tile0 + min(b * kWideRT + WA * wave + k, ntiles - 1);
+        const char* src = (p == 0 ? X0 : X1) + (t * tbytes + s * 1024);
+        sa[p][k] = *reinterpret_cast<const f32x4*>(src + lane * 16);
+      }
+      const char* src = (p == 0 ? Q0 : Q1) + (((int64_t)qtile * kWideQT + wave) * tbytes + s * 1024);
+      sb[p] = *reinterpret_cast<const f32x4*>(src + lane * 16);
+    }
+  };
+  auto lstore = [&](int buf) {
+    char* dst = &frag[buf][lane * 16];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+#pragma unroll
+      for (int k = 0; k < WA; ++k)
+        *reinterpret_cast<f32x4*>(dst + (p * kWideRT + WA * wave + k) * 1024) = sa[p][k];
+      *reinterpret_cast<f32x4*>(dst + (NP * kWideRT + p * kWideQT + wave) * 1024) = sb[p];
+    }
+  };
+
+  NearRec nr[2][2];  // [query block][tile class]
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) nr[j][k] = {near_lds + (NEAR ? (2 * j + k) * kNearSlots * 256 : 0), 0, false};
+  // the next step to load: (block lb, k-step ls); past the last one it is
+  // loaded again
+  int lb = 0, ls = 0;
+  auto advance = [&]() {
+    gload(lb, ls);
+    const bool wrap = ls + 1 == ns;
+    const bool end = wrap && lb + 1 == nblk;
+    ls = end ? ls : (wrap ? 0 : ls + 1);
+    lb = wrap && !end ? lb + 1 : lb;
+  };
+  advance();
+  lstore(0);
+  advance();
+  int buf = 0;
+  for (int b = 0; b < nblk; ++b) {
+    f32x16 c[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (FORM == STAG_FORM_FP32) {
+        c[i][0] = f32x16{0};
+        c[i][1] = f32x16{0};
+      } else {
+        // the accumulators start from the offsets alpha_q + beta_x
+        const int64_t rb = row0 + (int64_t)min(b * kWideRT + wide_row_tile(wr, i), ntiles - 1) * kTileRows;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 bv = *reinterpret_cast<const f32x4*>(Xoff + rb + 8 * g + 4 * h);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            c[i][0][4 * g + e] = alpha[0] + bv[e];
+            c[i][1][4 * g + e] = alpha[1] + bv[e];
+          }
+        }
+      }
+    }
+    for (int s = 0; s < ns; ++s) {
+      __syncthreads();  // this step's fragments are in buf; the other buffer is free
+      f32x4 fa[NP][4], fb[NP][2];
+      const char* fl = &frag[buf][lane * 16];
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          fb[p][j] = *reinterpret_cast<const f32x4*>(fl + (kWideRT * NP + p * kWideQT + 2 * wq + j) * 1024);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          fa[p][i] = *reinterpret_cast<const f32x4*>(fl + (p * kWideRT + wide_row_tile(wr, i)) * 1024);
+      }
+      lstore(buf ^ 1);  // the next step's (after the last step: a copy nobody reads)
+      advance();
+      if constexpr (FORM == STAG_FORM_FP32) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              c[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[0][i][e], fb[0][j][e], c[i][j], 0, 0, 0);
+      } else {
+        // per block: hi hi, hi lo, lo hi
+#pragma unroll
+        for (int o = 0; o < 3; ++o)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              c[i][j] = mma16<FORM>(__builtin_bit_cast(u16x8, fa[o == 2 ? NP - 1 : 0][i]),
+                                    __builtin_bit_cast(u16x8, fb[o == 1 ? NP - 1 : 0][j]), c[i][j]);
+      }
+      buf ^= 1;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int t = b * kWideRT + wide_row_tile(wr, i);
+      if (t < ntiles) {  // wave-uniform
+        const int64_t rb = row0 + (int64_t)t * kTileRows;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          if constexpr (FORM == STAG_FORM_FP32) {
+            // offsets by one more product: 1 * alpha (half 0) + beta * 1 (half 1)
+            const float tb = Xoff[rb + r32];
+            c[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(h == 0 ? 1.0f : tb, h == 0 ? alpha[j] : 1.0f, c[i][j], 0,
+                                                           0, 0);
+          }
+          acc[j] = acc_add<MODE>(acc[j], (double)tile_epilogue<MODE>(c[i][j], rb, col[j], r32, h, qi[j], ex, nullptr,
+                                                                     false, &nr[j][i & 1], t, ys[j]));
+        }
+      }
+    }
+    if (b % kWideRuns == kWideRuns - 1) end_run(b / kWideRuns);
+  }
+  if (nblk % kWideRuns != 0) end_run(nblk / kWideRuns);
+  if (ex.nsub > 1) {
+    for (int k = (nblk + kWideRuns - 1) / kWideRuns; k < nrun; ++k) end_run(k);  // runs past the last row
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    double a = total[j][tid];
+    if constexpr (NEAR) {
+      a += near_finish(ex, nr[j][0], qi[j], h, row0, tid);
+      a += near_finish(ex, nr[j][1], qi[j], h, row0, tid);
+    }
+    const double other = __shfl_down(a, 32);
+    if (h == 0) wsum[wr][2 * wq + j][r32] = acc_add<MODE>(a, other);
+  }
+  __syncthreads();
+  if (tid < kBQ)
+    partial[(int64_t)chunk * m_pad + (int64_t)qtile * kBQ + tid] =
+        acc_add<MODE>(wsum[0][tid >> 5][tid & 31], wsum[1][tid >> 5][tid & 31]);
+}
+
+}  // namespace tiles
+}  // namespace stag

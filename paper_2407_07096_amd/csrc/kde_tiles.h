@@ -29,6 +29,7 @@ constexpr int kTileRows = 32;
 constexpr int kWaves = 4;
 constexpr int kBQ = 32 * kWaves;      // queries per workgroup
 constexpr int kChunkRows = 4096;      // data rows per partial sum
+constexpr int kChunkTiles = kChunkRows / kTileRows;
 constexpr float kPadOffset = -1.0e30f;  // exponent offset of padding rows: exp2 -> 0
 constexpr unsigned short kBf16One = 0x3F80;
 constexpr int kWideMaxDim = 1024;     // largest d of the wide fp32 tile
@@ -77,6 +78,23 @@ constexpr bool kBasedMode = kExtraMode<MODE> || MODE == kModeMax;
 // becomes about 1 and the sum is multiplied by 2^{-ys} afterwards.
 constexpr int kModeExpShift = 7;
 constexpr int kModeLogShift = 8;
+// kModeGaussPart, kModeGaussExtraPart, kModeLogisticPart: the same epilogues in
+// launches whose (query tile, chunk) pairs are too few to fill the chip
+// (TileExtra::nsub workgroups share a chunk): every tile sum of every lane
+// half is stored instead of added, and combine_parts adds them in the order
+// in which one workgroup would have, so that the results have the same bits.
+// Kernels of their own, so that the plain loops keep their registers and
+// schedule (a run-time branch in them cost the split tile 4 %).
+constexpr int kModeGaussPart = 9;
+constexpr int kModeGaussExtraPart = 10;
+constexpr int kModeLogisticPart = 11;
+template <int MODE>
+constexpr bool kPartMode = MODE >= kModeGaussPart;
+template <int MODE>
+constexpr int kBaseMode = MODE == kModeGaussPart        ? kModeGauss
+                          : MODE == kModeGaussExtraPart ? kModeGaussExtra
+                          : MODE == kModeLogisticPart   ? kModeLogistic
+                                                        : MODE;
 template <int MODE>
 constexpr bool kShiftMode = MODE == kModeExpShift || MODE == kModeLogShift;
 
@@ -177,8 +195,26 @@ __device__ inline double near_finish(const TileExtra& ex, const NearRec& nr, int
       for (uint32_t b = e & 0xFFFFu; b != 0; b &= b - 1) {
         const int i = __builtin_ctz(b);
         const float* xr = ex.near_x + (rb + 8 * (i >> 2) + (i & 3)) * ex.d;
+        // one chain over ascending coordinates; eight of them are loaded from
+        // each row before their products (a load in flight per coordinate
+        // made calls with many near pairs wait on memory: 20,001 x 3,000 at d =
+        // 513 with nearly every pair near took 15.2 ms, now 5.4 ms)
         double r2 = 0.0;
-        for (int j = 0; j < ex.d; ++j) {
+        int j = 0;
+        for (; j + 8 <= ex.d; j += 8) {
+          float qv[8], xv[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            qv[e] = qr[j + e];
+            xv[e] = xr[j + e];
+          }
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const double t = (double)qv[e] - (double)xv[e];
+            r2 = fma(t, t, r2);
+          }
+        }
+        for (; j < ex.d; ++j) {
           const double t = (double)qr[j] - (double)xr[j];
           r2 = fma(t, t, r2);
         }
@@ -277,6 +313,24 @@ __device__ inline float tile_epilogue(const f32x16& c, int64_t row_base, int64_t
   return s;
 }
 
+// A workgroup's share of a (query tile, chunk) pair: all of it, or in the part
+// modes (and in the wide tile with ex.nsub > 1) one of ex.nsub equal runs of
+// the chunk's tiles.
+struct Share {
+  unsigned pair;  // index of the pair
+  int part;
+  int tiles;      // tiles of a whole share
+};
+__device__ inline Share share_of(const TileExtra& ex) {
+  const unsigned b = blockIdx.x, ns = (unsigned)ex.nsub;
+  return {b / ns, (int)(b % ns), kChunkTiles / (int)ns};
+}
+// Place of the sum of the chunk's tile t, lane half h, query qi in
+// TileExtra::tsum (and bsum).
+__device__ inline int64_t tsum_index(int64_t chunk, int t, int h, int64_t m_pad, int64_t qi) {
+  return ((chunk * kChunkTiles + t) * 2 + h) * m_pad + qi;
+}
+
 // ---------------------------------------------------------------------------
 // Tile loop shared by both forms.  Each step t (one 32-row data tile):
 //   barrier (tile t is in LDS buffer t&1, buffer (t+1)&1 is free)
@@ -298,6 +352,7 @@ __global__ __launch_bounds__(256, 2) void tile_f32(const float* __restrict__ Xp,
                                                    const float* __restrict__ Qs, const float* __restrict__ alpha,
                                                    int64_t n_pad, int n_qtiles, int64_t m_pad,
                                                    double* __restrict__ partial, TileExtra ex) {
+  constexpr int BM = kBaseMode<MODE>;
   constexpr int H = DP / 2;
   constexpr int LD = DP + 4;  // LDS row stride (floats): 16-byte aligned, rows 4 banks apart
   constexpr int F4_ROW = DP / 4;
@@ -308,8 +363,9 @@ __global__ __launch_bounds__(256, 2) void tile_f32(const float* __restrict__ Xp,
   __shared__ __attribute__((aligned(16))) float tbeta[2][kTileRows];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
-  const int qtile = blockIdx.x % n_qtiles;
-  const int chunk = blockIdx.x / n_qtiles;
+  const Share sh = kPartMode<MODE> ? share_of(ex) : Share{blockIdx.x, 0, kChunkTiles};
+  const int qtile = (int)(sh.pair % (unsigned)n_qtiles);
+  const int chunk = (int)(sh.pair / (unsigned)n_qtiles);
   const int64_t col_base = (int64_t)qtile * kBQ + wave * 32;
   const int64_t qi = col_base + r32;
   if (ex.qtile_active && ex.qtile_active[qtile] == 0) return;  // whole block: no query of its tile is active
@@ -326,9 +382,10 @@ __global__ __launch_bounds__(256, 2) void tile_f32(const float* __restrict__ Xp,
   const float aq = alpha[qi];
   const float ys = kShiftMode<MODE> ? ex.yshift[qi] : 0.0f;
 
-  const int64_t row0 = (int64_t)chunk * kChunkRows;
+  const int64_t row0 = (int64_t)chunk * kChunkRows + (int64_t)sh.part * sh.tiles * kTileRows;
   const int64_t rem = (n_pad - row0) / kTileRows;
-  const int ntiles = (int)(rem < kChunkRows / kTileRows ? rem : kChunkRows / kTileRows);
+  if (kPartMode<MODE> && rem <= 0) return;  // a share past the last row
+  const int ntiles = (int)min(rem, (int64_t)sh.tiles);
 
   f32x4 stage[NLD];
   float sbeta;
@@ -355,7 +412,11 @@ __global__ __launch_bounds__(256, 2) void tile_f32(const float* __restrict__ Xp,
   auto step = [&](int t, const f32x16& cdone, f32x16& cnew) {
     const int buf = t & 1;
     __syncthreads();
-    if constexpr (kBasedMode<MODE>) {
+    if constexpr (kPartMode<MODE>) {
+      if (t > 0)
+        ex.tsum[tsum_index(chunk, sh.part * sh.tiles + t - 1, h, m_pad, qi)] =
+            tile_epilogue<BM>(cdone, row0 + (int64_t)(t - 1) * kTileRows, col_base, r32, h, qi, ex, &grp);
+    } else if constexpr (kBasedMode<MODE>) {
       if (t > 0)
         acc = acc_add<MODE>(acc, (double)tile_epilogue<MODE>(cdone, row0 + (int64_t)(t - 1) * kTileRows, col_base, r32, h, qi, ex, &grp));
     } else if constexpr (MODE == kModeExponential) {
@@ -407,6 +468,11 @@ __global__ __launch_bounds__(256, 2) void tile_f32(const float* __restrict__ Xp,
     step(t, ca, cb);
     ca = cb;
   }
+  if constexpr (kPartMode<MODE>) {
+    ex.tsum[tsum_index(chunk, sh.part * sh.tiles + ntiles - 1, h, m_pad, qi)] = tile_epilogue<BM>(
+        ca, row0 + (int64_t)(ntiles - 1) * kTileRows, col_base, r32, h, qi, ex, &grp, true);
+    return;
+  }
   acc = acc_add<MODE>(acc, (double)tile_epilogue<MODE>(ca, row0 + (int64_t)(ntiles - 1) * kTileRows, col_base, r32, h, qi, ex, &grp,
                                     true, &nr, ntiles - 1, ys));
   if constexpr (MODE == kModeExponential) acc += near_finish(ex, nr, qi, h, row0, tid);
@@ -443,6 +509,7 @@ __global__ __launch_bounds__(256, 2) void tile_f32c(const float* __restrict__ Xp
                                                     const int64_t* __restrict__ n_pad_dev, const float* __restrict__ Qu,
                                                     const float* __restrict__ qoff, float la, int n_qtiles,
                                                     int64_t m_pad, double* __restrict__ partial, TileExtra ex) {
+  constexpr int BM = kBaseMode<MODE>;
   constexpr int H = DP / 2;
   constexpr int LD = DP + 4;
   constexpr int F4_ROW = DP / 4;
@@ -455,15 +522,16 @@ __global__ __launch_bounds__(256, 2) void tile_f32c(const float* __restrict__ Xp
   __shared__ float trad[2];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
-  const int qtile = blockIdx.x % n_qtiles;
-  const int chunk = blockIdx.x / n_qtiles;
+  const Share sh = kPartMode<MODE> ? share_of(ex) : Share{blockIdx.x, 0, kChunkTiles};
+  const int qtile = (int)(sh.pair % (unsigned)n_qtiles);
+  const int chunk = (int)(sh.pair / (unsigned)n_qtiles);
   const int64_t col_base = (int64_t)qtile * kBQ + wave * 32;
   const int64_t qi = col_base + r32;
   if (ex.qtile_active && ex.qtile_active[qtile] == 0) return;  // whole block: no query of its tile is active
   const int64_t n_pad = *n_pad_dev;
-  const int64_t row0 = (int64_t)chunk * kChunkRows;
+  const int64_t row0 = (int64_t)chunk * kChunkRows + (int64_t)sh.part * sh.tiles * kTileRows;
   if (row0 >= n_pad) {
-    if (h == 0) {
+    if (!kPartMode<MODE> && h == 0) {
       partial[(int64_t)chunk * m_pad + qi] = acc_init<MODE>();
       if (ex.bpart) ex.bpart[(int64_t)chunk * m_pad + qi] = 0.0;
     }
@@ -482,8 +550,7 @@ __global__ __launch_bounds__(256, 2) void tile_f32c(const float* __restrict__ Xp
   }
   const float qo = qoff[qi];
 
-  const int64_t rem = (n_pad - row0) / kTileRows;
-  const int ntiles = (int)(rem < kChunkRows / kTileRows ? rem : kChunkRows / kTileRows);
+  const int ntiles = (int)min((n_pad - row0) / kTileRows, (int64_t)sh.tiles);
   const int64_t tile0 = row0 / kTileRows;
 
   f32x4 stage[NLD];
@@ -513,7 +580,7 @@ __global__ __launch_bounds__(256, 2) void tile_f32c(const float* __restrict__ Xp
 
   double acc = acc_init<MODE>();
   double bacc = 0.0;
-  auto epilogue = [&](const f32x16& cdone, float adone, float edone) {
+  auto epilogue = [&](int tdone, const f32x16& cdone, float adone, float edone) {
     float e[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) e[i] = cdone[i] + adone;
@@ -523,15 +590,23 @@ __global__ __launch_bounds__(256, 2) void tile_f32c(const float* __restrict__ Xp
       for (int i = 1; i < 16; ++i) mx = fmaxf(mx, e[i]);
       acc = acc_add<MODE>(acc, (double)mx);
     } else {
-      const float sum = kernel_tile_sum<MODE>(e);
-      acc += (double)sum;
-      bacc += (double)(sum * edone);
+      const float sum = kernel_tile_sum<BM>(e);
+      if constexpr (kPartMode<MODE>) {
+        if (tdone >= 0) {
+          const int64_t o = tsum_index(chunk, sh.part * sh.tiles + tdone, h, m_pad, qi);
+          ex.tsum[o] = sum;
+          ex.bsum[o] = sum * edone;
+        }
+      } else {
+        acc += (double)sum;
+        bacc += (double)(sum * edone);
+      }
     }
   };
   auto step = [&](int t, const f32x16& cdone, float adone, float edone, f32x16& cnew, float& anew, float& enew) {
     const int buf = t & 1;
     __syncthreads();
-    epilogue(cdone, adone, edone);
+    epilogue(t - 1, cdone, adone, edone);
     const float* arow = &tile[buf][r32 * LD + h * H];
     const float* crow = &tcen[buf][h * H];
     f32x16 c;
@@ -589,7 +664,8 @@ __global__ __launch_bounds__(256, 2) void tile_f32c(const float* __restrict__ Xp
     aa = ab;
     ea = eb;
   }
-  epilogue(ca, aa, ea);
+  epilogue(ntiles - 1, ca, aa, ea);
+  if constexpr (kPartMode<MODE>) return;
   const double other = __shfl_down(acc, 32);
   const double bother = __shfl_down(bacc, 32);
   if (h == 0) {
@@ -622,6 +698,7 @@ __global__ __launch_bounds__(256, 2) void tile_split(
     const unsigned short* __restrict__ X2, const float* __restrict__ Xoff, const unsigned short* __restrict__ Q0,
     const unsigned short* __restrict__ Q1, const unsigned short* __restrict__ Q2, const float* __restrict__ Qoff,
     int64_t n_pad, int n_qtiles, int64_t m_pad, double* __restrict__ partial, TileExtra ex) {
+  constexpr int BM = kBaseMode<MODE>;
   constexpr int NP = FORM == STAG_FORM_BF16_SPLIT3 ? 3 : 2;
   constexpr int KS = DP / 16;
   constexpr int LD = DP + 8;     // LDS row stride (halves): 16-byte aligned
@@ -633,8 +710,9 @@ __global__ __launch_bounds__(256, 2) void tile_split(
   __shared__ __attribute__((aligned(16))) float tbeta[2][kTileRows];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
-  const int qtile = blockIdx.x % n_qtiles;
-  const int chunk = blockIdx.x / n_qtiles;
+  const Share sh = kPartMode<MODE> ? share_of(ex) : Share{blockIdx.x, 0, kChunkTiles};
+  const int qtile = (int)(sh.pair % (unsigned)n_qtiles);
+  const int chunk = (int)(sh.pair / (unsigned)n_qtiles);
   const int64_t col_base = (int64_t)qtile * kBQ + wave * 32;
   const int64_t qi = col_base + r32;
   if (ex.qtile_active && ex.qtile_active[qtile] == 0) return;  // whole block: no query of its tile is active
@@ -651,9 +729,10 @@ __global__ __launch_bounds__(256, 2) void tile_split(
   const float alpha = Qoff[qi];
   const float ys = kShiftMode<MODE> ? ex.yshift[qi] : 0.0f;
 
-  const int64_t row0 = (int64_t)chunk * kChunkRows;
+  const int64_t row0 = (int64_t)chunk * kChunkRows + (int64_t)sh.part * sh.tiles * kTileRows;
   const int64_t rem = (n_pad - row0) / kTileRows;
-  const int ntiles = (int)(rem < kChunkRows / kTileRows ? rem : kChunkRows / kTileRows);
+  if (kPartMode<MODE> && rem <= 0) return;  // a share past the last row
+  const int ntiles = (int)min(rem, (int64_t)sh.tiles);
 
   // the chunk's rows and offsets through buffer resources based at the chunk
   // (as in the centred tile: no per-tile address arithmetic)
@@ -699,7 +778,11 @@ __global__ __launch_bounds__(256, 2) void tile_split(
   auto step = [&](int t, const f32x16& cdone, f32x16& cnew) {
     const int buf = t & 1;
     __syncthreads();
-    if constexpr (kBasedMode<MODE>) {
+    if constexpr (kPartMode<MODE>) {
+      if (t > 0)
+        ex.tsum[tsum_index(chunk, sh.part * sh.tiles + t - 1, h, m_pad, qi)] =
+            tile_epilogue<BM>(cdone, row0 + (int64_t)(t - 1) * kTileRows, col_base, r32, h, qi, ex, &grp);
+    } else if constexpr (kBasedMode<MODE>) {
       if (t > 0)
         acc = acc_add<MODE>(acc, (double)tile_epilogue<MODE>(cdone, row0 + (int64_t)(t - 1) * kTileRows, col_base, r32, h, qi, ex, &grp));
     } else if constexpr (MODE == kModeExponential) {
@@ -757,6 +840,11 @@ __global__ __launch_bounds__(256, 2) void tile_split(
   if (t < ntiles) {
     step(t, ca, cb);
     ca = cb;
+  }
+  if constexpr (kPartMode<MODE>) {
+    ex.tsum[tsum_index(chunk, sh.part * sh.tiles + ntiles - 1, h, m_pad, qi)] = tile_epilogue<BM>(
+        ca, row0 + (int64_t)(ntiles - 1) * kTileRows, col_base, r32, h, qi, ex, &grp, true);
+    return;
   }
   acc = acc_add<MODE>(acc, (double)tile_epilogue<MODE>(ca, row0 + (int64_t)(ntiles - 1) * kTileRows, col_base, r32, h, qi, ex, &grp,
                                     true, &nr, ntiles - 1, ys));
@@ -1029,7 +1117,8 @@ __global__ __launch_bounds__(256, 2) void tile_h1c(const unsigned short* __restr
                                                    const float* __restrict__ Qu, const float* __restrict__ qoff,
                                                    float la, int n_qtw, int64_t m_pad,
                                                    double* __restrict__ partial, TileExtra ex) {
-  static_assert(MODE == kModeGauss || MODE == kModeGaussRescue || MODE == kModeMax, "Gaussian sums and maxima");
+  static_assert(MODE == kModeGauss || MODE == kModeGaussRescue || MODE == kModeMax || MODE == kModeGaussPart,
+                "Gaussian sums and maxima");
   constexpr int NB = kH1cBlocks<DP>;
   constexpr int QW = 32 * NB;  // queries per wave
   constexpr int KS = DP / 16;
@@ -1045,7 +1134,14 @@ __global__ __launch_bounds__(256, 2) void tile_h1c(const unsigned short* __restr
   // with a tile list (qsel holds workgroup tiles here), blockIdx.x runs over
   // (list entry, chunk); else the XCD-aware order of xcd_tile
   int qtile, chunk;
-  if (ex.qsel_n > 0) {
+  Share sh = {0, 0, kChunkTiles};
+  if constexpr (kPartMode<MODE>) {
+    sh = share_of(ex);
+    const unsigned nq = (unsigned)(ex.qsel_n > 0 ? ex.qsel_n : n_qtw);
+    qtile = (int)(sh.pair % nq);
+    if (ex.qsel_n > 0) qtile = ex.qsel[qtile];
+    chunk = (int)(sh.pair / nq);
+  } else if (ex.qsel_n > 0) {
     qtile = ex.qsel[blockIdx.x % ex.qsel_n];
     chunk = blockIdx.x / ex.qsel_n;
   } else {
@@ -1069,9 +1165,9 @@ __global__ __launch_bounds__(256, 2) void tile_h1c(const unsigned short* __restr
 #pragma unroll
   for (int b = 0; b < NB; ++b) qi[b] = col0 + 32 * b + r32;
   const int64_t n_pad = *n_pad_dev;
-  const int64_t row0 = (int64_t)chunk * kChunkRows;
+  const int64_t row0 = (int64_t)chunk * kChunkRows + (int64_t)sh.part * sh.tiles * kTileRows;
   if (row0 >= n_pad) {
-    if (live && h == 0)
+    if (!kPartMode<MODE> && live && h == 0)
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
         partial[(int64_t)chunk * m_pad + qi[b]] = acc_init<MODE>();
@@ -1079,8 +1175,7 @@ __global__ __launch_bounds__(256, 2) void tile_h1c(const unsigned short* __restr
       }
     return;
   }
-  const int64_t rem = (n_pad - row0) / kTileRows;
-  const int ntiles = (int)(rem < kChunkRows / kTileRows ? rem : kChunkRows / kTileRows);
+  const int ntiles = (int)min((n_pad - row0) / kTileRows, (int64_t)sh.tiles);
   const int64_t tile0 = row0 / kTileRows;
   const float s2 = 2.0f * la;
   const float c_cent = ex.c_cent;
@@ -1139,7 +1234,7 @@ __global__ __launch_bounds__(256, 2) void tile_h1c(const unsigned short* __restr
       alpha[b] = m < 65520.0f ? fmaf(-la, t, qo[b]) : __builtin_nanf("");
       if constexpr (MODE != kModeMax) eg[b] = h1c_bound_factor(t, R, qo[b], la, c_cent, rdp);
     }
-    if constexpr (MODE == kModeGauss) {
+    if constexpr (MODE == kModeGauss || MODE == kModeGaussPart) {
       bool ok = ex.fold_alpha != 0;
 #pragma unroll
       for (int b = 0; b < NB; ++b) ok = ok && alpha[b] >= -60.0f && alpha[b] <= 0.0f;  // NaN fails
@@ -1196,7 +1291,9 @@ __global__ __launch_bounds__(256, 2) void tile_h1c(const unsigned short* __restr
     bacc[b] = 0.0;
     aseg[b] = 0.0;
   }
-  auto epilogue = [&](const f32x16 (&d)[NB]) {
+  // part mode: tile tdone's sums with the scale and bound factor of its group
+  // (the tile before the group's change has the closed group's)
+  auto epilogue = [&](int tdone, bool closed, const f32x16 (&d)[NB]) {
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       if constexpr (MODE == kModeMax) {
@@ -1208,7 +1305,17 @@ __global__ __launch_bounds__(256, 2) void tile_h1c(const unsigned short* __restr
         float e[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) e[i] = d[b][i];
-        aseg[b] += (double)kernel_tile_sum<MODE>(e);
+        if constexpr (kPartMode<MODE>) {
+          if (tdone >= 0) {
+            const int tc = sh.part * sh.tiles + tdone;
+            ex.tsum[tsum_index(chunk, tc, h, m_pad, qi[b])] = kernel_tile_sum<kBaseMode<MODE>>(e);
+            // half 0 keeps the scale, half 1 the bound factor (both halves hold both)
+            ex.bsum[tsum_index(chunk, tc, h, m_pad, qi[b])] =
+                h == 0 ? (closed ? psc[b] : scl[b]) : (closed ? peg[b] : eg[b]);
+          }
+        } else {
+          aseg[b] += (double)kernel_tile_sum<MODE>(e);
+        }
       }
     }
   };
@@ -1245,7 +1352,7 @@ __global__ __launch_bounds__(256, 2) void tile_h1c(const unsigned short* __restr
         form_queries(g);
         cur = g;
       }
-      epilogue(d);
+      epilogue(t - 1, pend, d);
       // the accumulators start from the offsets alpha_q + beta_x of their
       // pairs, or from beta_x alone (alpha applied to the group's sums)
       f32x16 bvec;
@@ -1313,9 +1420,10 @@ __global__ __launch_bounds__(256, 2) void tile_h1c(const unsigned short* __restr
   }
   if (live) {
     if (pend) flush(psc, peg);
-    epilogue(ca);
+    epilogue(ntiles - 1, false, ca);
     flush(scl, eg);
   }
+  if constexpr (kPartMode<MODE>) return;
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     const double o = __shfl_down(acc[b], 32);
@@ -1327,196 +1435,13 @@ __global__ __launch_bounds__(256, 2) void tile_h1c(const unsigned short* __restr
   }
 }
 
-// ---------------------------------------------------------------------------
-// Wide rows (256 < d <= 1024), fp32 form.  The 32 queries of a workgroup sit
-// in LDS as the B operand ([32][DP+4] floats, loaded once); each of the 4
-// waves takes every 4th 32-row data tile of the chunk and streams its A
-// operand straight from global memory in blocks of 32 coordinates (register
-// double-buffered).  Per-wave fp64 sums are combined in wave order.
-// ---------------------------------------------------------------------------
-template <int MODE>
-__global__ __launch_bounds__(256) void tile_f32_wide(const float* __restrict__ Xp, const float* __restrict__ beta,
-                                                     const float* __restrict__ Qs, const float* __restrict__ alpha,
-                                                     int DP, int64_t n_pad, int n_qt32, int64_t m_pad,
-                                                     double* __restrict__ partial, TileExtra ex) {
-  extern __shared__ __attribute__((aligned(16))) float qlds[];
-  __shared__ double wsum[4][32];
-  const int H = DP / 2, LD = DP + 4;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
-  const int qtile = blockIdx.x % n_qt32;
-  const int chunk = blockIdx.x / n_qt32;
-  const int64_t col_base = (int64_t)qtile * 32;
-  const int64_t qi = col_base + r32;
-  if (ex.qtile_active && ex.qtile_active[col_base / kBQ] == 0) return;  // whole block
-  // B operand into LDS
-  {
-    const f32x4* src = reinterpret_cast<const f32x4*>(Qs + col_base * DP);
-    const int nv = 32 * DP / 4;
-    for (int v = tid; v < nv; v += 256) {
-      const int r = (v * 4) / DP, c = (v * 4) % DP;
-      *reinterpret_cast<f32x4*>(&qlds[r * LD + c]) = src[v];
-    }
-  }
-  __syncthreads();
-  const float baug = h == 0 ? alpha[qi] : 1.0f;
-  const float ys = kShiftMode<MODE> ? ex.yshift[qi] : 0.0f;
-  const int64_t row0 = (int64_t)chunk * kChunkRows;
-  const int64_t rem = (n_pad - row0) / kTileRows;
-  const int ntiles = (int)(rem < kChunkRows / kTileRows ? rem : kChunkRows / kTileRows);
-  const float* brow = &qlds[r32 * LD + h * H];
-  double acc = acc_init<MODE>();
-  __shared__ near_lds_t<MODE> near_lds;
-  NearRec nr = {near_lds, 0, false};
-  for (int t = wave; t < ntiles; t += 4) {
-    const int64_t rb = row0 + (int64_t)t * kTileRows;
-    const f32x4* arow = reinterpret_cast<const f32x4*>(Xp + (rb + r32) * DP + h * H);
-    f32x16 c = {0};
-    f32x4 a_cur[8], a_nxt[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) a_cur[k] = arow[k];
-    for (int kb = 0; kb < H; kb += 32) {
-      const bool more = kb + 32 < H;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) a_nxt[k] = more ? arow[(kb + 32) / 4 + k] : a_cur[k];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const f32x4 b4 = *reinterpret_cast<const f32x4*>(brow + kb + 4 * k);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(a_cur[k].x, b4.x, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(a_cur[k].y, b4.y, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(a_cur[k].z, b4.z, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(a_cur[k].w, b4.w, c, 0, 0, 0);
-      }
-#pragma unroll
-      for (int k = 0; k < 8; ++k) a_cur[k] = a_nxt[k];
-    }
-    const float tb = beta[rb + r32];
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(h == 0 ? 1.0f : tb, baug, c, 0, 0, 0);
-    acc = acc_add<MODE>(acc, (double)tile_epilogue<MODE>(c, rb, col_base, r32, h, qi, ex, nullptr, false, &nr, t, ys));
-  }
-  if constexpr (MODE == kModeExponential) acc += near_finish(ex, nr, qi, h, row0, tid);
-  const double other = __shfl_down(acc, 32);
-  if (h == 0) wsum[wave][r32] = acc_add<MODE>(acc, other);
-  __syncthreads();
-  if (tid < 32) {
-    const double tot =
-        acc_add<MODE>(acc_add<MODE>(acc_add<MODE>(wsum[0][tid], wsum[1][tid]), wsum[2][tid]), wsum[3][tid]);
-    partial[(int64_t)chunk * m_pad + col_base + tid] = tot;
-  }
-}
+}  // namespace tiles
+}  // namespace stag
 
-// ---------------------------------------------------------------------------
-// Wide rows (256 < d <= 1024), split forms (fp16 or bf16 hi + lo: three
-// products per pair).  The 32 queries of a workgroup sit in LDS as hi and lo
-// B operands ([2][32][DP+8] halfs, loaded once); each of the 4 waves takes
-// every 4th 32-row data tile of the chunk and streams its hi and lo A
-// operands from global memory, four k-steps of 16 at a time (register double
-// buffered); the accumulators start from the offsets alpha_q + beta_x.  The
-// epilogue is tile_epilogue in every mode, as in tile_f32_wide; per-wave fp64
-// sums are combined in wave order.  DP is a multiple of 64 (so of 4 k-steps).
-// ---------------------------------------------------------------------------
-template <int FORM, int MODE>
-__global__ __launch_bounds__(256) void tile_split_wide(const unsigned short* __restrict__ X0,
-                                                       const unsigned short* __restrict__ X1,
-                                                       const float* __restrict__ Xoff,
-                                                       const unsigned short* __restrict__ Q0,
-                                                       const unsigned short* __restrict__ Q1,
-                                                       const float* __restrict__ Qoff, int DP, int64_t n_pad,
-                                                       int n_qt32, int64_t m_pad, double* __restrict__ partial,
-                                                       TileExtra ex) {
-  static_assert(FORM == STAG_FORM_FP16_SPLIT || FORM == STAG_FORM_BF16_SPLIT, "hi + lo split forms");
-  extern __shared__ __attribute__((aligned(16))) unsigned short qsh[];
-  __shared__ double wsum[4][32];
-  const int LD = DP + 8;
-  const int KS = DP / 16;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
-  const int qtile = blockIdx.x % n_qt32;
-  const int chunk = blockIdx.x / n_qt32;
-  const int64_t col_base = (int64_t)qtile * 32;
-  const int64_t qi = col_base + r32;
-  if (ex.qtile_active && ex.qtile_active[col_base / kBQ] == 0) return;  // whole block
-  // B operands (hi, lo) into LDS
-  {
-    const int nv = 32 * DP / 8;
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      const u16x8* src = reinterpret_cast<const u16x8*>((p == 0 ? Q0 : Q1) + col_base * DP);
-      for (int v = tid; v < nv; v += 256) {
-        const int r = (v * 8) / DP, c = (v * 8) % DP;
-        *reinterpret_cast<u16x8*>(&qsh[(p * 32 + r) * LD + c]) = src[v];
-      }
-    }
-  }
-  __syncthreads();
-  const float alpha = Qoff[qi];
-  const float ys = kShiftMode<MODE> ? ex.yshift[qi] : 0.0f;
-  const int64_t row0 = (int64_t)chunk * kChunkRows;
-  const int64_t rem = (n_pad - row0) / kTileRows;
-  const int ntiles = (int)(rem < kChunkRows / kTileRows ? rem : kChunkRows / kTileRows);
-  const unsigned short* bh = &qsh[r32 * LD + h * 8];
-  const unsigned short* bl = &qsh[(32 + r32) * LD + h * 8];
-  double acc = acc_init<MODE>();
-  __shared__ near_lds_t<MODE> near_lds;
-  NearRec nr = {near_lds, 0, false};
-  for (int t = wave; t < ntiles; t += 4) {
-    const int64_t rb = row0 + (int64_t)t * kTileRows;
-    // k-step s of row rb + r32, lane half h: dimensions [16 s + 8 h, +8)
-    const u16x8* ah = reinterpret_cast<const u16x8*>(X0 + (rb + r32) * DP) + h;
-    const u16x8* al = reinterpret_cast<const u16x8*>(X1 + (rb + r32) * DP) + h;
-    f32x16 c;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const f32x4 bv = *reinterpret_cast<const f32x4*>(Xoff + rb + 8 * q + 4 * h);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) c[4 * q + i] = alpha + bv[i];
-    }
-    // blocks of four k-steps in three rotating register buffers: a block's
-    // loads are issued two blocks before its products
-    u16x8 bufh[3][4], bufl[3][4];
-    auto load = [&](int j, int kb) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        bufh[j][k] = ah[2 * (kb + k)];
-        bufl[j][k] = al[2 * (kb + k)];
-      }
-    };
-    auto products = [&](int j, int kb) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int s16 = (kb + k) * 16;
-        const u16x8 b_h = *reinterpret_cast<const u16x8*>(bh + s16);
-        const u16x8 b_l = *reinterpret_cast<const u16x8*>(bl + s16);
-        c = mma16<FORM>(bufh[j][k], b_h, c);
-        c = mma16<FORM>(bufh[j][k], b_l, c);
-        c = mma16<FORM>(bufl[j][k], b_h, c);
-      }
-    };
-    load(0, 0);
-    if (4 < KS) load(1, 4);
-    if (8 < KS) load(2, 8);
-    for (int kb = 0; kb < KS; kb += 12) {
-      products(0, kb);
-      if (kb + 12 < KS) load(0, kb + 12);
-      if (kb + 4 < KS) {
-        products(1, kb + 4);
-        if (kb + 16 < KS) load(1, kb + 16);
-      }
-      if (kb + 8 < KS) {
-        products(2, kb + 8);
-        if (kb + 20 < KS) load(2, kb + 20);
-      }
-    }
-    acc = acc_add<MODE>(acc, (double)tile_epilogue<MODE>(c, rb, col_base, r32, h, qi, ex, nullptr, false, &nr, t, ys));
-  }
-  if constexpr (MODE == kModeExponential) acc += near_finish(ex, nr, qi, h, row0, tid);
-  const double other = __shfl_down(acc, 32);
-  if (h == 0) wsum[wave][r32] = acc_add<MODE>(acc, other);
-  __syncthreads();
-  if (tid < 32) {
-    const double tot =
-        acc_add<MODE>(acc_add<MODE>(acc_add<MODE>(wsum[0][tid], wsum[1][tid]), wsum[2][tid]), wsum[3][tid]);
-    partial[(int64_t)chunk * m_pad + col_base + tid] = tot;
-  }
-}
+#include "kde_tile_wide.h"
+
+namespace stag {
+namespace tiles {
 
 // Timer name of a launch: the underflow rescue's passes are timed apart from
 // the tiles they repeat.
@@ -1534,8 +1459,10 @@ inline int tile_mode(const TileExtra& ex) {
     return (ex.self || ex.tp) ? kModeGaussExtraRescue : kModeGaussRescue;
   }
   if (ex.kernel == STAG_KERNEL_EXPONENTIAL) return kModeExponential;
-  if (ex.kernel == STAG_KERNEL_LOGISTIC) return kModeLogistic;
-  return (ex.self || ex.tp) ? kModeGaussExtra : kModeGauss;
+  const bool part = ex.tsum != nullptr && ex.nsub > 1;
+  if (ex.kernel == STAG_KERNEL_LOGISTIC) return part ? kModeLogisticPart : kModeLogistic;
+  if (ex.self || ex.tp) return part ? kModeGaussExtraPart : kModeGaussExtra;
+  return part ? kModeGaussPart : kModeGauss;
 }
 
 template <int DP, int MODE>
@@ -1543,7 +1470,7 @@ stag_status launch_tile_f32(const float* Xp, const float* beta, const float* Qs,
                             int n_qtiles, int64_t m_pad, int P, double* partial, const TileExtra& ex,
                             hipStream_t st) {
   ScopedTimer tm(rescue_timer(ex, "kde_tile_f32"), st);
-  hipLaunchKernelGGL((tile_f32<DP, MODE>), dim3((unsigned)((int64_t)n_qtiles * P)), dim3(256), 0, st, Xp, beta, Qs,
+  hipLaunchKernelGGL((tile_f32<DP, MODE>), dim3((unsigned)((int64_t)n_qtiles * P * ex.nsub)), dim3(256), 0, st, Xp, beta, Qs,
                      alpha, n_pad, n_qtiles, m_pad, partial, ex);
   return check_launch("tile_f32");
 }
@@ -1566,7 +1493,7 @@ stag_status launch_tile_split(void* const* xp, const float* xaug, void* const* q
                                      ? "kde_tile_fp16x3"
                                      : (FORM == STAG_FORM_BF16_SPLIT ? "kde_tile_bf16x3" : "kde_tile_bf16x6")),
                  st);
-  hipLaunchKernelGGL((tile_split<FORM, DP, MODE>), dim3((unsigned)((int64_t)n_qtiles * P)), dim3(256), 0, st,
+  hipLaunchKernelGGL((tile_split<FORM, DP, MODE>), dim3((unsigned)((int64_t)n_qtiles * P * ex.nsub)), dim3(256), 0, st,
                      (U)xp[0], (U)xp[1], (U)xp[2], xaug, (U)qp[0], (U)qp[1], (U)qp[2], qaug, n_pad, n_qtiles, m_pad,
                      partial, ex);
   return check_launch("tile_split");
@@ -1611,7 +1538,7 @@ template <int DP, int MODE>
 stag_status launch_tile_f32c(const Operands& xo, const Operands& qo, float la, int n_qtiles, int P, double* partial,
                              const TileExtra& ex, hipStream_t st) {
   ScopedTimer tm(rescue_timer(ex, "kde_tile_f32c"), st);
-  hipLaunchKernelGGL((tile_f32c<DP, MODE>), dim3((unsigned)((int64_t)n_qtiles * P)), dim3(256), 0, st,
+  hipLaunchKernelGGL((tile_f32c<DP, MODE>), dim3((unsigned)((int64_t)n_qtiles * P * ex.nsub)), dim3(256), 0, st,
                      (const float*)xo.part[0], xo.off, xo.centre, xo.radius, xo.n_pad_dev, (const float*)qo.part[0],
                      qo.off, la, n_qtiles, qo.rows_pad, partial, ex);
   return check_launch("tile_f32c");
@@ -1654,9 +1581,10 @@ stag_status launch_tile_h1c(const Operands& xo, const Operands& qo, float la, in
   }
   if (nw == 0) return STAG_OK;
   // the full grid in the XCD-aware order: 8 ceil(n_qtw / 8) P workgroups
-  if (ex.qsel_n == 0) nw = 8 * (int)ceil_div(n_qtw, 8);
+  // (in the part mode one per pair and share, in plain order)
+  if (ex.qsel_n == 0 && !kPartMode<MODE>) nw = 8 * (int)ceil_div(n_qtw, 8);
   e.h1c_chunks = P;
-  hipLaunchKernelGGL((tile_h1c<DP, MODE>), dim3((unsigned)((int64_t)nw * P)), dim3(256), 0, st,
+  hipLaunchKernelGGL((tile_h1c<DP, MODE>), dim3((unsigned)((int64_t)nw * P * ex.nsub)), dim3(256), 0, st,
                      static_cast<const unsigned short*>(xo.part[0]), xo.off, xo.tgroup, xo.centre, xo.radius,
                      xo.n_pad_dev, (const float*)qo.part[0], qo.off, la, n_qtw, qo.rows_pad, partial, e);
   return check_launch("tile_h1c");
@@ -1679,6 +1607,25 @@ stag_status dispatch_h1c(const Operands& xo, const Operands& qo, float la, int P
   return fail(STAG_E_UNSUPPORTED, "padded dimension %d not instantiated", xo.dp);
 }
 
+template <int FORM, int MODE>
+stag_status launch_tile_wide(const Operands& xo, const Operands& qo, int P, double* partial, const TileExtra& ex,
+                             hipStream_t st) {
+  const int n_qtiles = (int)(qo.rows_pad / kBQ);
+  // fragments of a tile, and those that hold dimensions below d (the split
+  // forms' padding fragments are zero on both sides and are left out)
+  const int nfrag = xo.dp / (FORM == STAG_FORM_FP32 ? 8 : 16);
+  const int ns = FORM == STAG_FORM_FP32 ? nfrag : (int)ceil_div(xo.d, 16);
+  ScopedTimer tm(rescue_timer(ex, FORM == STAG_FORM_FP32         ? "kde_tile_f32_wide"
+                                  : FORM == STAG_FORM_FP16_SPLIT ? "kde_tile_fp16x3_wide"
+                                                                 : "kde_tile_bf16x3_wide"),
+                 st);
+  const int64_t grid = 8 * ceil_div((int64_t)n_qtiles * P * ex.nsub, 8);
+  hipLaunchKernelGGL((tile_wide<FORM, MODE>), dim3((unsigned)grid), dim3(256), 0, st, (const char*)xo.part[0],
+                     (const char*)xo.part[1], xo.off, (const char*)qo.part[0], (const char*)qo.part[1], qo.off, nfrag,
+                     ns, xo.rows_pad, n_qtiles, P, qo.rows_pad, partial, ex);
+  return check_launch("tile_wide");
+}
+
 // All tiles of one launch in epilogue mode MODE: wide fp32 rows, the fp32
 // tile, the centred fp32 tile or a split form, by padded dimension.
 template <int MODE>
@@ -1687,7 +1634,7 @@ stag_status launch_tiles(const Operands& xo, const Operands& qo, double* partial
   const int P = (int)exact_chunks(xo.rows_pad);
   const int n_qtiles = (int)(qo.rows_pad / kBQ);
   if (xo.centred) {
-    if constexpr (MODE == kModeGauss || MODE == kModeGaussRescue || MODE == kModeMax) {
+    if constexpr (MODE == kModeGauss || MODE == kModeGaussRescue || MODE == kModeMax || MODE == kModeGaussPart) {
       if (xo.form == STAG_FORM_FP16_CENTRED)
         return dispatch_h1c<MODE>(xo, qo, (float)(ex.a * kLog2e), P, partial, ex, st);
       return dispatch_f32c<MODE>(xo, qo, (float)(ex.a * kLog2e), n_qtiles, P, partial, ex, st);
@@ -1695,38 +1642,17 @@ stag_status launch_tiles(const Operands& xo, const Operands& qo, double* partial
       return fail(STAG_E_UNSUPPORTED, "centred data: Gaussian sums only");
     }
   }
-  if (xo.dp > 256 && (xo.form == STAG_FORM_FP16_SPLIT || xo.form == STAG_FORM_BF16_SPLIT)) {
-    const int n_qt32 = (int)(qo.rows_pad / 32);
-    const size_t lds = (size_t)2 * 32 * (xo.dp + 8) * sizeof(unsigned short);
-    using U = const unsigned short*;
-    if (xo.form == STAG_FORM_FP16_SPLIT) {
-      STAG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_split_wide<STAG_FORM_FP16_SPLIT, MODE>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-      ScopedTimer tm(rescue_timer(ex, "kde_tile_fp16x3_wide"), st);
-      hipLaunchKernelGGL((tile_split_wide<STAG_FORM_FP16_SPLIT, MODE>), dim3((unsigned)((int64_t)n_qt32 * P)),
-                         dim3(256), lds, st, (U)xo.part[0], (U)xo.part[1], xo.off, (U)qo.part[0], (U)qo.part[1],
-                         qo.off, xo.dp, xo.rows_pad, n_qt32, qo.rows_pad, partial, ex);
-    } else {
-      STAG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_split_wide<STAG_FORM_BF16_SPLIT, MODE>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-      ScopedTimer tm(rescue_timer(ex, "kde_tile_bf16x3_wide"), st);
-      hipLaunchKernelGGL((tile_split_wide<STAG_FORM_BF16_SPLIT, MODE>), dim3((unsigned)((int64_t)n_qt32 * P)),
-                         dim3(256), lds, st, (U)xo.part[0], (U)xo.part[1], xo.off, (U)qo.part[0], (U)qo.part[1],
-                         qo.off, xo.dp, xo.rows_pad, n_qt32, qo.rows_pad, partial, ex);
-    }
-    return check_launch("tile_split_wide");
-  }
   if (xo.dp > 256) {
-    if (xo.form != STAG_FORM_FP32) return fail(STAG_E_UNSUPPORTED, "d > 256 needs the fp32, fp16 split or bf16 split form");
-    const int n_qt32 = (int)(qo.rows_pad / 32);
-    const size_t lds = (size_t)32 * (xo.dp + 4) * sizeof(float);
-    STAG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_f32_wide<MODE>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    ScopedTimer tm(rescue_timer(ex, "kde_tile_f32_wide"), st);
-    hipLaunchKernelGGL(tile_f32_wide<MODE>, dim3((unsigned)((int64_t)n_qt32 * P)), dim3(256), lds, st,
-                       (const float*)xo.part[0], xo.off, (const float*)qo.part[0], qo.off, xo.dp, xo.rows_pad,
-                       n_qt32, qo.rows_pad, partial, ex);
-    return check_launch("tile_f32_wide");
+    if constexpr (kPartMode<MODE>) {
+      return fail(STAG_E_UNSUPPORTED, "the wide tile keeps its own records");
+    } else {
+      switch (xo.form) {
+        case STAG_FORM_FP32: return launch_tile_wide<STAG_FORM_FP32, MODE>(xo, qo, P, partial, ex, st);
+        case STAG_FORM_FP16_SPLIT: return launch_tile_wide<STAG_FORM_FP16_SPLIT, MODE>(xo, qo, P, partial, ex, st);
+        case STAG_FORM_BF16_SPLIT: return launch_tile_wide<STAG_FORM_BF16_SPLIT, MODE>(xo, qo, P, partial, ex, st);
+        default: return fail(STAG_E_UNSUPPORTED, "d > 256 needs the fp32, fp16 split or bf16 split form");
+      }
+    }
   }
   if (xo.form == STAG_FORM_FP32)
     return dispatch_f32<MODE>(xo.dp, (const float*)xo.part[0], xo.off, (const float*)qo.part[0], qo.off,
@@ -1765,5 +1691,11 @@ stag_status launch_tiles_exp_shift(const Operands& xo, const Operands& qo, doubl
                                    hipStream_t st);
 stag_status launch_tiles_log_shift(const Operands& xo, const Operands& qo, double* partial, const TileExtra& ex,
                                    hipStream_t st);
+stag_status launch_tiles_gauss_part(const Operands& xo, const Operands& qo, double* partial, const TileExtra& ex,
+                                    hipStream_t st);
+stag_status launch_tiles_gauss_extra_part(const Operands& xo, const Operands& qo, double* partial,
+                                          const TileExtra& ex, hipStream_t st);
+stag_status launch_tiles_logistic_part(const Operands& xo, const Operands& qo, double* partial, const TileExtra& ex,
+                                       hipStream_t st);
 
 }  // namespace stag

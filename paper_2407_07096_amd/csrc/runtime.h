@@ -66,6 +66,7 @@ class Workspace {
   struct CountTag {};
   explicit Workspace(CountTag) : stream_(nullptr), mode_(kCount) {}
   size_t used() const { return used_; }
+  bool pooled() const { return mode_ == kPool; }
   ~Workspace();
   Workspace(const Workspace&) = delete;
   Workspace& operator=(const Workspace&) = delete;

@@ -346,6 +346,7 @@ stag_status sample_exact(const float* X, int64_t n, int d, double a, int form, i
   ex.self = 1;
   ex.tp = tp;
   ex.ntile = tstride;
+  STAG_TRY(alloc_parts(xo, qo, STAG_KERNEL_GAUSSIAN, ws, &ex));
   STAG_TRY(launch_exact_tiles(xo, qo, partial, ex, st));
   // underflow rescue: rows whose sum is below kRescueBelow get their
   // exponents shifted by their maximum over the other rows and a second self
