@@ -8,6 +8,7 @@
 #include <cmath>
 #include <map>
 #include <mutex>
+#include <vector>
 
 namespace stag {
 
@@ -31,10 +32,6 @@ stag_status check_launch(const char* what) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(STAG_E_DEVICE, "launch of %s failed: %s", what, hipGetErrorString(e));
   return STAG_OK;
-}
-
-Workspace::~Workspace() {
-  for (void* p : ptrs_) (void)hipFreeAsync(p, stream_);
 }
 
 namespace {
@@ -93,17 +90,145 @@ void cached_free(void* p, size_t bytes) {
   g_cache[dev].emplace(bytes, p);
 }
 
+// Blocks returned by workspaces, per device, for the next ones.  A pool
+// allocation cost 40 us and a stream-ordered free 150 us of host time on
+// average (1 ms at times) on the caller's critical path, more than all the
+// launches of a small call.  A block carries an event, recorded on the stream
+// that used it last when it is returned; whoever takes it makes its own stream
+// wait for that event, so any stream and any thread may take it (on the same
+// stream the wait is free).  At most kMaxIdle bytes per device lie idle and no
+// block above kMaxBlock is kept; the rest goes back to the pool, and when an
+// allocation fails everything idle does before it is tried again.  Requests
+// on a capturing stream bypass the cache both ways: a graph owns its memory.
+class BlockCache {
+ public:
+  static constexpr size_t kMaxIdle = (size_t)2 << 30, kMaxBlock = (size_t)1 << 30;
+
+  // The smallest idle block of at least `bytes` and at most twice as many.
+  bool take(int dev, size_t bytes, hipStream_t st, Workspace::Block* out) {
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      auto& d = dev_[dev];
+      auto it = d.idle.lower_bound(bytes);
+      if (it == d.idle.end() || it->first > 2 * bytes) return false;
+      *out = it->second;
+      d.idle.erase(it);
+      d.idle_bytes -= out->bytes;
+    }
+    if (hipStreamWaitEvent(st, out->ev, 0) == hipSuccess) return true;
+    (void)hipGetLastError();
+    give_back(*out, true);
+    return false;
+  }
+
+  void put(const Workspace::Block& b, hipStream_t st) {
+    if (b.ev == nullptr || hipEventRecord(b.ev, st) != hipSuccess) {
+      (void)hipFreeAsync(b.p, st);
+      drop_event(b.ev);
+      return;
+    }
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      auto& d = dev_[b.dev];
+      if (d.idle_bytes + b.bytes <= kMaxIdle) {
+        d.idle.emplace(b.bytes, b);
+        d.idle_bytes += b.bytes;
+        return;
+      }
+    }
+    (void)hipFreeAsync(b.p, st);
+    drop_event(b.ev);
+  }
+
+  // Returns every idle block of the device to the pool once its work is done.
+  bool trim(int dev) {
+    std::multimap<size_t, Workspace::Block> idle;
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      idle.swap(dev_[dev].idle);
+      dev_[dev].idle_bytes = 0;
+    }
+    for (auto& kv : idle) give_back(kv.second, false);
+    if (idle.empty()) return false;
+    (void)hipStreamSynchronize(nullptr);
+    return true;
+  }
+
+  static void drop_event(hipEvent_t ev) {
+    if (ev) (void)hipEventDestroy(ev);
+  }
+
+ private:
+  // Frees a block on the null stream after its last use.
+  void give_back(const Workspace::Block& b, bool sync) {
+    (void)hipEventSynchronize(b.ev);
+    (void)hipFreeAsync(b.p, nullptr);
+    drop_event(b.ev);
+    if (sync) (void)hipStreamSynchronize(nullptr);
+    (void)hipGetLastError();
+  }
+
+  struct Device {
+    std::multimap<size_t, Workspace::Block> idle;
+    size_t idle_bytes = 0;
+  };
+  std::mutex mu_;
+  std::map<int, Device> dev_;
+};
+
+namespace {
+// Never destroyed: its blocks go with the process, after the runtime may have.
+BlockCache& block_cache() {
+  static BlockCache* c = new BlockCache();
+  return *c;
+}
+}  // namespace
+
+Workspace::~Workspace() {
+  for (const Block& b : blocks_) block_cache().put(b, stream_);
+}
+
+std::vector<void*> Workspace::release() {
+  std::vector<void*> v;
+  for (const Block& b : blocks_) {
+    v.push_back(b.p);
+    BlockCache::drop_event(b.ev);
+  }
+  blocks_.clear();
+  cur_ = nullptr;
+  used_ = cap_ = 0;
+  return v;
+}
+
 stag_status Workspace::raw_alloc(void** p, size_t bytes) {
   *p = nullptr;
   keep_pool_memory();
-  hipError_t e = hipMallocAsync(p, bytes, stream_);
-  if (e != hipSuccess) {
-    *p = nullptr;
+  Block b = {nullptr, bytes, 0, nullptr};
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  const bool keep = bytes <= BlockCache::kMaxBlock && hipGetDevice(&b.dev) == hipSuccess &&
+                    hipStreamIsCapturing(stream_, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+  if (keep) {
+    if (block_cache().take(b.dev, bytes, stream_, &b)) {
+      blocks_.push_back(b);
+      *p = b.p;
+      return STAG_OK;
+    }
+    if (hipEventCreateWithFlags(&b.ev, hipEventDisableTiming) != hipSuccess) b.ev = nullptr;
+  }
+  (void)hipGetLastError();
+  hipError_t e = hipMallocAsync(&b.p, bytes, stream_);
+  if (e == hipErrorOutOfMemory && keep && block_cache().trim(b.dev)) {
     (void)hipGetLastError();
+    e = hipMallocAsync(&b.p, bytes, stream_);
+  }
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    BlockCache::drop_event(b.ev);
     return fail(e == hipErrorOutOfMemory ? STAG_E_NOMEM : STAG_E_DEVICE, "workspace allocation of %zu bytes: %s",
                 bytes, hipGetErrorString(e));
   }
-  ptrs_.push_back(*p);
+  blocks_.push_back(b);
+  *p = b.p;
   return STAG_OK;
 }
 

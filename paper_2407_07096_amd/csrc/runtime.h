@@ -40,7 +40,9 @@ stag_status check_launch(const char* what);
 // into a HIP graph).
 stag_status zero_async(void* p, size_t bytes, hipStream_t st);
 
-// Temporary device memory, allocated and released in stream order.
+// Temporary device memory, allocated and released in stream order.  Blocks
+// that a workspace returns are kept for the next one (see BlockCache in
+// runtime.cpp) instead of going back to the pool each time.
 // The current device's default stream-ordered pool keeps freed memory for
 // reuse (release threshold at the maximum) instead of returning it to the
 // system at every synchronisation; set once per device on first use.
@@ -84,14 +86,9 @@ class Workspace {
   // buffers, scans, partial sums of up to 32 MiB each) then come from one or
   // two pool allocations.
   stag_status alloc_bytes(void** p, size_t bytes);
-  // Hands the allocations to the caller (they are no longer freed here).
-  std::vector<void*> release() {
-    std::vector<void*> v;
-    v.swap(ptrs_);
-    cur_ = nullptr;
-    used_ = cap_ = 0;
-    return v;
-  }
+  // Hands the allocations (of the device's stream-ordered pool) to the caller;
+  // they are no longer freed here.
+  std::vector<void*> release();
   static constexpr size_t kSmallBytes = (size_t)32 << 20;
   static constexpr size_t kBlockBytes = (size_t)64 << 20;
 
@@ -100,7 +97,14 @@ class Workspace {
   enum Mode { kPool, kArena, kCount };
   hipStream_t stream_;
   Mode mode_ = kPool;
-  std::vector<void*> ptrs_;
+  struct Block {
+    void* p;
+    size_t bytes;
+    int dev;
+    hipEvent_t ev;  // null: not kept (goes back to the pool)
+  };
+  friend class BlockCache;
+  std::vector<Block> blocks_;
   char* cur_ = nullptr;
   size_t used_ = 0, cap_ = 0;
 };
