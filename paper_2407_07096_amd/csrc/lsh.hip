@@ -478,12 +478,13 @@ __device__ inline float dist2_both(const float* __restrict__ qrow, const float* 
 // which each lane decides the level in fp64 and computes its term:
 // on_batch(v, j, valid, i) receives it (0 outside the level), the point j
 // and the level i.  Levels whose bit (i - 1) is clear in `levels` are
-// skipped (callers pass a mask of the levels with a positive term).
-// Returns the number of candidates walked.
-template <class F>
+// skipped (callers pass a mask of the levels with a positive term), and so
+// are those for which dense(i) returns true (it has taken them itself, in
+// their place of the order).  Returns the number of candidates walked.
+template <class F, class DN>
 __device__ inline int64_t walk_copy(const IndexView& ix, const LevelConst& lc, int t, const uint64_t* __restrict__ qk,
                                     int64_t qs, WalkScratch& ws, const float* __restrict__ qrow, int64_t self_idx,
-                                    uint64_t levels, F&& on_batch) {
+                                    uint64_t levels, F&& on_batch, DN&& dense) {
   const int lane = threadIdx.x & 63;
   const int L = ix.L, d = ix.d;
   const double delta = screen_delta(d);
@@ -497,7 +498,7 @@ __device__ inline int64_t walk_copy(const IndexView& ix, const LevelConst& lc, i
   const double sq = sqrt(nq);
   int64_t walked = 0;
   for (int i = 1; i <= ix.J; ++i) {  // J <= 64
-    if (!((levels >> (i - 1)) & 1)) continue;
+    if (!((levels >> (i - 1)) & 1) || dense(i)) continue;
     const int seg = t * ix.J + (i - 1);
     const int64_t s0 = (int64_t)ix.seg_off[seg];
     const int64_t cnt = (int64_t)ix.seg_off[seg + 1] - s0;
@@ -606,12 +607,22 @@ __device__ inline int64_t walk_copy(const IndexView& ix, const LevelConst& lc, i
   return walked;
 }
 
-// One wave per (query, copy): the copy's estimate and candidate counts.
+}  // namespace
+}  // namespace stag
+
+#include "lsh_dense.h"
+
+namespace stag {
+namespace {
+
+// One wave per (query, copy): the copy's estimate and candidate counts from
+// its levels that are not in dense_levels.
 __global__ __launch_bounds__(256) void probe_queries(const float* __restrict__ Q, int ldq, int64_t q0, int64_t mb,
                                                      IndexView ix, LevelConst lc, const uint64_t* __restrict__ qkeys,
-                                                     int64_t ntab, int self_excl, double* __restrict__ Scopy,
-                                                     int64_t* __restrict__ ncand, int64_t* __restrict__ nacc,
-                                                     uint64_t* __restrict__ levels_out) {
+                                                     int64_t qs, int self_excl,
+                                                     const uint64_t* __restrict__ dense_levels,
+                                                     double* __restrict__ Scopy, int64_t* __restrict__ ncand,
+                                                     int64_t* __restrict__ nacc, uint64_t* __restrict__ levels_out) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t pair = (int64_t)blockIdx.x * 4 + wave;
@@ -623,12 +634,14 @@ __global__ __launch_bounds__(256) void probe_queries(const float* __restrict__ Q
   double acc = 0.0;
   int64_t nc = 0, na = 0;
   uint64_t hit = 0;  // levels with a positive term (wave-uniform)
-  nc = walk_copy(ix, lc, t, qkeys + ql, mb, wsc[wave], qrow, self_excl ? q0 + ql : -1, ~0ULL,
+  const uint64_t walk = dense_levels ? ~dense_levels[t] : ~0ULL;
+  nc = walk_copy(ix, lc, t, qkeys + ql, qs, wsc[wave], qrow, self_excl ? q0 + ql : -1, walk,
                  [&](double v, int32_t j, bool valid, int i) {
                    acc += v;
                    na += v > 0.0 ? 1 : 0;
                    if (__ballot(v > 0.0)) hit |= 1ULL << (i - 1);
-                 });
+                 },
+                 [](int) { return false; });
   for (int o = 32; o > 0; o >>= 1) {
     acc += __shfl_xor(acc, o);
     na += __shfl_xor(na, o);
@@ -655,13 +668,11 @@ __device__ inline double wave_incl_scan_f64(double v) {
 // the data without its own point).  Lane r < s holds draw r: target
 // U(i, r) * sum_t S'_t(i), its copy (cumulative over copies) and remainder;
 // each needed copy is walked once, in batches whose inclusive prefix sums
-// locate every pending remainder.
+// locate every pending remainder (its dense segments from the pairs' terms).
 __global__ __launch_bounds__(256) void draw_lsh(IndexView ix, LevelConst lc, const uint64_t* __restrict__ qkeys,
-                                                int64_t ntab, int64_t q0, int64_t mb, const double* __restrict__ Scopy,
-                                                const uint64_t* __restrict__ levels, const double* __restrict__ rest,
-                                                int s, uint64_t seed,
-                                                int64_t* __restrict__ src, int64_t* __restrict__ dst,
-                                                double* __restrict__ w) {
+                                                int64_t qs, int64_t q0, int64_t mb, const double* __restrict__ Scopy,
+                                                const uint64_t* __restrict__ levels, DensePairs dp, int s,
+                                                uint64_t seed, int64_t* __restrict__ src, int64_t* __restrict__ dst) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t ql = (int64_t)blockIdx.x * 4 + wave;
@@ -707,7 +718,8 @@ __global__ __launch_bounds__(256) void draw_lsh(IndexView ix, LevelConst lc, con
     // levels without a positive term change neither the running sum nor the
     // last positive point, so the walk skips them
     const uint64_t lv = levels ? levels[qi * ix.K1 + t] : ~0ULL;
-    walk_copy(ix, lc, t, qkeys + ql, mb, wsc[wave], qrow, qi, lv, [&](double v, int32_t j, bool valid, int) {
+    const uint64_t dense = dp.levels ? dp.levels[t] : 0ULL;
+    auto take = [&](double v, int32_t j, bool valid, int) {
       const double incl = wave_incl_scan_f64(v);
       const double btot = __shfl(incl, 63);
       const uint64_t pos = __ballot(v > 0.0);
@@ -726,6 +738,11 @@ __global__ __launch_bounds__(256) void draw_lsh(IndexView ix, LevelConst lc, con
         if (lane == r && over) pick = jj;
       }
       running += btot;
+    };
+    walk_copy(ix, lc, t, qkeys + ql, qs, wsc[wave], qrow, qi, lv, take, [&](int i) {
+      if (!((dense >> (i - 1)) & 1)) return false;
+      dense_walk(dp, ql, t * ix.J + (i - 1), i, take);
+      return true;
     });
     if (mine && tsel == t && pick < 0) pick = lastj;  // rounding left the remainder above the total
   }
@@ -733,8 +750,16 @@ __global__ __launch_bounds__(256) void draw_lsh(IndexView ix, LevelConst lc, con
     const int64_t e = qi * s + lane;
     src[e] = qi;
     dst[e] = pick;
-    w[e] = pick >= 0 ? 1.0 / ((double)s * (1.0 / rest[qi] + 1.0 / rest[pick])) : 0.0;
   }
+}
+
+// Weights of the drawn edges (every node's estimate is known by now).
+__global__ void edge_weights(const int64_t* __restrict__ dst, int64_t n, int s, const double* __restrict__ rest,
+                             double* __restrict__ w) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= n * s) return;
+  const int64_t pick = dst[e];
+  w[e] = pick >= 0 ? 1.0 / ((double)s * (1.0 / rest[e / s] + 1.0 / rest[pick])) : 0.0;
 }
 
 __global__ void mean_copies(const double* __restrict__ Scopy, int64_t q0, int64_t mb, int K1,
@@ -1287,6 +1312,15 @@ struct stag_lsh_index {
   double* cheb = nullptr;
   std::vector<double> h_cheb;
   uint64_t* thr = nullptr;
+  // dense segments (walked indexes only): their column tiles, the first one
+  // of each segment [nseg + 1], and the copies' level masks [K1]
+  int dense_tiles = 0;
+  std::vector<stag::DenseTile> h_dtiles;
+  std::vector<int32_t> h_dfirst;
+  std::vector<uint64_t> h_dlevels;
+  stag::DenseTile* dtiles = nullptr;
+  int32_t* dfirst = nullptr;
+  uint64_t* dlevels = nullptr;
 };
 
 struct stag_e2lsh_table {
@@ -1379,6 +1413,8 @@ __global__ __launch_bounds__(256) void row_norms(const float* __restrict__ X, in
   for (int o = 32; o > 0; o >>= 1) s2 += __shfl_xor(s2, o);
   if (lane == 0) xn[r] = sqrt(s2);
 }
+
+stag_status find_dense(stag_lsh_index* idx, const MemberBlock* blocks, int64_t nblocks, Workspace& ws, hipStream_t st);
 
 stag_status create_index(const float* X, int64_t n, int d, double a, double eps, const stag_lsh_params* p,
                          stag_lsh_index* idx, hipStream_t st) {
@@ -1490,8 +1526,8 @@ stag_status create_index(const float* X, int64_t n, int d, double a, double eps,
     tso[s + 1] = tso[s] + (uint64_t)cap[s] * L;
   }
   idx->total_slots = (int64_t)tso[idx->nseg];
+  MemberBlock* dblk = nullptr;
   if (!blocks.empty()) {
-    MemberBlock* dblk = nullptr;
     STAG_TRY(ws.alloc(&dblk, blocks.size()));
     STAG_HIP(hipMemcpyAsync(dblk, blocks.data(), sizeof(MemberBlock) * blocks.size(), hipMemcpyHostToDevice, st));
     ScopedTimer tm("lsh_hash_members", st);
@@ -1519,6 +1555,7 @@ stag_status create_index(const float* X, int64_t n, int d, double a, double eps,
                                  st));
   }
   STAG_HIP(hipGetDevice(&idx->device));
+  STAG_TRY(find_dense(idx, dblk, (int64_t)blocks.size(), ws, st));
   // the workspace (sort buffers, counts) is released in stream order
   return STAG_OK;
 }
@@ -1609,6 +1646,138 @@ bool join_applies(const stag_lsh_index* idx) {
   return idx->d <= 128 && idx->prm.shape.L <= 32 && idx->total_slots > 0 && idx->total_slots < INT32_MAX;
 }
 
+// The dense segments of an index whose queries are walked (see lsh_dense.h):
+// kDenseSamples evenly spaced points are hashed as queries and met counts
+// their meetings with each segment's members; a segment whose share is at
+// least kDenseShare is dense, in segment order while the columns last.  One
+// synchronisation.
+stag_status find_dense(stag_lsh_index* idx, const MemberBlock* blocks, int64_t nblocks, Workspace& ws, hipStream_t st) {
+  if (join_applies(idx) || nblocks == 0) return STAG_OK;
+  const int64_t n = idx->prm.n;
+  const int ns = (int)std::min<int64_t>(kDenseSamples, n);
+  const int J = idx->prm.shape.J, K1 = idx->prm.shape.K1;
+  if (idx->ntab * ns * 8 > kDenseMaxBytes) return STAG_OK;
+  const int64_t step = n / ns;
+  if (step * idx->dx > INT32_MAX) return STAG_OK;
+  uint64_t* skeys = nullptr;
+  unsigned long long* met = nullptr;
+  STAG_TRY(ws.alloc(&skeys, (size_t)idx->ntab * ns));
+  STAG_TRY(ws.alloc(&met, (size_t)idx->nseg));
+  STAG_TRY(hash_query_batch(idx, idx->X, (int)(step * idx->dx), 0, ns, skeys, st));
+  STAG_TRY(zero_async(met, sizeof(unsigned long long) * idx->nseg, st));
+  hipLaunchKernelGGL(count_met, dim3((unsigned)ceil_div(nblocks, 4)), dim3(256), 0, st, blocks, nblocks,
+                     idx->prm.shape.L, idx->seg_off, idx->mkeys, skeys, ns, met);
+  STAG_TRY(check_launch("count_met"));
+  std::vector<unsigned long long> h((size_t)idx->nseg);
+  STAG_HIP(hipMemcpyAsync(h.data(), met, sizeof(unsigned long long) * idx->nseg, hipMemcpyDeviceToHost, st));
+  STAG_HIP(hipStreamSynchronize(st));
+  // (kept with the index: their copies to the device may still be under way)
+  std::vector<DenseTile>& tiles = idx->h_dtiles;
+  std::vector<int32_t>& first = idx->h_dfirst;
+  std::vector<uint64_t>& levels = idx->h_dlevels;
+  first.assign((size_t)idx->nseg + 1, 0);
+  levels.assign((size_t)K1, 0);
+  for (int64_t sgm = 0; sgm < idx->nseg; ++sgm) {
+    first[sgm] = (int32_t)tiles.size();
+    const int64_t c = (int64_t)(idx->h_seg_off[sgm + 1] - idx->h_seg_off[sgm]);
+    if (c == 0 || (double)h[sgm] < kDenseShare * (double)c * ns) continue;
+    if (((int64_t)tiles.size() + ceil_div(c, kDenseTile)) * kDenseTile > kDenseMaxCols) continue;
+    for (int64_t u = 0; u < c; u += kDenseTile) tiles.push_back({(int32_t)sgm, (int32_t)u});
+    levels[sgm / J] |= 1ULL << (sgm % J);
+  }
+  first[idx->nseg] = (int32_t)tiles.size();
+  if (tiles.empty()) return STAG_OK;
+  STAG_TRY(own_alloc(idx, &idx->dtiles, tiles.size()));
+  STAG_TRY(own_alloc(idx, &idx->dfirst, first.size()));
+  STAG_TRY(own_alloc(idx, &idx->dlevels, levels.size()));
+  STAG_HIP(hipMemcpyAsync(idx->dtiles, tiles.data(), sizeof(DenseTile) * tiles.size(), hipMemcpyHostToDevice, st));
+  STAG_HIP(hipMemcpyAsync(idx->dfirst, first.data(), sizeof(int32_t) * first.size(), hipMemcpyHostToDevice, st));
+  STAG_HIP(hipMemcpyAsync(idx->dlevels, levels.data(), sizeof(uint64_t) * levels.size(), hipMemcpyHostToDevice, st));
+  idx->dense_tiles = (int)tiles.size();
+  return STAG_OK;
+}
+
+// Draws to take from a walked batch while its dense pairs are there.
+struct DrawArgs {
+  int s;
+  uint64_t seed;
+  int64_t *src, *dst;
+  uint64_t* levels;  // [n][K1]
+};
+
+// Copy sums (and draws) of one hashed query batch through the walk, the
+// dense segments' pairs formed for as many queries at a time as their buffer
+// holds.
+stag_status walk_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64_t q0, int64_t cur, int self_excl,
+                       const uint64_t* qkeys, double* scopy, int64_t* ncand, int64_t* nacc, const DrawArgs* draw,
+                       hipStream_t st) {
+  const int K1 = idx->prm.shape.K1;
+  const IndexView ix = make_view(idx);
+  const LevelConst lc = make_levels(idx->prm);
+  uint64_t* levels = draw ? draw->levels : nullptr;
+  Workspace ws(st);
+  DensePairs dp;
+  int64_t sub = cur;
+  double* qnorm = nullptr;
+  if (idx->dense_tiles > 0) {
+    dp.ncol = idx->dense_tiles * kDenseTile;
+    const int64_t fit = kDenseMaxBytes / ((int64_t)dp.ncol * (draw ? 21 : 9)) / kDenseTile * kDenseTile;
+    sub = std::min<int64_t>({std::max<int64_t>(fit, kDenseTile), round_up(cur, kDenseTile), (int64_t)65535 * kDenseTile});
+    STAG_TRY(ws.alloc(&dp.D, (size_t)sub * dp.ncol));
+    STAG_TRY(ws.alloc(&dp.F, (size_t)sub * dp.ncol));
+    STAG_TRY(ws.alloc(&dp.any, (size_t)(sub / kDenseTile) * idx->dense_tiles));
+    if (draw) {
+      STAG_TRY(ws.alloc(&dp.V, (size_t)sub * dp.ncol));
+      STAG_TRY(ws.alloc(&dp.J, (size_t)sub * dp.ncol));
+      STAG_TRY(ws.alloc(&dp.len, (size_t)sub * idx->dense_tiles));
+    }
+    STAG_TRY(ws.alloc(&qnorm, (size_t)std::min(sub, cur)));
+    dp.tiles = idx->dtiles;
+    dp.first = idx->dfirst;
+    dp.levels = idx->dlevels;
+  }
+  for (int64_t p = 0; p < cur; p += sub) {
+    const int64_t c = std::min(sub, cur - p);
+    double* sc = scopy + p * K1;
+    {
+      ScopedTimer tm("lsh_probe", st);
+      hipLaunchKernelGGL(probe_queries, dim3((unsigned)ceil_div(c * K1, 4)), dim3(256), 0, st, Q, ldq, q0 + p, c, ix,
+                         lc, qkeys + p, cur, self_excl, dp.levels, sc, ncand, nacc, levels);
+      STAG_TRY(check_launch("probe_queries"));
+    }
+    if (dp.ncol > 0) {
+      ScopedTimer tm("lsh_dense", st);
+      hipLaunchKernelGGL(row_norms, dim3((unsigned)ceil_div(c, 4)), dim3(256), 0, st, Q + (q0 + p) * ldq, c, ldq,
+                         qnorm);
+      const dim3 grid((unsigned)idx->dense_tiles, (unsigned)ceil_div(c, kDenseTile));
+      // 16-byte query loads where every row starts at one (rows at ldq >= d
+      // rounded up to 4 have the piece past d's last whole one too)
+      const bool vec = ldq % 4 == 0 && ((uintptr_t)Q & 15u) == 0;
+      auto launch = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(512), 0, st, ix, lc, Q, (int64_t)ldq, q0 + p, c, qkeys + p, cur, qnorm,
+                           self_excl, dp, ncand);
+      };
+      if (vec) launch(dense_pairs<true>);
+      else launch(dense_pairs<false>);
+      STAG_TRY(check_launch("dense_pairs"));
+      auto terms = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(c, 4)), dim3(256), 0, st, ix, lc, q0 + p, c, dp, sc, nacc,
+                           levels);
+      };
+      if (draw) terms(dense_terms<true>);
+      else terms(dense_terms<false>);
+      STAG_TRY(check_launch("dense_terms"));
+    }
+    if (draw) {
+      ScopedTimer tm("simgraph_draw_lsh", st);
+      hipLaunchKernelGGL(draw_lsh, dim3((unsigned)ceil_div(c, 4)), dim3(256), 0, st, ix, lc, qkeys + p, cur, q0 + p, c,
+                         sc, draw->levels, dp, draw->s, draw->seed, draw->src, draw->dst);
+      STAG_TRY(check_launch("draw_lsh"));
+    }
+  }
+  return STAG_OK;
+}
+
 // Copy sums of one hashed query batch through the bucket join.
 stag_status join_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64_t q0, int64_t cur, int self_excl,
                        const uint64_t* qkeys, double* scopy, int64_t* ncand, int64_t* nacc, hipStream_t st) {
@@ -1696,7 +1865,7 @@ stag_status join_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64
 // keys; when the queries fit one batch it holds their keys on return.
 stag_status query_index(const stag_lsh_index* idx, const float* Q, int ldq, int64_t m, int self_excl,
                         double* S_out, double* copies_out, int64_t* ncand, int64_t* nacc, hipStream_t st,
-                        uint64_t* levels_out = nullptr, uint64_t* keys_buf = nullptr) {
+                        uint64_t* keys_buf = nullptr, const DrawArgs* draw = nullptr) {
   const LshParams& prm = idx->prm;
   const int K1 = prm.shape.K1;
   Workspace ws(st);
@@ -1707,18 +1876,13 @@ stag_status query_index(const stag_lsh_index* idx, const float* Q, int ldq, int6
   STAG_TRY(ws.alloc(&scopy, (size_t)mb * K1));
   if (ncand) hipLaunchKernelGGL(zero_i64, dim3((unsigned)ceil_div(m, 256)), dim3(256), 0, st, ncand, m);
   if (nacc) hipLaunchKernelGGL(zero_i64, dim3((unsigned)ceil_div(m, 256)), dim3(256), 0, st, nacc, m);
-  const IndexView ix = make_view(idx);
-  const LevelConst lc = make_levels(prm);
   for (int64_t q0 = 0; q0 < m; q0 += mb) {
     const int64_t cur = std::min(mb, m - q0);
     STAG_TRY(hash_query_batch(idx, Q, ldq, q0, cur, qkeys, st));
     if (join_applies(idx)) {
       STAG_TRY(join_batch(idx, Q, ldq, q0, cur, self_excl, qkeys, scopy, ncand, nacc, st));
     } else {
-      ScopedTimer tm("lsh_probe", st);
-      hipLaunchKernelGGL(probe_queries, dim3((unsigned)ceil_div(cur * K1, 4)), dim3(256), 0, st, Q, ldq, q0, cur, ix,
-                         lc, qkeys, idx->ntab, self_excl, scopy, ncand, nacc, levels_out);
-      STAG_TRY(check_launch("probe_queries"));
+      STAG_TRY(walk_batch(idx, Q, ldq, q0, cur, self_excl, qkeys, scopy, ncand, nacc, draw, st));
     }
     hipLaunchKernelGGL(mean_copies, dim3((unsigned)ceil_div(cur, 256)), dim3(256), 0, st, scopy, q0, cur, K1, S_out,
                        copies_out);
@@ -1741,25 +1905,32 @@ stag_status lsh_sample_edges(const stag_lsh_index* idx, int s, uint64_t seed, in
   double* copies = nullptr;
   STAG_TRY(ws.alloc(&rest, (size_t)n));
   STAG_TRY(ws.alloc(&copies, (size_t)n * K1));
-  // with the per-query walk (not the bucket join) the estimate also records,
-  // per node and copy, the levels with a positive term for the draws
-  uint64_t* levels = nullptr;
-  if (!join_applies(idx)) STAG_TRY(ws.alloc(&levels, (size_t)n * K1));
   const int64_t mb = query_batch(idx, n);
   uint64_t* qkeys = nullptr;
   STAG_TRY(ws.alloc(&qkeys, (size_t)mb * idx->ntab));
-  STAG_TRY(query_index(idx, idx->X, idx->dx, n, 1, rest, copies, nullptr, nullptr, st, levels, qkeys));
-  const IndexView ix = make_view(idx);
-  const LevelConst lc = make_levels(prm);
-  for (int64_t q0 = 0; q0 < n; q0 += mb) {
-    const int64_t cur = std::min(mb, n - q0);
-    // with one batch the estimate's keys are still in qkeys
-    if (mb < n) STAG_TRY(hash_query_batch(idx, idx->X, idx->dx, q0, cur, qkeys, st));
-    ScopedTimer tm("simgraph_draw_lsh", st);
-    hipLaunchKernelGGL(draw_lsh, dim3((unsigned)ceil_div(cur, 4)), dim3(256), 0, st, ix, lc, qkeys, idx->ntab, q0,
-                       cur, copies + q0 * K1, levels, rest, s, seed, src, dst, w);
-    STAG_TRY(check_launch("draw_lsh"));
+  if (!join_applies(idx)) {
+    // with the per-query walk (not the bucket join) each batch draws right
+    // after its estimate, which also records, per node and copy, the levels
+    // with a positive term
+    DrawArgs draw = {s, seed, src, dst, nullptr};
+    STAG_TRY(ws.alloc(&draw.levels, (size_t)n * K1));
+    STAG_TRY(query_index(idx, idx->X, idx->dx, n, 1, rest, copies, nullptr, nullptr, st, qkeys, &draw));
+  } else {
+    STAG_TRY(query_index(idx, idx->X, idx->dx, n, 1, rest, copies, nullptr, nullptr, st, qkeys));
+    const IndexView ix = make_view(idx);
+    const LevelConst lc = make_levels(prm);
+    for (int64_t q0 = 0; q0 < n; q0 += mb) {
+      const int64_t cur = std::min(mb, n - q0);
+      // with one batch the estimate's keys are still in qkeys
+      if (mb < n) STAG_TRY(hash_query_batch(idx, idx->X, idx->dx, q0, cur, qkeys, st));
+      ScopedTimer tm("simgraph_draw_lsh", st);
+      hipLaunchKernelGGL(draw_lsh, dim3((unsigned)ceil_div(cur, 4)), dim3(256), 0, st, ix, lc, qkeys, cur, q0, cur,
+                         copies + q0 * K1, (const uint64_t*)nullptr, DensePairs{}, s, seed, src, dst);
+      STAG_TRY(check_launch("draw_lsh"));
+    }
   }
+  hipLaunchKernelGGL(edge_weights, dim3((unsigned)ceil_div(n * s, 256)), dim3(256), 0, st, dst, n, s, rest, w);
+  STAG_TRY(check_launch("edge_weights"));
   if (deg_out) {
     hipLaunchKernelGGL(one_plus, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st, rest, n, deg_out);
     STAG_TRY(check_launch("one_plus"));
