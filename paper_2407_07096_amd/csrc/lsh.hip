@@ -342,6 +342,75 @@ __global__ __launch_bounds__(256) void hash_queries(const float* __restrict__ Q,
   }
 }
 
+// Query keys of rows too wide for registers, K <= 8: a block takes 256 rows
+// (one per lane) and kHashTables tables.  The rows go through LDS kHashK
+// coordinates at a time, widened once, and a lane reads one coordinate for
+// the kHashTables * K chains that use it; the projections are wave-uniform
+// (scalar operands).  The same left-to-right chains as hash_queries, which
+// read its row's floats from memory for every table: 70,000 rows of 784, 136
+// tables of 6: 10.4 ms there, 3.9 ms here (1.15 ms of fused products at the
+// fp64 rate).  Two rows per lane (each scalar operand used twice) took 4.1 ms,
+// rows read in whole 64-byte pieces by four lanes each 4.4 ms.
+constexpr int kHashTables = 4, kHashK = 16;
+template <int K, bool VEC>
+__global__ __launch_bounds__(256) void hash_queries_wide(const float* __restrict__ Q, int64_t ldq, int64_t q0,
+                                                         int64_t mb, int d, int dg, const double* __restrict__ G8,
+                                                         const double* __restrict__ B, int L, int64_t ntab,
+                                                         uint64_t* __restrict__ qkeys) {
+  __shared__ double xs[kHashK * 256];
+  const int tid = threadIdx.x;
+  const int64_t ql = (int64_t)blockIdx.x * 256 + tid;
+  const bool live = ql < mb;
+  const float* xrow = Q + (q0 + (live ? ql : mb - 1)) * ldq;
+  const int64_t t0 = (int64_t)blockIdx.y * kHashTables;
+  double sum[kHashTables][K];
+#pragma unroll
+  for (int t = 0; t < kHashTables; ++t)
+#pragma unroll
+    for (int e = 0; e < K; ++e) sum[t][e] = 0.0;
+  const double* g[kHashTables];
+#pragma unroll
+  for (int t = 0; t < kHashTables; ++t) g[t] = G8 + min(t0 + t, ntab - 1) * dg * 8;
+  float st[kHashK];
+  auto gload = [&](int k0) {
+#pragma unroll
+    for (int k = 0; k < kHashK; k += 4) {
+      if (VEC && k0 + k + 4 <= d) {
+        const float4 v = *reinterpret_cast<const float4*>(xrow + k0 + k);
+        st[k] = v.x; st[k + 1] = v.y; st[k + 2] = v.z; st[k + 3] = v.w;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) st[k + e] = k0 + k + e < d ? xrow[k0 + k + e] : 0.0f;
+      }
+    }
+  };
+  gload(0);
+  for (int k0 = 0; k0 < d; k0 += kHashK) {
+    __syncthreads();  // the previous coordinates are used up
+#pragma unroll
+    for (int k = 0; k < kHashK; ++k) xs[k * 256 + tid] = (double)st[k];
+    __syncthreads();
+    if (k0 + kHashK < d) gload(k0 + kHashK);
+    const int kn = min(kHashK, d - k0);
+    for (int k = 0; k < kn; ++k) {
+      const double x = xs[k * 256 + tid];
+#pragma unroll
+      for (int t = 0; t < kHashTables; ++t)
+#pragma unroll
+        for (int e = 0; e < K; ++e) sum[t][e] = __builtin_fma(x, g[t][(int64_t)(k0 + k) * 8 + e], sum[t][e]);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < kHashTables; ++t) {
+    const int64_t tab = t0 + t;
+    if (tab >= ntab) break;
+    uint64_t h = mix64(kKeySalt ^ (uint64_t)(uint32_t)(tab % L));
+#pragma unroll
+    for (int e = 0; e < K; ++e) h = mix64(h ^ (uint64_t)(uint32_t)code_of(sum[t][e], B[tab * K + e]));
+    if (live) qkeys[tab * mb + ql] = h;
+  }
+}
+
 // Weight of an accepted term of level i, w_i(c) = exp(-a D) / (p_i R_i(c))
 // with c = sqrt(D) / r_i and R_i the recovery probability
 // 1 - (1 - p(c)^K)^L (R_i = 1 with STAG_LSH_LITERAL), from its Chebyshev
@@ -1633,6 +1702,31 @@ stag_status hash_query_batch(const stag_lsh_index* idx, const float* Q, int ldq,
         return fail(STAG_E_UNSUPPORTED, "query hashing: no register width");
       }
     });
+  }
+  const dim3 wide((unsigned)qb, (unsigned)ceil_div(idx->ntab, kHashTables));
+  // fewer blocks than 4 a compute unit leave the chip waiting on the longer
+  // chains of a block (5,000 rows of 200: 190 us per table, 310 us in fours)
+  if (idx->dreg == 0 && K <= 8 && wide.y <= 65535 && (int64_t)wide.x * wide.y >= 1024) {
+    const bool vec = ldq % 4 == 0 && ((uintptr_t)Q & 15u) == 0;
+    auto launch = [&](auto kern) {
+      hipLaunchKernelGGL(kern, wide, dim3(256), 0, st, Q, (int64_t)ldq, q0, cur, idx->d, idx->dg, idx->G8, idx->B,
+                         prm.shape.L, idx->ntab, qkeys);
+      return check_launch("hash_queries_wide");
+    };
+    auto by_k = [&](auto KC) {
+      constexpr int k = decltype(KC)::value;
+      return vec ? launch(hash_queries_wide<k, true>) : launch(hash_queries_wide<k, false>);
+    };
+    switch (K) {
+      case 1: return by_k(std::integral_constant<int, 1>());
+      case 2: return by_k(std::integral_constant<int, 2>());
+      case 3: return by_k(std::integral_constant<int, 3>());
+      case 4: return by_k(std::integral_constant<int, 4>());
+      case 5: return by_k(std::integral_constant<int, 5>());
+      case 6: return by_k(std::integral_constant<int, 6>());
+      case 7: return by_k(std::integral_constant<int, 7>());
+      default: return by_k(std::integral_constant<int, 8>());
+    }
   }
   return dispatch_dreg(idx->dreg, [&](auto D) {
     hipLaunchKernelGGL(hash_queries<decltype(D)::value>, dim3((unsigned)qb, (unsigned)ceil_div(idx->ntab, tpw)),

@@ -63,3 +63,21 @@ def test_dense_draws_match_oracle(n, d, s, kw):
     same = dst.cpu().numpy() == odst
     assert np.all(same[mg > 1e-9]) and same.mean() > 0.99
     np.testing.assert_allclose(w.cpu().numpy()[same], ow[same], rtol=1e-9)
+
+
+# enough queries that their keys are hashed a block of tables at a time; rows on
+# and off 16-byte boundaries, a ragged last block of rows and of tables
+@pytest.mark.parametrize("n,d,m,kw", [(900, 132, 13400, dict(k1=1, k2_constant=8, p_offset=0)),
+                                      (300, 131, 26001, dict(k1=2, k2_constant=3, p_offset=0))])
+def test_hashing_of_many_wide_queries(n, d, m, kw):
+    X, a, G0, B = _setup(n, d, 1500 + n, eps=0.5, **kw)
+    Q = np.resize(synth.sparse_uniform(700, d, 19), (m, d)).astype(np.float32)
+    announce(f"lsh wide hashing n={n} d={d} m={m} {kw}")
+    idx = stag.LshIndex(to_dev(X), a, G0=to_dev(G0), b=to_dev(B), seed=3, eps=0.5, **kw)
+    S, st = idx.query(to_dev(Q), stats=True)
+    R, sr = orc.lsh_kde(X, Q[:700], a, G0, B, seed=3, return_stats=True, eps=0.5, **kw)
+    S, nc = S.cpu().numpy(), st["n_cand"].cpu().numpy()
+    for k in range(0, m, 700):
+        c = min(700, m - k)
+        assert np.array_equal(nc[k:k + c], sr["n_cand"][:c])
+        np.testing.assert_allclose(S[k:k + c], R[:c], rtol=1e-9, atol=0)
