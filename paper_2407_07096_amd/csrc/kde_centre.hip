@@ -497,7 +497,6 @@ stag_status alloc_centred_operands(int64_t n, int d, Workspace& ws, Operands* ou
   for (int p = 0; p < 3; ++p) out->part[p] = nullptr;
   STAG_TRY(ws.alloc_bytes(&out->part[0], (size_t)rows_max * dp * sizeof(float)));
   STAG_TRY(ws.alloc(&out->off, (size_t)rows_max));
-  out->aug = nullptr;
   out->nrm = nullptr;
   out->max_nrm_bits = nullptr;
   out->centred = true;
@@ -575,7 +574,6 @@ stag_status alloc_centred_h_operands(int64_t n, int d, Workspace& ws, Operands* 
   for (int p = 0; p < 3; ++p) out->part[p] = nullptr;
   STAG_TRY(ws.alloc_bytes(&out->part[0], (size_t)rows_max * dp * sizeof(unsigned short)));
   STAG_TRY(ws.alloc(&out->off, (size_t)rows_max));
-  out->aug = nullptr;
   out->nrm = nullptr;
   out->max_nrm_bits = nullptr;
   out->centred = true;

@@ -17,7 +17,6 @@ struct Operands {
   int d = 0, dp = 0;
   void* part[3] = {nullptr, nullptr, nullptr};  // fp32 copy or split parts, [rows_pad][dp]
   float* off = nullptr;                         // -a log2(e) ||row||^2 (padding rows: -1e30 for data)
-  void* aug = nullptr;                          // 8 x bf16 augmentation operand per row (split forms)
   double* nrm = nullptr;                        // ||row||^2, fp64, [rows]
   unsigned long long* max_nrm_bits = nullptr;   // max ||row||^2 (fp64 bits)
   // Centred data (fp32 form, d <= 256): rows grouped into compact 32-row
@@ -220,6 +219,10 @@ stag_status prepare_operands(int form, const float* src, int64_t rows, int d, do
 // launch), then the preparation kernel into them.
 stag_status alloc_operands(int form, int64_t rows, int d, bool is_query, Workspace& ws, Operands* out);
 stag_status prep_operands(const float* src, double a, bool is_query, const Operands& o, hipStream_t st);
+// Both operand sets of a call in one launch, which also clears zero_words
+// 32-bit words at zero.  xo's largest norm is taken with `bound` only.
+stag_status prep_operand_pair(const float* X, const float* Q, double a, const Operands& xo, const Operands& qo,
+                              bool bound, void* zero, size_t zero_words, hipStream_t st);
 // Prepares `rows` query rows into a batch operand set (allocated by the
 // caller for batch.rows_pad rows) starting at row0 (a multiple of the query
 // tile, query_tile_rows()).
@@ -276,11 +279,15 @@ stag_status rescue_offsets_into(const Operands& xo, const Operands& qo, int P, d
 // pmax and p2 [P][m_pad]; Gaussian: shift, off2 [m_pad]; other kernels:
 // yshift [m_pad]).
 struct RescueBuffers {
-  int *flag = nullptr, *qflag = nullptr;
+  // one buffer of zero_words ints from flag on: flag [m], near_over [m]
+  // (exponential kernel), qflag [m_pad / 128]
+  int *flag = nullptr, *qflag = nullptr, *near_over = nullptr;
+  size_t zero_words = 0;
   double *pmax = nullptr, *p2 = nullptr, *shift = nullptr;
   float *off2 = nullptr, *yshift = nullptr;
 };
 stag_status alloc_rescue(int kernel, int P, const Operands& qo, Workspace& ws, RescueBuffers* rb);
+// (the flags cleared beforehand)
 stag_status reduce_with_rescue_into(const double* partial, int P, const Operands& qo, const Operands& xo,
                                     double a_tile, double scale, const BoundModel& bm, const RescueBuffers& rb,
                                     double* S_out, double* bound_out, hipStream_t st);

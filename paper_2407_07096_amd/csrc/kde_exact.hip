@@ -30,6 +30,7 @@
 // whatever other queries share a launch.
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 
 #include "runtime.h"
 #include "kde_exact.h"
@@ -68,75 +69,122 @@ __device__ inline void split_value(float v, unsigned short* p) {
   }
 }
 
-// One wave per row, 16 rows per wave, 64 rows per block.  `scale` multiplies
-// the operand (1 for data, 2a log2 e for queries); off = -a log2(e) ||row||^2
-// in fp32; aug = bf16 three-way parts of off laid out for the augmentation
-// step (data: [o1,o2,o3,1,1,1,0,0], queries: [1,1,1,o1,o2,o3,0,0]).  Rows >= n
-// are padding.  The block's largest norm goes to max_nrm_bits with one atomic.
-// With map, row r is src row map[r] (-1: padding), n unused.
-constexpr int kPrepRowsPerWave = 16;
-constexpr int kPrepRowsPerBlock = 4 * kPrepRowsPerWave;
+// One side (data or queries) of an operand preparation.  `scale` multiplies
+// the operand (1 for data, 2a log2 e for queries); off = neg_a_log2e ||row||^2
+// in fp32.  Rows >= n are padding; with map, row r is src row map[r] (-1:
+// padding), n unused.  max_nrm_bits (null: not wanted) takes the largest norm.
+struct PrepSide {
+  const float* src;
+  int64_t n, rows_pad;
+  double scale, neg_a_log2e;
+  int is_query;
+  void* part[3];
+  float* off;
+  double* nrm;
+  unsigned long long* max_nrm_bits;
+  const int* map;
+  int64_t blocks;  // workgroups of this side
+};
 
-template <int FORM>
-__global__ __launch_bounds__(256) void prep_rows(const float* __restrict__ src, int64_t n, int d, int dp,
-                                                 int64_t rows_pad, double scale, double neg_a_log2e,
-                                                 int is_query, void* __restrict__ part0, void* __restrict__ part1,
-                                                 void* __restrict__ part2, float* __restrict__ off,
-                                                 u16x8* __restrict__ aug, double* __restrict__ nrm,
-                                                 unsigned long long* __restrict__ max_nrm_bits,
-                                                 const int* __restrict__ map) {
+// Words that the preparation clears on the way (flags read by later launches).
+struct ZeroRange {
+  uint32_t* p = nullptr;
+  int64_t words = 0;
+};
+__device__ inline void clear_range(const ZeroRange& z) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < z.words; i += (int64_t)gridDim.x * 256) z.p[i] = 0u;
+}
+
+// Largest norm of a workgroup's rows, one atomic per workgroup.
+__device__ inline void block_max_norm(double mx, unsigned long long* out) {
   __shared__ double wmax[4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+  if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = mx;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const double b = fmax(fmax(wmax[0], wmax[1]), fmax(wmax[2], wmax[3]));
+    atomicMax(out, (unsigned long long)__double_as_longlong(b));
+  }
+}
+
+// Both sides of a call in one launch, LPR lanes per row (a power of two, 8
+// coordinates each), kPrepRows rows per thread with their loads in flight
+// together; VEC: every row starts at 16 bytes.  Bound by the rows' traffic (X
+// read once, the operands written once): 300,000 rows of 64 into the fp16
+// split form take 37 us (154 MB); a wave per row with one load in flight
+// took 93.
+constexpr int kPrepRows = 4;
+template <int FORM, int LPR, bool VEC>
+__global__ __launch_bounds__(256) void prep_rows(PrepSide x, PrepSide q, int d, int dp, ZeroRange zero) {
+  clear_range(zero);
+  const bool second = (int64_t)blockIdx.x >= x.blocks;
+  const PrepSide& side = second ? q : x;
+  const int64_t blk = second ? (int64_t)blockIdx.x - x.blocks : (int64_t)blockIdx.x;
+  constexpr int RPB = 256 / LPR;  // rows per round of the block
+  const int l = threadIdx.x % LPR, j0 = l * 8;
+  const bool act = j0 < dp;
+  int64_t row[kPrepRows];
+  bool real[kPrepRows];
+  float v[kPrepRows][8];
+#pragma unroll
+  for (int k = 0; k < kPrepRows; ++k) {
+    row[k] = (blk * kPrepRows + k) * RPB + threadIdx.x / LPR;
+    const int64_t sr = row[k] >= side.rows_pad ? -1 : (side.map ? (int64_t)side.map[row[k]] : row[k]);
+    real[k] = sr >= 0 && (side.map != nullptr || sr < side.n);
+    const float* src = side.src + (real[k] ? sr : 0) * (int64_t)d;
+    if (VEC && j0 + 8 <= d) {
+      const f32x4 lo = real[k] ? *reinterpret_cast<const f32x4*>(src + j0) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      const f32x4 hi = real[k] ? *reinterpret_cast<const f32x4*>(src + j0 + 4) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[k][e] = lo[e];
+        v[k][4 + e] = hi[e];
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[k][e] = real[k] && j0 + e < d ? src[j0 + e] : 0.0f;
+    }
+  }
   double mx = 0.0;
-  for (int rr = 0; rr < kPrepRowsPerWave; ++rr) {
-    const int64_t row = (int64_t)blockIdx.x * kPrepRowsPerBlock + wave * kPrepRowsPerWave + rr;
-    if (row >= rows_pad) break;
-    const int64_t srow = map ? (int64_t)map[row] : row;
-    const bool real = map ? srow >= 0 : row < n;
+#pragma unroll
+  for (int k = 0; k < kPrepRows; ++k) {
     double sq = 0.0;
-    for (int j = lane; j < dp; j += 64) {
-      float v = 0.0f;
-      if (real && j < d) v = src[srow * d + j];
-      sq += (double)v * (double)v;
-      const float w = (float)((double)v * scale);
-      const int64_t o = row * dp + j;
+    float w[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      sq += (double)v[k][e] * (double)v[k][e];
+      w[e] = (float)((double)v[k][e] * side.scale);
+    }
+    if (act && row[k] < side.rows_pad) {
+      const int64_t o = row[k] * dp + j0;
       if constexpr (FORM == STAG_FORM_FP32) {
-        static_cast<float*>(part0)[o] = w;
+        f32x4* dst = reinterpret_cast<f32x4*>(static_cast<float*>(side.part[0]) + o);
+        dst[0] = f32x4{w[0], w[1], w[2], w[3]};
+        dst[1] = f32x4{w[4], w[5], w[6], w[7]};
       } else {
-        unsigned short p[3] = {0, 0, 0};
-        split_value<FORM>(w, p);
-        static_cast<unsigned short*>(part0)[o] = p[0];
-        static_cast<unsigned short*>(part1)[o] = p[1];
-        if constexpr (FORM == STAG_FORM_BF16_SPLIT3) static_cast<unsigned short*>(part2)[o] = p[2];
+        constexpr int NP = FORM == STAG_FORM_BF16_SPLIT3 ? 3 : 2;
+        u16x8 p[3];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          unsigned short h[3] = {0, 0, 0};
+          split_value<FORM>(w[e], h);
+#pragma unroll
+          for (int i = 0; i < NP; ++i) p[i][e] = h[i];
+        }
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+          *reinterpret_cast<u16x8*>(static_cast<unsigned short*>(side.part[i]) + o) = p[i];
       }
     }
-    for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
-    if (real) mx = fmax(mx, sq);
-    if (lane == 0) {
-      const float ov = real ? (float)(neg_a_log2e * sq) : (is_query ? 0.0f : kPadOffset);
-      off[row] = ov;
-      if (aug) {
-        unsigned short p[3];
-        p[0] = bf16_rne(ov);
-        const float r = ov - bf16_to_f32(p[0]);
-        p[1] = bf16_rne(r);
-        p[2] = bf16_rne(r - bf16_to_f32(p[1]));
-        u16x8 v;
-        if (is_query) v = u16x8{kBf16One, kBf16One, kBf16One, p[0], p[1], p[2], 0, 0};
-        else v = u16x8{p[0], p[1], p[2], kBf16One, kBf16One, kBf16One, 0, 0};
-        aug[row] = v;
-      }
-      if (real && nrm) nrm[row] = sq;
+#pragma unroll
+    for (int o = LPR / 2; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+    if (real[k]) mx = fmax(mx, sq);
+    if (l == 0 && row[k] < side.rows_pad) {
+      side.off[row[k]] = real[k] ? (float)(side.neg_a_log2e * sq) : (side.is_query ? 0.0f : kPadOffset);
+      if (real[k] && side.nrm) side.nrm[row[k]] = sq;
     }
   }
-  if (max_nrm_bits) {
-    if (lane == 0) wmax[wave] = mx;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      const double b = fmax(fmax(wmax[0], wmax[1]), fmax(wmax[2], wmax[3]));
-      atomicMax(max_nrm_bits, (unsigned long long)__double_as_longlong(b));
-    }
-  }
+  if (side.max_nrm_bits) block_max_norm(mx, side.max_nrm_bits);
 }
 
 // Wide rows (dp > 256): the same preparation into the fragment layout of
@@ -147,24 +195,26 @@ __global__ __launch_bounds__(256) void prep_rows(const float* __restrict__ src, 
 // written once): 70,000 rows of 784 in the split form took 315 us with a wave
 // per row and one element per lane and load.
 template <int FORM, bool VEC>
-__global__ __launch_bounds__(256) void prep_wide(const float* __restrict__ src, int64_t n, int d, int dp, double scale,
-                                                 double neg_a_log2e, int is_query, char* __restrict__ part0,
-                                                 char* __restrict__ part1, float* __restrict__ off,
-                                                 double* __restrict__ nrm,
-                                                 unsigned long long* __restrict__ max_nrm_bits) {
+__global__ __launch_bounds__(256) void prep_wide(PrepSide x, PrepSide q, int d, int dp, ZeroRange zero) {
+  clear_range(zero);
+  const bool second = (int64_t)blockIdx.x >= x.blocks;
+  const PrepSide& side = second ? q : x;
   constexpr int E = FORM == STAG_FORM_FP32 ? 4 : 8;  // row elements per 16-byte piece
   __shared__ double psum[8][32];
   const int tid = threadIdx.x, r = tid & 31;
-  const int64_t tile = blockIdx.x;
+  const int64_t tile = second ? (int64_t)blockIdx.x - x.blocks : (int64_t)blockIdx.x;
   const int64_t row = tile * kTileRows + r;
-  const bool real = row < n;
-  const float* srow = src + (real ? row : 0) * (int64_t)d;
+  const bool real = row < side.n;
+  const float* srow = side.src + (real ? row : 0) * (int64_t)d;
+  char* part0 = static_cast<char*>(side.part[0]);
+  char* part1 = static_cast<char*>(side.part[1]);
+  const double scale = side.scale;
   const int pieces = dp / E, H = dp / 2;
   const int64_t base = tile * kTileRows * dp / E;  // the tile's first piece
   double sq = 0.0;
-  for (int q = tid >> 5; q < pieces; q += 8) {
-    // piece q = 2 s + h of its row
-    const int k0 = FORM == STAG_FORM_FP32 ? (q & 1) * H + 4 * (q >> 1) : 8 * q;
+  for (int pi = tid >> 5; pi < pieces; pi += 8) {
+    // piece pi = 2 s + h of its row
+    const int k0 = FORM == STAG_FORM_FP32 ? (pi & 1) * H + 4 * (pi >> 1) : 8 * pi;
     float v[E];
     if (VEC && real && k0 + E <= d) {
 #pragma unroll
@@ -176,7 +226,7 @@ __global__ __launch_bounds__(256) void prep_wide(const float* __restrict__ src, 
 #pragma unroll
       for (int e = 0; e < E; ++e) v[e] = real && k0 + e < d ? srow[k0 + e] : 0.0f;
     }
-    const int64_t o = (base + (int64_t)q * 32 + r) * 16;
+    const int64_t o = (base + (int64_t)pi * 32 + r) * 16;
     if constexpr (FORM == STAG_FORM_FP32) {
       f32x4 w;
 #pragma unroll
@@ -205,11 +255,12 @@ __global__ __launch_bounds__(256) void prep_wide(const float* __restrict__ src, 
     double s = psum[0][r];
 #pragma unroll
     for (int w = 1; w < 8; ++w) s += psum[w][r];
-    off[row] = real ? (float)(neg_a_log2e * s) : (is_query ? 0.0f : kPadOffset);
-    if (real && nrm) nrm[row] = s;
+    side.off[row] = real ? (float)(side.neg_a_log2e * s) : (side.is_query ? 0.0f : kPadOffset);
+    if (real && side.nrm) side.nrm[row] = s;
     double mx = real ? s : 0.0;
     for (int o = 16; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
-    if (tid == 0 && max_nrm_bits) atomicMax(max_nrm_bits, (unsigned long long)__double_as_longlong(mx));
+    if (tid == 0 && side.max_nrm_bits)
+      atomicMax(side.max_nrm_bits, (unsigned long long)__double_as_longlong(mx));
   }
 }
 
@@ -413,67 +464,59 @@ __global__ void scatter_results(const double* __restrict__ S_s, const double* __
   if (bound_out) bound_out[i] = B_s[q];
 }
 
+// One launch over both sides (the second may be empty: rows_pad 0).
 template <int FORM>
-stag_status launch_prep(const float* src, int64_t n, int d, int dp, int64_t rows_pad, double scale, double neg_a_l2e,
-                        int is_query, void* const* parts, float* off, u16x8* aug, double* nrm,
-                        unsigned long long* maxbits, hipStream_t st, const int* map) {
+stag_status launch_prep(PrepSide x, PrepSide q, int d, int dp, const ZeroRange& zero, hipStream_t st) {
   ScopedTimer tm("kde_prep", st);
-  hipLaunchKernelGGL(prep_rows<FORM>, dim3((unsigned)ceil_div(rows_pad, kPrepRowsPerBlock)), dim3(256), 0, st, src,
-                     n, d, dp, rows_pad, scale, neg_a_l2e, is_query, parts[0], parts[1], parts[2], off, aug, nrm,
-                     maxbits, map);
-  return check_launch("prep_rows");
-}
-
-template <int FORM>
-stag_status launch_prep_wide(const float* src, int64_t n, int d, int dp, int64_t rows_pad, double scale,
-                             double neg_a_l2e, int is_query, void* const* parts, float* off, double* nrm,
-                             unsigned long long* maxbits, hipStream_t st) {
-  ScopedTimer tm("kde_prep", st);
-  const dim3 grid((unsigned)(rows_pad / kTileRows));
   // 16-byte row reads where every row starts at one
-  const bool vec = d % 4 == 0 && ((uintptr_t)src & 15u) == 0;
-  auto launch = [&](auto kern) {
-    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, src, n, d, dp, scale, neg_a_l2e, is_query,
-                       static_cast<char*>(parts[0]), static_cast<char*>(parts[1]), off, nrm, maxbits);
+  const bool vec = d % 4 == 0 && (((uintptr_t)x.src | (uintptr_t)q.src) & 15u) == 0;
+  auto launch = [&](auto kern, int64_t rows_per_block) {
+    x.blocks = ceil_div(x.rows_pad, rows_per_block);
+    q.blocks = ceil_div(q.rows_pad, rows_per_block);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(x.blocks + q.blocks)), dim3(256), 0, st, x, q, d, dp, zero);
+    return check_launch("prep_rows");
   };
-  if (vec) launch(prep_wide<FORM, true>);
-  else launch(prep_wide<FORM, false>);
-  return check_launch("prep_wide");
-}
-
-stag_status prep_any(int form, const float* src, int64_t n, int d, int dp, int64_t rows_pad, double scale,
-                     double neg_a_l2e, int is_query, void* const* parts, float* off, u16x8* aug, double* nrm,
-                     unsigned long long* maxbits, hipStream_t st, const int* map = nullptr) {
   if (dp > 256) {  // the fragment layout of the wide tile
-    if (map || aug) return fail(STAG_E_UNSUPPORTED, "wide rows: no row map");
-    switch (form) {
-      case STAG_FORM_FP32:
-        return launch_prep_wide<STAG_FORM_FP32>(src, n, d, dp, rows_pad, scale, neg_a_l2e, is_query, parts, off, nrm,
-                                                maxbits, st);
-      case STAG_FORM_FP16_SPLIT:
-        return launch_prep_wide<STAG_FORM_FP16_SPLIT>(src, n, d, dp, rows_pad, scale, neg_a_l2e, is_query, parts, off,
-                                                      nrm, maxbits, st);
-      case STAG_FORM_BF16_SPLIT:
-        return launch_prep_wide<STAG_FORM_BF16_SPLIT>(src, n, d, dp, rows_pad, scale, neg_a_l2e, is_query, parts, off,
-                                                      nrm, maxbits, st);
-      default: return fail(STAG_E_UNSUPPORTED, "d > 256 needs the fp32, fp16 split or bf16 split form");
+    if constexpr (FORM == STAG_FORM_BF16_SPLIT3) {
+      return fail(STAG_E_UNSUPPORTED, "d > 256 needs the fp32, fp16 split or bf16 split form");
+    } else {
+      if (x.map || q.map) return fail(STAG_E_UNSUPPORTED, "wide rows: no row map");
+      return vec ? launch(prep_wide<FORM, true>, kTileRows) : launch(prep_wide<FORM, false>, kTileRows);
     }
   }
+  auto by_lanes = [&](auto LC) {
+    constexpr int lpr = decltype(LC)::value;
+    return vec ? launch(prep_rows<FORM, lpr, true>, kPrepRows * 256 / lpr)
+               : launch(prep_rows<FORM, lpr, false>, kPrepRows * 256 / lpr);
+  };
+  if (dp <= 16) return by_lanes(std::integral_constant<int, 2>());
+  if (dp <= 32) return by_lanes(std::integral_constant<int, 4>());
+  if (dp <= 64) return by_lanes(std::integral_constant<int, 8>());
+  if (dp <= 128) return by_lanes(std::integral_constant<int, 16>());
+  return by_lanes(std::integral_constant<int, 32>());
+}
+
+stag_status prep_sides(int form, const PrepSide& x, const PrepSide& q, int d, int dp, const ZeroRange& zero,
+                       hipStream_t st) {
   switch (form) {
-    case STAG_FORM_FP32:
-      return launch_prep<STAG_FORM_FP32>(src, n, d, dp, rows_pad, scale, neg_a_l2e, is_query, parts, off, aug, nrm,
-                                         maxbits, st, map);
-    case STAG_FORM_BF16_SPLIT:
-      return launch_prep<STAG_FORM_BF16_SPLIT>(src, n, d, dp, rows_pad, scale, neg_a_l2e, is_query, parts, off, aug,
-                                               nrm, maxbits, st, map);
-    case STAG_FORM_FP16_SPLIT:
-      return launch_prep<STAG_FORM_FP16_SPLIT>(src, n, d, dp, rows_pad, scale, neg_a_l2e, is_query, parts, off, aug,
-                                               nrm, maxbits, st, map);
-    default:
-      return launch_prep<STAG_FORM_BF16_SPLIT3>(src, n, d, dp, rows_pad, scale, neg_a_l2e, is_query, parts, off, aug,
-                                                nrm, maxbits, st, map);
+    case STAG_FORM_FP32: return launch_prep<STAG_FORM_FP32>(x, q, d, dp, zero, st);
+    case STAG_FORM_BF16_SPLIT: return launch_prep<STAG_FORM_BF16_SPLIT>(x, q, d, dp, zero, st);
+    case STAG_FORM_FP16_SPLIT: return launch_prep<STAG_FORM_FP16_SPLIT>(x, q, d, dp, zero, st);
+    default: return launch_prep<STAG_FORM_BF16_SPLIT3>(x, q, d, dp, zero, st);
   }
 }
+
+// The side of an operand set: the scaled split of src (data or queries), or,
+// plain, an unscaled copy with offset 0 (queries of centred data, whose tile
+// adds -a log2(e) ||q - c||^2 itself).
+PrepSide side_of(const float* src, double a, bool is_query, bool plain, const Operands& o, const int* map = nullptr) {
+  PrepSide p = {src, o.rows, o.rows_pad, plain || !is_query ? 1.0 : 2.0 * a * kLog2e, plain ? 0.0 : -a * kLog2e,
+                is_query ? 1 : 0, {o.part[0], o.part[1], o.part[2]}, o.off, o.nrm, o.max_nrm_bits, map, 0};
+  return p;
+}
+
+constexpr int kScanRowsPerWave = 16;
+constexpr int kScanRowsPerBlock = 4 * kScanRowsPerWave;
 
 // Statistics of an input for the form choice and the finiteness check: the
 // largest squared row norm (fp64 bits), the largest |element| (fp32 bits) and
@@ -485,8 +528,8 @@ __global__ __launch_bounds__(256) void scan_rows(const float* __restrict__ src, 
   double mx = 0.0;
   float amax = 0.0f;
   int nonfinite = 0;
-  for (int rr = 0; rr < kPrepRowsPerWave; ++rr) {
-    const int64_t row = (int64_t)blockIdx.x * kPrepRowsPerBlock + wave * kPrepRowsPerWave + rr;
+  for (int rr = 0; rr < kScanRowsPerWave; ++rr) {
+    const int64_t row = (int64_t)blockIdx.x * kScanRowsPerBlock + wave * kScanRowsPerWave + rr;
     if (row >= rows) break;
     double sq = 0.0;
     for (int j = lane; j < d; j += 64) {
@@ -536,7 +579,6 @@ stag_status alloc_operands(int form, int64_t rows, int d, bool is_query, Workspa
   for (int p = 0; p < form_parts(form); ++p)
     STAG_TRY(ws.alloc_bytes(&out->part[p], (size_t)rows_pad * dp * form_element_bytes(form)));
   STAG_TRY(ws.alloc(&out->off, (size_t)rows_pad));
-  out->aug = nullptr;  // the tiles take the offsets directly
   STAG_TRY(ws.alloc(&out->nrm, (size_t)rows));
   out->max_nrm_bits = nullptr;
   if (!is_query) STAG_TRY(ws.alloc(&out->max_nrm_bits, 1));
@@ -545,9 +587,16 @@ stag_status alloc_operands(int form, int64_t rows, int d, bool is_query, Workspa
 
 stag_status prep_operands(const float* src, double a, bool is_query, const Operands& o, hipStream_t st) {
   if (o.max_nrm_bits) STAG_TRY(zero_async(o.max_nrm_bits, sizeof(unsigned long long), st));
-  const double scale = is_query ? 2.0 * a * kLog2e : 1.0;
-  return prep_any(o.form, src, o.rows, o.d, o.dp, o.rows_pad, scale, -a * kLog2e, is_query ? 1 : 0, o.part, o.off,
-                  static_cast<u16x8*>(o.aug), o.nrm, o.max_nrm_bits, st);
+  return prep_sides(o.form, side_of(src, a, is_query, false, o), PrepSide{}, o.d, o.dp, ZeroRange(), st);
+}
+
+stag_status prep_operand_pair(const float* X, const float* Q, double a, const Operands& xo, const Operands& qo,
+                              bool bound, void* zero, size_t zero_words, hipStream_t st) {
+  PrepSide x = side_of(X, a, false, false, xo);
+  if (bound) STAG_TRY(zero_async(xo.max_nrm_bits, sizeof(unsigned long long), st));
+  else x.max_nrm_bits = nullptr;
+  return prep_sides(xo.form, x, side_of(Q, a, true, false, qo), xo.d, xo.dp,
+                    {static_cast<uint32_t*>(zero), (int64_t)zero_words}, st);
 }
 
 stag_status prepare_operands(int form, const float* src, int64_t rows, int d, double a, bool is_query,
@@ -560,17 +609,16 @@ int64_t exact_chunks(int64_t n_pad) { return ceil_div(n_pad, kChunkRows); }
 
 stag_status prep_query_into(int form, const float* src, int64_t rows, int d, double a, const Operands& batch,
                             int64_t row0, hipStream_t st, bool centred) {
-  const int dp = batch.dp;
-  const int64_t rows_pad = round_up(rows, kBQ);
-  const size_t eb = form_element_bytes(form);
-  void* parts[3] = {nullptr, nullptr, nullptr};
+  Operands o = batch;
+  o.rows = rows;
+  o.rows_pad = round_up(rows, kBQ);
   for (int p = 0; p < form_parts(form); ++p)
-    parts[p] = static_cast<char*>(batch.part[p]) + (size_t)row0 * dp * eb;
-  u16x8* aug = batch.aug ? static_cast<u16x8*>(batch.aug) + row0 : nullptr;
-  // queries of centred data are kept unscaled with offset 0 (the tile adds
-  // -a log2(e) ||q - c_T||^2 itself)
-  return prep_any(form, src, rows, d, dp, rows_pad, centred ? 1.0 : 2.0 * a * kLog2e, centred ? 0.0 : -a * kLog2e, 1,
-                  parts, batch.off + row0, aug, batch.nrm ? batch.nrm + row0 : nullptr, nullptr, st);
+    o.part[p] = static_cast<char*>(batch.part[p]) + (size_t)row0 * batch.dp * form_element_bytes(form);
+  o.off = batch.off + row0;
+  o.nrm = batch.nrm ? batch.nrm + row0 : nullptr;
+  o.max_nrm_bits = nullptr;
+  // queries of centred data are kept unscaled with offset 0
+  return prep_sides(form, side_of(src, a, true, centred, o), PrepSide{}, d, batch.dp, ZeroRange(), st);
 }
 
 stag_status row_stats_async(const float* A, int64_t rows, int d, unsigned long long* nrm_bits, unsigned int* abs_bits,
@@ -578,7 +626,7 @@ stag_status row_stats_async(const float* A, int64_t rows, int d, unsigned long l
   STAG_TRY(zero_async(nrm_bits, sizeof(unsigned long long), st));
   STAG_TRY(zero_async(abs_bits, sizeof(unsigned int), st));
   STAG_TRY(zero_async(bad, sizeof(int), st));
-  hipLaunchKernelGGL(scan_rows, dim3((unsigned)ceil_div(rows, kPrepRowsPerBlock)), dim3(256), 0, st, A, rows, d,
+  hipLaunchKernelGGL(scan_rows, dim3((unsigned)ceil_div(rows, kScanRowsPerBlock)), dim3(256), 0, st, A, rows, d,
                      nrm_bits, abs_bits, bad);
   return check_launch("scan_rows");
 }
@@ -952,8 +1000,16 @@ stag_status rescue_offsets(const Operands& xo, const Operands& qo, int P, double
 stag_status alloc_rescue(int kernel, int P, const Operands& qo, Workspace& ws, RescueBuffers* rb) {
   const int64_t m = qo.rows, m_pad = qo.rows_pad;
   *rb = RescueBuffers();
-  STAG_TRY(ws.alloc(&rb->flag, (size_t)m));
-  STAG_TRY(ws.alloc(&rb->qflag, (size_t)(m_pad / kBQ)));
+  // the flags in one buffer, cleared in one go
+  const int64_t mr = round_up(m, 64);
+  rb->zero_words = (size_t)(mr + m_pad / kBQ);
+  if (kernel == STAG_KERNEL_EXPONENTIAL) rb->zero_words = (size_t)(2 * mr + m_pad / kBQ);
+  STAG_TRY(ws.alloc(&rb->flag, rb->zero_words));
+  rb->qflag = rb->flag + mr;
+  if (kernel == STAG_KERNEL_EXPONENTIAL) {
+    rb->near_over = rb->flag + mr;
+    rb->qflag = rb->flag + 2 * mr;
+  }
   STAG_TRY(ws.alloc(&rb->pmax, (size_t)P * m_pad));
   STAG_TRY(ws.alloc(&rb->p2, (size_t)P * m_pad));
   if (kernel == STAG_KERNEL_GAUSSIAN) {
@@ -972,8 +1028,6 @@ stag_status reduce_with_rescue_y(const double* partial, int P, const Operands& q
                                  double scale, const BoundModel& bm, const int* near_over, const RescueBuffers& rb,
                                  double* S_out, double* bound_out, hipStream_t st) {
   const int64_t m = qo.rows, m_pad = qo.rows_pad;
-  STAG_TRY(zero_async(rb.flag, (size_t)m * sizeof(int), st));
-  STAG_TRY(zero_async(rb.qflag, (size_t)(m_pad / kBQ) * sizeof(int), st));
   STAG_TRY(launch_reduce(partial, P, qo, xo, scale, bm, S_out, bound_out, st, near_over, rb.flag, rb.qflag));
   TileExtra exm;
   exm.max_pass = 1;
@@ -995,8 +1049,6 @@ stag_status reduce_with_rescue_y(const double* partial, int P, const Operands& q
 stag_status reduce_with_rescue_into(const double* partial, int P, const Operands& qo, const Operands& xo,
                                     double a_tile, double scale, const BoundModel& bm, const RescueBuffers& rb,
                                     double* S_out, double* bound_out, hipStream_t st) {
-  STAG_TRY(zero_async(rb.flag, (size_t)qo.rows * sizeof(int), st));
-  STAG_TRY(zero_async(rb.qflag, (size_t)(qo.rows_pad / kBQ) * sizeof(int), st));
   STAG_TRY(launch_reduce(partial, P, qo, xo, scale, bm, S_out, bound_out, st, nullptr, rb.flag, rb.qflag));
   return rescue_underflow(xo, qo, P, a_tile, scale, bm, rb, S_out, bound_out, st);
 }
@@ -1006,6 +1058,7 @@ stag_status reduce_with_rescue(const double* partial, int P, const Operands& qo,
                                hipStream_t st) {
   RescueBuffers rb;
   STAG_TRY(alloc_rescue(STAG_KERNEL_GAUSSIAN, P, qo, ws, &rb));
+  STAG_TRY(zero_async(rb.flag, rb.zero_words * sizeof(int), st));
   return reduce_with_rescue_into(partial, P, qo, xo, a_tile, scale, bm, rb, S_out, bound_out, st);
 }
 
@@ -1028,10 +1081,10 @@ stag_status input_stats(const float* X, int64_t n, const float* Q, int64_t m, in
   STAG_HIP(hipMemsetAsync(nb, 0, 2 * sizeof(unsigned long long), st));
   STAG_HIP(hipMemsetAsync(ab, 0, 2 * sizeof(unsigned int), st));
   STAG_HIP(hipMemsetAsync(bad, 0, sizeof(int), st));
-  hipLaunchKernelGGL(scan_rows, dim3((unsigned)ceil_div(n, kPrepRowsPerBlock)), dim3(256), 0, st, X, n, d, nb, ab,
+  hipLaunchKernelGGL(scan_rows, dim3((unsigned)ceil_div(n, kScanRowsPerBlock)), dim3(256), 0, st, X, n, d, nb, ab,
                      bad);
   STAG_TRY(check_launch("scan_rows"));
-  hipLaunchKernelGGL(scan_rows, dim3((unsigned)ceil_div(m, kPrepRowsPerBlock)), dim3(256), 0, st, Q, m, d, nb + 1,
+  hipLaunchKernelGGL(scan_rows, dim3((unsigned)ceil_div(m, kScanRowsPerBlock)), dim3(256), 0, st, Q, m, d, nb + 1,
                      ab + 1, bad);
   STAG_TRY(check_launch("scan_rows"));
   unsigned long long hn[2];
@@ -1095,7 +1148,6 @@ struct ExactBuffers {
   Operands xo, qo;
   int P = 0;
   double* partial = nullptr;
-  int* near_over = nullptr;  // exponential kernel
   RescueBuffers rb;
   // centred data (fp32 or fp16 centred form, Gaussian kernel, d <= 256)
   bool centred = false;
@@ -1165,7 +1217,6 @@ stag_status alloc_exact(int form, int kernel, int64_t n, int64_t m, int d, Works
   STAG_TRY(alloc_operands(form, m, d, true, ws, &b->qo));
   b->P = (int)exact_chunks(b->xo.rows_pad);
   STAG_TRY(ws.alloc(&b->partial, (size_t)b->P * b->qo.rows_pad));
-  if (kernel == STAG_KERNEL_EXPONENTIAL) STAG_TRY(ws.alloc(&b->near_over, (size_t)m));
   STAG_TRY(alloc_parts(b->xo, b->qo, kernel, ws, &b->share));
   return alloc_rescue(kernel, b->P, b->qo, ws, &b->rb);
 }
@@ -1183,8 +1234,8 @@ stag_status run_centred(const float* X, int64_t n, const float* Q, int64_t m, in
     STAG_TRY(prep_centred_h_operands(X, a, xo, b.ct, st));
   else
     STAG_TRY(prep_centred_operands(X, a, xo, b.ct, st));
-  STAG_TRY(prep_any(STAG_FORM_FP32, Q, m, d, qo.dp, qo.rows_pad, 1.0, 0.0, 1, qo.part, qo.off, nullptr, qo.nrm,
-                    nullptr, st));
+  STAG_TRY(prep_sides(STAG_FORM_FP32, side_of(Q, a, true, true, qo), PrepSide{}, d, qo.dp,
+                      {reinterpret_cast<uint32_t*>(rb.flag), (int64_t)rb.zero_words}, st));
   const BoundModel bm = make_bound_model(STAG_FORM_FP32, d, a, STAG_KERNEL_GAUSSIAN);
   TileExtra ex = b.share;
   ex.a = a;
@@ -1193,8 +1244,6 @@ stag_status run_centred(const float* X, int64_t n, const float* Q, int64_t m, in
   STAG_TRY(launch_exact_tiles(xo, qo, b.partial, ex, st));
   const double scale = (flags & STAG_NORMALIZE) ? 1.0 / (double)n : 1.0;
   const int64_t m_pad = qo.rows_pad;
-  STAG_TRY(zero_async(rb.flag, (size_t)m * sizeof(int), st));
-  STAG_TRY(zero_async(rb.qflag, (size_t)(m_pad / kBQ) * sizeof(int), st));
   {
     ScopedTimer tm("kde_reduce", st);
     hipLaunchKernelGGL(reduce_centred, dim3((unsigned)ceil_div(m, 256)), dim3(256), 0, st, b.partial, b.bpart, b.P,
@@ -1243,13 +1292,11 @@ stag_status run_adaptive(const float* X, int64_t n, const float* Q, int64_t m, i
   const int n_qt256 = (int)ceil_div(m_pad, 256);
   STAG_TRY(prep_centred_h_operands(X, a, xo, b.ct, st));
   STAG_TRY(sort_queries(Q, m, m_pad, d, xo.dp, b.ct, b.qs, st));
-  STAG_TRY(prep_any(STAG_FORM_FP32, Q, m, d, qo.dp, m_pad, 1.0, 0.0, 1, qo.part, qo.off, nullptr, qo.nrm, nullptr,
-                    st, b.qs.perm));
+  STAG_TRY(prep_sides(STAG_FORM_FP32, side_of(Q, a, true, true, qo, b.qs.perm), PrepSide{}, d, qo.dp, ZeroRange(), st));
   STAG_TRY(zero_async(b.xs.max_nrm_bits, sizeof(unsigned long long), st));
-  STAG_TRY(prep_any(STAG_FORM_FP16_SPLIT, X, b.xs.rows, d, b.xs.dp, b.xs.rows_pad, 1.0, -a * kLog2e, 0, b.xs.part,
-                    b.xs.off, nullptr, b.xs.nrm, b.xs.max_nrm_bits, st, b.ct.map));
-  STAG_TRY(prep_any(STAG_FORM_FP16_SPLIT, Q, m, d, b.qsp.dp, b.qsp.rows_pad, 2.0 * a * kLog2e, -a * kLog2e, 1,
-                    b.qsp.part, b.qsp.off, nullptr, b.qsp.nrm, nullptr, st, b.qs.perm));
+  STAG_TRY(prep_sides(STAG_FORM_FP16_SPLIT, side_of(X, a, false, false, b.xs, b.ct.map),
+                      side_of(Q, a, true, false, b.qsp, b.qs.perm), d, b.xs.dp,
+                      {reinterpret_cast<uint32_t*>(b.rb.flag), (int64_t)b.rb.zero_words}, st));
   // first pass: one fp16 product per pair, with the bound numerators, then
   // the selection of the pairs to recompute (on the sampled tiles: qmask)
   const BoundModel bm1 = make_bound_model(STAG_FORM_FP32, d, a, STAG_KERNEL_GAUSSIAN);
@@ -1306,8 +1353,6 @@ stag_status run_adaptive(const float* X, int64_t n, const float* Q, int64_t m, i
   STAG_TRY(launch_exact_tiles(b.xs, b.qsp, b.partial, ex2, st));
   const BoundModel bm2 = make_bound_model(STAG_FORM_FP16_SPLIT, d, a, STAG_KERNEL_GAUSSIAN);
   const double scale = (flags & STAG_NORMALIZE) ? 1.0 / (double)n : 1.0;
-  STAG_TRY(zero_async(b.rb.flag, (size_t)m * sizeof(int), st));
-  STAG_TRY(zero_async(b.rb.qflag, (size_t)(m_pad / kBQ) * sizeof(int), st));
   {
     ScopedTimer tm("kde_reduce", st);
     hipLaunchKernelGGL(reduce_adaptive, dim3((unsigned)ceil_div(m, 256)), dim3(256), 0, st, b.partial, b.bpart,
@@ -1329,8 +1374,7 @@ stag_status run_exact(const float* X, int64_t n, const float* Q, int64_t m, int3
   if (b.adaptive) return run_adaptive(X, n, Q, m, d, a, flags, S_out, bound_out, b, stream);
   if (b.centred) return run_centred(X, n, Q, m, d, a, flags, S_out, bound_out, b, stream);
   const double at = kernel_tile_a(kernel, a);
-  STAG_TRY(prep_operands(X, at, false, b.xo, stream));
-  STAG_TRY(prep_operands(Q, at, true, b.qo, stream));
+  STAG_TRY(prep_operand_pair(X, Q, at, b.xo, b.qo, bound_out != nullptr, b.rb.flag, b.rb.zero_words, stream));
   TileExtra ex = b.share;
   ex.kernel = kernel;
   if (kernel == STAG_KERNEL_EXPONENTIAL) {
@@ -1340,8 +1384,7 @@ stag_status run_exact(const float* X, int64_t n, const float* Q, int64_t m, int3
     ex.near_e = (float)kNearY2;
     ex.a = a;
     ex.m_rows = m;
-    ex.near_over = b.near_over;
-    STAG_TRY(zero_async(ex.near_over, (size_t)m * sizeof(int), stream));
+    ex.near_over = b.rb.near_over;
   }
   STAG_TRY(launch_exact_tiles(b.xo, b.qo, b.partial, ex, stream));
   const double scale = (flags & STAG_NORMALIZE) ? 1.0 / (double)n : 1.0;

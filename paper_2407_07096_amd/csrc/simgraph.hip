@@ -329,8 +329,14 @@ stag_status sample_exact(const float* X, int64_t n, int d, double a, int form, i
                          int64_t* dst, double* w, double* deg_out, hipStream_t st) {
   Workspace ws(st);
   Operands xo, qo;
-  STAG_TRY(prepare_operands(form, X, n, d, a, false, ws, &xo, st));
-  STAG_TRY(prepare_operands(form, X, n, d, a, true, ws, &qo, st));
+  STAG_TRY(alloc_operands(form, n, d, false, ws, &xo));
+  STAG_TRY(alloc_operands(form, n, d, true, ws, &qo));
+  const int64_t nqt = qo.rows_pad / query_tile_rows();
+  const int64_t nr = round_up(n, 64);
+  int *flag = nullptr, *qflag = nullptr;
+  STAG_TRY(ws.alloc(&flag, (size_t)(nr + nqt)));
+  qflag = flag + nr;
+  STAG_TRY(prep_operand_pair(X, X, a, xo, qo, false, flag, (size_t)(nr + nqt), st));
   const int P = (int)exact_chunks(xo.rows_pad);
   const int64_t ntile = xo.rows_pad / 32;
   const int64_t tstride = round_up(ntile, 16);
@@ -351,17 +357,11 @@ stag_status sample_exact(const float* X, int64_t n, int d, double a, int form, i
   // underflow rescue: rows whose sum is below kRescueBelow get their
   // exponents shifted by their maximum over the other rows and a second self
   // pass (over their 128-row tiles only; other workgroups return at once)
-  const int64_t nqt = qo.rows_pad / query_tile_rows();
-  int *flag = nullptr, *qflag = nullptr;
   double *rest_draw = nullptr, *shift = nullptr;
   float* off2 = nullptr;
-  STAG_TRY(ws.alloc(&flag, (size_t)n));
-  STAG_TRY(ws.alloc(&qflag, (size_t)nqt));
   STAG_TRY(ws.alloc(&rest_draw, (size_t)n));
   STAG_TRY(ws.alloc(&shift, (size_t)qo.rows_pad));
   STAG_TRY(ws.alloc(&off2, (size_t)qo.rows_pad));
-  STAG_TRY(zero_async(flag, (size_t)n * sizeof(int), st));
-  STAG_TRY(zero_async(qflag, (size_t)nqt * sizeof(int), st));
   hipLaunchKernelGGL(row_rest, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st, partial, P, qo.rows_pad, n, rest,
                      deg_out, chunk_t, flag, qflag, (int)query_tile_rows());
   STAG_TRY(check_launch("row_rest"));

@@ -84,3 +84,21 @@ def test_shared_graph_pass_draws_as_the_oracle():
     same = dst.cpu().numpy() == o_dst
     # a draw differs only where its target lies within that error of a boundary
     assert np.all(same | (o_mg < tol))
+
+
+@pytest.mark.parametrize("form,d", [("fp32", 64), ("fp16_split", 128), ("bf16_split3", 32), ("fp16_adaptive", 96),
+                                    ("fp16_centred", 20), ("fp32", 320), ("bf16_split", 260)])
+def test_rows_off_16_bytes(form, d):
+    # the same rows at a 4-byte offset: read element by element, bit for bit the same operands
+    n, m = 1500, 70
+    X, Q, a = _data(n, m, d, 9300 + d)
+    Xd, Qd = to_dev(X), to_dev(Q)
+
+    def shifted(t):
+        buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+        buf[1:] = t.reshape(-1)
+        return buf[1:].view(t.shape)
+    announce(f"unaligned rows form={form} d={d}")
+    S, B = stag.kde_exact(Xd, Qd, a, form=form, return_bound=True)
+    S2, B2 = stag.kde_exact(shifted(Xd), shifted(Qd), a, form=form, return_bound=True)
+    assert torch.equal(S, S2) and torch.equal(B, B2)
