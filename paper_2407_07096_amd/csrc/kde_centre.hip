@@ -17,12 +17,14 @@
 //   assign_seeds      every row's nearest seed (largest (x - r).(s - r) -
 //                     ||s - r||^2/2, the product in fp16 on the matrix
 //                     cores, ties to the lower seed)
-//   label_hist        per 1024-row block, the rows of each seed
+//   label_hist        per 1024-row block, the rows of each seed (and the row
+//                     map cleared)
 //   scan_labels       per seed, the exclusive sum over blocks
-//   group_offsets     group k starts at sum_{k' < k} ceil32(count_k'), so
+//   scatter_labels    group k starts at sum_{k' < k} ceil32(count_k'), so
 //                     every group fills whole tiles; the padded row count
-//                     goes to device memory (the tiles read it there)
-//   scatter_labels    row i goes to its group in ascending i (ballot ranks)
+//                     goes to device memory (the tiles read it there); row i
+//                     goes to its group in ascending i (ballot ranks)
+//   group_small       the three in one workgroup where the rows are few
 //   build_tiles       per 32-row tile: centre c_T = fl32(mean of its rows),
 //                     rows fl32(x - c_T), beta = fl32(-a log2(e) ||x - c_T||^2)
 //                     (binary64 from the exact fp64 differences), radius
@@ -95,7 +97,8 @@ __global__ __launch_bounds__(256) void pick_seeds(const float* __restrict__ X, i
 // nearest seeds lie within about 2^-10 ||x - r|| ||s - r|| of each other to
 // the farther one: any assignment is valid (the centres and radii are
 // measured on the groups as formed), and this one is deterministic.
-template <int DP>
+// VEC: every row of X starts at 16 bytes.
+template <int DP, bool VEC>
 __global__ __launch_bounds__(256) void assign_seeds(const float* __restrict__ X, int64_t n, int d,
                                                     const float* __restrict__ seeds, const float* __restrict__ hn,
                                                     const float* __restrict__ ref, int K_pad,
@@ -110,10 +113,18 @@ __global__ __launch_bounds__(256) void assign_seeds(const float* __restrict__ X,
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
     u16x8 o;
+    const int j0 = s * 16 + h * 8;
+    if (VEC && j0 + 8 <= d) {
+      const f32x4* xp = reinterpret_cast<const f32x4*>(X + (row < n ? row : 0) * d + j0);
+      const f32x4 lo = xp[0], hi = xp[1];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int j = s * 16 + h * 8 + i;
-      o[i] = f16_rne((row < n && j < d) ? X[row * d + j] - ref[j] : 0.0f);
+      for (int i = 0; i < 8; ++i) o[i] = f16_rne(row < n ? (i < 4 ? lo[i & 3] : hi[i & 3]) - ref[j0 + i] : 0.0f);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int j = j0 + i;
+        o[i] = f16_rne((row < n && j < d) ? X[row * d + j] - ref[j] : 0.0f);
+      }
     }
     bq[s] = o;
   }
@@ -159,9 +170,11 @@ __global__ __launch_bounds__(256) void assign_seeds(const float* __restrict__ X,
   if (h == 0 && row < n) label[row] = (uint8_t)bests;
 }
 
-// hist[k * nblk + b] = rows of block b (kHistBlock rows) with label k.
+// hist[k * nblk + b] = rows of block b (kHistBlock rows) with label k; the
+// blocks also set the map_len entries of map to -1 between them.
 __global__ __launch_bounds__(256) void label_hist(const uint8_t* __restrict__ label, int64_t n, int K, int64_t nblk,
-                                                  uint32_t* __restrict__ hist) {
+                                                  uint32_t* __restrict__ hist, int* __restrict__ map,
+                                                  int64_t map_len) {
   __shared__ uint32_t cnt[256];
   cnt[threadIdx.x] = 0;
   __syncthreads();
@@ -170,8 +183,27 @@ __global__ __launch_bounds__(256) void label_hist(const uint8_t* __restrict__ la
     const int64_t i = base + r * 256 + threadIdx.x;
     if (i < n) atomicAdd(&cnt[label[i]], 1u);
   }
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < map_len; i += (int64_t)gridDim.x * 256) map[i] = -1;
   __syncthreads();
   if ((int)threadIdx.x < K) hist[(int64_t)threadIdx.x * nblk + blockIdx.x] = cnt[threadIdx.x];
+}
+
+// Exclusive sum over the first 256 threads of a workgroup (in thread order;
+// lds: 256 words); *total the sum.  Every thread of the workgroup calls it.
+__device__ inline uint32_t scan256(uint32_t v, uint32_t* lds, uint32_t* total) {
+  const int tid = threadIdx.x;
+  if (tid < 256) lds[tid] = v;
+  __syncthreads();
+  for (int o = 1; o < 256; o <<= 1) {
+    const uint32_t y = tid < 256 && tid >= o ? lds[tid - o] : 0u;
+    __syncthreads();
+    if (tid < 256) lds[tid] += y;
+    __syncthreads();
+  }
+  const uint32_t incl = tid < 256 ? lds[tid] : 0u;
+  *total = lds[255];
+  __syncthreads();
+  return incl - v;
 }
 
 // One workgroup per label k: exclusive sum of hist[k][0..nblk) in place;
@@ -184,19 +216,9 @@ __global__ __launch_bounds__(256) void scan_labels(uint32_t* __restrict__ hist, 
   const int64_t b0 = (int64_t)threadIdx.x * per;
   uint32_t s = 0;
   for (int64_t b = b0; b < b0 + per && b < nblk; ++b) s += h[b];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t run = 0;
-    for (int t = 0; t < 256; ++t) {
-      const uint32_t v = part[t];
-      part[t] = run;
-      run += v;
-    }
-    count[blockIdx.x] = run;
-  }
-  __syncthreads();
-  uint32_t run = part[threadIdx.x];
+  uint32_t total;
+  uint32_t run = scan256(s, part, &total);
+  if (threadIdx.x == 0) count[blockIdx.x] = total;
   for (int64_t b = b0; b < b0 + per && b < nblk; ++b) {
     const uint32_t v = h[b];
     h[b] = run;
@@ -204,29 +226,43 @@ __global__ __launch_bounds__(256) void scan_labels(uint32_t* __restrict__ hist, 
   }
 }
 
-// goff[k] = sum_{k' < k} count[k'] rounded up to a multiple of align_mask + 1
-// (32 for data: whole tiles; 1 for queries); n_pad = goff[K].  One thread.
-__global__ void group_offsets(const uint32_t* __restrict__ count, int K, uint32_t align_mask,
-                              uint32_t* __restrict__ goff, int64_t* __restrict__ n_pad) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  uint32_t run = 0;
-  for (int k = 0; k < K; ++k) {
-    goff[k] = run;
-    run += (count[k] + align_mask) & ~align_mask;
+// Lanes of the wave whose 8-bit key equals this lane's, among the valid ones.
+__device__ inline uint64_t key_peers(uint32_t key, bool valid) {
+  uint64_t peers = __ballot(valid);
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    const bool bit = (key >> b) & 1u;
+    const uint64_t ones = __ballot(bit);
+    peers &= bit ? ones : ~ones;
   }
-  goff[K] = run;
-  *n_pad = (int64_t)run;
+  return peers;
 }
 
-// map[goff[k] + (rank of row i among the rows of label k)] = i, rows in
-// ascending order within a label: the block's base from the scanned
-// histogram, then 256 rows per round ranked with 8 ballots per wave.
+// goff[k] = sum_{k' < k} count[k'] rounded up to a multiple of align_mask + 1
+// (32 for data: whole tiles; 1 for queries), n_pad = goff[K] (every block
+// takes the sums itself, block 0 writes them); then map[goff[k] + (rank of row
+// i among the rows of label k)] = i, rows in ascending order within a label:
+// the block's base from the scanned histogram, 256 rows per round ranked with
+// 8 ballots per wave.
 __global__ __launch_bounds__(256) void scatter_labels(const uint8_t* __restrict__ label, int64_t n, int64_t nblk,
                                                       const uint32_t* __restrict__ hist,
-                                                      const uint32_t* __restrict__ goff, int* __restrict__ map) {
+                                                      const uint32_t* __restrict__ count, int K, uint32_t align_mask,
+                                                      uint32_t* __restrict__ goff, int64_t* __restrict__ n_pad,
+                                                      int* __restrict__ map) {
+  __shared__ uint32_t start[256];
   __shared__ uint32_t running[256];
   __shared__ uint32_t wcount[4][256];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  uint32_t total;
+  const uint32_t s = scan256(tid < K ? (count[tid] + align_mask) & ~align_mask : 0u, running, &total);
+  start[tid] = s;
+  if (blockIdx.x == 0) {
+    if (tid < K) goff[tid] = s;
+    if (tid == 0) {
+      goff[K] = total;
+      *n_pad = (int64_t)total;
+    }
+  }
   running[tid] = 0;
   for (int w = 0; w < 4; ++w) wcount[w][tid] = 0;
   __syncthreads();
@@ -236,20 +272,14 @@ __global__ __launch_bounds__(256) void scatter_labels(const uint8_t* __restrict_
     const int64_t i = base + r * 256 + tid;
     const bool valid = i < n;
     const uint32_t key = valid ? label[i] : 0u;
-    uint64_t peers = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const bool bit = (key >> b) & 1u;
-      const uint64_t ones = __ballot(bit);
-      peers &= bit ? ones : ~ones;
-    }
+    const uint64_t peers = key_peers(key, valid);
     const uint32_t rank = (uint32_t)__popcll(peers & lt_mask);
     if (valid && rank == 0) wcount[wave][key] = (uint32_t)__popcll(peers);
     __syncthreads();
     if (valid) {
       uint32_t before = running[key];
       for (int w = 0; w < wave; ++w) before += wcount[w][key];
-      map[goff[key] + hist[(int64_t)key * nblk + blockIdx.x] + before + rank] = (int)i;
+      map[start[key] + hist[(int64_t)key * nblk + blockIdx.x] + before + rank] = (int)i;
     }
     __syncthreads();
     running[tid] += wcount[0][tid] + wcount[1][tid] + wcount[2][tid] + wcount[3][tid];
@@ -258,13 +288,108 @@ __global__ __launch_bounds__(256) void scatter_labels(const uint8_t* __restrict_
   }
 }
 
-__global__ void fill_minus_one(int* __restrict__ p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = -1;
+// label_hist, scan_labels and scatter_labels in one workgroup of 1024 threads
+// (n <= kGroupSmall): the counts with LDS atomics, the group starts, then 1024
+// rows per round ranked as in scatter_labels.  Three launches cost a small
+// call more than the rows do.
+constexpr int64_t kGroupSmall = 8192;
+__global__ __launch_bounds__(1024) void group_small(const uint8_t* __restrict__ label, int n, int K,
+                                                    uint32_t align_mask, uint32_t* __restrict__ count,
+                                                    uint32_t* __restrict__ goff, int64_t* __restrict__ n_pad,
+                                                    int* __restrict__ map, int64_t map_len) {
+  __shared__ uint32_t cnt[256], lds[256], running[256];
+  __shared__ uint16_t wcount[16][256];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (tid < 256) cnt[tid] = 0;
+  for (int k = tid; k < 16 * 256; k += 1024) wcount[k >> 8][k & 255] = 0;
+  for (int64_t i = tid; i < map_len; i += 1024) map[i] = -1;
+  __syncthreads();
+  for (int i = tid; i < n; i += 1024) atomicAdd(&cnt[label[i]], 1u);
+  __syncthreads();
+  uint32_t total;
+  const uint32_t c = tid < K ? cnt[tid] : 0u;
+  const uint32_t s = scan256((c + align_mask) & ~align_mask, lds, &total);
+  if (tid < 256) running[tid] = s;
+  if (tid < K) {
+    count[tid] = c;
+    goff[tid] = s;
+  }
+  if (tid == 0) {
+    goff[K] = total;
+    *n_pad = (int64_t)total;
+  }
+  // (the map's -1 entries are this workgroup's own stores, ordered by the barrier)
+  __threadfence_block();
+  __syncthreads();
+  const uint64_t lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  for (int base = 0; base < n; base += 1024) {
+    const int i = base + tid;
+    const bool valid = i < n;
+    const uint32_t key = valid ? label[i] : 0u;
+    const uint64_t peers = key_peers(key, valid);
+    const uint32_t rank = (uint32_t)__popcll(peers & lt_mask);
+    if (valid && rank == 0) wcount[wave][key] = (uint16_t)__popcll(peers);
+    __syncthreads();
+    if (valid) {
+      uint32_t before = running[key];
+      for (int w = 0; w < wave; ++w) before += wcount[w][key];
+      map[before + rank] = i;
+    }
+    __syncthreads();
+    if (tid < 256) {
+      uint32_t add = 0;
+      for (int w = 0; w < 16; ++w) {
+        add += wcount[w][tid];
+        wcount[w][tid] = 0;
+      }
+      running[tid] += add;
+    }
+    __syncthreads();
+  }
+}
+
+// Rows r0 .. r0 + R - 1 of a 32-row tile, lanes holding coordinates j = lane +
+// 64 c: every load issued before the first use.  m: lane l holds the index of
+// row l % 32 or -1; src[r] (uniform) row r0 + r's.
+template <int NC, int R>
+__device__ inline void load_rows(const float* __restrict__ X, int d, int m, int r0, int* src, float (*x)[NC]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    src[r] = __builtin_amdgcn_readlane(m, r0 + r);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int j = lane + 64 * c;
+      x[r][c] = src[r] >= 0 && j < d ? X[(int64_t)src[r] * d + j] : 0.0f;
+    }
+  }
+}
+
+// Wave sums of 32 values at once, the sum of value r in lanes 2r and 2r + 1:
+// each halving step adds lanes l and l ^ o for o = 32 .. 1, as a butterfly
+// per value would (the same pairs, so the same bits), with 32 exchanges
+// instead of 192.
+__device__ inline double wave_sums32(double* v) {
+  const int lane = threadIdx.x & 63;
+  int o = 32;
+#pragma unroll
+  for (int half = 16; half > 0; half >>= 1, o >>= 1) {
+    const bool up = (lane & o) != 0;
+#pragma unroll
+    for (int i = 0; i < half; ++i) {
+      const double keep = up ? v[half + i] : v[i], give = up ? v[i] : v[half + i];
+      v[i] = keep + __shfl_xor(give, o);
+    }
+  }
+  return v[0] + __shfl_xor(v[0], 1);
 }
 
 // One wave per 32-row tile below the padded row count (4 tiles per block).
-// Lanes hold coordinates j = lane + 64 c.
+// Lanes hold coordinates j = lane + 64 c.  The tile's rows are read once, all
+// loads in flight, and kept in registers (two passes of a load per row took
+// 46 us at n = 1e5, d = 64, now 27; 24 us at n = 1,000, d = 10, now 10).
+// (build_tiles_h keeps the row loop: at n = 2e6, d = 128 it takes 0.67 ms, 0.85
+// with eight rows in flight and 1.09 with all 32, for want of waves.)
 template <int DP>
 __global__ __launch_bounds__(256) void build_tiles(const float* __restrict__ X, int d, const int* __restrict__ map,
                                                    const int64_t* __restrict__ n_pad, double neg_a_log2e,
@@ -274,19 +399,20 @@ __global__ __launch_bounds__(256) void build_tiles(const float* __restrict__ X, 
   const int lane = threadIdx.x & 63;
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t * kTileRows >= *n_pad) return;
+  const int m = map[t * kTileRows + (lane & 31)];
+  int src[kTileRows];
+  float x[kTileRows][NC];
+  load_rows<NC, kTileRows>(X, d, m, 0, src, x);
   double sum[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) sum[c] = 0.0;
   int cnt = 0;
+#pragma unroll
   for (int r = 0; r < kTileRows; ++r) {
-    const int src = map[t * kTileRows + r];
-    if (src < 0) continue;
+    if (src[r] < 0) continue;
     ++cnt;
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int j = lane + 64 * c;
-      if (j < d) sum[c] += (double)X[(int64_t)src * d + j];
-    }
+    for (int c = 0; c < NC; ++c) sum[c] += (double)x[r][c];
   }
   float cen[NC];
 #pragma unroll
@@ -295,26 +421,28 @@ __global__ __launch_bounds__(256) void build_tiles(const float* __restrict__ X, 
     cen[c] = (j < d && cnt > 0) ? (float)(sum[c] / (double)cnt) : 0.0f;
     if (j < DP) centre[t * DP + j] = cen[c];
   }
-  double rmax = 0.0;
+  double sq[kTileRows];
+#pragma unroll
   for (int r = 0; r < kTileRows; ++r) {
-    const int64_t row = t * kTileRows + r;
-    const int src = map[row];
-    double sq = 0.0;
+    sq[r] = 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const int j = lane + 64 * c;
       float v = 0.0f;
-      if (src >= 0 && j < d) {
-        const double e = (double)X[(int64_t)src * d + j] - (double)cen[c];  // exact in binary64
+      if (src[r] >= 0 && j < d) {
+        const double e = (double)x[r][c] - (double)cen[c];  // exact in binary64
         v = (float)e;
-        sq = fma(e, e, sq);
+        sq[r] = fma(e, e, sq[r]);
       }
-      if (j < DP) Xc[row * DP + j] = v;
+      if (j < DP) Xc[(t * kTileRows + r) * DP + j] = v;
     }
-    for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
-    if (src >= 0) rmax = fmax(rmax, sq);
-    if (lane == 0) beta[row] = src >= 0 ? (float)(neg_a_log2e * sq) : kPadOffset;
   }
+  // lane l: row l / 2
+  const double s2 = wave_sums32(sq);
+  const bool real = map[t * kTileRows + (lane >> 1)] >= 0;
+  if ((lane & 1) == 0) beta[t * kTileRows + (lane >> 1)] = real ? (float)(neg_a_log2e * s2) : kPadOffset;
+  double rmax = real ? s2 : 0.0;
+  for (int o = 32; o > 0; o >>= 1) rmax = fmax(rmax, __shfl_xor(rmax, o));
   if (lane == 0) {
     const float rf = (float)sqrt(rmax);
     radius[t] = (double)rf < sqrt(rmax) ? nextafterf(rf, HUGE_VALF) : rf;
@@ -330,16 +458,20 @@ __global__ __launch_bounds__(256) void tile_sums(const float* __restrict__ X, in
   const int lane = threadIdx.x & 63;
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t * kTileRows >= *n_pad) return;
+  const int m = map[t * kTileRows + (lane & 31)];
   double sum[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) sum[c] = 0.0;
-  for (int r = 0; r < kTileRows; ++r) {
-    const int src = map[t * kTileRows + r];
-    if (src < 0) continue;
+#pragma unroll 1
+  for (int r0 = 0; r0 < kTileRows; r0 += 8) {
+    int src[8];
+    float x[8][NC];
+    load_rows<NC, 8>(X, d, m, r0, src, x);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int j = lane + 64 * c;
-      if (j < d) sum[c] += (double)X[(int64_t)src * d + j];
+    for (int r = 0; r < 8; ++r) {
+      if (src[r] < 0) continue;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) sum[c] += (double)x[r][c];
     }
   }
 #pragma unroll
@@ -362,7 +494,16 @@ __global__ __launch_bounds__(256) void group_centres(const double* __restrict__ 
     float c = 0.0f;
     if (g < K && count[g] > 0) {
       double s = 0.0;
-      for (uint32_t t = goff[g] / kTileRows; t < goff[g + 1] / kTileRows; ++t) s += tsum[(int64_t)t * DP + j];
+      uint32_t t = goff[g] / kTileRows;
+      const uint32_t te = goff[g + 1] / kTileRows;
+      for (; t + 8 <= te; t += 8) {  // loads eight at a time, added in order
+        double v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = tsum[(int64_t)(t + i) * DP + j];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s += v[i];
+      }
+      for (; t < te; ++t) s += tsum[(int64_t)t * DP + j];
       c = (float)(s / (double)count[g]);
     }
     centre[(int64_t)g * DP + j] = c;
@@ -429,8 +570,12 @@ __global__ __launch_bounds__(256) void build_tiles_h(const float* __restrict__ X
 
 template <int DP>
 stag_status launch_assign(const float* X, int64_t n, int d, const CentreTemp& t, hipStream_t st) {
-  hipLaunchKernelGGL(assign_seeds<DP>, dim3((unsigned)ceil_div(n, 128)), dim3(256), 0, st, X, n, d, t.seeds, t.hn,
-                     t.ref, t.K_pad, t.label);
+  auto launch = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(n, 128)), dim3(256), 0, st, X, n, d, t.seeds, t.hn, t.ref,
+                       t.K_pad, t.label);
+  };
+  if (d % 4 == 0 && ((uintptr_t)X & 15u) == 0) launch(assign_seeds<DP, true>);
+  else launch(assign_seeds<DP, false>);
   return check_launch("assign_seeds");
 }
 
@@ -506,6 +651,25 @@ stag_status alloc_centred_operands(int64_t n, int d, Workspace& ws, Operands* ou
   return STAG_OK;
 }
 
+// Rows (labels, n of them) ordered by label: counts, group starts (aligned to
+// align_mask + 1 rows), their total and the row map.
+static stag_status order_by_label(const uint8_t* label, int64_t n, int K, int64_t nblk, uint32_t align_mask,
+                                  uint32_t* hist, uint32_t* count, uint32_t* goff, int64_t* total, int* map,
+                                  int64_t map_len, hipStream_t st) {
+  if (n <= kGroupSmall) {
+    hipLaunchKernelGGL(group_small, dim3(1), dim3(1024), 0, st, label, (int)n, K, align_mask, count, goff, total, map,
+                       map_len);
+    return check_launch("group_small");
+  }
+  hipLaunchKernelGGL(label_hist, dim3((unsigned)nblk), dim3(256), 0, st, label, n, K, nblk, hist, map, map_len);
+  STAG_TRY(check_launch("label_hist"));
+  hipLaunchKernelGGL(scan_labels, dim3((unsigned)K), dim3(256), 0, st, hist, nblk, count);
+  STAG_TRY(check_launch("scan_labels"));
+  hipLaunchKernelGGL(scatter_labels, dim3((unsigned)nblk), dim3(256), 0, st, label, n, nblk, hist, count, K,
+                     align_mask, goff, total, map);
+  return check_launch("scatter_labels");
+}
+
 // The grouping shared by both centred forms: seeds, nearest seed of every
 // row, per-label counts and offsets (n_pad), and the row map.
 static stag_status group_rows(const float* X, const Operands& o, const CentreTemp& t, hipStream_t st) {
@@ -526,18 +690,7 @@ static stag_status group_rows(const float* X, const Operands& o, const CentreTem
     case 256: STAG_TRY(launch_assign<256>(X, n, d, t, st)); break;
     default: return fail(STAG_E_UNSUPPORTED, "centred operands: padded dimension %d", dp);
   }
-  hipLaunchKernelGGL(label_hist, dim3((unsigned)t.nblk), dim3(256), 0, st, t.label, n, t.K, t.nblk, t.hist);
-  STAG_TRY(check_launch("label_hist"));
-  hipLaunchKernelGGL(scan_labels, dim3((unsigned)t.K), dim3(256), 0, st, t.hist, t.nblk, t.count);
-  STAG_TRY(check_launch("scan_labels"));
-  hipLaunchKernelGGL(group_offsets, dim3(1), dim3(64), 0, st, t.count, t.K, 31u, t.goff, o.n_pad_dev);
-  STAG_TRY(check_launch("group_offsets"));
-  hipLaunchKernelGGL(fill_minus_one, dim3((unsigned)ceil_div(o.rows_pad, 256)), dim3(256), 0, st, t.map, o.rows_pad);
-  STAG_TRY(check_launch("fill_minus_one"));
-  hipLaunchKernelGGL(scatter_labels, dim3((unsigned)t.nblk), dim3(256), 0, st, t.label, n, t.nblk, t.hist, t.goff,
-                     t.map);
-  STAG_TRY(check_launch("scatter_labels"));
-  return STAG_OK;
+  return order_by_label(t.label, n, t.K, t.nblk, 31u, t.hist, t.count, t.goff, o.n_pad_dev, t.map, o.rows_pad, st);
 }
 
 stag_status prep_centred_operands(const float* X, double a_tile, const Operands& o, const CentreTemp& t,
@@ -633,17 +786,7 @@ stag_status sort_queries(const float* Q, int64_t m, int64_t m_pad, int d, int dp
     case 256: STAG_TRY(launch_assign<256>(Q, m, d, tq, st)); break;
     default: return fail(STAG_E_UNSUPPORTED, "query sort: padded dimension %d", dp);
   }
-  hipLaunchKernelGGL(label_hist, dim3((unsigned)qs.nblk), dim3(256), 0, st, qs.label, m, t.K, qs.nblk, qs.hist);
-  STAG_TRY(check_launch("label_hist"));
-  hipLaunchKernelGGL(scan_labels, dim3((unsigned)t.K), dim3(256), 0, st, qs.hist, qs.nblk, qs.count);
-  STAG_TRY(check_launch("scan_labels"));
-  hipLaunchKernelGGL(group_offsets, dim3(1), dim3(64), 0, st, qs.count, t.K, 0u, qs.goff, qs.total);
-  STAG_TRY(check_launch("group_offsets"));
-  hipLaunchKernelGGL(fill_minus_one, dim3((unsigned)ceil_div(m_pad, 256)), dim3(256), 0, st, qs.perm, m_pad);
-  STAG_TRY(check_launch("fill_minus_one"));
-  hipLaunchKernelGGL(scatter_labels, dim3((unsigned)qs.nblk), dim3(256), 0, st, qs.label, m, qs.nblk, qs.hist,
-                     qs.goff, qs.perm);
-  return check_launch("scatter_labels");
+  return order_by_label(qs.label, m, t.K, qs.nblk, 0u, qs.hist, qs.count, qs.goff, qs.total, qs.perm, m_pad, st);
 }
 
 }  // namespace stag

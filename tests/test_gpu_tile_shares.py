@@ -31,6 +31,8 @@ CASES = [
     ("fp32", "gaussian", 4097, 129, 257), ("fp16_split", "gaussian", 513, 130, 270),
     ("bf16_split", "gaussian", 8191, 3, 1000), ("fp16_split", "exponential", 257, 129, 300),
     ("fp32", "logistic", 31, 1, 1024), ("fp16_split", "logistic", 4097, 129, 784),
+    # rows and queries grouped by one workgroup (up to 8,192) and by three launches
+    ("fp32", "gaussian", 8192, 60, 20), ("fp32", "gaussian", 8193, 60, 131), ("fp16_adaptive", "gaussian", 1025, 8193, 24),
 ]
 
 
