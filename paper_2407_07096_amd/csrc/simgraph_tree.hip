@@ -25,10 +25,11 @@
 // c = l; degree samples: tag "TDEG", a = i, b = 0.  A uniform is the top 53
 // bits times 2^-53 and an index is floor(u53 P / 2^53), exact in integers.
 //
-// Layout and work: one wave per draw (4 per block), x_i staged in LDS; at
-// each level lanes 0-31 evaluate child A's samples (or rows), lanes 32-63
-// child B's, one kernel value per lane from fp64 direct differences; each
-// half sums its 32 values in a fixed butterfly order.  Work per draw: h
+// Layout and work: one wave per draw and level; lanes 0-31 hold child A's
+// samples (or rows), lanes 32-63 child B's (two or four draws a wave where 16
+// or 8 lanes hold a child's), one kernel value per lane from
+// fp64 direct differences, whose rows four lanes read together (tree_dist);
+// the values of a child are summed in a fixed butterfly order.  Work per draw: h
 // levels x 2t kernel values + 32 at the leaf, each d fp64 operations on a
 // gathered row.  Results are deterministic; against a sequential fp64 sum
 // they differ by rounding only, which moves a decision only when its target
@@ -58,77 +59,155 @@ __device__ inline uint64_t tstream(uint64_t seed, uint64_t tag, uint64_t a, uint
 }
 __device__ inline uint64_t tout(uint64_t st, uint64_t c) { return tmix(st + (c + 1) * kGammaTree); }
 __device__ inline double tuniform(uint64_t bits) { return (double)(bits >> 11) * 0x1.0p-53; }
-__device__ inline int64_t tpick(uint64_t bits, int64_t P) {
+// floor(u P / 2^53) for the top 53 bits u of `bits`, P < 2^31: with u =
+// h 2^32 + l, the bits of l P below 2^32 cannot carry.
+__device__ inline uint32_t tpick(uint64_t bits, uint32_t P) {
   const uint64_t u = bits >> 11;
-  const uint64_t hi = __umul64hi(u, (uint64_t)P), lo = u * (uint64_t)P;
-  return (int64_t)((hi << 11) | (lo >> 53));
+  return (uint32_t)(((u >> 32) * P + __umulhi((uint32_t)u, P)) >> 21);
 }
 
-// exp(-a ||x_i - x_j||^2), squared distance by direct differences, each
-// product and sum rounded separately (ascending coordinates).
-__device__ inline double tkernel(const float* __restrict__ xi, const float* __restrict__ xj, int d, double a,
-                                 bool vec4) {
-  double D = 0.0;
-  if (vec4) {
-    const float4* x4 = reinterpret_cast<const float4*>(xj);
-    auto piece = [&](const float4& v, int c) {
-      double t = (double)xi[4 * c] - (double)v.x;
-      D = __dadd_rn(D, __dmul_rn(t, t));
-      t = (double)xi[4 * c + 1] - (double)v.y;
-      D = __dadd_rn(D, __dmul_rn(t, t));
-      t = (double)xi[4 * c + 2] - (double)v.z;
-      D = __dadd_rn(D, __dmul_rn(t, t));
-      t = (double)xi[4 * c + 3] - (double)v.w;
-      D = __dadd_rn(D, __dmul_rn(t, t));
-    };
-    // eight 16-byte pieces' loads issued before their products (same order)
-    const int d4 = d / 4;
-    int c = 0;
-    for (; c + 7 < d4; c += 8) {
-      float4 v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = x4[c + u];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) piece(v[u], c + u);
+// Draw e < 2^31 belongs to row e / s; the quotient as (e m) >> shift, exact
+// with m = ceil(2^shift / s), shift = 31 + ceil(log2 s) (m < 2^32).
+struct DivBy {
+  uint32_t s, m;
+  int shift;
+};
+inline DivBy div_by(uint32_t s) {
+  int l = 0;
+  while ((1ull << l) < s) ++l;
+  return {s, (uint32_t)(((1ull << (31 + l)) + s - 1) / s), 31 + l};
+}
+__device__ inline uint32_t quotient(uint32_t e, const DivBy& q) { return (uint32_t)(((uint64_t)e * q.m) >> q.shift); }
+
+// v of lane ^ 1 or lane ^ 2 (quad permutations), all lanes active.
+template <int CTRL>
+__device__ inline double quad_perm(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false));
+}
+
+// ||x_i - x_j||^2 for the row j of each lane, by fp64 direct differences; i is
+// the same in the four lanes of a quad, and all lanes are active.
+//
+// d > 8: the quad reads its four rows one after the other, each lane 16 bytes
+// of every 64, and the four partial sums per row are added across the quad at
+// the end.  With a lane per row every load touches 64 cache lines, and the
+// rate of the L1's tag lookups bounds the gathers: 1e5 points of 64
+// coordinates, 1.7e6 draws over 12 levels took 36.5 ms that way (2.0 at the
+// leaves); now 20.9 (0.85), bound by the fp64 operations where a node's rows
+// fit an L2 and by the misses of the first three levels.  Two pieces at a time
+// leave 6 waves a SIMD; four took 25.2 with 4 waves.  d <= 8: a lane per row,
+// whose line or two it reads whole (n = 2e4, d = 4, t = 4: quads 2.7 ms a
+// call, a lane per row 0.9).
+//
+// Rows need only the alignment of a float: 16-byte loads need no more.
+enum TreeRows { kOwnRow, kQuad4, kQuad };  // d <= 8; d a multiple of 4; any d
+inline TreeRows tree_rows(int d) { return d <= 8 ? kOwnRow : d % 4 == 0 ? kQuad4 : kQuad; }
+
+using TreeVec = float __attribute__((ext_vector_type(4), aligned(4)));
+
+// U 64-byte pieces from coordinate c on; PART: the last may end before 64.
+template <TreeRows ROWS, int U, bool PART>
+__device__ __forceinline__ void tree_piece(const float* __restrict__ xi, const float* const (&xj)[4], int c, int d,
+                                           double (&acc)[4]) {
+  const int q = threadIdx.x & 3;
+  auto load = [&](const float* x, int u) {
+    const int at = c + (4 * u + q) * 4;
+    TreeVec v = {0.f, 0.f, 0.f, 0.f};
+    if (!PART || u < U - 1 || at + 4 <= d) {
+      v = *reinterpret_cast<const TreeVec*>(x + at);
+    } else if (ROWS == kQuad && at < d) {
+      v[0] = x[at];
+      if (at + 1 < d) v[1] = x[at + 1];
+      if (at + 2 < d) v[2] = x[at + 2];
     }
-    for (; c < d4; ++c) piece(x4[c], c);
-  } else {
-    for (int c = 0; c < d; ++c) {
-      const double t = (double)xi[c] - (double)xj[c];
-      D = __dadd_rn(D, __dmul_rn(t, t));
+    return v;
+  };
+  TreeVec y[4][U];
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int u = 0; u < U; ++u) y[r][u] = load(xj[r], u);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const TreeVec x = load(xi, u);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const double xd = x[w];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double t = xd - (double)y[r][u][w];
+        acc[r] = fma(t, t, acc[r]);
+      }
     }
   }
-  return exp(-a * D);
 }
 
-__device__ inline double half_sum(double v) {  // fixed butterfly within each 32-lane half
+template <TreeRows ROWS>
+__device__ __forceinline__ double tree_dist(const float* __restrict__ X, int64_t i, int64_t j, int d) {
+  const float* xi = X + i * d;
+  if constexpr (ROWS == kOwnRow) {
+    const float* x = X + j * d;
+    double D = 0.0;
+    int c = 0;
+    for (; c + 4 <= d; c += 4) {
+      const TreeVec u = *reinterpret_cast<const TreeVec*>(xi + c), v = *reinterpret_cast<const TreeVec*>(x + c);
 #pragma unroll
-  for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
+      for (int w = 0; w < 4; ++w) {
+        const double t = (double)u[w] - (double)v[w];
+        D = fma(t, t, D);
+      }
+    }
+    for (; c < d; ++c) {
+      const double t = (double)xi[c] - (double)x[c];
+      D = fma(t, t, D);
+    }
+    return D;
+  } else {
+    const int q = threadIdx.x & 3;
+    const float* xj[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) xj[r] = X + (int64_t)__shfl((int)j, r, 4) * d;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    int c = 0;
+    for (; c + 32 <= d; c += 32) tree_piece<ROWS, 2, false>(xi, xj, c, d, acc);
+    if (d - c > 16) tree_piece<ROWS, 2, true>(xi, xj, c, d, acc);
+    else if (d - c > 0) tree_piece<ROWS, 1, true>(xi, xj, c, d, acc);
+    const bool b1 = q & 2, b0 = q & 1;
+    const double k0 = (b1 ? acc[2] : acc[0]) + quad_perm<0x4E>(b1 ? acc[0] : acc[2]);  // rows 2 b1
+    const double k1 = (b1 ? acc[3] : acc[1]) + quad_perm<0x4E>(b1 ? acc[1] : acc[3]);  // rows 2 b1 + 1
+    return (b0 ? k1 : k0) + quad_perm<0xB1>(b0 ? k0 : k1);
+  }
+}
+
+// Sum over each group of LANES lanes (fixed butterfly).
+template <int LANES>
+__device__ inline double lanes_sum(double v) {
+#pragma unroll
+  for (int o = LANES / 2; o > 2; o >>= 1) v += __shfl_xor(v, o);
+  v += quad_perm<0x4E>(v);
+  return v + quad_perm<0xB1>(v);
 }
 
 // rest[i] = est(i, root) with t_deg samples; one wave per row i.
-__global__ __launch_bounds__(256) void tree_degrees(const float* __restrict__ X, int64_t n, int d, double a,
-                                                    int64_t t_deg, uint64_t seed, bool vec4,
-                                                    double* __restrict__ rest, double* __restrict__ deg_out) {
-  extern __shared__ float txi[];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+template <TreeRows ROWS>
+__global__ __launch_bounds__(256, 4) void tree_degrees(const float* __restrict__ X, int64_t n, int d, double a,
+                                                    int64_t t_deg, uint64_t seed, double* __restrict__ rest,
+                                                    double* __restrict__ deg_out) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int64_t i = (int64_t)blockIdx.x * kTreeWaves + wave;
-  float* xi = txi + wave * d;
-  if (i < n)
-    for (int c = lane; c < d; c += 64) xi[c] = X[i * d + c];
-  __syncthreads();
   if (i >= n) return;
   double s = 0.0;
-  if (n <= t_deg) {
-    for (int64_t j = lane; j < n; j += 64)
-      if (j != i) s += tkernel(xi, X + j * d, d, a, vec4);
-  } else {
-    const uint64_t st = tstream(seed, kTagTreeDegree, (uint64_t)i, 0);
-    for (int64_t c = lane; c < t_deg; c += 64) {
-      const int64_t j = tpick(tout(st, (uint64_t)c), n);
-      if (j != i) s += tkernel(xi, X + j * d, d, a, vec4);
-    }
+  const bool all = n <= t_deg;
+  const int64_t count = all ? n : t_deg;
+  const uint64_t st = tstream(seed, kTagTreeDegree, (uint64_t)i, 0);
+  for (int64_t c0 = 0; c0 < count; c0 += 64) {
+    const int64_t c = c0 + lane;
+    int64_t j = i;
+    if (c < count) j = all ? c : tpick(tout(st, (uint64_t)c), (uint32_t)n);
+    const double D = tree_dist<ROWS>(X, i, j, d);
+    if (j != i) s += exp(-a * D);
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
@@ -148,18 +227,11 @@ __global__ __launch_bounds__(256) void tree_degrees(const float* __restrict__ X,
 //
 // Workgroups go round-robin to the 8 XCDs: block b works on logical block
 // (b % 8) per + b / 8 (the grid is 8 per blocks), i.e. slots
-// [4 L, 4 L + 4) of the sorted order.
+// [4 L, 4 L + 4) of the sorted order, one per wave.
 __device__ inline int64_t tree_slot(int per) {
   const int b = blockIdx.x;
   const int64_t L = (int64_t)(b % 8) * per + b / 8;
-  return L * kTreeWaves + (threadIdx.x >> 6);
-}
-
-// Stage x_i of the draw in slot `slot` (if any) into this wave's LDS row.
-__device__ inline void stage_row(float* xi, const float* __restrict__ X, int64_t i, int d, bool active) {
-  const int lane = threadIdx.x & 63;
-  if (active)
-    for (int c = lane; c < d; c += 64) xi[c] = X[i * d + c];
+  return L * kTreeWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
 
 // perm[w] = w, node[w] = 0.
@@ -172,39 +244,43 @@ __global__ void tree_init(uint32_t* __restrict__ perm, uint32_t* __restrict__ no
 }
 
 // One level l < h for the draw in each slot: node_in[slot] -> node_out[slot].
-__global__ __launch_bounds__(256) void tree_level(const float* __restrict__ X, int64_t n, int d, double a, int s,
-                                                  int t, int h, int l, uint64_t seed, bool vec4,
-                                                  const uint32_t* __restrict__ perm,
-                                                  const uint32_t* __restrict__ node_in, uint32_t* __restrict__ node_out,
-                                                  int64_t total, int per) {
-  extern __shared__ float txi[];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t slot = tree_slot(per);
-  const bool active = slot < total;
-  const int64_t e = active ? (int64_t)perm[slot] : 0;
-  const int64_t i = e / s, r = e % s;
-  float* xi = txi + wave * d;
-  stage_row(xi, X, i, d, active);
-  __syncthreads();
-  if (!active) return;
-  const int side = lane >> 5, c = lane & 31;
+// LANES lanes per child (t <= LANES), 2 LANES per draw: with few samples a
+// wave takes two or four draws (n = 5e4, d = 30, t = 16: one draw a wave 17.9 ms
+// a call before the wider loads, two draws 10.5, and 5.4 with them).
+template <TreeRows ROWS, int LANES>
+__global__ __launch_bounds__(256, LANES == 32 ? 6 : 5) void tree_level(
+    const float* __restrict__ X, int64_t n, int d, double a, DivBy s, int t, int h, int l, uint64_t seed,
+    const uint32_t* __restrict__ perm, const uint32_t* __restrict__ node_in, uint32_t* __restrict__ node_out,
+    int64_t total, int per) {
+  constexpr int kDraws = 32 / LANES;  // of a wave
+  const int lane = threadIdx.x & 63;
+  const int64_t slot0 = kDraws * tree_slot(per);
+  if (slot0 >= total) return;
+  // the last wave's spare lanes repeat its last draw
+  const int64_t slot = kDraws == 1 ? slot0 : min(total - 1, slot0 + lane / (2 * LANES));
+  const uint32_t e = perm[slot];
+  const int64_t i = quotient(e, s);
+  const uint32_t r = e - (uint32_t)i * s.s;
+  const int side = (lane / LANES) & 1, c = lane % LANES;
   const int64_t k = node_in[slot];
   const int64_t span = (int64_t)kTreeLeaf << (h - l - 1);
-  const int64_t lo = min(n, (2 * k + side) * span), hi = min(n, (2 * k + side + 1) * span);
-  const int64_t P = hi - lo;
-  double v = 0.0;
-  if (P > 0 && P <= t) {
-    const int64_t j = lo + c;
-    if (c < P && j != i) v = tkernel(xi, X + j * d, d, a, vec4);
-  } else if (P > t && c < t) {
-    const uint64_t st =
-        tstream(seed, kTagTreeSamples, (uint64_t)i, ((uint64_t)r << 16) | ((uint64_t)l << 1) | (uint64_t)side);
-    const int64_t j = lo + tpick(tout(st, (uint64_t)c), P);
-    if (j != i) v = tkernel(xi, X + j * d, d, a, vec4);
+  const int64_t mid = min(n, (2 * k + 1) * span);
+  const int64_t lo = side ? mid : min(n, 2 * k * span), hi = side ? min(n, (2 * k + 2) * span) : mid;
+  const uint32_t P = (uint32_t)(hi - lo);
+  const uint64_t si = tmix(tmix(seed ^ kTagTreeSamples) ^ (uint64_t)i);
+  const uint64_t b = ((uint64_t)r << 16) | ((uint64_t)l << 1);
+  const uint64_t stA = tmix(si ^ b), stB = tmix(si ^ (b | 1));
+  int64_t j = i;  // i itself: no value
+  if (P > (uint32_t)t) {
+    if (c < t) j = lo + tpick(tout(side ? stB : stA, (uint64_t)c), P);
+  } else if (c < (int)P) {
+    j = lo + c;
   }
-  double est = half_sum(v);
-  if (P > t) est = est * ((double)P / (double)t);
-  const double eA = __shfl(est, 0), eB = __shfl(est, 32);
+  const double D = tree_dist<ROWS>(X, i, j, d);
+  const double v = j != i ? exp(-a * D) : 0.0;
+  double est = lanes_sum<LANES>(v);
+  if (P > (uint32_t)t) est = est * ((double)P / (double)t);
+  const double eA = __shfl(est, 0, 2 * LANES), eB = __shfl(est, LANES, 2 * LANES);
   const double u = tuniform(tout(tstream(seed, kTagTreeUniform, (uint64_t)i, (uint64_t)r), (uint64_t)l));
   const double tot = eA + eB;
   bool left;
@@ -216,51 +292,48 @@ __global__ __launch_bounds__(256) void tree_level(const float* __restrict__ X, i
     const int64_t mB = (bHi - aHi) - ((i >= aHi && i < bHi) ? 1 : 0);
     left = mA >= mB;
   }
-  if (lane == 0) node_out[slot] = (uint32_t)(left ? 2 * k : 2 * k + 1);
+  if (lane % (2 * LANES) == 0) node_out[slot] = (uint32_t)(left ? 2 * k : 2 * k + 1);
 }
 
-// The leaf (level h) of the draw in each slot: inverse CDF over its rows in
-// row order; outputs at the draw's own index e = i s + r.
-__global__ __launch_bounds__(256) void tree_leaf(const float* __restrict__ X, int64_t n, int d, double a, int s,
-                                                 int h, uint64_t seed, bool vec4, const uint32_t* __restrict__ perm,
+// The leaf (level h) of the draw in each slot, two draws per wave (lanes 0-31
+// and 32-63): inverse CDF over its rows in row order; outputs at the draw's own
+// index e = i s + r.
+template <TreeRows ROWS>
+__global__ __launch_bounds__(256, 5) void tree_leaf(const float* __restrict__ X, int64_t n, int d, double a, DivBy s,
+                                                 int h, uint64_t seed, const uint32_t* __restrict__ perm,
                                                  const uint32_t* __restrict__ node, const double* __restrict__ rest,
                                                  int64_t* __restrict__ src, int64_t* __restrict__ dst,
                                                  double* __restrict__ w, int64_t total, int per) {
-  extern __shared__ float txi[];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t slot = tree_slot(per);
+  const int side = (threadIdx.x >> 5) & 1, c = threadIdx.x & 31;
+  const int64_t slot = 2 * tree_slot(per) + side;
   const bool active = slot < total;
-  const int64_t e = active ? (int64_t)perm[slot] : 0;
-  const int64_t i = e / s, r = e % s;
-  float* xi = txi + wave * d;
-  stage_row(xi, X, i, d, active);
-  __syncthreads();
-  if (!active) return;
-  const int side = lane >> 5, c = lane & 31;
-  const int64_t k = node[slot];
+  const uint32_t e = active ? perm[slot] : 0;
+  const int64_t i = quotient(e, s);
+  const uint32_t r = e - (uint32_t)i * s.s;
+  const int64_t k = active ? node[slot] : 0;
   const int64_t lo = min(n, k * kTreeLeaf), hi = min(n, (k + 1) * kTreeLeaf);
-  const int64_t j = lo + c;
-  double v = 0.0;
-  if (side == 0 && j < hi && j != i) v = tkernel(xi, X + j * d, d, a, vec4);
-  double incl = v;  // inclusive prefix over lanes 0-31 (lanes 32-63 hold 0)
+  const int64_t j = lo + c < hi ? lo + c : i;
+  const double D = tree_dist<ROWS>(X, i, j, d);
+  const double v = j != i ? exp(-a * D) : 0.0;
+  double incl = v;  // inclusive prefix over the half's lanes
 #pragma unroll
   for (int o = 1; o < 32; o <<= 1) {
-    const double y = __shfl_up(incl, o);
+    const double y = __shfl_up(incl, o, 32);
     if (c >= o) incl += y;
   }
-  const double T = __shfl(incl, 31);
+  const double T = __shfl(incl, 31, 32);
   const double u = tuniform(tout(tstream(seed, kTagTreeUniform, (uint64_t)i, (uint64_t)r), (uint64_t)h));
   int64_t pick;
+  // only a row with a positive value can take the draw (the butterfly prefix
+  // need not be exactly monotone where a value is 0)
+  const double target = u * T;
+  const uint64_t positive = __ballot(v > 0.0), above = __ballot(v > 0.0 && incl > target);
   if (T > 0.0) {
-    const double target = u * T;
-    // only a row with a positive value can take the draw (the butterfly
-    // prefix need not be exactly monotone where a value is 0)
-    const uint64_t pass = __ballot(side == 0 && v > 0.0 && incl > target);
+    const uint32_t pass = (uint32_t)(above >> (32 * side));
     if (pass != 0) {
-      pick = lo + __builtin_ctzll(pass);
+      pick = lo + __builtin_ctz(pass);
     } else {  // rounding left the target above the total: the last positive value
-      const uint64_t pos = __ballot(side == 0 && v > 0.0);
-      pick = lo + 63 - __builtin_clzll(pos);
+      pick = lo + 31 - __builtin_clz((uint32_t)(positive >> (32 * side)));
     }
   } else {
     const int64_t m = (hi - lo) - ((i >= lo && i < hi) ? 1 : 0);
@@ -268,11 +341,11 @@ __global__ __launch_bounds__(256) void tree_leaf(const float* __restrict__ X, in
     pick = lo + idx;
     if (i >= lo && i < hi && pick >= i) ++pick;
   }
-  if (lane == 0) {
+  if (c == 0 && active) {
     src[e] = i;
     dst[e] = pick;
     const double ri = rest[i], rj = rest[pick];
-    w[e] = (ri > 0.0 && rj > 0.0) ? 1.0 / ((double)s * (1.0 / ri + 1.0 / rj)) : 0.0;
+    w[e] = (ri > 0.0 && rj > 0.0) ? 1.0 / ((double)s.s * (1.0 / ri + 1.0 / rj)) : 0.0;
   }
 }
 
@@ -304,17 +377,23 @@ extern "C" stag_status stag_simgraph_sample_tree(const float* X, int64_t n, int3
   Workspace ws(stream);
   double* rest = nullptr;
   STAG_TRY(ws.alloc(&rest, (size_t)n));
-  const size_t lds = (size_t)kTreeWaves * d * sizeof(float);
-  const bool vec4 = (d % 4) == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;  // float4 row loads
+  const TreeRows rows = tree_rows(d);
+  auto by_rows = [&](auto own, auto quad4, auto quad) { return rows == kOwnRow ? own : rows == kQuad4 ? quad4 : quad; };
   {
     ScopedTimer tm("tree_degrees", stream);
-    hipLaunchKernelGGL(tree_degrees, dim3((unsigned)ceil_div(n, kTreeWaves)), dim3(256), lds, stream, X, n, (int)d,
-                       a, degree_samples, seed, vec4, rest, deg_out);
+    hipLaunchKernelGGL(by_rows(tree_degrees<kOwnRow>, tree_degrees<kQuad4>, tree_degrees<kQuad>),
+                       dim3((unsigned)ceil_div(n, kTreeWaves)), dim3(256), 0, stream, X, n, (int)d, a, degree_samples,
+                       seed, rest, deg_out);
     STAG_TRY(check_launch("tree_degrees"));
   }
   // draws level by level, sorted by node between levels
-  const int per = (int)ceil_div(ceil_div(draws, kTreeWaves), 8);
+  const DivBy by = div_by((uint32_t)s);
+  const int lanes = est_samples <= 8 ? 8 : est_samples <= 16 ? 16 : 32;
+  const int per = (int)ceil_div(ceil_div(draws, kTreeWaves * (32 / lanes)), 8);
   const dim3 grid((unsigned)(8 * per));
+  auto level = lanes == 8    ? by_rows(tree_level<kOwnRow, 8>, tree_level<kQuad4, 8>, tree_level<kQuad, 8>)
+               : lanes == 16 ? by_rows(tree_level<kOwnRow, 16>, tree_level<kQuad4, 16>, tree_level<kQuad, 16>)
+                             : by_rows(tree_level<kOwnRow, 32>, tree_level<kQuad4, 32>, tree_level<kQuad, 32>);
   uint32_t *perm = nullptr, *perm2 = nullptr, *node = nullptr, *node2 = nullptr;
   STAG_TRY(ws.alloc(&perm, (size_t)draws));
   STAG_TRY(ws.alloc(&perm2, (size_t)draws));
@@ -325,8 +404,8 @@ extern "C" stag_status stag_simgraph_sample_tree(const float* X, int64_t n, int3
   for (int l = 0; l < h; ++l) {
     {
       ScopedTimer tm("tree_draws", stream);
-      hipLaunchKernelGGL(tree_level, grid, dim3(256), lds, stream, X, n, (int)d, a, s, (int)est_samples, h, l, seed,
-                         vec4, perm, node, node2, draws, per);
+      hipLaunchKernelGGL(level, grid, dim3(256), 0, stream, X, n, (int)d, a, by, (int)est_samples, h, l, seed,
+                         perm, node, node2, draws, per);
       STAG_TRY(check_launch("tree_level"));
     }
     ScopedTimer tm("tree_sort", stream);
@@ -335,8 +414,10 @@ extern "C" stag_status stag_simgraph_sample_tree(const float* X, int64_t n, int3
   }
   {
     ScopedTimer tm("tree_draws", stream);
-    hipLaunchKernelGGL(tree_leaf, grid, dim3(256), lds, stream, X, n, (int)d, a, s, h, seed, vec4, perm, node, rest,
-                       src_out, dst_out, w_out, draws, per);
+    const int leaf_per = (int)ceil_div(ceil_div(draws, 2 * kTreeWaves), 8);
+    hipLaunchKernelGGL(by_rows(tree_leaf<kOwnRow>, tree_leaf<kQuad4>, tree_leaf<kQuad>),
+                       dim3((unsigned)(8 * leaf_per)), dim3(256), 0, stream, X, n, (int)d, a, by, h, seed, perm, node,
+                       rest, src_out, dst_out, w_out, draws, leaf_per);
     STAG_TRY(check_launch("tree_leaf"));
   }
   return STAG_OK;
