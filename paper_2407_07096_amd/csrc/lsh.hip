@@ -421,7 +421,8 @@ __global__ __launch_bounds__(256) void hash_queries_wide(const float* __restrict
 constexpr int kChebTerms = 33;
 constexpr int kChebRow = kChebTerms + 2;
 
-__device__ inline double level_weight(const double* __restrict__ row, double c) {
+template <class Row>
+__device__ inline double level_weight(Row row, double c) {
   const double t = (c - row[0]) * row[1] - 1.0;
   const double t2 = 2.0 * t;
   double b1 = 0.0, b2 = 0.0;
@@ -857,28 +858,42 @@ __global__ void zero_i64(int64_t* p, int64_t n) {
 // ---------------------------------------------------------------------------
 // Bucket join (query batches with d <= 128 and L <= 32).  The batch's queries
 // are grouped by the bucket they fall in, per table; a wave then takes up to
-// 64 queries of one bucket (one per lane, row in registers) against up to
-// kJoinMembers members of that bucket, which it stages through LDS
-// kJoinChunk rows at a time, so that every member row is read once per 64
-// queries instead of once per query.  Per pair: first-table dedupe, self
-// exclusion and the fp32 distance screen; the survivors of a staged chunk are
-// then settled per lane in member order (fp64 distance, level test, term).
+// 64 queries of one bucket against up to kJoinMembers members of that bucket,
+// which it stages through LDS kJoinChunk rows at a time, so that every member
+// row is read once per 64 queries instead of once per query.  Per pair: the
+// fp32 distance screen, from a matrix product of the chunk; the chunk's
+// survivors are then settled 64 at a time, whichever queries they belong to
+// (first-table dedupe, self exclusion, fp64 distance, level test, term), and
+// each query's lane adds its own terms in member order.
 // A lane's partial over its member range goes to tpart; combine_groups adds
 // the ranges of a bucket in order and the tables of a copy in order, so a
 // query's estimate does not depend on the other queries of its batch.
+//
+// 1e5 queries and points of 64 coordinates, 7.8e8 pairs of which 2.8 % survive
+// took 4.9 ms with a query per lane: 1.4 for the screen's products (each lane
+// its own, the member row broadcast from LDS) and as much for the survivors
+// (every lane its own, 9 of 64 lanes active), the rest waiting, a task's
+// search for its bucket first of all.  Now 3.3: half of it products and other
+// vector work, the rest latency of the gathers at three waves a SIMD.
 // ---------------------------------------------------------------------------
-constexpr int kJoinMembers = 512;
+constexpr int kJoinMembers = 128;  // 512 left a tail of few long tasks: n = 3e4 graph 2.0 ms, 256 1.2, 128 0.6
 constexpr int kJoinChunk = 32;
+// A task of at most this many pairs skips the screen and its query tiles,
+// which cost as much as settling about two batches of 64 pairs.
+constexpr int kJoinDirect = 128;
+// With more survivors in a chunk than this the dedupe goes member by member,
+// each lane for its own query (32 steps), not pair by pair (64 a step, whose
+// pairs have to be looked up first): 3.5 against 3.7 ms with 1e5 points.
+constexpr int kJoinDense = 384;
 
 // Bytes of dynamic LDS of one join wave (layout: rows, point ids, member
-// norms, member keys, query keys).  With L <= kJoinRegKeys + 1 the query
-// keys of the earlier tables are held in registers instead (fewer LDS bytes
-// per wave, more waves per CU).
-constexpr int kJoinRegKeys = 7;
+// norms, survivors' places, queries, runs, terms, member keys, query keys).
+// The query keys in registers instead (7 pairs of them) made the 64-wide form
+// spill: 3.4 ms against 3.3.
 __host__ __device__ inline int join_lds_rows(int dq) { return kJoinChunk * (dq + 4) * 4; }
-__host__ __device__ inline int join_lds_bytes(int dq, int L, bool reg_keys) {
+__host__ __device__ inline int join_lds_bytes(int dq, int L) {
   const int lm1 = L > 1 ? L - 1 : 1;
-  return join_lds_rows(dq) + kJoinChunk * 8 + kJoinChunk * lm1 * 8 + (reg_keys ? 0 : lm1 * 64 * 8);
+  return join_lds_rows(dq) + kJoinChunk * 8 + 384 * 4 + 64 * 8 + kJoinChunk * lm1 * 8 + lm1 * 64 * 8;
 }
 
 // The bucket (global slot) of every (table, query) pair of the batch (pair
@@ -969,155 +984,353 @@ __device__ inline int64_t last_le(const uint64_t* __restrict__ v, int64_t n, uin
   return lo;
 }
 
-template <int DQ, int QKR>
-__global__ __launch_bounds__(64) void join_buckets(IndexView ix, LevelConst lc, const float* __restrict__ Q, int ldq,
-                                                   int64_t q0, const uint64_t* __restrict__ qkeys, int64_t mb,
-                                                   const uint32_t* __restrict__ qcount,
-                                                   const uint64_t* __restrict__ qstart,
-                                                   const int32_t* __restrict__ qlist,
-                                                   const uint64_t* __restrict__ task_base, int64_t nslots, int nseg,
-                                                   int self_excl, double* __restrict__ tpart,
-                                                   int64_t* __restrict__ nacc) {
+// What a task works on: members [mfirst, mfirst + nm) of the CSR, of segment
+// seg (level seg % J + 1) and table l, against qlist[qfirst .. qfirst + nq).
+struct JoinTask {
+  int64_t mfirst, qfirst, s0;
+  int32_t nm, nq, seg, l;
+};
+
+__global__ __launch_bounds__(256) void describe_tasks(IndexView ix, const uint32_t* __restrict__ qcount,
+                                                      const uint64_t* __restrict__ qstart,
+                                                      const uint64_t* __restrict__ task_base, int64_t nslots, int nseg,
+                                                      int64_t ntasks, JoinTask* __restrict__ tasks) {
+  const int64_t task = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (task >= ntasks) return;
+  const int64_t slot = last_le(task_base, nslots + 1, (uint64_t)task);
+  JoinTask t;
+  t.seg = (int32_t)last_le(ix.tab_seg_off, (int64_t)nseg + 1, (uint64_t)slot);
+  t.l = (int32_t)((slot - (int64_t)ix.tab_seg_off[t.seg]) / ix.seg_cap[t.seg]);
+  t.s0 = (int64_t)ix.seg_off[t.seg];
+  const int64_t cnt = (int64_t)ix.seg_off[t.seg + 1] - t.s0;
+  const uint32_t nq = qcount[slot], nm = ix.tab_cnt[slot];
+  const int64_t nmc = (nm + kJoinMembers - 1) / kJoinMembers;
+  const int64_t r = task - (int64_t)task_base[slot];
+  const uint32_t qb = (uint32_t)(r / nmc) * 64u, mb = (uint32_t)(r % nmc) * kJoinMembers;
+  t.mfirst = t.s0 * ix.L + (int64_t)t.l * cnt + ix.tab_start[slot] + mb;
+  t.qfirst = (int64_t)qstart[slot] + qb;
+  t.nm = (int32_t)min((uint32_t)kJoinMembers, nm - mb);
+  t.nq = (int32_t)min(64u, nq - qb);
+  tasks[task] = t;
+}
+
+using JoinVec = float __attribute__((ext_vector_type(4)));
+using JoinAcc = float __attribute__((ext_vector_type(16)));
+
+// Lane permutations within quads (all lanes active).
+template <int CTRL>
+__device__ inline int quad_i32(int v) {
+  return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
+}
+template <int CTRL>
+__device__ inline double quad_f64(double v) {
+  return __hiloint2double(quad_i32<CTRL>(__double2hiint(v)), quad_i32<CTRL>(__double2loint(v)));
+}
+
+// Keeps a wave's LDS accesses in program order (as the hardware then does) in
+// workgroups of one wave; unlike a barrier it does not wait for loads in flight.
+__device__ inline void lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Q: the batch's rows (from q0 of the call on) as the index's own are: dx
+// floats, 16-byte aligned, 0 from d on.
+template <int DQ>
+__global__ __launch_bounds__(64, DQ <= 32 ? 4 : DQ <= 64 ? 3 : 2) void join_buckets(
+    IndexView ix, LevelConst lc, const float* __restrict__ Q, int64_t q0, const uint64_t* __restrict__ qkeys,
+    int64_t mb, const int32_t* __restrict__ qlist, const JoinTask* __restrict__ tasks, int self_excl,
+    double* __restrict__ tpart, int64_t* __restrict__ nacc) {
   extern __shared__ __attribute__((aligned(16))) unsigned char jlds[];
   constexpr int RS = DQ + 4;  // LDS row stride (floats)
-  const int lane = threadIdx.x;
-  const int L = ix.L, d = ix.d, dx = ix.dx;
+  const int lane = threadIdx.x, col = lane & 31, half = lane >> 5;
+  const int L = ix.L, dx = ix.dx;
   const int lm1 = L > 1 ? L - 1 : 1;
   float* rows = reinterpret_cast<float*>(jlds);
   int32_t* jl = reinterpret_cast<int32_t*>(jlds + join_lds_rows(DQ));
   float* nxl = reinterpret_cast<float*>(jl + kJoinChunk);
-  uint64_t* mk = reinterpret_cast<uint64_t*>(jlds + join_lds_rows(DQ) + kJoinChunk * 8);
-  uint64_t* qk = mk + kJoinChunk * lm1;  // query keys in LDS (QKR == 0)
-  uint64_t qkr[QKR > 0 ? QKR : 1];       // or in registers (l <= QKR)
+  uint32_t* ends = reinterpret_cast<uint32_t*>(nxl + kJoinChunk);
+  uint32_t* masks = ends + 64;  // a query's survivors of the screen
+  uint32_t* open = ends + 128;  // survivors of the dedupe, up to 128
+  int32_t* qids = reinterpret_cast<int32_t*>(open + 128);
+  uint32_t* runs = open + 192;  // per query its run of the 64 being settled
+  double* terms = reinterpret_cast<double*>(runs + 64);
+  uint64_t* mk = reinterpret_cast<uint64_t*>(terms + 64);
+  uint64_t* qk = mk + kJoinChunk * lm1;
 
   const int64_t task = blockIdx.x;
-  const int64_t slot = last_le(task_base, nslots + 1, (uint64_t)task);
-  const int seg = (int)last_le(ix.tab_seg_off, (int64_t)nseg + 1, (uint64_t)slot);
-  const uint32_t cap = ix.seg_cap[seg];
-  const int l = (int)((slot - (int64_t)ix.tab_seg_off[seg]) / cap);
-  const int i = seg % ix.J + 1;
-  const int64_t s0 = (int64_t)ix.seg_off[seg];
-  const int64_t cnt = (int64_t)ix.seg_off[seg + 1] - s0;
-  const uint32_t nq = qcount[slot], nm = ix.tab_cnt[slot];
-  const int nmc = (int)((nm + kJoinMembers - 1) / kJoinMembers);
-  const int64_t r = task - (int64_t)task_base[slot];
-  const int qc = (int)(r / nmc), mc = (int)(r % nmc);
-  const int64_t mbase = s0 * L + (int64_t)l * cnt + ix.tab_start[slot];
+  const JoinTask t = tasks[task];
+  const int l = __builtin_amdgcn_readfirstlane(t.l);
+  const int i = __builtin_amdgcn_readfirstlane(t.seg) % ix.J + 1;
+  // read through the scalar cache: the interpolant is the same in every lane
+  // (its 28 values took 56 vector registers)
+  using ScalarRow = const __attribute__((address_space(4))) double*;
+  const ScalarRow cheb = (ScalarRow)(uintptr_t)(ix.cheb + i * kChebRow);
   const double Tlo = lc.T[i - 1], Thi = lc.T[i], ri = lc.r[i];
   const float Tlo_f = (float)Tlo, Thi_f = (float)Thi;
   // |fl(D) - D| <= ce (|q|^2 + |x|^2) for D = |q|^2 + |x|^2 - 2 q.x with fp32
-  // fused dot products and norms (gamma bounds, with margin)
-  const float ce = (float)(2 * DQ + 24) * 0x1.0p-24f;
+  // dot products and norms (gamma bounds, each operation within an ulp)
+  const float ce = (float)(4 * DQ + 48) * 0x1.0p-24f;
 
-  const uint32_t qp = (uint32_t)qc * 64u + (uint32_t)lane;
-  const bool qvalid = qp < nq;
-  const int32_t ql = qlist[qstart[slot] + (qvalid ? qp : 0u)];
-  const int64_t self_idx = self_excl ? q0 + ql : -1;
-  float q[DQ];
-  {
-    const float* qrow = Q + (q0 + ql) * (int64_t)ldq;
-#pragma unroll
-    for (int h = 0; h < DQ; ++h) q[h] = h < d ? qrow[h] : 0.0f;
-  }
-  float qnorm = 0.0f;
-#pragma unroll
-  for (int h = 0; h < DQ; ++h) qnorm = __builtin_fmaf(q[h], q[h], qnorm);
-  if constexpr (QKR > 0) {
-#pragma unroll
-    for (int l2 = 0; l2 < QKR; ++l2) qkr[l2] = l2 < l ? qkeys[((int64_t)seg * L + l2) * mb + ql] : 0ull;
-  } else {
-    for (int l2 = 0; l2 < l; ++l2) qk[l2 * 64 + lane] = qkeys[((int64_t)seg * L + l2) * mb + ql];
-  }
+  const int nq = __builtin_amdgcn_readfirstlane(t.nq), nm = __builtin_amdgcn_readfirstlane(t.nm);
+  const bool direct = nq * nm <= kJoinDirect, second = nq > 32;
+  const bool qvalid = lane < nq;
+  const int32_t ql = qlist[t.qfirst + (qvalid ? lane : 0)];
+  qids[lane] = ql;
+  // a row's 16-byte pieces are read by DQ / 4 lanes, kStage rows at a time
+  constexpr int kPieces = DQ / 4, kRows = 64 / kPieces, kStage = kJoinChunk / kRows;
+  const int piece = lane % kPieces, prow = lane / kPieces;
+  const bool piece_in = 4 * piece < dx;
+  const int at_piece = piece_in ? 4 * piece : 0;
   if (dx < DQ)
     for (int e = lane; e < kJoinChunk * RS; e += 64) rows[e] = 0.0f;
-
+  // B operands of the products (2 tiles of 32 queries): lane l supplies query
+  // l % 32 and, of every 8 coordinates, four from 4 (l / 32) on
+  JoinVec qb[2][DQ / 8];
+  float qlo[2], qhi[2];  // (1 +- ce) |q|^2
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    if (direct || (u == 1 && !second)) continue;
+    JoinVec v[kStage];
+#pragma unroll
+    for (int it = 0; it < kStage; ++it)
+      v[it] = *reinterpret_cast<const JoinVec*>(Q + (int64_t)qids[32 * u + it * kRows + prow] * dx + at_piece);
+    lds_order();
+    if (piece_in) {
+#pragma unroll
+      for (int it = 0; it < kStage; ++it)
+        *reinterpret_cast<JoinVec*>(&rows[(it * kRows + prow) * RS + 4 * piece]) = v[it];
+    }
+    lds_order();
+    float qn = 0.0f;
+#pragma unroll
+    for (int s = 0; s < DQ / 8; ++s) {
+      const JoinVec w = *reinterpret_cast<const JoinVec*>(&rows[col * RS + 8 * s + 4 * half]);
+      qb[u][s] = w;
+      qn = __builtin_fmaf(w[0], w[0], qn);
+      qn = __builtin_fmaf(w[1], w[1], qn);
+      qn = __builtin_fmaf(w[2], w[2], qn);
+      qn = __builtin_fmaf(w[3], w[3], qn);
+    }
+    qn += __shfl_xor(qn, 32);
+    qlo[u] = __builtin_fmaf(ce, qn, qn);
+    qhi[u] = __builtin_fmaf(-ce, qn, qn);
+  }
+  for (int l2 = 0; l2 < l; ++l2) qk[l2 * 64 + lane] = qkeys[((int64_t)t.seg * L + l2) * mb + ql];
+  runs[lane] = 0u;
   double acc = 0.0;
   int64_t na = 0;
-  const int dx4 = dx >> 2;
-  const int kbeg = mc * kJoinMembers;
-  const int kend = (int)min((uint32_t)(kbeg + kJoinMembers), nm);
-  for (int k0 = kbeg; k0 < kend; k0 += kJoinChunk) {
-    const int nk = min(kJoinChunk, kend - k0);
-    __builtin_amdgcn_wave_barrier();
-    if (lane < nk) {
-      const int32_t u = ix.csr[mbase + k0 + lane];
-      jl[lane] = ix.members[s0 + u];
-      const uint64_t* mrow = ix.mkeys + (s0 + u) * L;
-      for (int l2 = 0; l2 < l; ++l2) mk[lane * lm1 + l2] = mrow[l2];
+  // the chunk's places in the segment and point ids (places past its end
+  // repeat the last), loaded one chunk ahead
+  int32_t place = ix.csr[t.mfirst + min(col, nm - 1)];
+  int32_t id = ix.members[t.s0 + place];
+  for (int k0 = 0; k0 < nm; k0 += kJoinChunk) {
+    const int nk = min(kJoinChunk, nm - k0);
+    const uint64_t* mrow = ix.mkeys + (t.s0 + place) * L;
+    // chunk after: its places now, its ids after the screen
+    if (k0 + kJoinChunk < nm) place = ix.csr[t.mfirst + min(k0 + kJoinChunk + col, nm - 1)];
+    lds_order();
+    if (half == 0) jl[col] = id;
+    lds_order();
+    {
+      JoinVec v[kStage];
+#pragma unroll
+      for (int it = 0; it < kStage; ++it)
+        v[it] = *reinterpret_cast<const JoinVec*>(ix.X + (int64_t)jl[it * kRows + prow] * dx + at_piece);
+      if (piece_in) {
+#pragma unroll
+        for (int it = 0; it < kStage; ++it)
+          *reinterpret_cast<JoinVec*>(&rows[(it * kRows + prow) * RS + 4 * piece]) = v[it];
+      }
     }
-    __builtin_amdgcn_wave_barrier();
-    for (int e = lane; e < nk * dx4; e += 64) {
-      const int rr = e / dx4, c4 = e - rr * dx4;
-      const float4 v = reinterpret_cast<const float4*>(ix.X + (int64_t)jl[rr] * dx)[c4];
-      *reinterpret_cast<float4*>(&rows[rr * RS + 4 * c4]) = v;
-    }
-    __builtin_amdgcn_wave_barrier();
-    if (lane < nk) {
+    for (int l2 = half; l2 < l; l2 += 2) mk[col * lm1 + l2] = mrow[l2];
+    uint32_t mask = 0u;
+    if (!direct) {
+      // q.x of the chunk: lane l ends with query l % 32 of each tile, members
+      // 8 (r / 4) + 4 (l / 32) + r % 4
+      JoinAcc c[2];
       float nr = 0.0f;
 #pragma unroll
-      for (int h4 = 0; h4 < DQ / 4; ++h4) {
-        const float4 xv = *reinterpret_cast<const float4*>(&rows[lane * RS + 4 * h4]);
-        nr = __builtin_fmaf(xv.x, xv.x, nr);
-        nr = __builtin_fmaf(xv.y, xv.y, nr);
-        nr = __builtin_fmaf(xv.z, xv.z, nr);
-        nr = __builtin_fmaf(xv.w, xv.w, nr);
-      }
-      nxl[lane] = nr;
-    }
-    __builtin_amdgcn_wave_barrier();
-    uint32_t mask = 0;
-    for (int m = 0; m < nk; ++m) {
-      const float* xr = &rows[m * RS];
-      float p0 = 0.0f, p1 = 0.0f;
+      for (int u = 0; u < 2; ++u) {
 #pragma unroll
-      for (int h4 = 0; h4 < DQ / 4; ++h4) {
-        const float4 xv = *reinterpret_cast<const float4*>(xr + 4 * h4);
-        p0 = __builtin_fmaf(q[4 * h4], xv.x, p0);
-        p1 = __builtin_fmaf(q[4 * h4 + 1], xv.y, p1);
-        p0 = __builtin_fmaf(q[4 * h4 + 2], xv.z, p0);
-        p1 = __builtin_fmaf(q[4 * h4 + 3], xv.w, p1);
-      }
-      const float sn = qnorm + nxl[m];
-      const float D32 = __builtin_fmaf(-2.0f, p0 + p1, sn);
-      const float E = ce * sn;
-      bool keep = qvalid && D32 >= Tlo_f - E && D32 < Thi_f + E;
-      if (__ballot(keep)) {
-        bool seen = (int64_t)jl[m] == self_idx;
-        if constexpr (QKR > 0) {
+        for (int r = 0; r < 16; ++r) c[u][r] = 0.0f;
+        if (u == 1 && !second) continue;
 #pragma unroll
-          for (int l2 = 0; l2 < QKR; ++l2)
-            if (l2 < l) seen |= mk[m * lm1 + l2] == qkr[l2];
-        } else {
-          for (int l2 = 0; l2 < l; ++l2) seen |= mk[m * lm1 + l2] == qk[l2 * 64 + lane];
-        }
-        keep = keep && !seen;
-      }
-      mask |= keep ? (1u << m) : 0u;
-    }
-    // survivors, per lane in member order
-    while (__ballot(mask != 0u)) {
-      if (mask) {
-        const int m = __builtin_ctz(mask);
-        mask &= mask - 1u;
-        const float* xr = &rows[m * RS];
-        double D = 0.0;
-#pragma unroll
-        for (int h4 = 0; h4 < DQ / 4; ++h4) {
-          const float4 xv = *reinterpret_cast<const float4*>(xr + 4 * h4);
-          const float xs[4] = {xv.x, xv.y, xv.z, xv.w};
+        for (int s = 0; s < DQ / 8; ++s) {
+          const JoinVec xv = *reinterpret_cast<const JoinVec*>(&rows[col * RS + 8 * s + 4 * half]);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            float qh = q[4 * h4 + e];
-            asm volatile("" : "+v"(qh));  // keeps the widening here (no hoisted fp64 copy of the row)
-            const double t0 = (double)qh - (double)xs[e];
-            D = __builtin_fma(t0, t0, D);
+            c[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(xv[e], qb[u][s][e], c[u], 0, 0, 0);
+            if (u == 0) nr = __builtin_fmaf(xv[e], xv[e], nr);
           }
-          if (h4 % 2 == 1) __builtin_amdgcn_sched_barrier(0);
         }
-        if (D >= Tlo && D < Thi) {
-          acc += level_weight(ix.cheb + i * kChebRow, sqrt(D) / ri);
-          ++na;
+      }
+      nr += __shfl_xor(nr, 32);
+      if (half == 0) nxl[col] = nr;
+      lds_order();
+      uint32_t found[2] = {0u, 0u};
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const JoinVec nv = *reinterpret_cast<const JoinVec*>(&nxl[8 * g + 4 * half]);
+        const float ns[4] = {nv[0], nv[1], nv[2], nv[3]};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float lo = __builtin_fmaf(ce, ns[e], ns[e] - Tlo_f), hi = __builtin_fmaf(-ce, ns[e], ns[e] - Thi_f);
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            if (u == 1 && !second) continue;
+            // out if D + E < Tlo or D - E > Thi (not if a norm overflows)
+            const float p = 2.0f * c[u][4 * g + e];
+            const bool out = qlo[u] + lo < p || qhi[u] + hi > p;
+            found[u] |= out ? 0u : 1u << (8 * g + e);
+          }
         }
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        found[u] <<= 4 * half;
+        found[u] |= (uint32_t)__shfl_xor((int)found[u], 32);
+      }
+      mask = qvalid ? (half ? found[1] : found[0]) & (nk < 32 ? (1u << nk) - 1u : ~0u) : 0u;
+    }
+    if (k0 + kJoinChunk < nm) id = ix.members[t.s0 + place];
+    // settles open[0 .. min(64, count))
+    auto settle = [&](int count) {
+      const bool valid = lane < count;
+      const uint32_t code = open[valid ? lane : 0];
+      const int m = code & 31, pq = code >> 5;
+      const int qid = qids[pq];
+      // fp64 distances: a quad reads its four pairs' rows together, 16 bytes a
+      // lane of every 64, and adds the four partial sums of each
+      const float* const qrow[4] = {Q + (int64_t)quad_i32<0x00>(qid) * dx,
+                                    Q + (int64_t)quad_i32<0x55>(qid) * dx,
+                                    Q + (int64_t)quad_i32<0xAA>(qid) * dx,
+                                    Q + (int64_t)quad_i32<0xFF>(qid) * dx};
+      const int xrow[4] = {quad_i32<0x00>(m) * RS, quad_i32<0x55>(m) * RS, quad_i32<0xAA>(m) * RS,
+                           quad_i32<0xFF>(m) * RS};
+      double D4[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+      for (int u = 0; u < DQ / 16; ++u) {
+        const int at = 16 * u + 4 * (lane & 3);
+        JoinVec v[4];
+        if (16 * u >= dx) break;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = *reinterpret_cast<const JoinVec*>(qrow[r] + (at < dx ? at : 0));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const JoinVec xv = *reinterpret_cast<const JoinVec*>(&rows[xrow[r] + at]);
+          const float xs[4] = {xv[0], xv[1], xv[2], xv[3]}, qs[4] = {v[r][0], v[r][1], v[r][2], v[r][3]};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const double t0 = at < dx ? (double)qs[e] - (double)xs[e] : 0.0;
+            D4[r] = __builtin_fma(t0, t0, D4[r]);
+          }
+        }
+      }
+      const bool b1 = lane & 2, b0 = lane & 1;
+      const double d0 = (b1 ? D4[2] : D4[0]) + quad_f64<0x4E>(b1 ? D4[0] : D4[2]);  // pairs 2 b1
+      const double d1 = (b1 ? D4[3] : D4[1]) + quad_f64<0x4E>(b1 ? D4[1] : D4[3]);  // pairs 2 b1 + 1
+      const double D = (b0 ? d1 : d0) + quad_f64<0xB1>(b0 ? d0 : d1);
+      const bool take = valid && D >= Tlo && D < Thi;
+      terms[lane] = take ? level_weight(cheb, sqrt(D) / ri) : 0.0;
+      const uint64_t taken = __ballot(take);
+      // a query's pairs are neighbours: its run's first lane leaves their place
+      const int before = __shfl_up(pq, 1);
+      const uint64_t heads = __ballot(valid && (lane == 0 || before != pq));
+      if (valid && (lane == 0 || before != pq)) {
+        const uint64_t later = lane < 63 ? heads >> (lane + 1) : 0ull;
+        const int len = later ? __builtin_ctzll(later) + 1 : min(count, 64) - lane;
+        runs[pq] = (uint32_t)lane | ((uint32_t)len << 8);
+      }
+      lds_order();
+      const uint32_t run = runs[lane];
+      const int x0 = run & 255, len = run >> 8;
+      for (int x = x0; x < x0 + len; ++x) acc += terms[x];
+      if (len > 0) {
+        na += __popcll((taken >> x0) & (~0ull >> (64 - len)));
+        runs[lane] = 0u;
+      }
+      lds_order();
+    };
+    // the chunk's survivors, query by query, in member order: 64 at a time
+    // deduped, and the rest settled 64 at a time
+    int total = nq * nk, nopen = 0;
+    auto place_pairs = [&] {  // ends[lane]: pairs up to this lane
+      const int mine = __popc(mask);
+      int end = mine;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(end, o);
+        if (lane >= o) end += v;
+      }
+      total = __builtin_amdgcn_readlane(end, 63);
+      lds_order();
+      ends[lane] = (uint32_t)end;
+      masks[lane] = mask;
+      lds_order();
+    };
+    bool deduped = false;
+    if (!direct) {
+      place_pairs();
+      deduped = total > kJoinDense;
+      if (deduped) {  // many: member by member, every lane for its own query
+        const int64_t self = self_excl ? q0 + ql : -1;
+        uint32_t kept = 0u;
+        for (int m = 0; m < nk; ++m) {
+          bool seen = (int64_t)jl[m] == self;
+          for (int l2 = 0; l2 < l; ++l2) seen |= mk[m * lm1 + l2] == qk[l2 * 64 + lane];
+          kept |= seen ? 0u : 1u << m;
+        }
+        mask &= kept;
+        place_pairs();
+      }
+    }
+    for (int base = 0; base < total || nopen > 0; base += 64) {
+      if (base < total) {
+        const bool valid = base + lane < total;
+        uint32_t code = 0u;
+        if (direct) {
+          const uint32_t p = (uint32_t)(base + lane), pq = p / (uint32_t)nk;
+          if (valid) code = (pq << 5) | (p - pq * nk);
+        } else if (valid) {
+          // pair base + lane: the first query whose pairs end past it, and of
+          // that query's members the one at the place that is left
+          const uint32_t p = (uint32_t)(base + lane);
+          int pq = 0;
+#pragma unroll
+          for (int o = 32; o > 0; o >>= 1)
+            if (ends[pq + o - 1] <= p) pq += o;
+          uint32_t w = masks[pq], r = p - (ends[pq] - (uint32_t)__popc(w));
+          int m = 0;
+#pragma unroll
+          for (int o = 16; o > 0; o >>= 1) {
+            const uint32_t low = (uint32_t)__popc(w & ((1u << o) - 1u));
+            const bool up = r >= low;
+            r -= up ? low : 0u;
+            m += up ? o : 0;
+            w = up ? w >> o : w;
+          }
+          code = ((uint32_t)pq << 5) | (uint32_t)m;
+        }
+        bool seen = !valid;
+        if (!deduped) {
+          const int m = code & 31, pq = code >> 5;
+          const int64_t self = self_excl ? q0 + qids[pq] : -1;
+          seen |= (int64_t)jl[m] == self;
+          for (int l2 = 0; l2 < l; ++l2) seen |= mk[m * lm1 + l2] == qk[l2 * 64 + pq];
+        }
+        const uint64_t left = __ballot(!seen);
+        if (!seen) open[nopen + __popcll(left & ((1ull << lane) - 1ull))] = code;
+        nopen += __popcll(left);
+        lds_order();
+      }
+      if (nopen >= 64 || (nopen > 0 && base + 64 >= total)) {  // never none: open[0] is read
+        settle(min(nopen, 64));
+        nopen = max(nopen - 64, 0);
+        const uint32_t moved = lane < nopen ? open[64 + lane] : 0u;
+        lds_order();
+        if (lane < nopen) open[lane] = moved;
+        lds_order();
       }
     }
   }
@@ -1916,31 +2129,36 @@ stag_status join_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64
                                                 (unsigned long long)ntasks);
   double* tpart = nullptr;
   STAG_TRY(ws.alloc(&tpart, (size_t)std::max<uint64_t>(ntasks, 1) * 64));
+  JoinTask* tasks = nullptr;
+  STAG_TRY(ws.alloc(&tasks, (size_t)std::max<uint64_t>(ntasks, 1)));
   const IndexView ix = make_view(idx);
   const LevelConst lc = make_levels(prm);
   if (ntasks > 0) {
     ScopedTimer tm("lsh_join", st);
     const int dq = idx->d <= 16 ? 16 : idx->d <= 32 ? 32 : idx->d <= 64 ? 64 : 128;
-    const bool reg_keys = L <= kJoinRegKeys + 1;
-    const size_t lds = (size_t)join_lds_bytes(dq, L, reg_keys);
+    const size_t lds = (size_t)join_lds_bytes(dq, L);
+    hipLaunchKernelGGL(describe_tasks, dim3((unsigned)ceil_div((int64_t)ntasks, 256)), dim3(256), 0, st, ix, qcount,
+                       qstart, task_base, nslots, (int)idx->nseg, (int64_t)ntasks, tasks);
+    STAG_TRY(check_launch("describe_tasks"));
+    // query rows as the index's own are (16-byte pieces, zeros up to dx)
+    const float* rows = Q + q0 * ldq;
+    if (ldq != idx->dx || ((uintptr_t)Q & 15u) != 0) {
+      float* padded = nullptr;
+      STAG_TRY(ws.alloc(&padded, (size_t)cur * idx->dx));
+      hipLaunchKernelGGL(copy_rows, dim3((unsigned)std::min<int64_t>(ceil_div(cur * idx->dx, 256), 65536)), dim3(256),
+                         0, st, rows, cur, ldq, idx->dx, padded);
+      STAG_TRY(check_launch("copy_rows"));
+      rows = padded;
+    }
     auto launch = [&](auto kern) {
-      hipLaunchKernelGGL(kern, dim3((unsigned)ntasks), dim3(64), lds, st, ix, lc, Q, ldq, q0, qkeys, cur, qcount,
-                         qstart, qlist, task_base, nslots, (int)idx->nseg, self_excl, tpart, nacc);
+      hipLaunchKernelGGL(kern, dim3((unsigned)ntasks), dim3(64), lds, st, ix, lc, rows, q0, qkeys, cur, qlist, tasks,
+                         self_excl, tpart, nacc);
     };
-    if (reg_keys) {
-      switch (dq) {
-        case 16: launch(join_buckets<16, kJoinRegKeys>); break;
-        case 32: launch(join_buckets<32, kJoinRegKeys>); break;
-        case 64: launch(join_buckets<64, kJoinRegKeys>); break;
-        default: launch(join_buckets<128, kJoinRegKeys>); break;
-      }
-    } else {
-      switch (dq) {
-        case 16: launch(join_buckets<16, 0>); break;
-        case 32: launch(join_buckets<32, 0>); break;
-        case 64: launch(join_buckets<64, 0>); break;
-        default: launch(join_buckets<128, 0>); break;
-      }
+    switch (dq) {
+      case 16: launch(join_buckets<16>); break;
+      case 32: launch(join_buckets<32>); break;
+      case 64: launch(join_buckets<64>); break;
+      default: launch(join_buckets<128>); break;
     }
     STAG_TRY(check_launch("join_buckets"));
   }
