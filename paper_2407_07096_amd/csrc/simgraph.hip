@@ -21,6 +21,7 @@
 
 #include "kde_exact.h"
 #include "lsh.h"
+#include "row_dist.h"
 #include "runtime.h"
 #include "sort.h"
 
@@ -30,10 +31,11 @@ namespace {
 constexpr uint64_t kGammaS = 0x9E3779B97F4A7C15ULL;
 constexpr uint64_t kTagDrawS = 0x44524157ULL;
 // Rows up to this width draw in one fused kernel, wider ones through the
-// tile sort (measured at n = 100,000, 17 draws per node: the fused draw is
-// faster by 20% at d = 64 and by 5% at d = 256, the sorted one by 9% at
-// d = 512 and, on sparse rows at n = 70,000, by 43% at d = 784).
-constexpr int kDrawFusedMaxDim = 256;
+// tile sort.  Measured at n = 100,000, 17 draws per node, fused against sorted:
+// 1.78 against 1.80 ms at d = 64, 7.5 against 3.0 at d = 256, 15.8 against 5.1
+// at d = 512 and, on sparse rows at n = 70,000, 22.6 against 5.0 at d = 784
+// (the tiles of narrow rows stay in cache in any order).
+constexpr int kDrawFusedMaxDim = 64;
 constexpr int kChunkTiles = 128;  // 32-row tiles per 4096-row chunk
 constexpr double kLog2eS = 1.4426950408889634074;
 
@@ -43,15 +45,19 @@ __device__ inline uint64_t mixs(uint64_t z) {
   return z ^ (z >> 31);
 }
 
-__device__ inline double scan64(double v) {
-  const int lane = threadIdx.x & 63;
+// Inclusive sums over each half of the wave.
+__device__ inline double scan32(double v) {
+  const int c = threadIdx.x & 31;
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const double u = __shfl_up(v, o);
-    if (lane >= o) v += u;
+  for (int o = 1; o < 32; o <<= 1) {
+    const double u = __shfl_up(v, o, 32);
+    if (c >= o) v += u;
   }
   return v;
 }
+
+// The lanes of this half among those where `p` holds (all lanes active).
+__device__ inline uint32_t half_ballot(bool p) { return (uint32_t)(__ballot(p) >> (threadIdx.x & 32)); }
 
 // rest_i (chunk order) and a node-major copy of the chunk sums, so that a
 // draw reads its node's P sums from consecutive addresses.
@@ -102,37 +108,58 @@ __global__ void rescue_rows(const double* __restrict__ partial, int P, int64_t m
   if (deg) deg[i] = 1.0 + t;
 }
 
-// Inverts a cumulative sum over `count` values v(k) (k ascending, fetched by
-// the lane that owns k) for `target`; returns the index and the remainder
-// below it.  Past the total (rounding), the last positive value is taken with
-// an infinite remainder so that lower levels also take their last element.
-template <class Fetch>
-__device__ inline int invert_level(int count, double target, Fetch&& fetch, double* resid_out) {
-  const int lane = threadIdx.x & 63;
-  double running = 0.0;
-  int last = -1;
-  for (int k0 = 0; k0 < count; k0 += 64) {
-    const int k = k0 + lane;
-    const double v = k < count ? fetch(k) : 0.0;
-    const double incl = scan64(v);
-    const double btot = __shfl(incl, 63);
-    const uint64_t pos = __ballot(v > 0.0);
-    if (pos) last = k0 + 63 - __clzll((long long)pos);
-    if (running + btot > target) {
-      // only a positive value can be the crossing: past the block's last
-      // positive value the tree scan may differ from it by a rounding, and a
-      // crossing found there means the target lies beyond this block
-      const uint64_t over = __ballot(running + incl > target) & pos;
+// Each half of the wave inverts a cumulative sum over `count` values (the same
+// count in both) for its own `target`: 32 N values at a time, fetch(k0, v)
+// giving lane c the values k0 + N c .. + N - 1 (0 past the end).  Returns the
+// index and the remainder below it.  Past the total (rounding), the last
+// positive value is taken with an infinite remainder so that lower levels also
+// take their last element; -1 if no value is positive.  All lanes active.
+template <int N, class Fetch>
+__device__ inline int invert_half(int count, double target, Fetch&& fetch, double* resid_out) {
+  const int c = threadIdx.x & 31;
+  double running = 0.0, resid = INFINITY;
+  int found = -1, last = -1;
+  for (int k0 = 0; k0 < count; k0 += 32 * N) {
+    double v[N], sum[N];
+    fetch(k0, v);
+    sum[0] = v[0];
+#pragma unroll
+    for (int q = 1; q < N; ++q) sum[q] = sum[q - 1] + v[q];
+    const double incl = scan32(sum[N - 1]);
+    double before = __shfl_up(incl, 1, 32);
+    before = c == 0 ? running : running + before;
+    // only a positive value can be the crossing: past the last positive value
+    // the tree scan may differ from it by a rounding, and a crossing found
+    // there means the target lies beyond these values
+    int at = N, lastq = -1;
+#pragma unroll
+    for (int q = N - 1; q >= 0; --q)
+      if (v[q] > 0.0) {
+        lastq = lastq < 0 ? q : lastq;
+        if (before + sum[q] > target) at = q;
+      }
+    const uint32_t pos = half_ballot(lastq >= 0), over = half_ballot(at < N);
+    double below = before;  // of the crossing
+    if constexpr (N > 1) {
+#pragma unroll
+      for (int q = 1; q < N; ++q) below = at == q ? before + sum[q - 1] : below;
+    }
+    const int lo = over ? __builtin_ctz(over) : 0, lp = pos ? 31 - __builtin_clz(pos) : 0;
+    const int q_over = __shfl(at, lo, 32), q_last = __shfl(lastq, lp, 32);
+    const double r = target - __shfl(below, lo, 32), total = __shfl(incl, 31, 32);
+    if (found < 0) {
       if (over) {
-        const int kl = __ffsll((long long)over) - 1;
-        *resid_out = target - (running + __shfl(incl - v, kl));
-        return k0 + kl;
+        found = k0 + N * lo + q_over;
+        resid = r;
+      } else if (pos) {
+        last = k0 + N * lp + q_last;
       }
     }
-    running += btot;
+    running += total;
+    if (__ballot(found < 0) == 0ull) break;
   }
-  *resid_out = INFINITY;
-  return last;
+  *resid_out = found >= 0 ? resid : INFINITY;
+  return found >= 0 ? found : last;
 }
 
 // A draw of node i takes a chunk, then a 32-row tile within it, then a row
@@ -144,6 +171,12 @@ __device__ inline int invert_level(int count, double target, Fetch&& fetch, doub
 // gather the same tile run side by side and hit in that XCD's L2.  For
 // narrow rows, whose tiles stay in cache anyway, one fused kernel does both.
 // The order changes only where a draw runs, not what it computes.
+//
+// A draw is a chain of dependent loads and scans, so it is the waves in flight
+// that bound it: half a wave per draw, the tile sums of a chunk in one scan of
+// four a lane, and the rows of the tile read by quads of lanes.  With a wave
+// per draw, two scans of 64 tile sums and two lanes a row, 1.7e6 draws at
+// n = 1e5, d = 64 took 2.6 ms; now 1.8.
 
 // The uniform of draw r of node i.
 __device__ inline double draw_uniform(uint64_t seed, int64_t i, int r) {
@@ -151,178 +184,132 @@ __device__ inline double draw_uniform(uint64_t seed, int64_t i, int r) {
   return (double)(mixs(ds + (uint64_t)(r + 1) * kGammaS) >> 11) * 0x1.0p-53;
 }
 
-// Steps 1 and 2 of a draw (the whole wave): the tile (ntile when the draw
-// finds none) and the remainder of the target below it.
+// e / s (the 64-bit quotient is a long sequence)
+__device__ inline int64_t node_of(int64_t e, int s) {
+  return e < ((int64_t)1 << 31) ? (int64_t)((uint32_t)e / (uint32_t)s) : e / s;
+}
+
+// Steps 1 and 2 of a draw (half a wave): the tile (ntile when the draw finds
+// none) and the remainder of the target below it.
 __device__ inline int64_t draw_tile_of(int64_t i, double u, int P, int64_t ntile, int64_t tstride,
                                        const double* __restrict__ chunk_t, const float* __restrict__ tp,
                                        const double* __restrict__ rest, const double* __restrict__ rest_draw,
                                        double* resid2) {
   // rest_draw: the total in the scale of the chunk and tile sums (2^{-m_i}
   // times the true one for a row of the underflow rescue, else the same)
+  const int lane32 = threadIdx.x & 31;
   const double tot = rest_draw[i];
-  *resid2 = 0.0;
-  if (!(rest[i] > 0.0 && tot > 0.0)) return ntile;
+  const bool any = rest[i] > 0.0 && tot > 0.0;
   double resid = 0.0;
-  const int c = invert_level(P, u * tot, [&](int k) { return chunk_t[i * P + k]; }, &resid);
-  if (c < 0) return ntile;
-  const int64_t t0 = (int64_t)c * kChunkTiles;
-  const int nt = (int)((ntile - t0) < kChunkTiles ? (ntile - t0) : kChunkTiles);
-  const int tl = invert_level(nt, resid, [&](int k) { return (double)tp[i * tstride + t0 + k]; }, resid2);
-  return tl >= 0 ? t0 + tl : ntile;
-}
-
-__device__ inline double sq_diff4(double D, const float4& p, const float4& q) {
-  double t = (double)p.x - (double)q.x;
-  D = __builtin_fma(t, t, D);
-  t = (double)p.y - (double)q.y;
-  D = __builtin_fma(t, t, D);
-  t = (double)p.z - (double)q.z;
-  D = __builtin_fma(t, t, D);
-  t = (double)p.w - (double)q.w;
-  return __builtin_fma(t, t, D);
-}
-
-// Copies x_i into this wave's LDS row xs (16-byte pieces when vec4).
-__device__ inline void stage_xi(float* xs, const float* __restrict__ X, int64_t i, int d, int vec4, bool active) {
-  const int lane = threadIdx.x & 63;
-  if (!active) return;
-  if (vec4) {
-    const float4* src4 = reinterpret_cast<const float4*>(X + i * d);
-    float4* xs4 = reinterpret_cast<float4*>(xs);
-    for (int c = lane; c < (d >> 2); c += 64) xs4[c] = src4[c];
-  } else {
-    for (int c = lane; c < d; c += 64) xs[c] = X[i * d + c];
+  const int c = invert_half<1>(
+      P, u * tot,
+      [&](int k0, double (&v)[1]) { v[0] = any && k0 + lane32 < P ? chunk_t[i * P + k0 + lane32] : 0.0; }, &resid);
+  const int64_t t0 = (int64_t)(c < 0 ? 0 : c) * kChunkTiles;
+  const int nt = c < 0 ? 0 : (int)((ntile - t0) < kChunkTiles ? (ntile - t0) : kChunkTiles);
+  static_assert(kChunkTiles == 4 * 32, "one scan of four a lane");
+  const int tl = invert_half<4>(
+      kChunkTiles, resid,
+      [&](int, double (&v)[4]) {
+        // tstride and t0 are multiples of 16: aligned, and inside the row
+        const int k = 4 * lane32;
+        float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (k < nt) f = *reinterpret_cast<const float4*>(&tp[i * tstride + t0 + k]);
+        v[0] = (double)f.x;
+        v[1] = k + 1 < nt ? (double)f.y : 0.0;
+        v[2] = k + 2 < nt ? (double)f.z : 0.0;
+        v[3] = k + 3 < nt ? (double)f.w : 0.0;
+      },
+      resid2);
+  if (tl < 0) {
+    *resid2 = 0.0;
+    return ntile;
   }
+  return t0 + tl;
 }
 
-// Step 3 (the whole wave): the row of tile T for remainder resid2, or -1;
-// xi is node i's row staged in LDS.  Rows of the tile: lanes l and l + 32
-// share row l % 32 and take alternate 16-byte pieces (or alternate
-// elements) of it, summed in order; the loads of four pieces are issued
-// before their products so that they overlap.
-__device__ inline int64_t draw_row_of(const float* xi, const float* __restrict__ X, int64_t n, int d, double a,
-                                      int64_t i, int64_t T, double resid2, double sh, int vec4) {
-  const int lane = threadIdx.x & 63;
-  const int64_t rb = T * 32;
-  const int half = lane >> 5;
-  const int64_t j = rb + (lane & 31);
-  const bool live = j < n && j != i;
-  double D = 0.0;
-  if (live) {
-    const float* xj = X + j * d;
-    if (vec4) {
-      const float4* a4 = reinterpret_cast<const float4*>(xi);
-      const float4* b4 = reinterpret_cast<const float4*>(xj);
-      const int n4 = d >> 2;
-      int k4 = half;
-      for (; k4 + 6 < n4; k4 += 8) {
-        const float4 p0 = a4[k4], q0 = b4[k4], p1 = a4[k4 + 2], q1 = b4[k4 + 2];
-        const float4 p2 = a4[k4 + 4], q2 = b4[k4 + 4], p3 = a4[k4 + 6], q3 = b4[k4 + 6];
-        D = sq_diff4(D, p0, q0);
-        D = sq_diff4(D, p1, q1);
-        D = sq_diff4(D, p2, q2);
-        D = sq_diff4(D, p3, q3);
-      }
-      for (; k4 < n4; k4 += 2) D = sq_diff4(D, a4[k4], b4[k4]);
-    } else {
-      for (int h = half; h < d; h += 2) {
-        const double t = (double)xi[h] - (double)xj[h];
-        D = __builtin_fma(t, t, D);
-      }
-    }
-  }
-  D += __shfl_xor(D, 32);
+// Step 3 (half a wave): the row of tile T for remainder resid2, or -1 (also
+// for T = ntile).
+template <RowRead ROWS>
+__device__ inline int64_t draw_row_of(const float* __restrict__ X, int64_t n, int64_t ntile, int d, double a,
+                                      int64_t i, int64_t T, double resid2, double sh) {
+  const int64_t rb = T * 32, j = rb + (threadIdx.x & 31);
+  const bool live = T < ntile && j < n && j != i;
+  const double D = row_dist2<ROWS>(X, i, live ? j : i, d);
   // a shifted row's values are 2^{E - m_i} with E = -a log2(e) D in one
   // exponent (2^{-m_i} alone overflows for m_i < -1024, and exp(-a D) is
   // subnormal there)
   double kv = 0.0;
-  if (lane < 32 && live) kv = sh == 0.0 ? exp(-a * D) : exp2(fma(-a * kLog2eS, D, -sh));
+  if (live) kv = sh == 0.0 ? exp(-a * D) : exp2(fma(-a * kLog2eS, D, -sh));
   double resid3 = 0.0;
-  const int jl = invert_level(32, resid2, [&](int) { return kv; }, &resid3);  // lane k owns row k
+  const int jl = invert_half<1>(32, resid2, [&](int, double (&v)[1]) { v[0] = kv; }, &resid3);
   return jl >= 0 ? rb + jl : -1;
 }
 
 __device__ inline void draw_store(int64_t e, int64_t i, int64_t pick, int s, const double* __restrict__ rest,
                                   int64_t* __restrict__ src, int64_t* __restrict__ dst, double* __restrict__ w) {
-  if ((threadIdx.x & 63) == 0) {
-    src[e] = i;
-    dst[e] = pick;
-    w[e] = pick >= 0 ? 1.0 / ((double)s * (1.0 / rest[i] + 1.0 / rest[pick])) : 0.0;
-  }
+  src[e] = i;
+  dst[e] = pick;
+  w[e] = pick >= 0 ? 1.0 / ((double)s * (1.0 / rest[i] + 1.0 / rest[pick])) : 0.0;
 }
 
-// Fused draw, one wave per draw e = (node i, draw r); dynamic LDS: one
-// row of d floats per wave.
+// Fused draw, half a wave per draw e = (node i, draw r).
+template <RowRead ROWS>
 __global__ __launch_bounds__(256) void draw_exact(const float* __restrict__ X, int64_t n, int d, double a, int s,
                                                   uint64_t seed, int P, int64_t ntile, int64_t tstride,
                                                   const double* __restrict__ chunk_t, const float* __restrict__ tp,
                                                   const double* __restrict__ rest,
                                                   const double* __restrict__ rest_draw,
-                                                  const double* __restrict__ shift, int vec4,
-                                                  int64_t* __restrict__ src, int64_t* __restrict__ dst,
-                                                  double* __restrict__ w) {
-  extern __shared__ float4 dxs4[];
-  float* xs = reinterpret_cast<float*>(dxs4) + (threadIdx.x >> 6) * d;
-  const int64_t e = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const bool active = e < n * s;
-  const int64_t i = active ? e / s : 0;
-  stage_xi(xs, X, i, d, vec4, active);
+                                                  const double* __restrict__ shift, int64_t* __restrict__ src,
+                                                  int64_t* __restrict__ dst, double* __restrict__ w) {
+  const int64_t e0 = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 5);
+  const int64_t e = e0 < n * s ? e0 : n * s - 1;  // the last wave's spare half repeats
+  const int64_t i = node_of(e, s);
   double resid2 = 0.0;
-  int64_t T = ntile;
-  if (active)
-    T = draw_tile_of(i, draw_uniform(seed, i, (int)(e % s)), P, ntile, tstride, chunk_t, tp, rest, rest_draw,
-                     &resid2);
-  __syncthreads();
-  if (!active) return;
-  const int64_t pick = T < ntile ? draw_row_of(xs, X, n, d, a, i, T, resid2, shift[i], vec4) : -1;
-  draw_store(e, i, pick, s, rest, src, dst, w);
+  const int64_t T = draw_tile_of(i, draw_uniform(seed, i, (int)(e - i * s)), P, ntile, tstride, chunk_t, tp, rest,
+                                 rest_draw, &resid2);
+  const int64_t pick = draw_row_of<ROWS>(X, n, ntile, d, a, i, T, resid2, shift[i]);
+  if ((threadIdx.x & 31) == 0 && e0 == e) draw_store(e, i, pick, s, rest, src, dst, w);
 }
 
-// Split draw, step 1 (one wave per draw e): tile[e], order[e] = e and the
+// Split draw, step 1 (half a wave per draw e): tile[e], order[e] = e and the
 // remainder.
 __global__ __launch_bounds__(256) void draw_tile(int64_t n, int s, uint64_t seed, int P, int64_t ntile,
                                                  int64_t tstride, const double* __restrict__ chunk_t,
                                                  const float* __restrict__ tp, const double* __restrict__ rest,
                                                  const double* __restrict__ rest_draw, uint32_t* __restrict__ tile,
                                                  uint32_t* __restrict__ order, double* __restrict__ resid_out) {
-  const int64_t e = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (e >= n * s) return;
-  const int64_t i = e / s;
+  const int64_t e0 = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 5);
+  const int64_t e = e0 < n * s ? e0 : n * s - 1;
+  const int64_t i = node_of(e, s);
   double resid2 = 0.0;
-  const int64_t T =
-      draw_tile_of(i, draw_uniform(seed, i, (int)(e % s)), P, ntile, tstride, chunk_t, tp, rest, rest_draw, &resid2);
-  if ((threadIdx.x & 63) == 0) {
+  const int64_t T = draw_tile_of(i, draw_uniform(seed, i, (int)(e - i * s)), P, ntile, tstride, chunk_t, tp, rest,
+                                 rest_draw, &resid2);
+  if ((threadIdx.x & 31) == 0 && e0 == e) {
     tile[e] = (uint32_t)T;
     order[e] = (uint32_t)e;
     resid_out[e] = resid2;
   }
 }
 
-// Split draw, step 2, one wave per draw in the order given by `order`
-// (tile[k] is the tile of draw order[k]); dynamic LDS: one row of d floats
-// per wave.  Workgroups go round-robin to the 8 XCDs: block b works on
-// logical block (b % 8) per + b / 8 (the grid is 8 per blocks), i.e. slots
-// [4 L, 4 L + 4).
+// Split draw, step 2, half a wave per draw in the order given by `order`
+// (tile[k] is the tile of draw order[k]).  Workgroups go round-robin to the 8
+// XCDs: block b works on logical block (b % 8) per + b / 8 (the grid is 8 per
+// blocks), i.e. slots [8 L, 8 L + 8).
+template <RowRead ROWS>
 __global__ __launch_bounds__(256) void draw_row(const float* __restrict__ X, int64_t n, int d, double a, int s,
                                                 int64_t ntile, int per, const uint32_t* __restrict__ tile,
                                                 const uint32_t* __restrict__ order,
                                                 const double* __restrict__ resid_in,
                                                 const double* __restrict__ rest, const double* __restrict__ shift,
-                                                int vec4, int64_t* __restrict__ src, int64_t* __restrict__ dst,
+                                                int64_t* __restrict__ src, int64_t* __restrict__ dst,
                                                 double* __restrict__ w) {
-  extern __shared__ float4 dxs4[];
-  float* xs = reinterpret_cast<float*>(dxs4) + (threadIdx.x >> 6) * d;
   const int b = blockIdx.x;
-  const int64_t slot = ((int64_t)(b % 8) * per + b / 8) * 4 + (threadIdx.x >> 6);
-  const bool active = slot < n * s;
-  const int64_t e = active ? (int64_t)order[slot] : 0;
-  const int64_t i = e / s;
-  stage_xi(xs, X, i, d, vec4, active);
-  __syncthreads();
-  if (!active) return;
-  const int64_t T = tile[slot];
-  const int64_t pick = T < ntile ? draw_row_of(xs, X, n, d, a, i, T, resid_in[e], shift[i], vec4) : -1;
-  draw_store(e, i, pick, s, rest, src, dst, w);
+  const int64_t slot0 = ((int64_t)(b % 8) * per + b / 8) * 8 + (threadIdx.x >> 5);
+  const int64_t slot = slot0 < n * s ? slot0 : n * s - 1;
+  const int64_t e = (int64_t)order[slot];
+  const int64_t i = node_of(e, s);
+  const int64_t pick = draw_row_of<ROWS>(X, n, ntile, d, a, i, tile[slot], resid_in[e], shift[i]);
+  if ((threadIdx.x & 31) == 0 && slot0 == slot) draw_store(e, i, pick, s, rest, src, dst, w);
 }
 
 stag_status sample_exact(const float* X, int64_t n, int d, double a, int form, int s, uint64_t seed, int64_t* src,
@@ -374,18 +361,20 @@ stag_status sample_exact(const float* X, int64_t n, int d, double a, int form, i
   hipLaunchKernelGGL(rescue_rows, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st, partial, P, qo.rows_pad, n,
                      flag, shift, rest, rest_draw, deg_out, chunk_t);
   STAG_TRY(check_launch("rescue_rows"));
-  const int vec4 = (d % 4 == 0) && (reinterpret_cast<uintptr_t>(X) % 16 == 0);
   const int64_t nd = n * s;
-  const size_t lds = (size_t)4 * d * sizeof(float);  // x_i of each of the 4 waves
+  const RowRead rows = row_read(d);
+  auto by_rows = [&](auto own, auto quad4, auto quad) { return rows == kOwnRow ? own : rows == kQuad4 ? quad4 : quad; };
   ScopedTimer tm("simgraph_draw_exact", st);
-  if (d <= kDrawFusedMaxDim) {
-    hipLaunchKernelGGL(draw_exact, dim3((unsigned)ceil_div(nd, 4)), dim3(256), lds, st, X, n, d, a, s, seed, P, ntile,
-                       tstride, chunk_t, tp, rest, rest_draw, shift, vec4, src, dst, w);
-    return check_launch("draw_exact");
-  }
   // the sort carries draw indices in 32 bits (the n x n/32 tile sums above
   // bound n far below this in practice)
-  if (nd >= ((int64_t)1 << 31)) return fail(STAG_E_UNSUPPORTED, "stag_simgraph_sample: n * s >= 2^31 draws");
+  const bool sortable = nd < ((int64_t)1 << 31);
+  if (d <= kDrawFusedMaxDim || (d <= 256 && !sortable)) {
+    hipLaunchKernelGGL(by_rows(draw_exact<kOwnRow>, draw_exact<kQuad4>, draw_exact<kQuad>),
+                       dim3((unsigned)ceil_div(nd, 8)), dim3(256), 0, st, X, n, d, a, s, seed, P, ntile, tstride,
+                       chunk_t, tp, rest, rest_draw, shift, src, dst, w);
+    return check_launch("draw_exact");
+  }
+  if (!sortable) return fail(STAG_E_UNSUPPORTED, "stag_simgraph_sample: n * s >= 2^31 draws");
   uint32_t *tile = nullptr, *order = nullptr, *tile_s = nullptr, *order_s = nullptr;
   double* resid = nullptr;
   STAG_TRY(ws.alloc(&tile, (size_t)nd));
@@ -393,15 +382,15 @@ stag_status sample_exact(const float* X, int64_t n, int d, double a, int form, i
   STAG_TRY(ws.alloc(&tile_s, (size_t)nd));
   STAG_TRY(ws.alloc(&order_s, (size_t)nd));
   STAG_TRY(ws.alloc(&resid, (size_t)nd));
-  hipLaunchKernelGGL(draw_tile, dim3((unsigned)ceil_div(nd, 4)), dim3(256), 0, st, n, s, seed, P, ntile, tstride,
+  hipLaunchKernelGGL(draw_tile, dim3((unsigned)ceil_div(nd, 8)), dim3(256), 0, st, n, s, seed, P, ntile, tstride,
                      chunk_t, tp, rest, rest_draw, tile, order, resid);
   STAG_TRY(check_launch("draw_tile"));
   int bits = 1;
   while (((int64_t)1 << bits) <= ntile) ++bits;  // keys 0..ntile
   STAG_TRY(radix_sort_pairs_u32(tile, order, tile_s, order_s, nd, bits, ws, st));
-  const int per = (int)ceil_div(ceil_div(nd, 4), 8);
-  hipLaunchKernelGGL(draw_row, dim3((unsigned)(8 * per)), dim3(256), lds, st, X, n, d, a, s, ntile, per, tile_s,
-                     order_s, resid, rest, shift, vec4, src, dst, w);
+  const int per = (int)ceil_div(ceil_div(nd, 8), 8);
+  hipLaunchKernelGGL(by_rows(draw_row<kOwnRow>, draw_row<kQuad4>, draw_row<kQuad>), dim3((unsigned)(8 * per)),
+                     dim3(256), 0, st, X, n, d, a, s, ntile, per, tile_s, order_s, resid, rest, shift, src, dst, w);
   return check_launch("draw_row");
 }
 

@@ -28,7 +28,7 @@
 // Layout and work: one wave per draw and level; lanes 0-31 hold child A's
 // samples (or rows), lanes 32-63 child B's (two or four draws a wave where 16
 // or 8 lanes hold a child's), one kernel value per lane from
-// fp64 direct differences, whose rows four lanes read together (tree_dist);
+// fp64 direct differences, whose rows four lanes read together (row_dist2);
 // the values of a child are summed in a fixed butterfly order.  Work per draw: h
 // levels x 2t kernel values + 32 at the leaf, each d fp64 operations on a
 // gathered row.  Results are deterministic; against a sequential fp64 sum
@@ -36,6 +36,7 @@
 // lies within that rounding of a boundary.
 #include <utility>
 
+#include "row_dist.h"
 #include "runtime.h"
 #include "sort.h"
 
@@ -79,108 +80,6 @@ inline DivBy div_by(uint32_t s) {
 }
 __device__ inline uint32_t quotient(uint32_t e, const DivBy& q) { return (uint32_t)(((uint64_t)e * q.m) >> q.shift); }
 
-// v of lane ^ 1 or lane ^ 2 (quad permutations), all lanes active.
-template <int CTRL>
-__device__ inline double quad_perm(double v) {
-  const int lo = __double2loint(v), hi = __double2hiint(v);
-  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false),
-                          __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false));
-}
-
-// ||x_i - x_j||^2 for the row j of each lane, by fp64 direct differences; i is
-// the same in the four lanes of a quad, and all lanes are active.
-//
-// d > 8: the quad reads its four rows one after the other, each lane 16 bytes
-// of every 64, and the four partial sums per row are added across the quad at
-// the end.  With a lane per row every load touches 64 cache lines, and the
-// rate of the L1's tag lookups bounds the gathers: 1e5 points of 64
-// coordinates, 1.7e6 draws over 12 levels took 36.5 ms that way (2.0 at the
-// leaves); now 20.9 (0.85), bound by the fp64 operations where a node's rows
-// fit an L2 and by the misses of the first three levels.  Two pieces at a time
-// leave 6 waves a SIMD; four took 25.2 with 4 waves.  d <= 8: a lane per row,
-// whose line or two it reads whole (n = 2e4, d = 4, t = 4: quads 2.7 ms a
-// call, a lane per row 0.9).
-//
-// Rows need only the alignment of a float: 16-byte loads need no more.
-enum TreeRows { kOwnRow, kQuad4, kQuad };  // d <= 8; d a multiple of 4; any d
-inline TreeRows tree_rows(int d) { return d <= 8 ? kOwnRow : d % 4 == 0 ? kQuad4 : kQuad; }
-
-using TreeVec = float __attribute__((ext_vector_type(4), aligned(4)));
-
-// U 64-byte pieces from coordinate c on; PART: the last may end before 64.
-template <TreeRows ROWS, int U, bool PART>
-__device__ __forceinline__ void tree_piece(const float* __restrict__ xi, const float* const (&xj)[4], int c, int d,
-                                           double (&acc)[4]) {
-  const int q = threadIdx.x & 3;
-  auto load = [&](const float* x, int u) {
-    const int at = c + (4 * u + q) * 4;
-    TreeVec v = {0.f, 0.f, 0.f, 0.f};
-    if (!PART || u < U - 1 || at + 4 <= d) {
-      v = *reinterpret_cast<const TreeVec*>(x + at);
-    } else if (ROWS == kQuad && at < d) {
-      v[0] = x[at];
-      if (at + 1 < d) v[1] = x[at + 1];
-      if (at + 2 < d) v[2] = x[at + 2];
-    }
-    return v;
-  };
-  TreeVec y[4][U];
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int u = 0; u < U; ++u) y[r][u] = load(xj[r], u);
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const TreeVec x = load(xi, u);
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const double xd = x[w];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const double t = xd - (double)y[r][u][w];
-        acc[r] = fma(t, t, acc[r]);
-      }
-    }
-  }
-}
-
-template <TreeRows ROWS>
-__device__ __forceinline__ double tree_dist(const float* __restrict__ X, int64_t i, int64_t j, int d) {
-  const float* xi = X + i * d;
-  if constexpr (ROWS == kOwnRow) {
-    const float* x = X + j * d;
-    double D = 0.0;
-    int c = 0;
-    for (; c + 4 <= d; c += 4) {
-      const TreeVec u = *reinterpret_cast<const TreeVec*>(xi + c), v = *reinterpret_cast<const TreeVec*>(x + c);
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const double t = (double)u[w] - (double)v[w];
-        D = fma(t, t, D);
-      }
-    }
-    for (; c < d; ++c) {
-      const double t = (double)xi[c] - (double)x[c];
-      D = fma(t, t, D);
-    }
-    return D;
-  } else {
-    const int q = threadIdx.x & 3;
-    const float* xj[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) xj[r] = X + (int64_t)__shfl((int)j, r, 4) * d;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    int c = 0;
-    for (; c + 32 <= d; c += 32) tree_piece<ROWS, 2, false>(xi, xj, c, d, acc);
-    if (d - c > 16) tree_piece<ROWS, 2, true>(xi, xj, c, d, acc);
-    else if (d - c > 0) tree_piece<ROWS, 1, true>(xi, xj, c, d, acc);
-    const bool b1 = q & 2, b0 = q & 1;
-    const double k0 = (b1 ? acc[2] : acc[0]) + quad_perm<0x4E>(b1 ? acc[0] : acc[2]);  // rows 2 b1
-    const double k1 = (b1 ? acc[3] : acc[1]) + quad_perm<0x4E>(b1 ? acc[1] : acc[3]);  // rows 2 b1 + 1
-    return (b0 ? k1 : k0) + quad_perm<0xB1>(b0 ? k0 : k1);
-  }
-}
-
 // Sum over each group of LANES lanes (fixed butterfly).
 template <int LANES>
 __device__ inline double lanes_sum(double v) {
@@ -191,7 +90,7 @@ __device__ inline double lanes_sum(double v) {
 }
 
 // rest[i] = est(i, root) with t_deg samples; one wave per row i.
-template <TreeRows ROWS>
+template <RowRead ROWS>
 __global__ __launch_bounds__(256, 4) void tree_degrees(const float* __restrict__ X, int64_t n, int d, double a,
                                                     int64_t t_deg, uint64_t seed, double* __restrict__ rest,
                                                     double* __restrict__ deg_out) {
@@ -206,7 +105,7 @@ __global__ __launch_bounds__(256, 4) void tree_degrees(const float* __restrict__
     const int64_t c = c0 + lane;
     int64_t j = i;
     if (c < count) j = all ? c : tpick(tout(st, (uint64_t)c), (uint32_t)n);
-    const double D = tree_dist<ROWS>(X, i, j, d);
+    const double D = row_dist2<ROWS>(X, i, j, d);
     if (j != i) s += exp(-a * D);
   }
 #pragma unroll
@@ -247,7 +146,7 @@ __global__ void tree_init(uint32_t* __restrict__ perm, uint32_t* __restrict__ no
 // LANES lanes per child (t <= LANES), 2 LANES per draw: with few samples a
 // wave takes two or four draws (n = 5e4, d = 30, t = 16: one draw a wave 17.9 ms
 // a call before the wider loads, two draws 10.5, and 5.4 with them).
-template <TreeRows ROWS, int LANES>
+template <RowRead ROWS, int LANES>
 __global__ __launch_bounds__(256, LANES == 32 ? 6 : 5) void tree_level(
     const float* __restrict__ X, int64_t n, int d, double a, DivBy s, int t, int h, int l, uint64_t seed,
     const uint32_t* __restrict__ perm, const uint32_t* __restrict__ node_in, uint32_t* __restrict__ node_out,
@@ -276,7 +175,7 @@ __global__ __launch_bounds__(256, LANES == 32 ? 6 : 5) void tree_level(
   } else if (c < (int)P) {
     j = lo + c;
   }
-  const double D = tree_dist<ROWS>(X, i, j, d);
+  const double D = row_dist2<ROWS>(X, i, j, d);
   const double v = j != i ? exp(-a * D) : 0.0;
   double est = lanes_sum<LANES>(v);
   if (P > (uint32_t)t) est = est * ((double)P / (double)t);
@@ -298,7 +197,7 @@ __global__ __launch_bounds__(256, LANES == 32 ? 6 : 5) void tree_level(
 // The leaf (level h) of the draw in each slot, two draws per wave (lanes 0-31
 // and 32-63): inverse CDF over its rows in row order; outputs at the draw's own
 // index e = i s + r.
-template <TreeRows ROWS>
+template <RowRead ROWS>
 __global__ __launch_bounds__(256, 5) void tree_leaf(const float* __restrict__ X, int64_t n, int d, double a, DivBy s,
                                                  int h, uint64_t seed, const uint32_t* __restrict__ perm,
                                                  const uint32_t* __restrict__ node, const double* __restrict__ rest,
@@ -313,7 +212,7 @@ __global__ __launch_bounds__(256, 5) void tree_leaf(const float* __restrict__ X,
   const int64_t k = active ? node[slot] : 0;
   const int64_t lo = min(n, k * kTreeLeaf), hi = min(n, (k + 1) * kTreeLeaf);
   const int64_t j = lo + c < hi ? lo + c : i;
-  const double D = tree_dist<ROWS>(X, i, j, d);
+  const double D = row_dist2<ROWS>(X, i, j, d);
   const double v = j != i ? exp(-a * D) : 0.0;
   double incl = v;  // inclusive prefix over the half's lanes
 #pragma unroll
@@ -377,7 +276,7 @@ extern "C" stag_status stag_simgraph_sample_tree(const float* X, int64_t n, int3
   Workspace ws(stream);
   double* rest = nullptr;
   STAG_TRY(ws.alloc(&rest, (size_t)n));
-  const TreeRows rows = tree_rows(d);
+  const RowRead rows = row_read(d);
   auto by_rows = [&](auto own, auto quad4, auto quad) { return rows == kOwnRow ? own : rows == kQuad4 ? quad4 : quad; };
   {
     ScopedTimer tm("tree_degrees", stream);
