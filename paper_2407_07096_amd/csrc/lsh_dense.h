@@ -158,8 +158,7 @@ __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst l
       }
     }
   }
-  const double delta = screen_delta(d);
-  const double lo_s = lc.T[lev - 1] * (1.0 - delta), hi_s = lc.T[lev] * (1.0 + delta);
+  const double Tlo = lc.T[lev - 1], Thi = lc.T[lev];
   bool need = false;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
@@ -176,7 +175,7 @@ __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst l
       const double sx = ix.xn[m];
       const double e = 4e-12 * (sq + sx);
       const double up = sq + sx + e, dn = fmax(fabs(sq - sx) - e, 0.0);
-      const bool out = up * up * (1.0 + delta) < lo_s || dn * dn * (1.0 - delta) >= hi_s;
+      const bool out = up * up < Tlo || dn * dn >= Thi;
       if (!rlive || c >= mcnt || m == self_idx || out) drop |= 0xFFu << (8 * j);
     }
     first[i] |= drop;

@@ -16,8 +16,9 @@ __device__ inline double quad_perm(double v) {
                           __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false));
 }
 
-// ||x_i - x_j||^2 for the row j of each lane, by fp64 direct differences; i is
-// the same in the four lanes of a quad, and all lanes are active.
+// ||xi - x_j||^2 for the row j of each lane (rows of d floats, ld apart), by fp64
+// direct differences; xi is the same in the four lanes of a quad, and all lanes
+// are active.
 //
 // d > 8: the quad reads its four rows one after the other, each lane 16 bytes
 // of every 64, and the four partial sums per row are added across the quad at
@@ -74,10 +75,10 @@ __device__ __forceinline__ void row_piece(const float* __restrict__ xi, const fl
 }
 
 template <RowRead ROWS>
-__device__ __forceinline__ double row_dist2(const float* __restrict__ X, int64_t i, int64_t j, int d) {
-  const float* xi = X + i * d;
+__device__ __forceinline__ double row_dist2(const float* __restrict__ xi, const float* __restrict__ X, int64_t ld,
+                                            int64_t j, int d) {
   if constexpr (ROWS == kOwnRow) {
-    const float* x = X + j * d;
+    const float* x = X + j * ld;
     double D = 0.0;
     int c = 0;
     for (; c + 4 <= d; c += 4) {
@@ -97,7 +98,7 @@ __device__ __forceinline__ double row_dist2(const float* __restrict__ X, int64_t
     const int q = threadIdx.x & 3;
     const float* xj[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) xj[r] = X + (int64_t)__shfl((int)j, r, 4) * d;
+    for (int r = 0; r < 4; ++r) xj[r] = X + (int64_t)__shfl((int)j, r, 4) * ld;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     int c = 0;
     for (; c + 32 <= d; c += 32) row_piece<ROWS, 2, false>(xi, xj, c, d, acc);

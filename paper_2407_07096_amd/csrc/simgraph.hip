@@ -234,7 +234,7 @@ __device__ inline int64_t draw_row_of(const float* __restrict__ X, int64_t n, in
                                       int64_t i, int64_t T, double resid2, double sh) {
   const int64_t rb = T * 32, j = rb + (threadIdx.x & 31);
   const bool live = T < ntile && j < n && j != i;
-  const double D = row_dist2<ROWS>(X, i, live ? j : i, d);
+  const double D = row_dist2<ROWS>(X + i * d, X, d, live ? j : i, d);
   // a shifted row's values are 2^{E - m_i} with E = -a log2(e) D in one
   // exponent (2^{-m_i} alone overflows for m_i < -1024, and exp(-a D) is
   // subnormal there)

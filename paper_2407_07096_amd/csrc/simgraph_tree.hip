@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256, 4) void tree_degrees(const float* __restrict__
     const int64_t c = c0 + lane;
     int64_t j = i;
     if (c < count) j = all ? c : tpick(tout(st, (uint64_t)c), (uint32_t)n);
-    const double D = row_dist2<ROWS>(X, i, j, d);
+    const double D = row_dist2<ROWS>(X + i * d, X, d, j, d);
     if (j != i) s += exp(-a * D);
   }
 #pragma unroll
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(256, LANES == 32 ? 6 : 5) void tree_level(
   } else if (c < (int)P) {
     j = lo + c;
   }
-  const double D = row_dist2<ROWS>(X, i, j, d);
+  const double D = row_dist2<ROWS>(X + i * d, X, d, j, d);
   const double v = j != i ? exp(-a * D) : 0.0;
   double est = lanes_sum<LANES>(v);
   if (P > (uint32_t)t) est = est * ((double)P / (double)t);
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256, 5) void tree_leaf(const float* __restrict__ X,
   const int64_t k = active ? node[slot] : 0;
   const int64_t lo = min(n, k * kTreeLeaf), hi = min(n, (k + 1) * kTreeLeaf);
   const int64_t j = lo + c < hi ? lo + c : i;
-  const double D = row_dist2<ROWS>(X, i, j, d);
+  const double D = row_dist2<ROWS>(X + i * d, X, d, j, d);
   const double v = j != i ? exp(-a * D) : 0.0;
   double incl = v;  // inclusive prefix over the half's lanes
 #pragma unroll

@@ -48,3 +48,28 @@ def test_join_shapes(stag, orc, n, m, d, k2):  # noqa: F811
     buf[1:] = torch.from_numpy(Q.reshape(-1)).cuda()
     assert np.array_equal(S, idx.query(buf[1:].view(Q.shape)).cpu().numpy())
     idx.close()
+
+
+@pytest.mark.parametrize("n,d,s", [(300, 4, 3), (400, 8, 2), (400, 9, 3), (500, 30, 5), (600, 64, 64), (500, 100, 3),
+                                   (500, 129, 4), (400, 200, 3), (300, 258, 2)])
+def test_draws_from_join_and_walk(stag, orc, n, d, s):  # noqa: F811
+    """Edge draws after the join (d <= 128: the levels it flags) and after the
+    walk, with rows read one lane each (d <= 8) and by quads, against the
+    oracle as in test_gpu_simgraph."""
+    from tests.gpu_util import to_dev
+    rng = np.random.default_rng(7 * n + d)
+    X, _ = _points(n, 1, d, rng)
+    a = 0.5 / d
+    kw = dict(eps=0.5, k1=2, k2_constant=4)
+    announce(f"lsh draws n={n} d={d} s={s}")
+    sh, G0, B = _randomness(orc, n, d, a, 31, **kw)
+    got = stag.simgraph_sample(to_dev(X), a, samples_per_node=s, mode="lsh", seed=77, G0=to_dev(G0), b=to_dev(B),
+                               lsh_seed=0, **kw)
+    src, dst, w, deg = (t.cpu().numpy() for t in got)
+    osrc, odst, ow, odeg, mg = orc.simgraph_lsh(X, a, s, 77, G0, B, lsh_seed=0, **kw)
+    assert np.array_equal(src, osrc)
+    assert np.allclose(deg, odeg, rtol=1e-9)
+    same = dst == odst
+    assert np.all(same[mg > 1e-9])
+    ok = same & (dst >= 0)
+    assert np.allclose(w[ok], ow[ok], rtol=1e-9)
