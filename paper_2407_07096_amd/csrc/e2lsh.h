@@ -131,7 +131,7 @@ __device__ inline int32_t code_sel(double s, double b) {
 // the registers; dg is the regrouped copy's row width (DG, or d when the
 // copy is not padded).
 template <int DG, bool TQ, bool GF = false>
-__global__ __launch_bounds__(256) void hash_lanes(const float* __restrict__ Q, int ldq, int64_t q0, int64_t mb, int d,
+__global__ __launch_bounds__(256, DG == 64 ? 3 : 1) void hash_lanes(const float* __restrict__ Q, int ldq, int64_t q0, int64_t mb, int d,
                                                   const double* __restrict__ G8, int dg, const double* __restrict__ B,
                                                   int K, int L, int nch, int64_t ntab, int TW, int qbatches,
                                                   uint64_t* __restrict__ qkeys, int32_t* __restrict__ codes) {

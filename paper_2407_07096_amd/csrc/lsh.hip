@@ -882,7 +882,8 @@ __global__ __launch_bounds__(256) void locate_queries(const uint64_t* __restrict
     }
     // group the wave's lanes by bucket (ballots only), then let every
     // group's lowest lane take the group's ranks with one atomic, all groups
-    // in the same instruction
+    // in the same instruction (1e5 queries, 136 tables: 0.5 ms; with only the
+    // first four groups formed and an atomic a lane for the rest, 0.8)
     int leader_of = lane;
     uint32_t gsize = 0, intra = 0;
     uint64_t pending = __ballot(slot >= 0);
@@ -1300,18 +1301,44 @@ __global__ __launch_bounds__(256) void combine_groups(const int32_t* __restrict_
   int64_t nc = 0;
   for (int t = 0; t < K1; ++t) {
     double acc = 0.0;
-    for (int64_t g = (int64_t)t * per_copy; g < (int64_t)(t + 1) * per_copy; ++g) {
-      const int64_t e = g * mb + ql;
-      const int32_t slot = qslot[e];
-      if (slot < 0) continue;
-      const uint32_t rank = qrank[e], nm = tab_cnt[slot];
-      const int64_t nmc = (nm + kJoinMembers - 1) / kJoinMembers;
-      const int64_t base = (int64_t)task_base[slot] + (int64_t)(rank / 64) * nmc;
-      const int lane = (int)(rank % 64);
-      double gs = 0.0;
-      for (int64_t c = 0; c < nmc; ++c) gs += tpart[(base + c) * 64 + lane];
-      acc += gs;
-      nc += nm;
+    // kAhead groups at a time, the loads of each step of the chain (slot,
+    // bucket, partial) in flight together; the additions stay in order (one
+    // group at a time: 0.23 ms with 1e5 queries and 136 tables, now 0.16)
+    constexpr int kAhead = 8;
+    const int64_t gend = (int64_t)(t + 1) * per_copy;
+    for (int64_t g = (int64_t)t * per_copy; g < gend; g += kAhead) {
+      int32_t slot[kAhead];
+      uint32_t rank[kAhead], nm[kAhead];
+      int64_t base[kAhead];
+      double first[kAhead];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) {
+        const int64_t e = min(g + k, gend - 1) * mb + ql;
+        slot[k] = qslot[e];
+        rank[k] = qrank[e];
+        if (g + k >= gend) slot[k] = -1;
+      }
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) {
+        const int32_t sl = slot[k] < 0 ? 0 : slot[k];
+        nm[k] = slot[k] < 0 ? 0u : tab_cnt[sl];
+        base[k] = (int64_t)task_base[sl];
+      }
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) {
+        const int64_t nmc = (nm[k] + kJoinMembers - 1) / kJoinMembers;
+        base[k] = (base[k] + (int64_t)(rank[k] / 64) * nmc) * 64 + rank[k] % 64;
+        first[k] = nm[k] > 0 ? tpart[base[k]] : 0.0;
+      }
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) {
+        if (nm[k] == 0) continue;
+        const int64_t nmc = (nm[k] + kJoinMembers - 1) / kJoinMembers;
+        double gs = first[k];
+        for (int64_t c = 1; c < nmc; ++c) gs += tpart[base[k] + c * 64];
+        acc += gs;
+        nc += nm[k];
+      }
     }
     Scopy[ql * K1 + t] = acc;
   }
@@ -1841,10 +1868,13 @@ stag_status hash_query_batch(const stag_lsh_index* idx, const float* Q, int ldq,
   const int64_t tpw = std::max<int64_t>(1, std::min<int64_t>(idx->ntab, idx->ntab * qb / 2048));
   const int K = prm.shape.K;
   if ((idx->dreg > 0 || idx->d <= 128) && K <= 64) {
-    // one lane per projection: blocks of 4 waves x TW tables, 8 batches of 64 queries each
+    // one lane per projection: blocks of 4 waves x TW tables, 2 batches of 64
+    // queries each: with 8, the 784 blocks of 1e5 queries and 136 tables were
+    // one and a half rounds of the chip (0.94 ms; n = 3e4: 0.39), now 0.66 and
+    // 0.17, also from three waves a SIMD instead of two
     // (64 < d <= 128: the lane's coefficients held as fp32)
     const int TW = 64 / K;
-    const int qbatches = (int)std::max<int64_t>(8, ceil_div(cur, (int64_t)64 * 65535));  // grid.y <= 65535
+    const int qbatches = (int)std::max<int64_t>(2, ceil_div(cur, (int64_t)64 * 65535));  // grid.y <= 65535
     const dim3 grid((unsigned)ceil_div(idx->ntab, 4 * TW), (unsigned)ceil_div(cur, (int64_t)64 * qbatches));
     if (idx->dreg == 0) {
       hipLaunchKernelGGL((hash_lanes<128, true, true>), grid, dim3(256), 0, st, Q, ldq, q0, cur, idx->d, idx->G8,
