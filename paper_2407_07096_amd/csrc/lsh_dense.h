@@ -27,9 +27,15 @@ constexpr int kDenseTile = 128;         // queries and members per workgroup
 constexpr int kDenseSamples = 64;       // points whose candidates decide
 constexpr double kDenseShare = 0.25;
 constexpr int64_t kDenseMaxCols = 65536;               // columns of the pair matrix
-constexpr int64_t kDenseMaxBytes = (int64_t)512 << 20;  // pair buffers of one batch
+// Pair buffers of one batch.  Each launch ends with a round that leaves part of
+// the chip idle; 70,000 rows of 784 took 21.9 ms of pairs in 28 launches at
+// 512 MB, 19.3 in 14 at 1 GB (their terms 6.8 and 7.2: the buffers leave the
+// last-level cache).
+constexpr int64_t kDenseMaxBytes = (int64_t)1 << 30;
 constexpr int kDenseK = 8;              // coordinates staged at a time
-constexpr int kDensePad = kDenseK + 1;  // LDS row stride (doubles): 16 rows on distinct banks
+constexpr int kDensePad = kDenseK + 2;  // LDS row stride (doubles): 8 rows' 16 bytes on distinct banks
+
+using DensePair = double __attribute__((ext_vector_type(2)));
 
 struct DenseTile {
   int32_t seg;  // segment
@@ -93,10 +99,10 @@ __global__ __launch_bounds__(256) void count_met(const MemberBlock* __restrict__
 // One workgroup of 512 threads per (column tile, row tile).  Thread (ty, tx) =
 // (tid / 32, tid % 32) holds rows ty + 16 i and columns tx + 32 j, i < 8, j <
 // 4: 32 fp64 chains D = fma(e, e, D), e = (double)q - (double)x over ascending
-// coordinates (the walk's chain: distances bit for bit the same), fed by 8 + 4
-// LDS reads per coordinate.  Bound by the fp64 rate (a subtraction and a
-// fused product per coordinate and pair at 39 T/s).  8 x 8 chains per thread
-// spilled.  A pair that the norm bounds of the walk put outside its level
+// coordinates, fed by 8 + 4 LDS reads of 16 bytes for two coordinates (one at a
+// time 22.4 ms, two 21.9 for 70,000 rows of 784 against 4,345 members).  Bound
+// by the fp64 rate (a subtraction and a fused product per coordinate and pair,
+// 4.65 cycles each: 14.9 ms of it).  8 x 8 chains per thread spilled.  A pair that the norm bounds of the walk put outside its level
 // needs no distance; a tile without a pair that does is left out whole.
 template <bool QVEC>
 __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst lc, const float* __restrict__ Q,
@@ -218,11 +224,9 @@ __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst l
     }
   };
   auto lstore = [&](int buf) {
-    double* o = &sh.row[buf][side][pr * kDensePad + pc];
-    o[0] = (double)st4.x;
-    o[1] = (double)st4.y;
-    o[2] = (double)st4.z;
-    o[3] = (double)st4.w;
+    DensePair* o = reinterpret_cast<DensePair*>(&sh.row[buf][side][pr * kDensePad + pc]);
+    o[0] = DensePair{(double)st4.x, (double)st4.y};
+    o[1] = DensePair{(double)st4.z, (double)st4.w};
   };
   double D[8][4];
 #pragma unroll
@@ -239,18 +243,20 @@ __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst l
     const double* ql = sh.row[buf][0] + ty * kDensePad;
     const double* xl = sh.row[buf][1] + tx * kDensePad;
 #pragma unroll 1  // unrolled, the reads of all coordinates are held at once (spills)
-    for (int k = 0; k < kDenseK; ++k) {
-      double xd[4];
+    for (int k = 0; k < kDenseK; k += 2) {
+      DensePair xd[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) xd[j] = xl[32 * j * kDensePad + k];
+      for (int j = 0; j < 4; ++j) xd[j] = *reinterpret_cast<const DensePair*>(&xl[32 * j * kDensePad + k]);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const double qd = ql[16 * i * kDensePad + k];
+        const DensePair qd = *reinterpret_cast<const DensePair*>(&ql[16 * i * kDensePad + k]);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const double t = qd - xd[j];
-          D[i][j] = __builtin_fma(t, t, D[i][j]);
-        }
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const double t = qd[e] - xd[j][e];
+            D[i][j] = __builtin_fma(t, t, D[i][j]);
+          }
       }
     }
     if (kb + 1 < nk) lstore(buf ^ 1);
