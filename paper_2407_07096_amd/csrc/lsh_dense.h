@@ -277,7 +277,7 @@ __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst l
 // strided, one butterfly sum per copy.  LIST: the terms take their distances'
 // place (table 255 outside the level) and are then listed per segment in the
 // walk's order: a count per table, a scan over the tables and a second pass
-// that ranks a batch's equal tables by ballots.
+// that ranks a batch's equal tables, both by ballots of the tables' bits.
 template <bool LIST>
 __global__ __launch_bounds__(256) void dense_terms(IndexView ix, LevelConst lc, int64_t qrow0, int64_t nq,
                                                    DensePairs dp, double* __restrict__ Scopy,
@@ -289,6 +289,44 @@ __global__ __launch_bounds__(256) void dense_terms(IndexView ix, LevelConst lc, 
   const int nct = dp.ncol / kDenseTile;
   const uint8_t* any = dp.any + (r / kDenseTile) * nct;
   const uint64_t below = (1ull << lane) - 1ull;
+  // the column tiles in [c0, c1) that hold a pair, the next one's values
+  // loaded before this one's are used (a wave's loads one after the other
+  // were what the terms waited for: 7.2 ms for 70,000 rows, then 6.7; 6.2 with the ranks below from ballots
+  // instead of a loop over the tables met)
+  struct Piece {
+    double D[kDenseTile / 64];
+    uint8_t f[kDenseTile / 64];
+  };
+  auto each_tile = [&](int c0, int c1, auto&& use) {
+    for (int cb = c0; cb < c1; cb += 64) {
+      uint64_t left = __ballot(cb + lane < c1 && any[min(cb + lane, c1 - 1)]);
+      Piece next;
+      int64_t o = 0;
+      int ct = cb;
+      auto load = [&] {
+        ct = cb + __builtin_ctzll(left);
+        left &= left - 1;
+        o = r * dp.ncol + (int64_t)ct * kDenseTile + lane;
+#pragma unroll
+        for (int k = 0; k < kDenseTile; k += 64) {
+          next.D[k / 64] = dp.D[o + k];
+          next.f[k / 64] = dp.F[o + k];
+        }
+      };
+      bool some = left != 0;
+      if (some) load();
+      while (some) {
+        const Piece p = next;
+        const int64_t at = o;
+        const int tile = ct;
+        some = left != 0;
+        if (some) load();
+        use(tile, at, p);
+      }
+    }
+  };
+  int lbits = 0;  // of a table's number
+  while ((1 << lbits) < ix.L) ++lbits;
   int64_t na = 0;
   for (int t = 0; t < ix.K1; ++t) {
     double acc = 0.0;
@@ -299,31 +337,30 @@ __global__ __launch_bounds__(256) void dense_terms(IndexView ix, LevelConst lc, 
       if (c0 == c1) continue;
       const double Tlo = lc.T[i - 1], Thi = lc.T[i], ri = lc.r[i];
       uint32_t count = 0;  // lane l: positive terms of table l, then its next place
-      for (int ct = c0; ct < c1; ++ct) {
-        if (!any[ct]) continue;
-        const int64_t o = r * dp.ncol + (int64_t)ct * kDenseTile + lane;
+      each_tile(c0, c1, [&](int, int64_t o, const Piece& p) {
 #pragma unroll
         for (int k = 0; k < kDenseTile; k += 64) {
-          const double D = dp.D[o + k];
-          const uint8_t f = dp.F[o + k];
+          const double D = p.D[k / 64];
+          const uint8_t f = p.f[k / 64];
           const bool in = f != 255 && D >= Tlo && D < Thi;
           const double v = in ? level_weight(ix.cheb + i * kChebRow, sqrt(D) / ri) : 0.0;
           acc += v;
           na += v > 0.0 ? 1 : 0;
-          uint64_t open = __ballot(v > 0.0);
+          const uint64_t open = __ballot(v > 0.0);
           if (open) hit |= 1ull << (i - 1);
           if constexpr (LIST) {
             dp.D[o + k] = v;
             if (!(v > 0.0)) dp.F[o + k] = 255;
-            while (open) {
-              const int l = __builtin_amdgcn_readlane((int)f, __ffsll((long long)open) - 1);
-              const uint64_t same = __ballot((int)f == l) & open;
-              open &= ~same;
-              count += lane == l ? (uint32_t)__popcll(same) : 0u;
+            // lane l: the terms of table l, from the ballots of the tables' bits
+            uint64_t same = lane < ix.L ? open : 0ull;
+            for (int q = 0; q < lbits; ++q) {
+              const uint64_t ones = __ballot((f >> q) & 1);
+              same &= (lane >> q) & 1 ? ones : ~ones;
             }
+            count += (uint32_t)__popcll(same);
           }
         }
-      }
+      });
       if constexpr (LIST) {
         uint32_t incl = count;
 #pragma unroll
@@ -335,28 +372,25 @@ __global__ __launch_bounds__(256) void dense_terms(IndexView ix, LevelConst lc, 
         if (lane == 63) dp.len[r * nct + c0] = (int32_t)incl;
         const int64_t s0 = (int64_t)ix.seg_off[seg];
         const int64_t out = r * dp.ncol + (int64_t)c0 * kDenseTile;
-        for (int ct = c0; ct < c1; ++ct) {
-          if (!any[ct]) continue;
-          const int64_t o = r * dp.ncol + (int64_t)ct * kDenseTile + lane;
+        each_tile(c0, c1, [&](int ct, int64_t, const Piece& p) {
 #pragma unroll
           for (int k = 0; k < kDenseTile; k += 64) {
-            const uint8_t f = dp.F[o + k];
-            uint64_t open = __ballot(f != 255);
-            uint32_t place = 0;
-            while (open) {
-              const int l = __builtin_amdgcn_readlane((int)f, __ffsll((long long)open) - 1);
-              const uint64_t same = __ballot((int)f == l) & open;
-              open &= ~same;
-              const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)count, l);
-              if ((int)f == l) place = base + (uint32_t)__popcll(same & below);
-              count += lane == l ? (uint32_t)__popcll(same) : 0u;
+            const uint8_t f = p.f[k / 64];
+            const uint64_t open = __ballot(f != 255);
+            uint64_t same = lane < ix.L ? open : 0ull, peers = open;  // terms of table `lane`; of this term's table
+            for (int q = 0; q < lbits; ++q) {
+              const uint64_t ones = __ballot((f >> q) & 1);
+              same &= (lane >> q) & 1 ? ones : ~ones;
+              peers &= (f >> q) & 1 ? ones : ~ones;
             }
+            const uint32_t place = (uint32_t)__shfl((int)count, f & 63) + (uint32_t)__popcll(peers & below);
+            count += (uint32_t)__popcll(same);
             if (f != 255) {
-              dp.V[out + place] = dp.D[o + k];
+              dp.V[out + place] = p.D[k / 64];
               dp.J[out + place] = ix.members[s0 + (int64_t)(ct - c0) * kDenseTile + k + lane];
             }
           }
-        }
+        });
       }
     }
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
