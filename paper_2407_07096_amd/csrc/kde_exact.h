@@ -245,7 +245,8 @@ int64_t query_tile_rows();
 // whose pairs of a 128-query tile and a chunk alone would leave compute units
 // idle: below kFewPairs pairs, the smallest power of two up to 8 that gives
 // kSplitGrid workgroups (2 per compute unit; 37 queries against
-// 300,000 rows at d = 64, 74 pairs: 232 us a call, now 155).  Wide rows, whose
+// 300,000 rows at d = 64, 74 pairs: 232 us a call, 155 with the shares, 84 with the
+// operands prepared by vector loads).  Wide rows, whose
 // workgroups are long and whose records are small, share up to
 // kFewPairsWide pairs, so that the last round of workgroups is short as well
 // (10,000 queries against 70,000
