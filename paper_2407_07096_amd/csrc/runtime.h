@@ -101,7 +101,8 @@ class Workspace {
     void* p;
     size_t bytes;
     int dev;
-    hipEvent_t ev;  // null: not kept (goes back to the pool)
+    hipEvent_t ev;     // null: not kept (goes back to the pool)
+    hipStream_t last;  // the stream that used it last
   };
   friend class BlockCache;
   std::vector<Block> blocks_;

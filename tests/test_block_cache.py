@@ -1,0 +1,107 @@
+"""Host-only tests of the workspace block cache (runtime.cpp) against a mock
+of the HIP runtime: whose blocks a stream is given."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2407_07096_amd", "csrc")
+MB = 1 << 20
+GB = 1 << 30
+COUNTS = ["mallocs", "frees", "cross_waits", "unsafe_calls", "host_waits", "trims", "used"]
+
+
+@pytest.fixture(scope="module")
+def so(tmp_path_factory):
+    out = tmp_path_factory.mktemp("hipmock") / "libhipmock.so"
+    # -Bsymbolic: the mock's own functions, also where the process has the real runtime loaded
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-pthread", "-Wl,-Bsymbolic",
+                    "-D__HIP_PLATFORM_AMD__", "-Wno-unused-result", "-I", "/opt/rocm/include", "-I", CSRC,
+                    os.path.join(CSRC, "runtime.cpp"), os.path.join(ROOT, "tests", "runtime_mock", "mock_hip.cpp"),
+                    "-o", str(out)], check=True)
+    return out
+
+
+class Mock:
+    def __init__(self, path):
+        lib = C.CDLL(str(path))
+        for f in ("mock_stream", "ws_new"):
+            getattr(lib, f).restype = C.c_void_p
+        lib.mock_count.restype = C.c_int64
+        lib.mock_hammer.restype = C.c_int64
+        lib.ws_new.argtypes = lib.ws_delete.argtypes = [C.c_void_p]
+        lib.ws_alloc.argtypes = [C.c_void_p, C.c_size_t, C.POINTER(C.c_void_p)]
+        lib.dev_alloc.argtypes = [C.c_size_t, C.POINTER(C.c_void_p)]
+        lib.mock_capacity.argtypes = [C.c_size_t]
+        lib.mock_capture.argtypes = [C.c_void_p, C.c_int]
+        lib.mock_work.argtypes = lib.mock_finish.argtypes = [C.c_void_p]
+        self.lib = lib
+
+    def stream(self, dev=0):
+        return self.lib.mock_stream(dev)
+
+    def call(self, stream, *sizes, work=True, expect=0):
+        """One library call: allocates the sizes, enqueues work, returns the blocks."""
+        ws = self.lib.ws_new(stream)
+        out = []
+        for b in sizes:
+            p = C.c_void_p()
+            assert self.lib.ws_alloc(ws, b, C.byref(p)) == expect
+            out.append(p.value)
+        if work:
+            self.lib.mock_work(stream)
+        self.lib.ws_delete(ws)
+        return out
+
+    def __getattr__(self, name):
+        if name in COUNTS:
+            return self.lib.mock_count(COUNTS.index(name))
+        return getattr(self.lib, "mock_" + name)
+
+
+@pytest.fixture
+def mock(so, tmp_path):
+    # a copy per test: each loads a library with state of its own
+    copy = tmp_path / "libhipmock.so"
+    copy.write_bytes(so.read_bytes())
+    return Mock(copy)
+
+
+def test_same_stream_reuses_its_block(mock):
+    s = mock.stream()
+    blocks = {mock.call(s, 100 * MB)[0] for _ in range(10)}
+    assert len(blocks) == 1 and mock.mallocs == 1 and mock.cross_waits == 0
+
+
+def test_streams_do_not_wait_for_each_other(mock):
+    a, b, c = mock.stream(), mock.stream(), mock.stream()
+    for _ in range(4):  # nothing finishes: every stream keeps to its own blocks
+        pa, pb, pc = (mock.call(s, 100 * MB, 1024)[0] for s in (a, b, c))
+        assert len({pa, pb, pc}) == 3
+    assert mock.cross_waits == 0
+    assert mock.mallocs == 6  # two blocks a stream
+
+
+def test_finished_block_serves_any_stream(mock):
+    a, b = mock.stream(), mock.stream()
+    p = mock.call(a, 100 * MB)
+    mock.finish(a)
+    assert mock.call(b, 90 * MB) == p
+    assert mock.mallocs == 1 and mock.cross_waits == 0
+
+
+def test_no_query_that_a_capture_elsewhere_forbids(mock):
+    a, b, c = mock.stream(), mock.stream(), mock.stream()
+    mock.call(a, 100 * MB)
+    mock.capture(c, 1)
+    mock.call(b, 100 * MB)  # looks at a's busy block
+    mock.call(c, 100 * MB)  # the capturing stream owns its memory: no cached block
+    assert mock.unsafe_calls == 0 and mock.mallocs == 3 and mock.cross_waits == 0
+    mock.capture(c, 0)
+
+
+def test_threads_never_share_a_block(mock):
+    assert mock.hammer(8, 400) == 0
+    assert mock.cross_waits == 0
