@@ -58,6 +58,10 @@ std::mutex g_cache_mu;
 std::map<int, std::multimap<size_t, void*>> g_cache;
 }  // namespace
 
+// Gives the idle workspace blocks of device dev back to the system (see
+// BlockCache); st: a stream of that device.  False if there were none.
+static bool release_idle(int dev, hipStream_t st);
+
 stag_status cached_alloc(void** p, size_t bytes) {
   *p = nullptr;
   int dev = 0;
@@ -73,6 +77,10 @@ stag_status cached_alloc(void** p, size_t bytes) {
     }
   }
   hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory && release_idle(dev, nullptr)) {
+    (void)hipGetLastError();
+    e = hipMalloc(p, bytes);
+  }
   if (e != hipSuccess) {
     *p = nullptr;
     (void)hipGetLastError();
@@ -112,9 +120,10 @@ class RelaxedCapture {
 // 100,000 points and 300 queries took 291 us on four streams and 229 on one;
 // on four streams now 174).
 // At most kMaxIdle bytes per device lie idle and no block above kMaxBlock is
-// kept; the rest goes back to the pool, and when an allocation fails
-// everything idle does before it is tried again.  Requests on a capturing
-// stream bypass the cache both ways: a graph owns its memory.
+// kept; the rest goes back to the pool, and when an allocation of any size
+// fails, a workspace's or an index's, everything idle goes back to the system
+// before it is tried again.  Requests on a capturing stream bypass the cache
+// both ways: a graph owns its memory.
 class BlockCache {
  public:
   static constexpr size_t kMaxIdle = (size_t)2 << 30, kMaxBlock = (size_t)1 << 30;
@@ -140,7 +149,8 @@ class BlockCache {
     // (also for its own stream: the handle may be that of a newer stream)
     if (hipStreamWaitEvent(st, out->ev, 0) == hipSuccess) return true;
     (void)hipGetLastError();
-    give_back(*out, true);
+    RelaxedCapture relaxed;
+    give_back(*out, st);
     return false;
   }
 
@@ -164,17 +174,21 @@ class BlockCache {
     drop_event(b.ev);
   }
 
-  // Returns every idle block of the device to the pool once its work is done.
-  bool trim(int dev) {
+  // Returns every idle block of the device to the system once its work is done.
+  bool trim(int dev, hipStream_t st) {
     std::multimap<size_t, Workspace::Block> idle;
     {
       std::lock_guard<std::mutex> lk(mu_);
       idle.swap(dev_[dev].idle);
       dev_[dev].idle_bytes = 0;
     }
-    for (auto& kv : idle) give_back(kv.second, false);
     if (idle.empty()) return false;
-    (void)hipStreamSynchronize(nullptr);
+    RelaxedCapture relaxed;
+    for (auto& kv : idle) give_back(kv.second, st);
+    (void)hipStreamSynchronize(st);
+    hipMemPool_t pool = nullptr;
+    if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess && pool) (void)hipMemPoolTrimTo(pool, 0);
+    (void)hipGetLastError();
     return true;
   }
 
@@ -183,12 +197,11 @@ class BlockCache {
   }
 
  private:
-  // Frees a block on the null stream after its last use.
-  void give_back(const Workspace::Block& b, bool sync) {
+  // Frees a block on stream st after its last use.
+  void give_back(const Workspace::Block& b, hipStream_t st) {
     (void)hipEventSynchronize(b.ev);
-    (void)hipFreeAsync(b.p, nullptr);
+    (void)hipFreeAsync(b.p, st);
     drop_event(b.ev);
-    if (sync) (void)hipStreamSynchronize(nullptr);
     (void)hipGetLastError();
   }
 
@@ -207,6 +220,8 @@ BlockCache& block_cache() {
   return *c;
 }
 }  // namespace
+
+static bool release_idle(int dev, hipStream_t st) { return block_cache().trim(dev, st); }
 
 Workspace::~Workspace() {
   for (const Block& b : blocks_) block_cache().put(b, stream_);
@@ -229,9 +244,9 @@ stag_status Workspace::raw_alloc(void** p, size_t bytes) {
   keep_pool_memory();
   Block b = {nullptr, bytes, 0, nullptr, stream_};
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  const bool keep = bytes <= BlockCache::kMaxBlock && hipGetDevice(&b.dev) == hipSuccess &&
-                    hipStreamIsCapturing(stream_, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
-  if (keep) {
+  const bool cached = hipGetDevice(&b.dev) == hipSuccess && hipStreamIsCapturing(stream_, &cap) == hipSuccess &&
+                      cap == hipStreamCaptureStatusNone;
+  if (cached && bytes <= BlockCache::kMaxBlock) {
     if (block_cache().take(b.dev, bytes, stream_, &b)) {
       blocks_.push_back(b);
       *p = b.p;
@@ -241,7 +256,7 @@ stag_status Workspace::raw_alloc(void** p, size_t bytes) {
   }
   (void)hipGetLastError();
   hipError_t e = hipMallocAsync(&b.p, bytes, stream_);
-  if (e == hipErrorOutOfMemory && keep && block_cache().trim(b.dev)) {
+  if (e == hipErrorOutOfMemory && cached && release_idle(b.dev, stream_)) {
     (void)hipGetLastError();
     e = hipMallocAsync(&b.p, bytes, stream_);
   }

@@ -105,3 +105,54 @@ def test_no_query_that_a_capture_elsewhere_forbids(mock):
 def test_threads_never_share_a_block(mock):
     assert mock.hammer(8, 400) == 0
     assert mock.cross_waits == 0
+
+
+def _idle(mock, s, count, size):
+    """`count` idle blocks of `size` bytes, their work done."""
+    ws = [mock.lib.ws_new(s) for _ in range(count)]
+    for w in ws:
+        assert mock.lib.ws_alloc(w, size, C.byref(C.c_void_p())) == 0
+        mock.lib.mock_work(s)
+    for w in ws:
+        mock.lib.ws_delete(w)
+    mock.finish(s)
+
+
+@pytest.mark.parametrize("size", [900 * MB, 3 * GB])  # below and above what the cache keeps
+def test_idle_blocks_are_given_back_when_a_request_fails(mock, size):
+    s = mock.stream()
+    mock.capacity(4 * GB)
+    _idle(mock, s, 9, 200 * MB)
+    assert mock.used >= 1800 * MB
+    mock.capacity(size + 100 * MB)
+    mock.call(s, size)
+    assert mock.used <= size + 100 * MB and mock.trims >= 1
+
+
+def test_idle_blocks_are_given_back_when_an_index_block_fails(mock):
+    s = mock.stream()
+    mock.capacity(2 * GB)
+    _idle(mock, s, 8, 200 * MB)
+    assert mock.lib.dev_alloc(1 * GB, C.byref(C.c_void_p())) == 0
+
+
+def test_a_request_past_the_memory_still_fails(mock):
+    s = mock.stream()
+    mock.capacity(2 * GB)
+    _idle(mock, s, 8, 200 * MB)
+    nomem = 2  # STAG_E_NOMEM
+    mock.call(s, 3 * GB, work=False, expect=nomem)
+    assert mock.lib.dev_alloc(3 * GB, C.byref(C.c_void_p())) == nomem
+    mock.call(s, 100 * MB)
+
+
+def test_capturing_request_that_fails_leaves_the_cache_alone(mock):
+    s, c = mock.stream(), mock.stream()
+    mock.capacity(2 * GB)
+    _idle(mock, s, 8, 200 * MB)
+    mock.capture(c, 1)
+    mock.call(c, 1 * GB, work=False, expect=2)
+    assert mock.frees == 0 and mock.unsafe_calls == 0
+    # on a stream that does not capture: nothing that would end the capture
+    mock.call(s, 3 * GB // 2)
+    assert mock.unsafe_calls == 0
