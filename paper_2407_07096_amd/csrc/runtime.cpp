@@ -119,8 +119,9 @@ class RelaxedCapture {
 // stream still works on would tie the two streams together (four calls of
 // 100,000 points and 300 queries took 291 us on four streams and 229 on one;
 // on four streams now 174).
-// At most kMaxIdle bytes per device lie idle and no block above kMaxBlock is
-// kept; the rest goes back to the pool, and when an allocation of any size
+// At most kMaxIdle bytes per device lie idle (the blocks returned longest ago
+// make room for a new one, unless they are still at work) and no block above
+// kMaxBlock is kept; the rest goes back to the pool, and when an allocation of any size
 // fails, a workspace's or an index's, everything idle goes back to the system
 // before it is tried again.  Requests on a capturing stream bypass the cache
 // both ways: a graph owns its memory.
@@ -161,17 +162,24 @@ class BlockCache {
       drop_event(b.ev);
       return;
     }
+    std::vector<Workspace::Block> out;
     {
       std::lock_guard<std::mutex> lk(mu_);
       auto& d = dev_[b.dev];
+      while (d.idle_bytes + b.bytes > kMaxIdle && evict_oldest(&d, &out)) {
+      }
       if (d.idle_bytes + b.bytes <= kMaxIdle) {
+        b.returned = ++returns_;
         d.idle.emplace(b.bytes, b);
         d.idle_bytes += b.bytes;
-        return;
+      } else {
+        out.push_back(b);
       }
     }
-    (void)hipFreeAsync(b.p, st);
-    drop_event(b.ev);
+    for (const Workspace::Block& o : out) {
+      (void)hipFreeAsync(o.p, st);
+      drop_event(o.ev);
+    }
   }
 
   // Returns every idle block of the device to the system once its work is done.
@@ -209,8 +217,27 @@ class BlockCache {
     std::multimap<size_t, Workspace::Block> idle;
     size_t idle_bytes = 0;
   };
+
+  // Takes the idle block that was returned first among those whose work is
+  // done; false if there is none.
+  bool evict_oldest(Device* d, std::vector<Workspace::Block>* out) {
+    RelaxedCapture relaxed;
+    auto oldest = d->idle.end();
+    for (auto it = d->idle.begin(); it != d->idle.end(); ++it) {
+      if (oldest != d->idle.end() && oldest->second.returned < it->second.returned) continue;
+      if (hipEventQuery(it->second.ev) == hipSuccess) oldest = it;
+      else (void)hipGetLastError();
+    }
+    if (oldest == d->idle.end()) return false;
+    out->push_back(oldest->second);
+    d->idle_bytes -= oldest->second.bytes;
+    d->idle.erase(oldest);
+    return true;
+  }
+
   std::mutex mu_;
   std::map<int, Device> dev_;
+  uint64_t returns_ = 0;
 };
 
 namespace {
@@ -242,7 +269,7 @@ std::vector<void*> Workspace::release() {
 stag_status Workspace::raw_alloc(void** p, size_t bytes) {
   *p = nullptr;
   keep_pool_memory();
-  Block b = {nullptr, bytes, 0, nullptr, stream_};
+  Block b = {nullptr, bytes, 0, nullptr, stream_, 0};
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   const bool cached = hipGetDevice(&b.dev) == hipSuccess && hipStreamIsCapturing(stream_, &cap) == hipSuccess &&
                       cap == hipStreamCaptureStatusNone;

@@ -103,6 +103,7 @@ class Workspace {
     int dev;
     hipEvent_t ev;     // null: not kept (goes back to the pool)
     hipStream_t last;  // the stream that used it last
+    uint64_t returned;  // order in which idle blocks were returned
   };
   friend class BlockCache;
   std::vector<Block> blocks_;

@@ -156,3 +156,26 @@ def test_capturing_request_that_fails_leaves_the_cache_alone(mock):
     # on a stream that does not capture: nothing that would end the capture
     mock.call(s, 3 * GB // 2)
     assert mock.unsafe_calls == 0
+
+
+def test_sizes_that_nobody_asks_for_make_room(mock):
+    s = mock.stream()
+    _idle(mock, s, 20, 100 * MB)  # 2000 MB idle, the limit is 2 GiB
+    before = mock.mallocs
+    for _ in range(10):
+        mock.call(s, 300 * MB)
+        mock.finish(s)
+    assert mock.mallocs == before + 1  # kept after its first use
+    assert mock.used <= 2 * GB
+
+
+def test_blocks_at_work_are_not_evicted(mock):
+    a, b = mock.stream(), mock.stream()
+    ws = [mock.lib.ws_new(a) for _ in range(20)]
+    for w in ws:
+        assert mock.lib.ws_alloc(w, 100 * MB, C.byref(C.c_void_p())) == 0
+    mock.lib.mock_work(a)
+    for w in ws:
+        mock.lib.ws_delete(w)
+    mock.call(b, 300 * MB)  # goes back to the pool itself: all else is in use
+    assert mock.cross_waits == 0 and mock.host_waits == 0 and mock.used == 2000 * MB
