@@ -271,8 +271,9 @@ stag_status Workspace::raw_alloc(void** p, size_t bytes) {
   keep_pool_memory();
   Block b = {nullptr, bytes, 0, nullptr, stream_, 0};
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  const bool cached = hipGetDevice(&b.dev) == hipSuccess && hipStreamIsCapturing(stream_, &cap) == hipSuccess &&
-                      cap == hipStreamCaptureStatusNone;
+  // the stream's device, which need not be the current one
+  const bool cached = hipStreamGetDevice(stream_, &b.dev) == hipSuccess &&
+                      hipStreamIsCapturing(stream_, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
   if (cached && bytes <= BlockCache::kMaxBlock) {
     if (block_cache().take(b.dev, bytes, stream_, &b)) {
       blocks_.push_back(b);

@@ -179,3 +179,13 @@ def test_blocks_at_work_are_not_evicted(mock):
         mock.lib.ws_delete(w)
     mock.call(b, 300 * MB)  # goes back to the pool itself: all else is in use
     assert mock.cross_waits == 0 and mock.host_waits == 0 and mock.used == 2000 * MB
+
+
+def test_blocks_stay_on_their_streams_device(mock):
+    a, b = mock.stream(0), mock.stream(1)  # device 0 is current throughout
+    pa = mock.call(a, 100 * MB)
+    mock.finish(a)
+    pb = mock.call(b, 100 * MB)
+    mock.finish(b)
+    assert pa != pb
+    assert mock.call(a, 100 * MB) == pa and mock.call(b, 100 * MB) == pb
