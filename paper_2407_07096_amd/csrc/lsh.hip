@@ -847,10 +847,11 @@ __host__ __device__ inline int join_lds_bytes(int dq, int L) {
 }
 
 // The bucket (global slot) of every (table, query) pair of the batch (pair
-// e = table * mb + query), or -1, and the pair's rank among the bucket's
-// queries (arrival order; lanes of a wave that share a bucket take one atomic).
+// e = table * mb + query, its key at qkeys[table * qs + query]), or -1, and the
+// pair's rank among the bucket's queries (arrival order; lanes of a wave that
+// share a bucket take one atomic).
 __global__ __launch_bounds__(256) void locate_queries(const uint64_t* __restrict__ qkeys, int64_t total, int64_t mb,
-                                                      int L, const uint64_t* __restrict__ tab_seg_off,
+                                                      int64_t qs, int L, const uint64_t* __restrict__ tab_seg_off,
                                                       const uint32_t* __restrict__ seg_cap,
                                                       const uint64_t* __restrict__ tab_key, int32_t* __restrict__ qslot,
                                                       uint32_t* __restrict__ qrank, uint32_t* __restrict__ qcount) {
@@ -865,7 +866,7 @@ __global__ __launch_bounds__(256) void locate_queries(const uint64_t* __restrict
       const int l = (int)(g % L);
       const uint32_t cap = seg_cap[seg];
       if (cap > 0) {
-        const uint64_t key = qkeys[e];
+        const uint64_t key = qkeys[e + g * (qs - mb)];
         const int64_t tb = (int64_t)tab_seg_off[seg] + (int64_t)l * cap;
         uint32_t sl = (uint32_t)key & (cap - 1);
         while (true) {
@@ -914,14 +915,19 @@ __global__ __launch_bounds__(256) void scatter_queries(const int32_t* __restrict
   }
 }
 
-// Tasks of a bucket: ceil(queries / 64) x ceil(members / kJoinMembers).
+// Tasks of a bucket: ceil(queries / 64) x ceil(members / kJoinMembers), at
+// most 2^32 - 1 (more than any batch is let to have).
+__host__ __device__ inline uint32_t bucket_tasks(uint32_t nq, uint32_t nm) {
+  const uint64_t t = ((uint64_t)nq + 63) / 64 * (((uint64_t)nm + kJoinMembers - 1) / kJoinMembers);
+  return t < 0xFFFFFFFFull ? (uint32_t)t : 0xFFFFFFFFu;
+}
+
 __global__ __launch_bounds__(256) void count_tasks(const uint32_t* __restrict__ qcount,
                                                    const uint32_t* __restrict__ tab_cnt, int64_t nslots,
                                                    uint32_t* __restrict__ ntask) {
   const int64_t sl = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (sl >= nslots) return;
-  const uint32_t nq = qcount[sl], nm = tab_cnt[sl];
-  ntask[sl] = (nq > 0 && nm > 0) ? ((nq + 63) / 64) * ((nm + kJoinMembers - 1) / kJoinMembers) : 0u;
+  ntask[sl] = bucket_tasks(qcount[sl], tab_cnt[sl]);
 }
 
 // Largest index s in [0, n) with v[s] <= x (v ascending, v[0] <= x).
@@ -983,7 +989,7 @@ __device__ inline double quad_f64(double v) {
 template <int DQ>
 __global__ __launch_bounds__(64, DQ <= 32 ? 4 : DQ <= 64 ? 3 : 2) void join_buckets(
     IndexView ix, LevelConst lc, const float* __restrict__ Q, int64_t q0, const uint64_t* __restrict__ qkeys,
-    int64_t mb, const int32_t* __restrict__ qlist, const JoinTask* __restrict__ tasks, int self_excl,
+    int64_t qs, const int32_t* __restrict__ qlist, const JoinTask* __restrict__ tasks, int self_excl,
     double* __restrict__ tpart, int64_t* __restrict__ nacc, uint64_t* __restrict__ levels) {
   extern __shared__ __attribute__((aligned(16))) unsigned char jlds[];
   constexpr int RS = DQ + 4;  // LDS row stride (floats)
@@ -1060,7 +1066,7 @@ __global__ __launch_bounds__(64, DQ <= 32 ? 4 : DQ <= 64 ? 3 : 2) void join_buck
     qlo[u] = __builtin_fmaf(ce, qn, qn);
     qhi[u] = __builtin_fmaf(-ce, qn, qn);
   }
-  for (int l2 = 0; l2 < l; ++l2) qk[l2 * 64 + lane] = qkeys[((int64_t)t.seg * L + l2) * mb + ql];
+  for (int l2 = 0; l2 < l; ++l2) qk[l2 * 64 + lane] = qkeys[((int64_t)t.seg * L + l2) * qs + ql];
   runs[lane] = 0u;
   double acc = 0.0;
   int64_t na = 0;
@@ -2071,10 +2077,11 @@ stag_status walk_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64
   return STAG_OK;
 }
 
-// Copy sums of one hashed query batch through the bucket join.
-stag_status join_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64_t q0, int64_t cur, int self_excl,
-                       const uint64_t* qkeys, double* scopy, int64_t* ncand, int64_t* nacc, uint64_t* levels,
-                       hipStream_t st) {
+// Copy sums of `cur` queries (keys at qkeys + table * qs) through the bucket
+// join, if it needs no more than max_tasks tasks; *tasks: how many.
+stag_status join_slice(const stag_lsh_index* idx, const float* Q, int ldq, int64_t q0, int64_t cur, int self_excl,
+                       const uint64_t* qkeys, int64_t qs, double* scopy, int64_t* ncand, int64_t* nacc,
+                       uint64_t* levels, uint64_t max_tasks, uint64_t* tasks_out, hipStream_t st) {
   const LshParams& prm = idx->prm;
   const int L = prm.shape.L, K1 = prm.shape.K1;
   const int64_t ntab = idx->ntab, nslots = idx->total_slots, pairs = cur * ntab;
@@ -2099,7 +2106,7 @@ stag_status join_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64
     ScopedTimer tm("lsh_join_setup", st);
     hipLaunchKernelGGL(zero_u32, dim3((unsigned)std::min<int64_t>(ceil_div(nslots, 256), 65536)), dim3(256), 0, st,
                        qcount, nslots);
-    hipLaunchKernelGGL(locate_queries, dim3(gpairs), dim3(256), 0, st, qkeys, pairs, cur, L, idx->tab_seg_off,
+    hipLaunchKernelGGL(locate_queries, dim3(gpairs), dim3(256), 0, st, qkeys, pairs, cur, qs, L, idx->tab_seg_off,
                        idx->seg_cap, idx->tab_key, qslot, qrank, qcount);
     STAG_TRY(check_launch("locate_queries"));
     STAG_TRY(exclusive_scan_u32(qcount, qstart, nslots, ws, st));
@@ -2112,8 +2119,8 @@ stag_status join_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64
     STAG_HIP(hipMemcpyAsync(&ntasks, task_base + nslots, sizeof(uint64_t), hipMemcpyDeviceToHost, st));
     STAG_HIP(hipStreamSynchronize(st));
   }
-  if (ntasks > (uint64_t)INT32_MAX) return fail(STAG_E_UNSUPPORTED, "lsh: %llu join tasks in one batch",
-                                                (unsigned long long)ntasks);
+  *tasks_out = ntasks;
+  if (ntasks > max_tasks) return STAG_OK;
   double* tpart = nullptr;
   STAG_TRY(ws.alloc(&tpart, (size_t)std::max<uint64_t>(ntasks, 1) * 64));
   JoinTask* tasks = nullptr;
@@ -2138,7 +2145,7 @@ stag_status join_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64
       rows = padded;
     }
     auto launch = [&](auto kern) {
-      hipLaunchKernelGGL(kern, dim3((unsigned)ntasks), dim3(64), lds, st, ix, lc, rows, q0, qkeys, cur, qlist, tasks,
+      hipLaunchKernelGGL(kern, dim3((unsigned)ntasks), dim3(64), lds, st, ix, lc, rows, q0, qkeys, qs, qlist, tasks,
                          self_excl, tpart, nacc, levels);
     };
     switch (dq) {
@@ -2154,6 +2161,45 @@ stag_status join_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64
     hipLaunchKernelGGL(combine_groups, dim3((unsigned)ceil_div(cur, 256)), dim3(256), 0, st, qslot, qrank, cur, ntab,
                        K1, idx->tab_cnt, task_base, tpart, q0, scopy, ncand);
     STAG_TRY(check_launch("combine_groups"));
+  }
+  return STAG_OK;
+}
+
+// Bytes of a join task (its description and 64 partials), and the tasks that
+// a batch may have: kJoinMaxBytes of them, though a single query is let to have
+// as many as a launch takes (2^32 threads).
+constexpr int64_t kJoinTaskBytes = 64 * sizeof(double) + sizeof(JoinTask);
+constexpr int64_t kJoinMaxBytes = (int64_t)4 << 30;
+constexpr uint64_t kJoinMaxLaunch = ((uint64_t)1 << 26) - 1;
+
+// Copy sums of one hashed query batch through the bucket join: in slices where
+// its tasks are too many or don't fit the memory.  How many they are is known
+// once the queries are located, and grows with the square of the points where
+// most share a bucket (wide kernels).  A query's sums are the same in any slice.
+stag_status join_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64_t q0, int64_t cur, int self_excl,
+                       const uint64_t* qkeys, double* scopy, int64_t* ncand, int64_t* nacc, uint64_t* levels,
+                       hipStream_t st) {
+  const uint64_t limit = (uint64_t)(kJoinMaxBytes / kJoinTaskBytes);
+  int64_t slice = cur;
+  for (int64_t p = 0; p < cur;) {
+    const int64_t c = std::min(slice, cur - p);
+    const uint64_t most = c > 1 ? limit : kJoinMaxLaunch;
+    uint64_t ntasks = 0;
+    const stag_status s = join_slice(idx, Q, ldq, q0 + p, c, self_excl, qkeys + p, cur, scopy + p * idx->prm.shape.K1,
+                                     ncand, nacc, levels, most, &ntasks, st);
+    if (s == STAG_OK && ntasks <= most) {
+      p += c;
+    } else if (s == STAG_OK && c > 1) {
+      // whole waves of queries where that is enough
+      slice = (int64_t)(0.9 * (double)c * (double)limit / (double)ntasks);
+      slice = slice >= 64 ? slice / 64 * 64 : std::max<int64_t>(slice, 1);
+    } else if (s == STAG_E_NOMEM && c > 64) {
+      clear_error();
+      slice = round_up(c / 2, 64);
+    } else {
+      return s != STAG_OK ? s
+                          : fail(STAG_E_UNSUPPORTED, "lsh: %llu join tasks for one query", (unsigned long long)ntasks);
+    }
   }
   return STAG_OK;
 }

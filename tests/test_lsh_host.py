@@ -1,0 +1,110 @@
+"""Host-only tests of the memory that CKNS queries take (lsh.hip on a mock of
+the HIP runtime, kernels not run): what fits, what is done in slices and what
+fails."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2407_07096_amd", "csrc")
+MOCK = os.path.join(ROOT, "tests", "runtime_mock")
+GB = 1 << 30
+OK, NOMEM, UNSUPPORTED = 0, 2, 4
+
+
+def build(out, unit):
+    """The mocked library around one test unit that includes a HIP source."""
+    flags = ["-O1", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", CSRC, "-I", MOCK]
+    obj = str(out / "unit.o")
+    subprocess.run(["hipcc", "-x", "hip", "--offload-host-only", "--offload-arch=gfx950", *flags, "-c",
+                    os.path.join(MOCK, unit), "-o", obj], check=True)
+    und = subprocess.run(["nm", "-u", obj], check=True, capture_output=True, text=True).stdout
+    fat = [s.split()[-1] for s in und.splitlines() if "__hip_fatbin" in s]
+    lib = str(out / "libmock.so")
+    subprocess.run(["g++", "-shared", "-pthread", "-Wl,-Bsymbolic", "-Wno-unused-result", *flags, obj,
+                    os.path.join(CSRC, "runtime.cpp"), os.path.join(MOCK, "mock_hip.cpp"),
+                    os.path.join(MOCK, "mock_launch.cpp"), *[f"-Wl,--defsym={f}=mock_fatbin" for f in fat],
+                    "-o", lib], check=True)
+    return lib
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    lib = C.CDLL(build(tmp_path_factory.mktemp("lshmock"), "lsh_host.cpp"))
+    for f in ("mock_stream", "lsh_index"):
+        getattr(lib, f).restype = C.c_void_p
+    for f in ("mock_count", "lsh_combined", "launch_threads", "launch_count"):
+        getattr(lib, f).restype = C.c_int64
+    lib.mock_capacity.argtypes = [C.c_size_t]
+    lib.lsh_index.argtypes = [C.c_int] * 5 + [C.c_int64]
+    lib.lsh_free.argtypes = [C.c_void_p]
+    lib.lsh_query.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_int64]
+    lib.lsh_combined.argtypes = [C.c_void_p, C.c_void_p, C.c_int64]
+    lib.launch_count.argtypes = [C.c_char_p]
+    lib.lsh_bucket_tasks.restype = C.c_uint32
+    lib.lsh_bucket_tasks.argtypes = [C.c_uint32, C.c_uint32]
+    return lib
+
+
+@pytest.fixture
+def stream(lib):
+    lib.mock_capacity(C.c_size_t(-1).value)
+    return lib.mock_stream(0)
+
+
+def combined(lib):
+    """The query ranges whose results were combined, in order."""
+    cap = 100000
+    q0, count = (C.c_int64 * cap)(), (C.c_int64 * cap)()
+    k = lib.lsh_combined(q0, count, cap)
+    return [(q0[i], count[i]) for i in range(k)]
+
+
+def covers(lib, m):
+    at = 0
+    for q0, c in combined(lib):
+        assert q0 == at and c > 0
+        at += c
+    return at == m
+
+
+def test_join_in_one_slice(lib, stream):
+    idx = lib.lsh_index(64, 1, 17, 4, 6, 1 << 20)
+    assert lib.lsh_query(idx, stream, 4096, 100) == OK
+    assert combined(lib) == [(0, 4096)]
+    lib.lsh_free(idx)
+
+
+@pytest.mark.parametrize("tasks", [3000, 40000, 1000000])  # a query: 1e7, 1.6e8 and 4e9 in a batch
+def test_join_with_many_tasks(lib, stream, tasks):
+    # wide kernels, where most points share a bucket: more tasks than a launch
+    # or the memory takes are done in slices of the queries
+    idx = lib.lsh_index(64, 1, 17, 4, 6, 1 << 20)
+    lib.mock_capacity(20 * GB)
+    assert lib.lsh_query(idx, stream, 4096, tasks) == OK
+    assert covers(lib, 4096)
+    assert lib.launch_threads() < 1 << 32
+    lib.lsh_free(idx)
+
+
+def test_join_in_little_memory(lib, stream):
+    idx = lib.lsh_index(64, 1, 17, 4, 6, 1 << 20)
+    lib.mock_capacity(1 * GB)
+    assert lib.lsh_query(idx, stream, 4096, 1000) == OK  # 2.3 GB of tasks at once
+    assert covers(lib, 4096)
+    lib.mock_capacity(32 << 20)  # not even a block
+    assert lib.lsh_query(idx, stream, 100000, 1000) == NOMEM
+    lib.lsh_free(idx)
+
+
+def test_tasks_of_a_bucket(lib):
+    for nq, nm in [(0, 5), (5, 0), (1, 1), (64, 128), (65, 129), (1 << 27, 1 << 20), (1 << 27, (1 << 31) - 1)]:
+        assert lib.lsh_bucket_tasks(nq, nm) == min(-(-nq // 64) * -(-nm // 128), (1 << 32) - 1)
+
+
+def test_join_of_a_query_past_the_launch(lib, stream):
+    idx = lib.lsh_index(64, 1, 17, 4, 6, 1 << 20)
+    assert lib.lsh_query(idx, stream, 64, 1 << 27) == UNSUPPORTED
+    lib.lsh_free(idx)
