@@ -2002,37 +2002,36 @@ K by_rows(int d, K own, K quad4, K quad) {
   return r == kOwnRow ? own : r == kQuad4 ? quad4 : quad;
 }
 
+// Pair buffers for `rows` (a multiple of kDenseTile) queries at a time, and
+// the norms of `rows` or of all `cur` queries, if fewer.
+stag_status alloc_dense(const stag_lsh_index* idx, int64_t rows, int64_t cur, bool draw, Workspace& ws, DensePairs* dp,
+                        double** qnorm) {
+  dp->ncol = idx->dense_tiles * kDenseTile;
+  STAG_TRY(ws.alloc(&dp->D, (size_t)rows * dp->ncol));
+  STAG_TRY(ws.alloc(&dp->F, (size_t)rows * dp->ncol));
+  STAG_TRY(ws.alloc(&dp->any, (size_t)(rows / kDenseTile) * idx->dense_tiles));
+  if (draw) {
+    STAG_TRY(ws.alloc(&dp->V, (size_t)rows * dp->ncol));
+    STAG_TRY(ws.alloc(&dp->J, (size_t)rows * dp->ncol));
+    STAG_TRY(ws.alloc(&dp->len, (size_t)rows * idx->dense_tiles));
+  }
+  STAG_TRY(ws.alloc(qnorm, (size_t)std::min(rows, cur)));
+  dp->tiles = idx->dtiles;
+  dp->first = idx->dfirst;
+  dp->levels = idx->dlevels;
+  return STAG_OK;
+}
+
 // Copy sums (and draws) of one hashed query batch through the walk, the
-// dense segments' pairs formed for as many queries at a time as their buffer
-// holds.
-stag_status walk_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64_t q0, int64_t cur, int self_excl,
-                       const uint64_t* qkeys, double* scopy, int64_t* ncand, int64_t* nacc, const DrawArgs* draw,
-                       hipStream_t st) {
+// dense segments' pairs (if dp has any columns) formed for `sub` queries at a
+// time.
+stag_status walk_rows(const stag_lsh_index* idx, const float* Q, int ldq, int64_t q0, int64_t cur, int self_excl,
+                      const uint64_t* qkeys, double* scopy, int64_t* ncand, int64_t* nacc, const DrawArgs* draw,
+                      const DensePairs& dp, double* qnorm, int64_t sub, hipStream_t st) {
   const int K1 = idx->prm.shape.K1;
   const IndexView ix = make_view(idx);
   const LevelConst lc = make_levels(idx->prm);
   uint64_t* levels = draw ? draw->levels : nullptr;
-  Workspace ws(st);
-  DensePairs dp;
-  int64_t sub = cur;
-  double* qnorm = nullptr;
-  if (idx->dense_tiles > 0) {
-    dp.ncol = idx->dense_tiles * kDenseTile;
-    const int64_t fit = kDenseMaxBytes / ((int64_t)dp.ncol * (draw ? 21 : 9)) / kDenseTile * kDenseTile;
-    sub = std::min<int64_t>({std::max<int64_t>(fit, kDenseTile), round_up(cur, kDenseTile), (int64_t)65535 * kDenseTile});
-    STAG_TRY(ws.alloc(&dp.D, (size_t)sub * dp.ncol));
-    STAG_TRY(ws.alloc(&dp.F, (size_t)sub * dp.ncol));
-    STAG_TRY(ws.alloc(&dp.any, (size_t)(sub / kDenseTile) * idx->dense_tiles));
-    if (draw) {
-      STAG_TRY(ws.alloc(&dp.V, (size_t)sub * dp.ncol));
-      STAG_TRY(ws.alloc(&dp.J, (size_t)sub * dp.ncol));
-      STAG_TRY(ws.alloc(&dp.len, (size_t)sub * idx->dense_tiles));
-    }
-    STAG_TRY(ws.alloc(&qnorm, (size_t)std::min(sub, cur)));
-    dp.tiles = idx->dtiles;
-    dp.first = idx->dfirst;
-    dp.levels = idx->dlevels;
-  }
   for (int64_t p = 0; p < cur; p += sub) {
     const int64_t c = std::min(sub, cur - p);
     double* sc = scopy + p * K1;
@@ -2075,6 +2074,34 @@ stag_status walk_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64
     }
   }
   return STAG_OK;
+}
+
+// Copy sums (and draws) of one hashed query batch through the walk.  The dense
+// segments' pairs are formed for as many queries at a time as kDenseMaxBytes
+// hold, or the memory that is left: half as many for as long as the buffers
+// can't be had, and when those of one row tile can't either, every segment is
+// walked, which needs none.
+stag_status walk_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64_t q0, int64_t cur, int self_excl,
+                       const uint64_t* qkeys, double* scopy, int64_t* ncand, int64_t* nacc, const DrawArgs* draw,
+                       hipStream_t st) {
+  int64_t sub = 0;
+  if (idx->dense_tiles > 0) {
+    const int64_t row = (int64_t)idx->dense_tiles * kDenseTile * (draw ? 21 : 9);
+    sub = std::min<int64_t>({std::max<int64_t>(kDenseMaxBytes / row / kDenseTile * kDenseTile, kDenseTile),
+                             round_up(cur, kDenseTile), (int64_t)65535 * kDenseTile});
+  }
+  for (;;) {
+    Workspace ws(st);
+    DensePairs dp;
+    double* qnorm = nullptr;
+    const stag_status s = sub > 0 ? alloc_dense(idx, sub, cur, draw != nullptr, ws, &dp, &qnorm) : STAG_OK;
+    if (s == STAG_OK)
+      return walk_rows(idx, Q, ldq, q0, cur, self_excl, qkeys, scopy, ncand, nacc, draw, dp, qnorm, sub > 0 ? sub : cur,
+                       st);
+    if (s != STAG_E_NOMEM) return s;
+    clear_error();
+    sub = sub > kDenseTile ? round_up(sub / 2, kDenseTile) : 0;
+  }
 }
 
 // Copy sums of `cur` queries (keys at qkeys + table * qs) through the bucket

@@ -58,6 +58,19 @@ void* lsh_index(int d, int K1, int J, int L, int K, int64_t slots) {
   idx->total_slots = slots;
   return idx;
 }
+// `tiles` column tiles of dense segments (walked indexes: d > 128 or L > 32).
+void lsh_dense(void* idx, int tiles) {
+  auto* x = static_cast<stag_lsh_index*>(idx);
+  x->dense_tiles = tiles;
+  x->dlevels = reinterpret_cast<uint64_t*>(64);
+}
+int lsh_sample(void* idx, void* stream, int64_t n, int s) {
+  auto* x = static_cast<stag_lsh_index*>(idx);
+  x->prm.n = n;
+  mock::launches().clear();
+  auto* p = reinterpret_cast<int64_t*>((uintptr_t)1 << 42);
+  return (int)lsh_sample_edges(x, s, 1, p, p, (double*)p, nullptr, (hipStream_t)stream);
+}
 void lsh_free(void* idx) { delete static_cast<stag_lsh_index*>(idx); }
 
 // A query of m rows; tasks: join tasks that every query makes.

@@ -3,6 +3,7 @@ the HIP runtime, kernels not run): what fits, what is done in slices and what
 fails."""
 import ctypes as C
 import os
+import shutil
 import subprocess
 
 import pytest
@@ -31,8 +32,15 @@ def build(out, unit):
 
 
 @pytest.fixture(scope="module")
-def lib(tmp_path_factory):
-    lib = C.CDLL(build(tmp_path_factory.mktemp("lshmock"), "lsh_host.cpp"))
+def so(tmp_path_factory):
+    return build(tmp_path_factory.mktemp("lshmock"), "lsh_host.cpp")
+
+
+@pytest.fixture
+def lib(so, tmp_path):
+    copy = tmp_path / "libmock.so"  # a state of its own for every test
+    shutil.copy(so, copy)
+    lib = C.CDLL(str(copy))
     for f in ("mock_stream", "lsh_index"):
         getattr(lib, f).restype = C.c_void_p
     for f in ("mock_count", "lsh_combined", "launch_threads", "launch_count"):
@@ -43,6 +51,8 @@ def lib(tmp_path_factory):
     lib.lsh_query.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_int64]
     lib.lsh_combined.argtypes = [C.c_void_p, C.c_void_p, C.c_int64]
     lib.launch_count.argtypes = [C.c_char_p]
+    lib.lsh_dense.argtypes = [C.c_void_p, C.c_int]
+    lib.lsh_sample.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_int]
     lib.lsh_bucket_tasks.restype = C.c_uint32
     lib.lsh_bucket_tasks.argtypes = [C.c_uint32, C.c_uint32]
     return lib
@@ -50,7 +60,6 @@ def lib(tmp_path_factory):
 
 @pytest.fixture
 def stream(lib):
-    lib.mock_capacity(C.c_size_t(-1).value)
     return lib.mock_stream(0)
 
 
@@ -107,4 +116,25 @@ def test_tasks_of_a_bucket(lib):
 def test_join_of_a_query_past_the_launch(lib, stream):
     idx = lib.lsh_index(64, 1, 17, 4, 6, 1 << 20)
     assert lib.lsh_query(idx, stream, 64, 1 << 27) == UNSUPPORTED
+    lib.lsh_free(idx)
+
+
+@pytest.mark.parametrize("capacity,pairs", [(8192, True), (1000, True), (600, True), (220, True), (90, False)])
+@pytest.mark.parametrize("draws", [0, 5])
+def test_dense_levels_in_little_memory(lib, stream, capacity, pairs, draws):
+    # 38,400 dense columns: 1.4 GB of pairs for 4,096 queries at once (3.3 with
+    # draws), 44 MB (103) for 128, and twice 64 MB of small buffers; without even
+    # these every level is walked
+    idx = lib.lsh_index(200, 1, 17, 4, 6, 1 << 20)
+    lib.lsh_dense(idx, 300)
+    if draws:
+        capacity *= 2
+    lib.mock_capacity(capacity << 20)
+    if draws:
+        assert lib.lsh_sample(idx, stream, 4096, draws) == OK
+    else:
+        assert lib.lsh_query(idx, stream, 4096, 0) == OK
+    assert (lib.launch_count(b"dense_pairs") > 0) == pairs
+    assert lib.launch_count(b"dense_pairs") == lib.launch_count(b"dense_terms")
+    assert lib.launch_count(b"probe_queries") > 0
     lib.lsh_free(idx)
