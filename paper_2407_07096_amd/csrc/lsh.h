@@ -24,4 +24,12 @@ stag_status lsh_derive_params(int64_t n, double a, double eps, const stag_lsh_pa
 stag_status lsh_sample_edges(const stag_lsh_index* idx, int s, uint64_t seed, int64_t* src, int64_t* dst, double* w,
                              double* deg_out, hipStream_t st);
 
+// The bytes that a query of m rows can use for what its rows meet: candidate
+// pairs of the dense levels, or tasks of the bucket join.
+size_t lsh_pair_bytes(const stag_lsh_index* idx, int64_t m);
+// stag_lsh_index_query with at most pair_bytes of them at a time (but enough
+// for 128 queries' pairs, or one query's tasks).
+stag_status lsh_query_within(const stag_lsh_index* idx, const float* Q, int64_t m, double* S_out, size_t pair_bytes,
+                             hipStream_t st);
+
 }  // namespace stag

@@ -2002,6 +2002,11 @@ K by_rows(int d, K own, K quad4, K quad) {
   return r == kOwnRow ? own : r == kQuad4 ? quad4 : quad;
 }
 
+// Bytes of the pair buffers for one query.
+int64_t dense_row_bytes(const stag_lsh_index* idx, bool draw) {
+  return (int64_t)idx->dense_tiles * kDenseTile * (draw ? 21 : 9);
+}
+
 // Pair buffers for `rows` (a multiple of kDenseTile) queries at a time, and
 // the norms of `rows` or of all `cur` queries, if fewer.
 stag_status alloc_dense(const stag_lsh_index* idx, int64_t rows, int64_t cur, bool draw, Workspace& ws, DensePairs* dp,
@@ -2083,11 +2088,11 @@ stag_status walk_rows(const stag_lsh_index* idx, const float* Q, int ldq, int64_
 // walked, which needs none.
 stag_status walk_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64_t q0, int64_t cur, int self_excl,
                        const uint64_t* qkeys, double* scopy, int64_t* ncand, int64_t* nacc, const DrawArgs* draw,
-                       hipStream_t st) {
+                       int64_t pair_bytes, hipStream_t st) {
   int64_t sub = 0;
   if (idx->dense_tiles > 0) {
-    const int64_t row = (int64_t)idx->dense_tiles * kDenseTile * (draw ? 21 : 9);
-    sub = std::min<int64_t>({std::max<int64_t>(kDenseMaxBytes / row / kDenseTile * kDenseTile, kDenseTile),
+    const int64_t row = dense_row_bytes(idx, draw != nullptr);
+    sub = std::min<int64_t>({std::max<int64_t>(std::min(pair_bytes, kDenseMaxBytes) / row / kDenseTile * kDenseTile, kDenseTile),
                              round_up(cur, kDenseTile), (int64_t)65535 * kDenseTile});
   }
   for (;;) {
@@ -2205,8 +2210,8 @@ constexpr uint64_t kJoinMaxLaunch = ((uint64_t)1 << 26) - 1;
 // most share a bucket (wide kernels).  A query's sums are the same in any slice.
 stag_status join_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64_t q0, int64_t cur, int self_excl,
                        const uint64_t* qkeys, double* scopy, int64_t* ncand, int64_t* nacc, uint64_t* levels,
-                       hipStream_t st) {
-  const uint64_t limit = (uint64_t)(kJoinMaxBytes / kJoinTaskBytes);
+                       int64_t pair_bytes, hipStream_t st) {
+  const uint64_t limit = (uint64_t)(std::min(pair_bytes, kJoinMaxBytes) / kJoinTaskBytes);
   int64_t slice = cur;
   for (int64_t p = 0; p < cur;) {
     const int64_t c = std::min(slice, cur - p);
@@ -2235,9 +2240,11 @@ stag_status join_batch(const stag_lsh_index* idx, const float* Q, int ldq, int64
 // row's own point is left out).  Optional per-copy values and counts.
 // keys_buf (optional): the caller's buffer of query_batch(idx, m) x ntab
 // keys; when the queries fit one batch it holds their keys on return.
+// pair_bytes: see lsh_query_within.
 stag_status query_index(const stag_lsh_index* idx, const float* Q, int ldq, int64_t m, int self_excl,
                         double* S_out, double* copies_out, int64_t* ncand, int64_t* nacc, hipStream_t st,
-                        uint64_t* keys_buf = nullptr, const DrawArgs* draw = nullptr, uint64_t* levels = nullptr) {
+                        uint64_t* keys_buf = nullptr, const DrawArgs* draw = nullptr, uint64_t* levels = nullptr,
+                        int64_t pair_bytes = INT64_MAX) {
   const LshParams& prm = idx->prm;
   const int K1 = prm.shape.K1;
   Workspace ws(st);
@@ -2252,9 +2259,9 @@ stag_status query_index(const stag_lsh_index* idx, const float* Q, int ldq, int6
     const int64_t cur = std::min(mb, m - q0);
     STAG_TRY(hash_query_batch(idx, Q, ldq, q0, cur, qkeys, st));
     if (join_applies(idx)) {
-      STAG_TRY(join_batch(idx, Q, ldq, q0, cur, self_excl, qkeys, scopy, ncand, nacc, levels, st));
+      STAG_TRY(join_batch(idx, Q, ldq, q0, cur, self_excl, qkeys, scopy, ncand, nacc, levels, pair_bytes, st));
     } else {
-      STAG_TRY(walk_batch(idx, Q, ldq, q0, cur, self_excl, qkeys, scopy, ncand, nacc, draw, st));
+      STAG_TRY(walk_batch(idx, Q, ldq, q0, cur, self_excl, qkeys, scopy, ncand, nacc, draw, pair_bytes, st));
     }
     hipLaunchKernelGGL(mean_copies, dim3((unsigned)ceil_div(cur, 256)), dim3(256), 0, st, scopy, q0, cur, K1, S_out,
                        copies_out);
@@ -2264,6 +2271,26 @@ stag_status query_index(const stag_lsh_index* idx, const float* Q, int ldq, int6
 }
 
 }  // namespace
+
+size_t lsh_pair_bytes(const stag_lsh_index* idx, int64_t m) {
+  if (m < 1) return 0;
+  m = std::min(m, query_batch(idx, m));
+  if (!join_applies(idx))
+    return (size_t)std::min(kDenseMaxBytes, round_up(m, kDenseTile) * dense_row_bytes(idx, false));
+  // tasks: ceil(nq / 64) ceil(nm / kJoinMembers) over the buckets that are hit, at
+  // most m in each table
+  const double groups = (double)(m / 64 + 1);
+  const double tasks = groups * ((double)idx->prm.shape.L * (double)idx->M / kJoinMembers) +
+                       (double)idx->ntab * ((double)m + groups);
+  return (size_t)std::min((double)kJoinMaxBytes, tasks * (double)kJoinTaskBytes);
+}
+
+stag_status lsh_query_within(const stag_lsh_index* idx, const float* Q, int64_t m, double* S_out, size_t pair_bytes,
+                             hipStream_t st) {
+  clear_error();
+  return query_index(idx, Q, idx->d, m, 0, S_out, nullptr, nullptr, nullptr, st, nullptr, nullptr, nullptr,
+                     (int64_t)std::min<size_t>(pair_bytes, INT64_MAX));
+}
 
 // Edge sampling with the CKNS estimator (see draw_lsh): rest_i = mean over
 // copies of the estimate of sum_{j != i} k_ij; deg = 1 + rest.

@@ -30,6 +30,7 @@
 #include <vector>
 
 #include "kde_exact.h"
+#include "lsh.h"
 #include "runtime.h"
 #include "serve_core.h"
 
@@ -143,7 +144,7 @@ class Worker {
 
 class GpuExecutor : public serve::Executor {
  public:
-  explicit GpuExecutor(int n_streams) {
+  GpuExecutor(int n_streams, size_t budget, int64_t chunk) : budget_(budget), chunk_(chunk) {
     streams_.resize(n_streams, nullptr);
     events_.resize(n_streams, nullptr);
     pinned_.resize(n_streams, nullptr);
@@ -238,18 +239,16 @@ class GpuExecutor : public serve::Executor {
   size_t footprint(int dsi, int key, int64_t m) override {
     if (dsi < 0 || dsi >= (int)datasets_.size()) return 0;
     const Dataset& ds = *datasets_[dsi];
-    const int64_t mp = round_up(m, kQueryTile);
     if (key == kKeyLsh) {
       if (!ds.lsh) return 0;
-      const stag_lsh_shape& sh = ds.lsh_shape;
-      return (size_t)mp * ((size_t)sh.K1 * sh.J * sh.L * 16 + 64) + ((size_t)64 << 20);
+      return lsh_base(ds, m) + (size_t)serve::chunks_at_once(m, chunk_, n_streams()) * lsh_allowance(ds, m);
     }
     if (key < 0 || key > 3 || !(ds.forms & (1u << key))) return 0;
     const Operands& xo = ds.ops[key];
     const int P = (int)exact_chunks(xo.rows_pad);
     const size_t per_row = (size_t)xo.dp * form_element_bytes(key) * form_parts(key) + 4 + 8 +
                            (size_t)P * 8 * (xo.centred ? 2 : 1);
-    return (size_t)mp * per_row;
+    return (size_t)round_up(m, kQueryTile) * per_row;
   }
 
   int launch(int dsi, int key, const std::vector<serve::Item>& batch, int s) override {
@@ -260,12 +259,15 @@ class GpuExecutor : public serve::Executor {
     ReqSeg* pinned = pinned_[s];
     std::vector<serve::Item> items = batch;
     if (key == kKeyLsh) {
-      workers_[s]->post([ds, items, st, ev]() -> int {
+      std::vector<size_t> allowed;
+      for (const serve::Item& it : items) allowed.push_back(lsh_allowance(*ds, it.r->m));
+      workers_[s]->post([ds, items, allowed, st, ev]() -> int {
         int rc = STAG_OK;
-        for (const serve::Item& it : items) {
+        for (size_t k = 0; k < items.size(); ++k) {
+          const serve::Item& it = items[k];
           const float* Q = static_cast<const float*>(it.r->Q) + it.row0 * ds->d;
           double* S = static_cast<double*>(it.r->S) + it.row0;
-          rc = stag_lsh_index_query(ds->lsh, Q, it.m, S, st);
+          rc = lsh_query_within(ds->lsh, Q, it.m, S, allowed[k], st);
           if (rc != STAG_OK) break;
         }
         if (hipEventRecord(ev, st) != hipSuccess && rc == STAG_OK) rc = STAG_E_DEVICE;
@@ -299,6 +301,17 @@ class GpuExecutor : public serve::Executor {
   const Dataset* dataset(int i) const { return datasets_[i].get(); }
 
  private:
+  // An LSH request of m queries: the bytes that its queries take whatever they
+  // meet, and what each of its chunks may take for what they do.
+  static size_t lsh_base(const Dataset& ds, int64_t m) {
+    const stag_lsh_shape& sh = ds.lsh_shape;
+    return (size_t)round_up(m, kQueryTile) * ((size_t)sh.K1 * sh.J * sh.L * 16 + 64) + ((size_t)64 << 20);
+  }
+  size_t lsh_allowance(const Dataset& ds, int64_t m) const {
+    return serve::chunk_allowance(budget_, n_streams(), chunk_, m, lsh_base(ds, m),
+                                  lsh_pair_bytes(ds.lsh, std::min(m, chunk_)));
+  }
+
   // One exact batch on stream st: chunk queries into one operand set, tiles,
   // segmented reduction.  Temporaries are stream-ordered pool allocations.
   static stag_status run_exact_batch(const Dataset& ds, int form, const std::vector<serve::Item>& items,
@@ -347,6 +360,8 @@ class GpuExecutor : public serve::Executor {
     return check_launch("serve_reduce");
   }
 
+  size_t budget_;
+  int64_t chunk_;
   std::vector<hipStream_t> streams_;
   std::vector<hipEvent_t> events_;
   std::vector<ReqSeg*> pinned_;
@@ -384,10 +399,11 @@ stag_status stag_server_create(size_t budget_bytes, int32_t n_streams, int64_t m
   const int ns = n_streams > 0 ? n_streams : 4;
   const int64_t mb = max_batch_queries > 0 ? max_batch_queries : 65536;
   const int64_t ch = chunk_queries > 0 ? chunk_queries : 4096;
-  sv->ex.reset(new GpuExecutor(ns));
+  const size_t budget = budget_bytes > 0 ? budget_bytes : ((size_t)8 << 30);
+  sv->ex.reset(new GpuExecutor(ns, budget, ch));
   STAG_TRY(sv->ex->init());
   STAG_HIP(hipGetDevice(&sv->device));
-  sv->sched.reset(new serve::Scheduler(sv->ex.get(), budget_bytes > 0 ? budget_bytes : ((size_t)8 << 30), mb, ch));
+  sv->sched.reset(new serve::Scheduler(sv->ex.get(), budget, mb, ch));
   *out = sv.release();
   return STAG_OK;
 }

@@ -25,6 +25,7 @@
 // A failure reported for one chunk fails only its request.
 #pragma once
 
+#include <algorithm>
 #include <condition_variable>
 #include <cstddef>
 #include <cstdint>
@@ -37,6 +38,21 @@
 
 namespace stag {
 namespace serve {
+
+// Bytes of buffers that a chunk takes by what its queries meet (candidate pairs,
+// join tasks) and can make do with fewer of: what the chunks of a request of m
+// queries may have each.  need: the most a chunk can use; base: the request's
+// other bytes.  A stream's share of half the budget, and with the base never
+// more than the budget: a request is not refused for buffers that only make
+// it faster.  The request's footprint is base + chunks_at_once() of them.
+inline int64_t chunks_at_once(int64_t m, int64_t chunk, int streams) {
+  return std::min<int64_t>((m + chunk - 1) / chunk, streams);
+}
+inline size_t chunk_allowance(size_t budget, int streams, int64_t chunk, int64_t m, size_t base, size_t need) {
+  if (m < 1 || base >= budget) return 0;
+  const size_t share = budget / (2 * (size_t)streams);
+  return std::min({need, share, (budget - base) / (size_t)chunks_at_once(m, chunk, streams)});
+}
 
 struct Request {
   uint64_t id = 0;

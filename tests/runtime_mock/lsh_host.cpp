@@ -73,8 +73,12 @@ int lsh_sample(void* idx, void* stream, int64_t n, int s) {
 }
 void lsh_free(void* idx) { delete static_cast<stag_lsh_index*>(idx); }
 
-// A query of m rows; tasks: join tasks that every query makes.
-int lsh_query(void* idx, void* stream, int64_t m, int64_t tasks) {
+void lsh_members(void* idx, int64_t members) { static_cast<stag_lsh_index*>(idx)->M = members; }
+uint64_t lsh_pairs(void* idx, int64_t m) { return lsh_pair_bytes(static_cast<stag_lsh_index*>(idx), m); }
+
+// A query of m rows (pair_bytes > 0: with at most that many); tasks: join
+// tasks that every query makes.
+int lsh_query(void* idx, void* stream, int64_t m, int64_t tasks, uint64_t pair_bytes) {
   g_combined.clear();
   mock::launches().clear();
   g_tasks = tasks;
@@ -86,6 +90,7 @@ int lsh_query(void* idx, void* stream, int64_t m, int64_t tasks) {
   };
   const float* Q = reinterpret_cast<const float*>((uintptr_t)1 << 40);
   double* S = reinterpret_cast<double*>((uintptr_t)1 << 41);
+  if (pair_bytes > 0) return (int)lsh_query_within((stag_lsh_index*)idx, Q, m, S, pair_bytes, (hipStream_t)stream);
   return (int)stag_lsh_index_query((stag_lsh_index*)idx, Q, m, S, (hipStream_t)stream);
 }
 int64_t lsh_combined(int64_t* q0, int64_t* count, int64_t cap) {

@@ -4,6 +4,7 @@
 // are never dereferenced.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstdint>
 #include <map>
@@ -29,7 +30,7 @@ struct State {
   std::recursive_mutex mu;
   std::vector<Stream*> streams;
   int device = 0;
-  size_t capacity = SIZE_MAX, used = 0;
+  size_t capacity = SIZE_MAX, used = 0, peak = 0;
   uintptr_t next = 1 << 20;
   std::map<void*, size_t> live;
   int64_t mallocs = 0, frees = 0, cross_waits = 0, unsafe_calls = 0, host_waits = 0, trims = 0;
@@ -56,6 +57,7 @@ hipError_t take(void** p, size_t bytes) {
     return hipErrorOutOfMemory;
   }
   s.used += bytes;
+  s.peak = std::max(s.peak, s.used);
   *p = reinterpret_cast<void*>(s.next);
   s.next += (bytes + 4095) / 4096 * 4096;
   s.live[*p] = bytes;
@@ -137,7 +139,8 @@ void mock_finish(void* s) { LOCK; of((hipStream_t)s)->finished = of((hipStream_t
 int64_t mock_count(int what) {
   LOCK;
   const State& s = S();
-  const int64_t v[] = {s.mallocs, s.frees, s.cross_waits, s.unsafe_calls, s.host_waits, s.trims, (int64_t)s.used};
+  const int64_t v[] = {s.mallocs, s.frees, s.cross_waits, s.unsafe_calls, s.host_waits, s.trims, (int64_t)s.used,
+                       (int64_t)s.peak};
   return v[what];
 }
 void* ws_new(void* stream) { return new stag::Workspace((hipStream_t)stream); }

@@ -3,6 +3,7 @@ the HIP runtime, kernels not run): what fits, what is done in slices and what
 fails."""
 import ctypes as C
 import os
+import random
 import shutil
 import subprocess
 
@@ -48,7 +49,9 @@ def lib(so, tmp_path):
     lib.mock_capacity.argtypes = [C.c_size_t]
     lib.lsh_index.argtypes = [C.c_int] * 5 + [C.c_int64]
     lib.lsh_free.argtypes = [C.c_void_p]
-    lib.lsh_query.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_int64]
+    lib.lsh_query.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_int64, C.c_uint64]
+    lib.lsh_members.argtypes = lib.lsh_pairs.argtypes = [C.c_void_p, C.c_int64]
+    lib.lsh_pairs.restype = C.c_uint64
     lib.lsh_combined.argtypes = [C.c_void_p, C.c_void_p, C.c_int64]
     lib.launch_count.argtypes = [C.c_char_p]
     lib.lsh_dense.argtypes = [C.c_void_p, C.c_int]
@@ -81,7 +84,7 @@ def covers(lib, m):
 
 def test_join_in_one_slice(lib, stream):
     idx = lib.lsh_index(64, 1, 17, 4, 6, 1 << 20)
-    assert lib.lsh_query(idx, stream, 4096, 100) == OK
+    assert lib.lsh_query(idx, stream, 4096, 100, 0) == OK
     assert combined(lib) == [(0, 4096)]
     lib.lsh_free(idx)
 
@@ -92,7 +95,7 @@ def test_join_with_many_tasks(lib, stream, tasks):
     # or the memory takes are done in slices of the queries
     idx = lib.lsh_index(64, 1, 17, 4, 6, 1 << 20)
     lib.mock_capacity(20 * GB)
-    assert lib.lsh_query(idx, stream, 4096, tasks) == OK
+    assert lib.lsh_query(idx, stream, 4096, tasks, 0) == OK
     assert covers(lib, 4096)
     assert lib.launch_threads() < 1 << 32
     lib.lsh_free(idx)
@@ -101,10 +104,10 @@ def test_join_with_many_tasks(lib, stream, tasks):
 def test_join_in_little_memory(lib, stream):
     idx = lib.lsh_index(64, 1, 17, 4, 6, 1 << 20)
     lib.mock_capacity(1 * GB)
-    assert lib.lsh_query(idx, stream, 4096, 1000) == OK  # 2.3 GB of tasks at once
+    assert lib.lsh_query(idx, stream, 4096, 1000, 0) == OK  # 2.3 GB of tasks at once
     assert covers(lib, 4096)
     lib.mock_capacity(32 << 20)  # not even a block
-    assert lib.lsh_query(idx, stream, 100000, 1000) == NOMEM
+    assert lib.lsh_query(idx, stream, 100000, 1000, 0) == NOMEM
     lib.lsh_free(idx)
 
 
@@ -115,7 +118,7 @@ def test_tasks_of_a_bucket(lib):
 
 def test_join_of_a_query_past_the_launch(lib, stream):
     idx = lib.lsh_index(64, 1, 17, 4, 6, 1 << 20)
-    assert lib.lsh_query(idx, stream, 64, 1 << 27) == UNSUPPORTED
+    assert lib.lsh_query(idx, stream, 64, 1 << 27, 0) == UNSUPPORTED
     lib.lsh_free(idx)
 
 
@@ -133,8 +136,47 @@ def test_dense_levels_in_little_memory(lib, stream, capacity, pairs, draws):
     if draws:
         assert lib.lsh_sample(idx, stream, 4096, draws) == OK
     else:
-        assert lib.lsh_query(idx, stream, 4096, 0) == OK
+        assert lib.lsh_query(idx, stream, 4096, 0, 0) == OK
     assert (lib.launch_count(b"dense_pairs") > 0) == pairs
     assert lib.launch_count(b"dense_pairs") == lib.launch_count(b"dense_terms")
     assert lib.launch_count(b"probe_queries") > 0
     lib.lsh_free(idx)
+
+
+PEAK = 7
+
+
+@pytest.mark.parametrize("limit", [60 << 20, 200 << 20, 500 << 20])
+def test_dense_pairs_within_a_limit(lib, stream, limit):
+    idx = lib.lsh_index(200, 1, 17, 4, 6, 1 << 20)
+    lib.lsh_dense(idx, 300)
+    assert lib.lsh_pairs(idx, 100) == 128 * 38400 * 9 and lib.lsh_pairs(idx, 1 << 20) == 1 << 30
+    assert lib.lsh_query(idx, stream, 4096, 0, limit) == OK
+    assert lib.launch_count(b"dense_pairs") > 0
+    assert lib.mock_count(PEAK) <= limit + (2 * 64 << 20)  # and the blocks of the small buffers
+    lib.lsh_free(idx)
+
+
+@pytest.mark.parametrize("limit", [1 << 20, 100 << 20])
+def test_join_tasks_within_a_limit(lib, stream, limit):
+    idx = lib.lsh_index(64, 1, 17, 4, 6, 1 << 16)
+    assert lib.lsh_query(idx, stream, 4096, 1000, limit) == OK
+    assert covers(lib, 4096)
+    assert lib.mock_count(PEAK) <= limit + (2 * 64 << 20)
+    lib.lsh_free(idx)
+
+
+def test_pair_bytes_bound_the_tasks_of_a_join(lib):
+    rng = random.Random(3)
+    for _ in range(200):
+        m, members, buckets = rng.randint(1, 5000), rng.randint(1, 20000), rng.choice([1, 2, 10, 300])
+        nq, nm = [0] * buckets, [0] * buckets
+        for _ in range(m):
+            nq[min(rng.randrange(buckets), rng.randrange(buckets))] += 1
+        for _ in range(members):
+            nm[min(rng.randrange(buckets), rng.randrange(buckets))] += 1
+        idx = lib.lsh_index(64, 1, 1, 1, 6, 1 << 16)
+        lib.lsh_members(idx, members)
+        tasks = sum(lib.lsh_bucket_tasks(a, b) for a, b in zip(nq, nm))
+        assert tasks * 552 <= lib.lsh_pairs(idx, m)
+        lib.lsh_free(idx)
