@@ -25,8 +25,19 @@ __device__ inline int64_t sub_index(int64_t chunk, int k, int C, int c, int64_t 
   return ((chunk * kSubs + k) * C + c) * m_pad + qi;
 }
 constexpr int kWideWinQ = 8, kWideWinC = 8;
+// Launches of at most this many pairs (128 queries x chunk) that don't share
+// chunks (the exponential kernel, whose near pairs are kept per chunk, the
+// no-allocation call and the rescue's passes) take 32 queries a workgroup.
+// fp32 is bound by the matrix products of a compute unit's one workgroup:
+// 1,992 us with 128 queries and 727 with 32 at d = 784 and 64 pairs, 1,992 and
+// 1,309 at 128, 2,000 and 1,890 at 192, 1,997 and 2,470 at 224 (three quarters
+// of the last round of 256 compute units idle).  The split forms wait on memory
+// instead, where 128 queries share a row: 653 and 470 us at 64 pairs, 652 and
+// 739 at 80.
+template <int FORM>
+constexpr int64_t kWideNarrowPairs = FORM == STAG_FORM_FP32 ? 192 : 64;
 
-// Workgroup b -> (128-query tile, chunk).  Workgroups are dealt to the 8 XCDs
+// Workgroup b -> (query tile, chunk).  Workgroups are dealt to the 8 XCDs
 // in turn; XCD x takes the x-th eighth of the list of all pairs, ordered by
 // windows of 8 query tiles x 8 chunks, so that the 64 workgroups an XCD runs
 // together read 8 chunks' rows and 8 tiles' queries instead of 64 different
@@ -46,77 +57,107 @@ __device__ inline bool wide_tile(int64_t b, int nq, int P, int* qtile, int* chun
   return true;
 }
 
-// Row tile i (0 .. 3) of wave half wr among the 8 of a step: 0, 1, 4, 5 or 2, 3, 6, 7.
-__device__ inline int wide_row_tile(int wr, int i) { return (i & 1) + 2 * wr + 4 * (i >> 1); }
-
 template <int FORM>
 constexpr int kWideParts = FORM == STAG_FORM_FP32 ? 1 : 2;
+// k-steps (fragments) loaded at a time
+template <int FORM, int QT>
+constexpr int kWideK = QT == 1 ? (FORM == STAG_FORM_FP32 ? 4 : 2) : 1;
 
-// A workgroup takes one (128 queries, 4096-row chunk) pair (or a share of
-// it: ex.nsub workgroups per pair, each storing its sub-chunks' sums, which
-// combine_subs adds in the same order), 256 data rows at a time: the four waves split the 8 x 4
-// blocks of 32 rows x 32 queries as 2 x 2, 4 row tiles x 2 query blocks (128
-// accumulators) each.  Wave half wr takes the tiles t with (t / 2) % 2 = wr.
-// Per k-step the 8 row and 4 query fragments (per part) go through registers
-// to LDS, loaded from memory two steps ahead of their use (two buffers, one
-// barrier per step); a wave reads 12 fragments for its 24 products (split).
-// Products of one block come in ascending k with the parts in a fixed order on
-// one accumulator, so a result has the same bits as with any other tiling.
+// A workgroup takes QT blocks of 32 queries against a 4096-row chunk, 256 data
+// rows at a time, which its four waves split by row tile and query block:
+//   QT = 4 (128 queries; or a share of the chunk: ex.nsub workgroups per pair,
+//     each storing its sub-chunks' sums, which combine_subs adds in the same
+//     order): the 8 x 4 blocks of 32 rows x 32 queries as 2 x 2, 4 row tiles x
+//     2 query blocks (128 accumulators) each; wave half wr takes the tiles t
+//     with (t / 2) % 2 = wr.
+//   QT = 1 (32 queries): wave w takes the tiles t with t % 4 = w.  For
+//     launches whose 128-query pairs leave compute units idle and that can't
+//     share a chunk (see kWideNarrowPairs): four times as many workgroups with
+//     a quarter of the products each.
+// Per step the 8 row and QT query fragments (per part and k-step) go through
+// registers to LDS, loaded from memory two steps ahead of their use (two
+// buffers, one barrier per step); with QT = 4 a wave reads 12 fragments for its
+// 24 products (split).  With QT = 1 a step takes several k-steps (kWideK), as
+// its products no longer cover the loads: 8 queries against 70,000 rows of 784
+// in the fp16 split form took 892 us a call with one k-step at a time, 495 with
+// two (fp32 1,115 and 929 with four).  Products of one block come in ascending
+// k with the parts in a fixed order on one accumulator, so a result has the
+// same bits as with any other tiling.
 // Measured at n = 70,000, d = 784: against 10,000 queries in the fp16 split
 // form 7.8 -> 2.3 ms (1.29 PFLOP/s of products; library GEMMs reach 1.25 here),
 // against itself 55 -> 17.5 ms, in fp32 88 -> 66 ms (the tile before this one
 // kept 32 queries per workgroup in LDS and streamed every row from the
 // last-level cache for them: 0.5 TB a call).
-// Sums: per lane fp64 over the tiles of a sub-chunk in order, the sub-chunks
-// in order, then lane halves, then the two waves of a query block.
+// Sums: per lane fp64 over the tiles of a sub-chunk of a class t % 4 in order,
+// classes 0 + 1 and 2 + 3, the sub-chunks in order, then lane halves, then the
+// two pairs of classes.
 // Near pairs (exponential kernel): the first kNearSlots tiles that hold some
-// are taken of each class t % 4 (two classes per wave) and lane.
-template <int FORM, int MODE>
+// are taken of each class and lane.
+template <int FORM, int MODE, int QT>
 __global__ __launch_bounds__(256, 2) void tile_wide(const char* __restrict__ X0, const char* __restrict__ X1,
                                                     const float* __restrict__ Xoff, const char* __restrict__ Q0,
                                                     const char* __restrict__ Q1, const float* __restrict__ Qoff,
                                                     int nfrag, int ns, int64_t n_pad, int n_qtiles, int P,
                                                     int64_t m_pad, double* __restrict__ partial, TileExtra ex) {
+  static_assert(QT == 1 || QT == kWideQT, "32 or 128 queries");
   constexpr int NP = kWideParts<FORM>;
-  constexpr int NF = (kWideRT + kWideQT) * NP;  // fragments per step
+  constexpr int NF = (kWideRT + QT) * NP;  // fragments per k-step
+  constexpr int NK = kWideK<FORM, QT>;
+  constexpr int NR = QT == 1 ? 2 : 4;      // row tiles of a wave and step
+  constexpr int NB = QT == 1 ? 1 : 2;      // query blocks of a wave
+  constexpr int NC = QT == 1 ? 1 : 2;      // tile classes of a wave: that of row tile i is i % NC
   constexpr bool NEAR = MODE == kModeExponential;
-  __shared__ __attribute__((aligned(16))) char frag[2][NF * 1024];
-  __shared__ double wsum[2][4][32];
-  __shared__ uint32_t near_lds[NEAR ? 4 * kNearSlots * 256 : 1];
-  __shared__ double total[2][256];
+  __shared__ __attribute__((aligned(16))) char frag[2][NK * NF * 1024];
+  __shared__ double wsum[2][QT][32];
+  __shared__ uint32_t near_lds[NEAR ? NB * NC * kNearSlots * 256 : 1];
+  // QT = 4: the sums so far of a lane's query blocks; 1: those of each sub-chunk
+  constexpr int NT = QT == 1 ? kSubs : NB;
+  __shared__ double total[NT][256];
   const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wr = wave >> 1, wq = wave & 1;
+  const int wr = QT == 1 ? wave : wave >> 1, wq = QT == 1 ? 0 : wave & 1;
+  // row tile i of this wave among the 8 of a step
+  auto row_tile = [&](int i) { return QT == 1 ? wr + 4 * i : (i & 1) + 2 * wr + 4 * (i >> 1); };
   int qtile, chunk;
   // shares of a chunk are neighbours in the order of the list
   if (!wide_tile(blockIdx.x, n_qtiles, P * ex.nsub, &qtile, &chunk)) return;
   const int part = chunk % ex.nsub;
   chunk /= ex.nsub;
-  if (ex.qtile_active && ex.qtile_active[qtile] == 0) return;  // whole block
+  if (ex.qtile_active && ex.qtile_active[qtile * QT / kWideQT] == 0) return;  // whole block
   const int nrun = kSubs / ex.nsub;  // sub-chunks of this workgroup
   const int64_t row0 = (int64_t)chunk * kChunkRows + (int64_t)part * nrun * kSubTiles * kTileRows;
   const int ntiles = (int)max((int64_t)0, min((n_pad - row0) / kTileRows, (int64_t)nrun * kSubTiles));
   const int nblk = (ntiles + kWideRT - 1) / kWideRT;
   const int64_t tile0 = row0 / kTileRows;
-  int64_t col[2], qi[2];
-  float alpha[2], ys[2];
+  int64_t col[NB], qi[NB];
+  float alpha[NB], ys[NB];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    col[j] = (int64_t)qtile * kBQ + (2 * wq + j) * 32;
+  for (int j = 0; j < NB; ++j) {
+    col[j] = ((int64_t)qtile * QT + NB * wq + j) * 32;
     qi[j] = col[j] + r32;
     alpha[j] = Qoff[qi[j]];
     ys[j] = kShiftMode<MODE> ? ex.yshift[qi[j]] : 0.0f;
   }
 
-  double acc[2] = {acc_init<MODE>(), acc_init<MODE>()};
+  double acc[NB][NC];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) total[j][tid] = acc[j];
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[j][c] = acc_init<MODE>();
+#pragma unroll
+  for (int j = 0; j < NT; ++j) total[j][tid] = acc_init<MODE>();
   auto end_run = [&](int k) {  // end of this workgroup's sub-chunk k
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (ex.nsub > 1) ex.sub[sub_index(chunk, part * nrun + k, 4, 2 * wr + h, m_pad, qi[j])] = acc[j];
-      else total[j][tid] = acc_add<MODE>(total[j][tid], acc[j]);
-      acc[j] = acc_init<MODE>();
+    for (int j = 0; j < NB; ++j) {
+      if constexpr (QT == 1) {
+        total[k][tid] = acc[0][0];
+      } else {
+        const double a = acc_add<MODE>(acc[j][0], acc[j][NC - 1]);
+        if (ex.nsub > 1) ex.sub[sub_index(chunk, part * nrun + k, 4, 2 * wr + h, m_pad, qi[j])] = a;
+        else total[j][tid] = acc_add<MODE>(total[j][tid], a);
+      }
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[j][c] = acc_init<MODE>();
     }
   };
   if (ntiles == 0) {  // a share past the last row (nsub > 1)
@@ -124,49 +165,58 @@ __global__ __launch_bounds__(256, 2) void tile_wide(const char* __restrict__ X0,
     return;
   }
 
-  // This wave's fragments of a step: row tiles 2 wave and 2 wave + 1 and query
-  // tile wave, every part (scalar addresses; past the chunk's last tile the
-  // last one is read again and its results left out).
+  // This wave's fragments of a step: row tiles 2 wave and 2 wave + 1 and, if
+  // there is one, query block wave, every part (scalar addresses; past the
+  // chunk's last tile the last one is read again and its results left out).
   constexpr int WA = kWideRT / 4;
   const int64_t tbytes = (int64_t)nfrag * 1024;
-  f32x4 sa[NP][WA], sb[NP];
+  f32x4 sa[NK][NP][WA], sb[NK][NP];
   auto gload = [&](int b, int s) {
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
+    for (int u = 0; u < NK; ++u) {
 #pragma unroll
-      for (int k = 0; k < WA; ++k) {
-        const int64_t t = tile0 + min(b * kWideRT + WA * wave + k, ntiles - 1);
-        const char* src = (p == 0 ? X0 : X1) + (t * tbytes + s * 1024);
-        sa[p][k] = *reinterpret_cast<const f32x4*>(src + lane * 16);
+      for (int p = 0; p < NP; ++p) {
+#pragma unroll
+        for (int k = 0; k < WA; ++k) {
+          const int64_t t = tile0 + min(b * kWideRT + WA * wave + k, ntiles - 1);
+          const char* src = (p == 0 ? X0 : X1) + (t * tbytes + (s + u) * 1024);
+          sa[u][p][k] = *reinterpret_cast<const f32x4*>(src + lane * 16);
+        }
+        if (QT == kWideQT || wave < QT) {
+          const char* src = (p == 0 ? Q0 : Q1) + (((int64_t)qtile * QT + wave) * tbytes + (s + u) * 1024);
+          sb[u][p] = *reinterpret_cast<const f32x4*>(src + lane * 16);
+        }
       }
-      const char* src = (p == 0 ? Q0 : Q1) + (((int64_t)qtile * kWideQT + wave) * tbytes + s * 1024);
-      sb[p] = *reinterpret_cast<const f32x4*>(src + lane * 16);
     }
   };
   auto lstore = [&](int buf) {
     char* dst = &frag[buf][lane * 16];
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
+    for (int u = 0; u < NK; ++u) {
 #pragma unroll
-      for (int k = 0; k < WA; ++k)
-        *reinterpret_cast<f32x4*>(dst + (p * kWideRT + WA * wave + k) * 1024) = sa[p][k];
-      *reinterpret_cast<f32x4*>(dst + (NP * kWideRT + p * kWideQT + wave) * 1024) = sb[p];
+      for (int p = 0; p < NP; ++p) {
+#pragma unroll
+        for (int k = 0; k < WA; ++k)
+          *reinterpret_cast<f32x4*>(dst + (u * NF + p * kWideRT + WA * wave + k) * 1024) = sa[u][p][k];
+        if (QT == kWideQT || wave < QT)
+          *reinterpret_cast<f32x4*>(dst + (u * NF + NP * kWideRT + p * QT + wave) * 1024) = sb[u][p];
+      }
     }
   };
 
-  NearRec nr[2][2];  // [query block][tile class]
+  NearRec nr[NB][NC];  // [query block][tile class]
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int j = 0; j < NB; ++j)
 #pragma unroll
-    for (int k = 0; k < 2; ++k) nr[j][k] = {near_lds + (NEAR ? (2 * j + k) * kNearSlots * 256 : 0), 0, false};
+    for (int k = 0; k < NC; ++k) nr[j][k] = {near_lds + (NEAR ? (NC * j + k) * kNearSlots * 256 : 0), 0, false};
   // the next step to load: (block lb, k-step ls); past the last one it is
   // loaded again
   int lb = 0, ls = 0;
   auto advance = [&]() {
     gload(lb, ls);
-    const bool wrap = ls + 1 == ns;
+    const bool wrap = ls + NK == ns;
     const bool end = wrap && lb + 1 == nblk;
-    ls = end ? ls : (wrap ? 0 : ls + 1);
+    ls = end ? ls : (wrap ? 0 : ls + NK);
     lb = wrap && !end ? lb + 1 : lb;
   };
   advance();
@@ -174,77 +224,88 @@ __global__ __launch_bounds__(256, 2) void tile_wide(const char* __restrict__ X0,
   advance();
   int buf = 0;
   for (int b = 0; b < nblk; ++b) {
-    f32x16 c[4][2];
+    f32x16 c[NR][NB];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < NR; ++i) {
       if constexpr (FORM == STAG_FORM_FP32) {
-        c[i][0] = f32x16{0};
-        c[i][1] = f32x16{0};
+#pragma unroll
+        for (int j = 0; j < NB; ++j) c[i][j] = f32x16{0};
       } else {
         // the accumulators start from the offsets alpha_q + beta_x
-        const int64_t rb = row0 + (int64_t)min(b * kWideRT + wide_row_tile(wr, i), ntiles - 1) * kTileRows;
+        const int64_t rb = row0 + (int64_t)min(b * kWideRT + row_tile(i), ntiles - 1) * kTileRows;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const f32x4 bv = *reinterpret_cast<const f32x4*>(Xoff + rb + 8 * g + 4 * h);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            c[i][0][4 * g + e] = alpha[0] + bv[e];
-            c[i][1][4 * g + e] = alpha[1] + bv[e];
-          }
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) c[i][j][4 * g + e] = alpha[j] + bv[e];
         }
       }
     }
-    for (int s = 0; s < ns; ++s) {
-      __syncthreads();  // this step's fragments are in buf; the other buffer is free
-      f32x4 fa[NP][4], fb[NP][2];
-      const char* fl = &frag[buf][lane * 16];
+    for (int s = 0; s < ns; s += NK) {
+      __syncthreads();  // these steps' fragments are in buf; the other buffer is free
+      f32x4 fa[NP][NR], fb[NP][NB];
+      auto fetch = [&](int u) {
+        const char* fl = &frag[buf][u * NF * 1024 + lane * 16];
 #pragma unroll
-      for (int p = 0; p < NP; ++p) {
+        for (int p = 0; p < NP; ++p) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-          fb[p][j] = *reinterpret_cast<const f32x4*>(fl + (kWideRT * NP + p * kWideQT + 2 * wq + j) * 1024);
+          for (int j = 0; j < NB; ++j)
+            fb[p][j] = *reinterpret_cast<const f32x4*>(fl + (kWideRT * NP + p * QT + NB * wq + j) * 1024);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          fa[p][i] = *reinterpret_cast<const f32x4*>(fl + (p * kWideRT + wide_row_tile(wr, i)) * 1024);
-      }
-      lstore(buf ^ 1);  // the next step's (after the last step: a copy nobody reads)
+          for (int i = 0; i < NR; ++i)
+            fa[p][i] = *reinterpret_cast<const f32x4*>(fl + (p * kWideRT + row_tile(i)) * 1024);
+        }
+      };
+      auto products = [&] {
+        if constexpr (FORM == STAG_FORM_FP32) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < NR; ++i)
+#pragma unroll
+              for (int j = 0; j < NB; ++j)
+                c[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[0][i][e], fb[0][j][e], c[i][j], 0, 0, 0);
+        } else {
+          // per block: hi hi, hi lo, lo hi
+#pragma unroll
+          for (int o = 0; o < 3; ++o)
+#pragma unroll
+            for (int i = 0; i < NR; ++i)
+#pragma unroll
+              for (int j = 0; j < NB; ++j)
+                c[i][j] = mma16<FORM>(__builtin_bit_cast(u16x8, fa[o == 2 ? NP - 1 : 0][i]),
+                                      __builtin_bit_cast(u16x8, fb[o == 1 ? NP - 1 : 0][j]), c[i][j]);
+        }
+      };
+      fetch(0);
+      lstore(buf ^ 1);  // the next steps' (after the last: a copy nobody reads)
       advance();
-      if constexpr (FORM == STAG_FORM_FP32) {
+      products();
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-              c[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[0][i][e], fb[0][j][e], c[i][j], 0, 0, 0);
-      } else {
-        // per block: hi hi, hi lo, lo hi
-#pragma unroll
-        for (int o = 0; o < 3; ++o)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-              c[i][j] = mma16<FORM>(__builtin_bit_cast(u16x8, fa[o == 2 ? NP - 1 : 0][i]),
-                                    __builtin_bit_cast(u16x8, fb[o == 1 ? NP - 1 : 0][j]), c[i][j]);
+      for (int u = 1; u < NK; ++u) {
+        fetch(u);
+        products();
       }
       buf ^= 1;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int t = b * kWideRT + wide_row_tile(wr, i);
+    for (int i = 0; i < NR; ++i) {
+      const int t = b * kWideRT + row_tile(i);
       if (t < ntiles) {  // wave-uniform
         const int64_t rb = row0 + (int64_t)t * kTileRows;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < NB; ++j) {
           if constexpr (FORM == STAG_FORM_FP32) {
             // offsets by one more product: 1 * alpha (half 0) + beta * 1 (half 1)
             const float tb = Xoff[rb + r32];
             c[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(h == 0 ? 1.0f : tb, h == 0 ? alpha[j] : 1.0f, c[i][j], 0,
                                                            0, 0);
           }
-          acc[j] = acc_add<MODE>(acc[j], (double)tile_epilogue<MODE>(c[i][j], rb, col[j], r32, h, qi[j], ex, nullptr,
-                                                                     false, &nr[j][i & 1], t, ys[j]));
+          double& a = acc[j][i % NC];
+          a = acc_add<MODE>(a, (double)tile_epilogue<MODE>(c[i][j], rb, col[j], r32, h, qi[j], ex, nullptr, false,
+                                                           &nr[j][i % NC], t, ys[j]));
         }
       }
     }
@@ -255,19 +316,37 @@ __global__ __launch_bounds__(256, 2) void tile_wide(const char* __restrict__ X0,
     for (int k = (nblk + kWideRuns - 1) / kWideRuns; k < nrun; ++k) end_run(k);  // runs past the last row
     return;
   }
+  if constexpr (QT == 1) {
+    __shared__ double near_sum[NEAR ? 256 : 1];
+    if constexpr (NEAR) near_sum[tid] = near_finish(ex, nr[0][0], qi[0], h, row0, tid);
+    __syncthreads();
+    if (wave < 2) {  // wave w adds up the classes 2 w and 2 w + 1
+      const int c0 = 128 * wave + lane, c1 = c0 + 64;
+      double a = acc_init<MODE>();
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    double a = total[j][tid];
-    if constexpr (NEAR) {
-      a += near_finish(ex, nr[j][0], qi[j], h, row0, tid);
-      a += near_finish(ex, nr[j][1], qi[j], h, row0, tid);
+      for (int k = 0; k < kSubs; ++k) a = acc_add<MODE>(a, acc_add<MODE>(total[k][c0], total[k][c1]));
+      if constexpr (NEAR) {
+        a += near_sum[c0];
+        a += near_sum[c1];
+      }
+      const double other = __shfl_down(a, 32);
+      if (h == 0) wsum[wave][0][r32] = acc_add<MODE>(a, other);
     }
-    const double other = __shfl_down(a, 32);
-    if (h == 0) wsum[wr][2 * wq + j][r32] = acc_add<MODE>(a, other);
+  } else {
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      double a = total[j][tid];
+      if constexpr (NEAR) {
+        a += near_finish(ex, nr[j][0], qi[j], h, row0, tid);
+        a += near_finish(ex, nr[j][NC - 1], qi[j], h, row0, tid);
+      }
+      const double other = __shfl_down(a, 32);
+      if (h == 0) wsum[wr][2 * wq + j][r32] = acc_add<MODE>(a, other);
+    }
   }
   __syncthreads();
-  if (tid < kBQ)
-    partial[(int64_t)chunk * m_pad + (int64_t)qtile * kBQ + tid] =
+  if (tid < 32 * QT)
+    partial[(int64_t)chunk * m_pad + (int64_t)qtile * 32 * QT + tid] =
         acc_add<MODE>(wsum[0][tid >> 5][tid & 31], wsum[1][tid >> 5][tid & 31]);
 }
 

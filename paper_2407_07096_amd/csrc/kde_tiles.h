@@ -1610,20 +1610,26 @@ stag_status dispatch_h1c(const Operands& xo, const Operands& qo, float la, int P
 template <int FORM, int MODE>
 stag_status launch_tile_wide(const Operands& xo, const Operands& qo, int P, double* partial, const TileExtra& ex,
                              hipStream_t st) {
-  const int n_qtiles = (int)(qo.rows_pad / kBQ);
   // fragments of a tile, and those that hold dimensions below d (the split
   // forms' padding fragments are zero on both sides and are left out)
   const int nfrag = xo.dp / (FORM == STAG_FORM_FP32 ? 8 : 16);
-  const int ns = FORM == STAG_FORM_FP32 ? nfrag : (int)ceil_div(xo.d, 16);
+  const int used = FORM == STAG_FORM_FP32 ? nfrag : (int)ceil_div(xo.d, 16);
   ScopedTimer tm(rescue_timer(ex, FORM == STAG_FORM_FP32         ? "kde_tile_f32_wide"
                                   : FORM == STAG_FORM_FP16_SPLIT ? "kde_tile_fp16x3_wide"
                                                                  : "kde_tile_bf16x3_wide"),
                  st);
-  const int64_t grid = 8 * ceil_div((int64_t)n_qtiles * P * ex.nsub, 8);
-  hipLaunchKernelGGL((tile_wide<FORM, MODE>), dim3((unsigned)grid), dim3(256), 0, st, (const char*)xo.part[0],
-                     (const char*)xo.part[1], xo.off, (const char*)qo.part[0], (const char*)qo.part[1], qo.off, nfrag,
-                     ns, xo.rows_pad, n_qtiles, P, qo.rows_pad, partial, ex);
-  return check_launch("tile_wide");
+  auto launch = [&](auto kern, int qt, int ns) {
+    const int n_qtiles = (int)(qo.rows_pad / (32 * qt));
+    const int64_t grid = 8 * ceil_div((int64_t)n_qtiles * P * ex.nsub, 8);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), 0, st, (const char*)xo.part[0], (const char*)xo.part[1],
+                       xo.off, (const char*)qo.part[0], (const char*)qo.part[1], qo.off, nfrag, ns, xo.rows_pad,
+                       n_qtiles, P, qo.rows_pad, partial, ex);
+    return check_launch("tile_wide");
+  };
+  const int64_t pairs = qo.rows_pad / kBQ * P;
+  if (ex.nsub == 1 && pairs <= kWideNarrowPairs<FORM>)
+    return launch(tile_wide<FORM, MODE, 1>, 1, (int)round_up(used, kWideK<FORM, 1>));
+  return launch(tile_wide<FORM, MODE, kWideQT>, kWideQT, used);
 }
 
 // All tiles of one launch in epilogue mode MODE: wide fp32 rows, the fp32
