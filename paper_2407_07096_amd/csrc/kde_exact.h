@@ -244,17 +244,19 @@ int64_t query_tile_rows();
 // Sets ex->nsub and allocates the records of a Gaussian or logistic launch
 // whose pairs of a 128-query tile and a chunk alone would leave compute units
 // idle: below kFewPairs pairs, the smallest power of two up to 8 that gives
-// kSplitGrid workgroups (2 per compute unit; 37 queries against
-// 300,000 rows at d = 64, 74 pairs: 232 us a call, 155 with the shares, 84 with the
-// operands prepared by vector loads).  Wide rows, whose
-// workgroups are long and whose records are small, share up to
-// kFewPairsWide pairs, so that the last round of workgroups is short as well
-// (10,000 queries against 70,000
-// rows at d = 784, 1,422 pairs: 3.95 ms whole, 3.72 ms in halves, measured on
-// an earlier form of the wide tile).  One workgroup per pair otherwise, with a workspace
-// that is not the pool (the no-allocation call's need is part of its
-// interface), and for the exponential kernel, whose near pairs are kept per
-// chunk.
+// kSplitGrid workgroups (2 per compute unit; 37 queries against 300,000 rows at
+// d = 64, 74 pairs: 232 us a call, 155 with the shares, 84 with the operands
+// prepared by vector loads).  Wide rows, whose workgroups are long and whose
+// records are small, share in eighths up to kFewPairsWide pairs, so that the
+// last round of workgroups is short as well.  Unshared against eighths, in ms,
+// fp16 split and fp32, at d = 784 and 18 chunks: 0.67 and 0.35, 2.03 and 1.03
+// at 126 pairs, 1.04 and 0.98, 3.60 and 3.57 at 504, 2.21 and 1.78, 8.69 and
+// 7.17 at 1,026, 2.57 and 2.36, 10.4 and 9.72 at 1,422 (in halves 2.55 and
+// 10.3), 3.37 and 3.26, 13.8 and 13.5 at 1,998; at 2,988, 4.98 and 4.71, 20.5 and
+// 20.1 (d = 300: 2.00 and 2.00, 7.99 and 7.90), hardly worth the records.  One
+// workgroup per pair otherwise, with a workspace that is not the pool (the
+// no-allocation call's need is part of its interface), and for the exponential
+// kernel, whose near pairs are kept per chunk.
 constexpr int64_t kFewPairs = 128, kSplitGrid = 512, kFewPairsWide = 2048;
 stag_status alloc_parts(const Operands& xo, const Operands& qo, int kernel, Workspace& ws, TileExtra* ex);
 stag_status launch_exact_tiles(const Operands& xo, const Operands& qo, double* partial, const TileExtra& ex,

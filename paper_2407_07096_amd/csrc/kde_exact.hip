@@ -750,8 +750,8 @@ stag_status alloc_parts(const Operands& xo, const Operands& qo, int kernel, Work
   const int64_t P = exact_chunks(xo.rows_pad), pairs = P * (qo.rows_pad / kBQ);
   const bool wide = xo.dp > 256;
   if (pairs >= (wide ? kFewPairsWide : kFewPairs)) return STAG_OK;
-  int nsub = 2;
-  while (nsub < 8 && pairs * nsub < (wide ? kFewPairsWide : kSplitGrid)) nsub *= 2;
+  int nsub = wide ? kSubs : 2;
+  while (nsub < kSubs && pairs * nsub < kSplitGrid) nsub *= 2;
   if (wide) {
     STAG_TRY(ws.alloc(&ex->sub, (size_t)P * kSubs * 4 * qo.rows_pad));
   } else {

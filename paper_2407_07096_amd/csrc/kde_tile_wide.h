@@ -83,11 +83,10 @@ constexpr int kWideK = QT == 1 ? (FORM == STAG_FORM_FP32 ? 4 : 2) : 1;
 // two (fp32 1,115 and 929 with four).  Products of one block come in ascending
 // k with the parts in a fixed order on one accumulator, so a result has the
 // same bits as with any other tiling.
-// Measured at n = 70,000, d = 784: against 10,000 queries in the fp16 split
-// form 7.8 -> 2.3 ms (1.29 PFLOP/s of products; library GEMMs reach 1.25 here),
-// against itself 55 -> 17.5 ms, in fp32 88 -> 66 ms (the tile before this one
-// kept 32 queries per workgroup in LDS and streamed every row from the
-// last-level cache for them: 0.5 TB a call).
+// Measured at n = 70,000, d = 784 (a whole call): against 10,000 queries in the
+// fp16 split form 8.2 -> 2.3 ms, in fp32 9.7 (the tile before this one kept 32
+// queries per workgroup in LDS and streamed every row from the last-level cache
+// for them: 0.5 TB a call).
 // Sums: per lane fp64 over the tiles of a sub-chunk of a class t % 4 in order,
 // classes 0 + 1 and 2 + 3, the sub-chunks in order, then lane halves, then the
 // two pairs of classes.
