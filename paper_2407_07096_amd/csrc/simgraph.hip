@@ -30,12 +30,18 @@ namespace {
 
 constexpr uint64_t kGammaS = 0x9E3779B97F4A7C15ULL;
 constexpr uint64_t kTagDrawS = 0x44524157ULL;
-// Rows up to this width draw in one fused kernel, wider ones through the
-// tile sort.  Measured at n = 100,000, 17 draws per node, fused against sorted:
-// 1.78 against 1.80 ms at d = 64, 7.5 against 3.0 at d = 256, 15.8 against 5.1
-// at d = 512 and, on sparse rows at n = 70,000, 22.6 against 5.0 at d = 784
-// (the tiles of narrow rows stay in cache in any order).
+// Rows up to this width, and data of up to so many bytes (an XCD's L2 holds 4
+// MB), draw in one fused kernel, others (and all above 256 wide) through the
+// tile sort: the tiles of narrow rows and small data stay in cache in any order.
+// Measured by call, fused against sorted, 17 draws per node at n = 100,000: 4.72
+// against 4.95 ms at d = 48, 5.29 and 5.24 at 64, 7.68 and 6.97 at 65, 10.1 and
+// 8.66 at 128, 15.8 and 12.8 at 192; in us at other sizes, 146 and 181 at 5,000 x
+// 128 (2.6 MB), 583 and 628 at 20,000 x 80 (6.4 MB), 269 and 282 at 8,000 x 192
+// (6.1 MB), 759 and 710 at 20,000 x 100 (8.0 MB), 358 and 329 at 8,000 x 256
+// (8.2 MB), 486 and 505 at 16,000 x 128 (8.2 MB), 856 and 831 at 26,000 x 80 (8.3
+// MB), 546 and 507 at 12,000 x 192 (9.2 MB).
 constexpr int kDrawFusedMaxDim = 64;
+constexpr int64_t kDrawFusedMaxBytes = (int64_t)7 << 20;
 constexpr int kChunkTiles = 128;  // 32-row tiles per 4096-row chunk
 constexpr double kLog2eS = 1.4426950408889634074;
 
@@ -368,7 +374,8 @@ stag_status sample_exact(const float* X, int64_t n, int d, double a, int form, i
   // the sort carries draw indices in 32 bits (the n x n/32 tile sums above
   // bound n far below this in practice)
   const bool sortable = nd < ((int64_t)1 << 31);
-  if (d <= kDrawFusedMaxDim || (d <= 256 && !sortable)) {
+  const bool cached = n * d * (int64_t)sizeof(float) <= kDrawFusedMaxBytes;
+  if (d <= kDrawFusedMaxDim || (d <= 256 && (cached || !sortable))) {
     hipLaunchKernelGGL(by_rows(draw_exact<kOwnRow>, draw_exact<kQuad4>, draw_exact<kQuad>),
                        dim3((unsigned)ceil_div(nd, 8)), dim3(256), 0, st, X, n, d, a, s, seed, P, ntile, tstride,
                        chunk_t, tp, rest, rest_draw, shift, src, dst, w);
