@@ -78,7 +78,9 @@ inline DivBy div_by(uint32_t s) {
   while ((1ull << l) < s) ++l;
   return {s, (uint32_t)(((1ull << (31 + l)) + s - 1) / s), 31 + l};
 }
-__device__ inline uint32_t quotient(uint32_t e, const DivBy& q) { return (uint32_t)(((uint64_t)e * q.m) >> q.shift); }
+__host__ __device__ inline uint32_t quotient(uint32_t e, const DivBy& q) {
+  return (uint32_t)(((uint64_t)e * q.m) >> q.shift);
+}
 
 // Sum over each group of LANES lanes (fixed butterfly).
 template <int LANES>
