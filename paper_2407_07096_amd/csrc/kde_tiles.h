@@ -1476,7 +1476,7 @@ stag_status launch_tile_f32(const float* Xp, const float* beta, const float* Qs,
 }
 
 template <int FORM, int DP, int MODE>
-stag_status launch_tile_split(void* const* xp, const float* xaug, void* const* qp, const float* qaug, int64_t n_pad,
+stag_status launch_tile_split(void* const* xp, const float* xoff, void* const* qp, const float* qoff, int64_t n_pad,
                               int n_qtiles, int64_t m_pad, int P, double* partial, const TileExtra& ex,
                               hipStream_t st) {
   using U = const unsigned short*;
@@ -1485,7 +1485,7 @@ stag_status launch_tile_split(void* const* xp, const float* xaug, void* const* q
     ScopedTimer tm(FORM == STAG_FORM_FP16_SPLIT ? "kde_tile_fp16x3" : "kde_tile_bf16x3", st);
     const int n_qt256 = (int)ceil_div(m_pad, 256);
     hipLaunchKernelGGL((tile_split_w64<FORM, DP, MODE>), dim3((unsigned)((int64_t)n_qt256 * P)), dim3(256), 0, st,
-                       (U)xp[0], (U)xp[1], xaug, (U)qp[0], (U)qp[1], qaug, n_pad, n_qt256, m_pad, partial, ex);
+                       (U)xp[0], (U)xp[1], xoff, (U)qp[0], (U)qp[1], qoff, n_pad, n_qt256, m_pad, partial, ex);
     (void)n_qtiles;
     return check_launch("tile_split_w64");
   }
@@ -1494,25 +1494,25 @@ stag_status launch_tile_split(void* const* xp, const float* xaug, void* const* q
                                      : (FORM == STAG_FORM_BF16_SPLIT ? "kde_tile_bf16x3" : "kde_tile_bf16x6")),
                  st);
   hipLaunchKernelGGL((tile_split<FORM, DP, MODE>), dim3((unsigned)((int64_t)n_qtiles * P * ex.nsub)), dim3(256), 0, st,
-                     (U)xp[0], (U)xp[1], (U)xp[2], xaug, (U)qp[0], (U)qp[1], (U)qp[2], qaug, n_pad, n_qtiles, m_pad,
+                     (U)xp[0], (U)xp[1], (U)xp[2], xoff, (U)qp[0], (U)qp[1], (U)qp[2], qoff, n_pad, n_qtiles, m_pad,
                      partial, ex);
   return check_launch("tile_split");
 }
 
 template <int FORM, int MODE>
-stag_status dispatch_split(int dp, void* const* xp, const float* xaug, void* const* qp, const float* qaug,
+stag_status dispatch_split(int dp, void* const* xp, const float* xoff, void* const* qp, const float* qoff,
                            int64_t n_pad, int n_qtiles, int64_t m_pad, int P, double* partial, const TileExtra& ex,
                            hipStream_t st) {
   switch (dp) {
-    case 16: return launch_tile_split<FORM, 16, MODE>(xp, xaug, qp, qaug, n_pad, n_qtiles, m_pad, P, partial, ex, st);
-    case 32: return launch_tile_split<FORM, 32, MODE>(xp, xaug, qp, qaug, n_pad, n_qtiles, m_pad, P, partial, ex, st);
-    case 64: return launch_tile_split<FORM, 64, MODE>(xp, xaug, qp, qaug, n_pad, n_qtiles, m_pad, P, partial, ex, st);
-    case 96: return launch_tile_split<FORM, 96, MODE>(xp, xaug, qp, qaug, n_pad, n_qtiles, m_pad, P, partial, ex, st);
-    case 128: return launch_tile_split<FORM, 128, MODE>(xp, xaug, qp, qaug, n_pad, n_qtiles, m_pad, P, partial, ex, st);
-    case 160: return launch_tile_split<FORM, 160, MODE>(xp, xaug, qp, qaug, n_pad, n_qtiles, m_pad, P, partial, ex, st);
-    case 192: return launch_tile_split<FORM, 192, MODE>(xp, xaug, qp, qaug, n_pad, n_qtiles, m_pad, P, partial, ex, st);
-    case 224: return launch_tile_split<FORM, 224, MODE>(xp, xaug, qp, qaug, n_pad, n_qtiles, m_pad, P, partial, ex, st);
-    case 256: return launch_tile_split<FORM, 256, MODE>(xp, xaug, qp, qaug, n_pad, n_qtiles, m_pad, P, partial, ex, st);
+    case 16: return launch_tile_split<FORM, 16, MODE>(xp, xoff, qp, qoff, n_pad, n_qtiles, m_pad, P, partial, ex, st);
+    case 32: return launch_tile_split<FORM, 32, MODE>(xp, xoff, qp, qoff, n_pad, n_qtiles, m_pad, P, partial, ex, st);
+    case 64: return launch_tile_split<FORM, 64, MODE>(xp, xoff, qp, qoff, n_pad, n_qtiles, m_pad, P, partial, ex, st);
+    case 96: return launch_tile_split<FORM, 96, MODE>(xp, xoff, qp, qoff, n_pad, n_qtiles, m_pad, P, partial, ex, st);
+    case 128: return launch_tile_split<FORM, 128, MODE>(xp, xoff, qp, qoff, n_pad, n_qtiles, m_pad, P, partial, ex, st);
+    case 160: return launch_tile_split<FORM, 160, MODE>(xp, xoff, qp, qoff, n_pad, n_qtiles, m_pad, P, partial, ex, st);
+    case 192: return launch_tile_split<FORM, 192, MODE>(xp, xoff, qp, qoff, n_pad, n_qtiles, m_pad, P, partial, ex, st);
+    case 224: return launch_tile_split<FORM, 224, MODE>(xp, xoff, qp, qoff, n_pad, n_qtiles, m_pad, P, partial, ex, st);
+    case 256: return launch_tile_split<FORM, 256, MODE>(xp, xoff, qp, qoff, n_pad, n_qtiles, m_pad, P, partial, ex, st);
   }
   return fail(STAG_E_UNSUPPORTED, "padded dimension %d not instantiated", dp);
 }

@@ -974,16 +974,6 @@ __global__ __launch_bounds__(256) void describe_tasks(IndexView ix, const uint32
 using JoinVec = float __attribute__((ext_vector_type(4)));
 using JoinAcc = float __attribute__((ext_vector_type(16)));
 
-// Lane permutations within quads (all lanes active).
-template <int CTRL>
-__device__ inline int quad_i32(int v) {
-  return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
-}
-template <int CTRL>
-__device__ inline double quad_f64(double v) {
-  return __hiloint2double(quad_i32<CTRL>(__double2hiint(v)), quad_i32<CTRL>(__double2loint(v)));
-}
-
 // Q: the batch's rows (from q0 of the call on) as the index's own are: dx
 // floats, 16-byte aligned, 0 from d on.
 template <int DQ>
@@ -1152,12 +1142,12 @@ __global__ __launch_bounds__(64, DQ <= 32 ? 4 : DQ <= 64 ? 3 : 2) void join_buck
       const int qid = qids[pq];
       // fp64 distances: a quad reads its four pairs' rows together, 16 bytes a
       // lane of every 64, and adds the four partial sums of each
-      const float* const qrow[4] = {Q + (int64_t)quad_i32<0x00>(qid) * dx,
-                                    Q + (int64_t)quad_i32<0x55>(qid) * dx,
-                                    Q + (int64_t)quad_i32<0xAA>(qid) * dx,
-                                    Q + (int64_t)quad_i32<0xFF>(qid) * dx};
-      const int xrow[4] = {quad_i32<0x00>(m) * RS, quad_i32<0x55>(m) * RS, quad_i32<0xAA>(m) * RS,
-                           quad_i32<0xFF>(m) * RS};
+      const float* const qrow[4] = {Q + (int64_t)quad_perm<0x00>(qid) * dx,
+                                    Q + (int64_t)quad_perm<0x55>(qid) * dx,
+                                    Q + (int64_t)quad_perm<0xAA>(qid) * dx,
+                                    Q + (int64_t)quad_perm<0xFF>(qid) * dx};
+      const int xrow[4] = {quad_perm<0x00>(m) * RS, quad_perm<0x55>(m) * RS, quad_perm<0xAA>(m) * RS,
+                           quad_perm<0xFF>(m) * RS};
       double D4[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 2
       for (int u = 0; u < DQ / 16; ++u) {
@@ -1177,10 +1167,7 @@ __global__ __launch_bounds__(64, DQ <= 32 ? 4 : DQ <= 64 ? 3 : 2) void join_buck
           }
         }
       }
-      const bool b1 = lane & 2, b0 = lane & 1;
-      const double d0 = (b1 ? D4[2] : D4[0]) + quad_f64<0x4E>(b1 ? D4[0] : D4[2]);  // pairs 2 b1
-      const double d1 = (b1 ? D4[3] : D4[1]) + quad_f64<0x4E>(b1 ? D4[1] : D4[3]);  // pairs 2 b1 + 1
-      const double D = (b0 ? d1 : d0) + quad_f64<0xB1>(b0 ? d0 : d1);
+      const double D = quad_sums(D4);
       const bool take = valid && D >= Tlo && D < Thi;
       terms[lane] = take ? level_weight(cheb, sqrt(D) / ri) : 0.0;
       const uint64_t taken = __ballot(take);

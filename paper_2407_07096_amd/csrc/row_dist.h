@@ -8,12 +8,23 @@
 namespace stag {
 namespace {
 
-// v of lane ^ 1 or lane ^ 2 (quad permutations), all lanes active.
+// v of another lane of the quad (a quad permutation), all lanes active: 0x00,
+// 0x55, 0xAA, 0xFF that of lane 0 .. 3, 0xB1 of lane ^ 1, 0x4E of lane ^ 2.
+template <int CTRL>
+__device__ inline int quad_perm(int v) {
+  return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
+}
 template <int CTRL>
 __device__ inline double quad_perm(double v) {
-  const int lo = __double2loint(v), hi = __double2hiint(v);
-  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false),
-                          __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false));
+  return __hiloint2double(quad_perm<CTRL>(__double2hiint(v)), quad_perm<CTRL>(__double2loint(v)));
+}
+
+// Sums over a quad of four values each, the sum of value r in lane r.
+__device__ inline double quad_sums(const double (&v)[4]) {
+  const bool b1 = threadIdx.x & 2, b0 = threadIdx.x & 1;
+  const double k0 = (b1 ? v[2] : v[0]) + quad_perm<0x4E>(b1 ? v[0] : v[2]);  // values 2 b1
+  const double k1 = (b1 ? v[3] : v[1]) + quad_perm<0x4E>(b1 ? v[1] : v[3]);  // values 2 b1 + 1
+  return (b0 ? k1 : k0) + quad_perm<0xB1>(b0 ? k0 : k1);
 }
 
 // ||xi - x_j||^2 for the row j of each lane (rows of d floats, ld apart), by fp64
@@ -95,7 +106,6 @@ __device__ __forceinline__ double row_dist2(const float* __restrict__ xi, const 
     }
     return D;
   } else {
-    const int q = threadIdx.x & 3;
     const float* xj[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) xj[r] = X + (int64_t)__shfl((int)j, r, 4) * ld;
@@ -104,10 +114,7 @@ __device__ __forceinline__ double row_dist2(const float* __restrict__ xi, const 
     for (; c + 32 <= d; c += 32) row_piece<ROWS, 2, false>(xi, xj, c, d, acc);
     if (d - c > 16) row_piece<ROWS, 2, true>(xi, xj, c, d, acc);
     else if (d - c > 0) row_piece<ROWS, 1, true>(xi, xj, c, d, acc);
-    const bool b1 = q & 2, b0 = q & 1;
-    const double k0 = (b1 ? acc[2] : acc[0]) + quad_perm<0x4E>(b1 ? acc[0] : acc[2]);  // rows 2 b1
-    const double k1 = (b1 ? acc[3] : acc[1]) + quad_perm<0x4E>(b1 ? acc[1] : acc[3]);  // rows 2 b1 + 1
-    return (b0 ? k1 : k0) + quad_perm<0xB1>(b0 ? k0 : k1);
+    return quad_sums(acc);
   }
 }
 
