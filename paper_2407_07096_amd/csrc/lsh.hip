@@ -349,7 +349,7 @@ __global__ __launch_bounds__(256) void hash_queries(const float* __restrict__ Q,
 // the kHashTables * K chains that use it; the projections are wave-uniform
 // (scalar operands).  The same left-to-right chains as hash_queries, which
 // read its row's floats from memory for every table: 70,000 rows of 784, 136
-// tables of 6: 10.4 ms there, 3.9 ms here (1.15 ms of fused products at the
+// tables of 6: 10.4 ms there, 3.6 ms here (1.15 ms of fused products at the
 // fp64 rate).  Two rows per lane (each scalar operand used twice) took 4.1 ms,
 // rows read in whole 64-byte pieces by four lanes each 4.4 ms.
 constexpr int kHashTables = 4, kHashK = 16;
