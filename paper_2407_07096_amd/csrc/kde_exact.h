@@ -246,17 +246,28 @@ int64_t query_tile_rows();
 // idle: below kFewPairs pairs, the smallest power of two up to 8 that gives
 // kSplitGrid workgroups (2 per compute unit; 37 queries against 300,000 rows at
 // d = 64, 74 pairs: 232 us a call, 155 with the shares, 84 with the operands
-// prepared by vector loads).  Wide rows, whose workgroups are long and whose
-// records are small, share in eighths up to kFewPairsWide pairs, so that the
-// last round of workgroups is short as well.  Unshared against eighths, in ms,
-// fp16 split and fp32, at d = 784 and 18 chunks: 0.67 and 0.35, 2.03 and 1.03
-// at 126 pairs, 1.04 and 0.98, 3.60 and 3.57 at 504, 2.21 and 1.78, 8.69 and
-// 7.17 at 1,026, 2.57 and 2.36, 10.4 and 9.72 at 1,422 (in halves 2.55 and
-// 10.3), 3.37 and 3.26, 13.8 and 13.5 at 1,998; at 2,988, 4.98 and 4.71, 20.5 and
-// 20.1 (d = 300: 2.00 and 2.00, 7.99 and 7.90), hardly worth the records.  One
-// workgroup per pair otherwise, with a workspace that is not the pool (the
-// no-allocation call's need is part of its interface), and for the exponential
-// kernel, whose near pairs are kept per chunk.
+// prepared by vector loads).  Data of a single chunk share it if they fill more
+// than an eighth of one (16 tiles of 32 rows), which one workgroup gets anyway:
+// 16,000 queries against 500 rows at d = 64, logistic bf16 split, 40.5 us
+// unshared, 48.5 shared, against 1,000 51.4 and 47.6.  A share costs its stores
+// and the launch that adds them, 5 us, which 32 tiles don't save Gaussian sums
+// of up to 32 coordinates (1,000 rows, d = 16, fp16 split: 38 and 41 us), and the
+// centred fp16 tile above 128 forms its queries again in every share: it needs 64
+// tiles (8,000 queries, d = 200: 1,000 rows 206 and 216 us, 2,000 rows 257 and
+// 236).  Wide rows can take 32 queries a workgroup instead: at d = 784 and 1,000
+// queries fp32 139 and 265 us with 600 rows, 178 and 266 with 1,000, 324 and 268
+// with 2,000; the fp16 split form 88 and 101, 108 and 104, 178 and 104.
+// Wide rows, whose workgroups are long and whose records are small, share in
+// eighths up to kFewPairsWide pairs, so that the last round of workgroups is
+// short as well.  Unshared against eighths, in ms, fp16 split and fp32, at d =
+// 784 and 18 chunks: 0.67 and 0.35, 2.03 and 1.03 at 126 pairs, 1.04 and 0.98,
+// 3.60 and 3.57 at 504, 2.21 and 1.78, 8.69 and 7.17 at 1,026, 2.57 and 2.36,
+// 10.4 and 9.72 at 1,422 (in halves 2.55 and 10.3), 3.37 and 3.26, 13.8 and
+// 13.5 at 1,998; at 2,988, 4.98 and 4.71, 20.5 and 20.1 (d = 300: 2.00 and
+// 2.00, 7.99 and 7.90), hardly worth the records.  One workgroup per pair
+// otherwise, with a workspace that is not the pool (the no-allocation call's
+// need is part of its interface), and for the exponential kernel, whose near
+// pairs are kept per chunk.
 constexpr int64_t kFewPairs = 128, kSplitGrid = 512, kFewPairsWide = 2048;
 stag_status alloc_parts(const Operands& xo, const Operands& qo, int kernel, Workspace& ws, TileExtra* ex);
 stag_status launch_exact_tiles(const Operands& xo, const Operands& qo, double* partial, const TileExtra& ex,

@@ -750,6 +750,14 @@ stag_status alloc_parts(const Operands& xo, const Operands& qo, int kernel, Work
   const int64_t P = exact_chunks(xo.rows_pad), pairs = P * (qo.rows_pad / kBQ);
   const bool wide = xo.dp > 256;
   if (pairs >= (wide ? kFewPairsWide : kFewPairs)) return STAG_OK;
+  if (P == 1) {
+    // one short chunk: what an eighth of a whole one holds is not shared
+    int64_t unshared = kSubTiles;
+    if (wide) unshared = xo.form == STAG_FORM_FP32 ? 3 * kSubTiles : 3 * kSubTiles / 2;
+    if (kernel == STAG_KERNEL_GAUSSIAN && !xo.centred && xo.dp <= 32) unshared = 2 * kSubTiles;
+    if (xo.form == STAG_FORM_FP16_CENTRED && xo.dp > 128) unshared = 4 * kSubTiles - 1;
+    if (xo.rows_pad / kTileRows <= unshared) return STAG_OK;
+  }
   int nsub = wide ? kSubs : 2;
   while (nsub < kSubs && pairs * nsub < kSplitGrid) nsub *= 2;
   if (wide) {
