@@ -29,6 +29,7 @@
 //              ascending within a bucket (deterministic construction)
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "e2lsh.h"
@@ -1567,9 +1568,7 @@ struct stag_lsh_index {
   // dense segments (walked indexes only): their column tiles, the first one
   // of each segment [nseg + 1], and the copies' level masks [K1]
   int dense_tiles = 0;
-  std::vector<stag::DenseTile> h_dtiles;
-  std::vector<int32_t> h_dfirst;
-  std::vector<uint64_t> h_dlevels;
+  std::vector<char> h_dense;
   stag::DenseTile* dtiles = nullptr;
   int32_t* dfirst = nullptr;
   uint64_t* dlevels = nullptr;
@@ -1666,7 +1665,7 @@ __global__ __launch_bounds__(256) void row_norms(const float* __restrict__ X, in
   if (lane == 0) xn[r] = sqrt(s2);
 }
 
-stag_status find_dense(stag_lsh_index* idx, const MemberBlock* blocks, int64_t nblocks, Workspace& ws, hipStream_t st);
+stag_status find_dense(stag_lsh_index* idx, Workspace& ws, hipStream_t st);
 
 stag_status create_index(const float* X, int64_t n, int d, double a, double eps, const stag_lsh_params* p,
                          stag_lsh_index* idx, hipStream_t st) {
@@ -1807,7 +1806,7 @@ stag_status create_index(const float* X, int64_t n, int d, double a, double eps,
                                  st));
   }
   STAG_HIP(hipGetDevice(&idx->device));
-  STAG_TRY(find_dense(idx, dblk, (int64_t)blocks.size(), ws, st));
+  STAG_TRY(find_dense(idx, ws, st));
   // the workspace (sort buffers, counts) is released in stream order
   return STAG_OK;
 }
@@ -1927,52 +1926,49 @@ bool join_applies(const stag_lsh_index* idx) {
 }
 
 // The dense segments of an index whose queries are walked (see lsh_dense.h):
-// kDenseSamples evenly spaced points are hashed as queries and met counts
-// their meetings with each segment's members; a segment whose share is at
-// least kDenseShare is dense, in segment order while the columns last.  One
-// synchronisation.
-stag_status find_dense(stag_lsh_index* idx, const MemberBlock* blocks, int64_t nblocks, Workspace& ws, hipStream_t st) {
-  if (join_applies(idx) || nblocks == 0) return STAG_OK;
-  const int64_t n = idx->prm.n;
-  const int ns = (int)std::min<int64_t>(kDenseSamples, n);
+// those where count_met's share of pairs that meet, without the samples' with
+// themselves, is at least kDenseShare, in segment order while the columns last.
+// One synchronisation.
+stag_status find_dense(stag_lsh_index* idx, Workspace& ws, hipStream_t st) {
+  if (join_applies(idx) || idx->M == 0) return STAG_OK;
   const int J = idx->prm.shape.J, K1 = idx->prm.shape.K1;
-  if (idx->ntab * ns * 8 > kDenseMaxBytes) return STAG_OK;
-  const int64_t step = n / ns;
-  if (step * idx->dx > INT32_MAX) return STAG_OK;
-  uint64_t* skeys = nullptr;
-  unsigned long long* met = nullptr;
-  STAG_TRY(ws.alloc(&skeys, (size_t)idx->ntab * ns));
+  uint32_t* met = nullptr;
   STAG_TRY(ws.alloc(&met, (size_t)idx->nseg));
-  STAG_TRY(hash_query_batch(idx, idx->X, (int)(step * idx->dx), 0, ns, skeys, st));
-  STAG_TRY(zero_async(met, sizeof(unsigned long long) * idx->nseg, st));
-  hipLaunchKernelGGL(count_met, dim3((unsigned)ceil_div(nblocks, 4)), dim3(256), 0, st, blocks, nblocks,
-                     idx->prm.shape.L, idx->seg_off, idx->mkeys, skeys, ns, met);
+  hipLaunchKernelGGL(count_met, dim3((unsigned)idx->nseg), dim3(kDenseMembers * kMetGroups), 0, st,
+                     idx->prm.shape.L, idx->seg_off, idx->mkeys, met);
   STAG_TRY(check_launch("count_met"));
-  std::vector<unsigned long long> h((size_t)idx->nseg);
-  STAG_HIP(hipMemcpyAsync(h.data(), met, sizeof(unsigned long long) * idx->nseg, hipMemcpyDeviceToHost, st));
+  std::vector<uint32_t> h((size_t)idx->nseg);
+  STAG_HIP(hipMemcpyAsync(h.data(), met, sizeof(uint32_t) * idx->nseg, hipMemcpyDeviceToHost, st));
   STAG_HIP(hipStreamSynchronize(st));
-  // (kept with the index: their copies to the device may still be under way)
-  std::vector<DenseTile>& tiles = idx->h_dtiles;
-  std::vector<int32_t>& first = idx->h_dfirst;
-  std::vector<uint64_t>& levels = idx->h_dlevels;
-  first.assign((size_t)idx->nseg + 1, 0);
-  levels.assign((size_t)K1, 0);
+  std::vector<DenseTile> tiles;
+  std::vector<int32_t> first((size_t)idx->nseg + 1);
+  std::vector<uint64_t> levels((size_t)K1);
   for (int64_t sgm = 0; sgm < idx->nseg; ++sgm) {
     first[sgm] = (int32_t)tiles.size();
     const int64_t c = (int64_t)(idx->h_seg_off[sgm + 1] - idx->h_seg_off[sgm]);
-    if (c == 0 || (double)h[sgm] < kDenseShare * (double)c * ns) continue;
+    const int64_t ns = std::min<int64_t>(c, kDenseSamples), nm = std::min<int64_t>(c, kDenseMembers);
+    if (c < 2 || (double)(h[sgm] - ns) < kDenseShare * (double)(nm - 1) * (double)ns) continue;
     if (((int64_t)tiles.size() + ceil_div(c, kDenseTile)) * kDenseTile > kDenseMaxCols) continue;
     for (int64_t u = 0; u < c; u += kDenseTile) tiles.push_back({(int32_t)sgm, (int32_t)u});
     levels[sgm / J] |= 1ULL << (sgm % J);
   }
   first[idx->nseg] = (int32_t)tiles.size();
   if (tiles.empty()) return STAG_OK;
-  STAG_TRY(own_alloc(idx, &idx->dtiles, tiles.size()));
-  STAG_TRY(own_alloc(idx, &idx->dfirst, first.size()));
-  STAG_TRY(own_alloc(idx, &idx->dlevels, levels.size()));
-  STAG_HIP(hipMemcpyAsync(idx->dtiles, tiles.data(), sizeof(DenseTile) * tiles.size(), hipMemcpyHostToDevice, st));
-  STAG_HIP(hipMemcpyAsync(idx->dfirst, first.data(), sizeof(int32_t) * first.size(), hipMemcpyHostToDevice, st));
-  STAG_HIP(hipMemcpyAsync(idx->dlevels, levels.data(), sizeof(uint64_t) * levels.size(), hipMemcpyHostToDevice, st));
+  // one copy to the device: levels, tiles, first columns
+  static_assert(sizeof(DenseTile) == 8, "after the levels, before the int32s");
+  const size_t nl = sizeof(uint64_t) * levels.size(), nt = sizeof(DenseTile) * tiles.size(),
+               nf = sizeof(int32_t) * first.size();
+  std::vector<char>& all = idx->h_dense;  // kept with the index: its copy may still be under way
+  all.resize(nl + nt + nf);
+  std::memcpy(all.data(), levels.data(), nl);
+  std::memcpy(all.data() + nl, tiles.data(), nt);
+  std::memcpy(all.data() + nl + nt, first.data(), nf);
+  char* dev = nullptr;
+  STAG_TRY(own_alloc(idx, &dev, all.size()));
+  STAG_HIP(hipMemcpyAsync(dev, all.data(), all.size(), hipMemcpyHostToDevice, st));
+  idx->dlevels = reinterpret_cast<uint64_t*>(dev);
+  idx->dtiles = reinterpret_cast<DenseTile*>(dev + nl);
+  idx->dfirst = reinterpret_cast<int32_t*>(dev + nl + nt);
   idx->dense_tiles = (int)tiles.size();
   return STAG_OK;
 }

@@ -10,7 +10,7 @@
 // the draws read again instead of walking.
 //
 // Which segments (copy, level) are dense is decided once per index, from the
-// index's own points: the share of (sampled point, member) pairs that meet in
+// index's own points: the share of (sampled member, member) pairs that meet in
 // some table (find_dense).  A result therefore never depends on the queries
 // that share its batch.  Measured: where every pair meets (70,000 sparse rows
 // of 784 against 4,400 members) the walk took 5.2e-10 s a candidate and the
@@ -61,40 +61,53 @@ struct DensePairs {
   const uint64_t* levels = nullptr;  // [K1] bit i - 1: level i of the copy is dense
 };
 
-// met[seg] += pairs (sampled point, member) of the segment that meet in some
-// table, all points: also with themselves.  One member per thread; the
-// samples' keys [ntab][kDenseSamples] of 8 tables at a time in LDS.
-__global__ __launch_bounds__(256) void count_met(const MemberBlock* __restrict__ blocks, int64_t nblocks, int L,
-                                                 const uint64_t* __restrict__ seg_off,
-                                                 const uint64_t* __restrict__ mkeys,
-                                                 const uint64_t* __restrict__ skeys, int ns,
-                                                 unsigned long long* __restrict__ met) {
-  __shared__ uint64_t sk[4][8][kDenseSamples];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t b = (int64_t)blockIdx.x * 4 + wave;
-  if (b >= nblocks) return;
-  const MemberBlock blk = blocks[b];
-  const int64_t s0 = (int64_t)seg_off[blk.seg];
-  const int64_t cnt = (int64_t)seg_off[blk.seg + 1] - s0;
-  const int64_t u = blk.u0 + lane;
-  const bool live = u < cnt;
+// met[seg] = pairs (sample, member) of the segment that meet in some table, of
+// up to kDenseSamples samples and kDenseMembers members, both evenly spaced (k
+// of m: members r cnt / m), so that a sample is among the members and meets
+// itself.  A workgroup per segment: thread (g, c) takes member c through every
+// fourth group of kMetTables tables, against the samples' keys in LDS, their
+// low halves.  The keys are the members' own and only that many members count:
+// hashing 64 points of the data for the samples took 0.98 ms of the 20.9 that an
+// index of 40,000 rows of 200 took to build, all its members 0.68; 0.03 as it is.
+constexpr int kDenseMembers = 256, kMetTables = 4, kMetGroups = 4;
+__global__ __launch_bounds__(kDenseMembers* kMetGroups) void count_met(int L, const uint64_t* __restrict__ seg_off,
+                                                                       const uint64_t* __restrict__ mkeys,
+                                                                       uint32_t* __restrict__ met) {
+  __shared__ __attribute__((aligned(16))) uint32_t sk[kMetGroups][kMetTables][kDenseSamples];
+  __shared__ unsigned long long met_by[kDenseMembers];
+  __shared__ uint32_t total;
+  const int c = threadIdx.x % kDenseMembers, g = threadIdx.x / kDenseMembers;
+  const int64_t s0 = (int64_t)seg_off[blockIdx.x], cnt = (int64_t)seg_off[blockIdx.x + 1] - s0;
+  if (threadIdx.x == 0) total = 0;
+  if (g == 0) met_by[c] = 0;
+  const int ns = (int)min(cnt, (int64_t)kDenseSamples), nm = (int)min(cnt, (int64_t)kDenseMembers);
+  const int64_t u = cnt > 0 ? s0 + min(c, nm - 1) * cnt / nm : 0;
+  const int sr = c % kDenseSamples, sl = c / kDenseSamples;  // this thread's sample and table of a group
+  const int64_t us = cnt > 0 ? s0 + min(sr, ns - 1) * cnt / ns : 0;
   uint64_t hit = 0;
-  for (int l0 = 0; l0 < L; l0 += 8) {
-    const int nl = min(8, L - l0);
-    __builtin_amdgcn_wave_barrier();
-    for (int l = 0; l < nl; ++l)
-      sk[wave][l][lane] = lane < ns ? skeys[((int64_t)blk.seg * L + l0 + l) * ns + lane] : 0;
-    __builtin_amdgcn_wave_barrier();
-    if (live)
-      for (int l = 0; l < nl; ++l) {
-        const uint64_t key = mkeys[(s0 + u) * L + l0 + l];
-        for (int r = 0; r < ns; ++r) hit |= (uint64_t)(sk[wave][l][r] == key) << r;
-      }
+  for (int l0 = 0; cnt > 0 && l0 < L; l0 += kMetTables * kMetGroups) {
+    const int lg = l0 + kMetTables * g;
+    __syncthreads();  // the last tables' keys are used up
+    if (lg + sl < L) sk[g][sl][sr] = (uint32_t)mkeys[us * L + lg + sl];
+    __syncthreads();
+    for (int l = 0; l < kMetTables && lg + l < L; ++l) {
+      const uint32_t key = (uint32_t)mkeys[u * L + lg + l];
+#pragma unroll
+      for (int r = 0; r < kDenseSamples; ++r) hit |= (uint64_t)(sk[g][l][r] == key) << r;
+    }
   }
-  uint32_t c = (uint32_t)__popcll(hit);
-  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
-  if (lane == 0 && c > 0) atomicAdd(met + blk.seg, (unsigned long long)c);
+  __syncthreads();
+  if (c < nm) atomicOr(&met_by[c], hit & (ns < 64 ? (1ull << ns) - 1 : ~0ull));
+  __syncthreads();
+  if (g == 0) {
+    uint32_t n = (uint32_t)__popcll(met_by[c]);
+    for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
+    if (c % 64 == 0) atomicAdd(&total, n);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) met[blockIdx.x] = total;
 }
+static_assert(kDenseMembers == kDenseSamples * kMetTables && kDenseSamples == 64, "a key per thread, a bit per sample");
 
 // One workgroup of 512 threads per (column tile, row tile).  Thread (ty, tx) =
 // (tid / 32, tid % 32) holds rows ty + 16 i and columns tx + 32 j, i < 8, j <
