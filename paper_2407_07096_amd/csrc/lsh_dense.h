@@ -117,7 +117,8 @@ static_assert(kDenseMembers == kDenseSamples * kMetTables && kDenseSamples == 64
 // by the fp64 rate (a subtraction and a fused product per coordinate and pair,
 // 4.65 cycles each: 14.9 ms of it).  8 x 8 chains per thread spilled.  A pair that the norm bounds of the walk put outside its level
 // needs no distance; a tile without a pair that does is left out whole.
-template <bool QVEC>
+// NI < 8: batches of at most 16 NI queries, whose tile has no other rows.
+template <bool QVEC, int NI>
 __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst lc, const float* __restrict__ Q,
                                                    int64_t ldq, int64_t qrow0, int64_t nq,
                                                    const uint64_t* __restrict__ qkeys, int64_t qs,
@@ -139,10 +140,10 @@ __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst l
   if (tid < kDenseTile) mj[tid] = ix.members[s0 + ct.u0 + min(tid, mcnt - 1)];
 
   // first table of each pair: byte j of first[i] (255: none)
-  uint32_t first[8];
-  uint32_t met[8];  // tables in which the row meets this thread's members
+  uint32_t first[NI];
+  uint32_t met[NI];  // tables in which the row meets this thread's members
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < NI; ++i) {
     first[i] = ~0u;
     met[i] = 0;
   }
@@ -160,7 +161,7 @@ __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst l
 #pragma unroll
       for (int j = 0; j < 4; ++j) km[j] = sh.key[1][l][tx + 32 * j];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
+      for (int i = 0; i < NI; ++i) {
         const uint64_t kq = sh.key[0][l][ty + 16 * i];
         uint32_t eq = 0;  // 0xFF in the byte of every member that meets here
 #pragma unroll
@@ -180,7 +181,7 @@ __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst l
   const double Tlo = lc.T[lev - 1], Thi = lc.T[lev];
   bool need = false;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < NI; ++i) {
     const int r = ty + 16 * i;
     const bool rlive = r < rcnt;
     const double sq = qnorm[r0 + min(r, rcnt - 1)];
@@ -210,7 +211,7 @@ __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst l
   if (tid == 0) dp.any[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = any ? 1 : 0;
   if (!any) return;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < NI; ++i) {
     const int r = ty + 16 * i;
     uint8_t* f = dp.F + (r0 + r) * dp.ncol + (int64_t)blockIdx.x * kDenseTile + tx;
     if (r < rcnt)
@@ -241,9 +242,9 @@ __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst l
     o[0] = DensePair{(double)st4.x, (double)st4.y};
     o[1] = DensePair{(double)st4.z, (double)st4.w};
   };
-  double D[8][4];
+  double D[NI][4];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < NI; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) D[i][j] = 0.0;
   const int nk = (d + kDenseK - 1) / kDenseK;
@@ -261,7 +262,7 @@ __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst l
 #pragma unroll
       for (int j = 0; j < 4; ++j) xd[j] = *reinterpret_cast<const DensePair*>(&xl[32 * j * kDensePad + k]);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
+      for (int i = 0; i < NI; ++i) {
         const DensePair qd = *reinterpret_cast<const DensePair*>(&ql[16 * i * kDensePad + k]);
 #pragma unroll
         for (int e = 0; e < 2; ++e)
@@ -275,7 +276,7 @@ __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst l
     if (kb + 1 < nk) lstore(buf ^ 1);
   }
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < NI; ++i) {
     const int r = ty + 16 * i;
     if (r < rcnt) {
       double* o = dp.D + (r0 + r) * dp.ncol + (int64_t)blockIdx.x * kDenseTile + tx;
@@ -286,8 +287,9 @@ __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst l
 }
 
 // Terms of the dense pairs and what they add to each query's copy sums, level
-// masks and accepted counts.  One wave per query: columns in order, lanes
-// strided, one butterfly sum per copy.  LIST: the terms take their distances'
+// masks and accepted counts.  One wave per query and copy: columns in order,
+// lanes strided, one butterfly sum (one query of an index of 5,000 rows of 200:
+// a wave for all copies 162 us, 7 with one for each).  LIST: the terms take their distances'
 // place (table 255 outside the level) and are then listed per segment in the
 // walk's order: a count per table, a scan over the tables and a second pass
 // that ranks a batch's equal tables, both by ballots of the tables' bits.
@@ -340,77 +342,76 @@ __global__ __launch_bounds__(256) void dense_terms(IndexView ix, LevelConst lc, 
   };
   int lbits = 0;  // of a table's number
   while ((1 << lbits) < ix.L) ++lbits;
+  const int t = blockIdx.y;
   int64_t na = 0;
-  for (int t = 0; t < ix.K1; ++t) {
-    double acc = 0.0;
-    uint64_t hit = 0;
-    for (int i = 1; i <= ix.J; ++i) {
-      const int seg = t * ix.J + (i - 1);
-      const int c0 = dp.first[seg], c1 = dp.first[seg + 1];
-      if (c0 == c1) continue;
-      const double Tlo = lc.T[i - 1], Thi = lc.T[i], ri = lc.r[i];
-      uint32_t count = 0;  // lane l: positive terms of table l, then its next place
-      each_tile(c0, c1, [&](int, int64_t o, const Piece& p) {
+  double acc = 0.0;
+  uint64_t hit = 0;
+  for (int i = 1; i <= ix.J; ++i) {
+    const int seg = t * ix.J + (i - 1);
+    const int c0 = dp.first[seg], c1 = dp.first[seg + 1];
+    if (c0 == c1) continue;
+    const double Tlo = lc.T[i - 1], Thi = lc.T[i], ri = lc.r[i];
+    uint32_t count = 0;  // lane l: positive terms of table l, then its next place
+    each_tile(c0, c1, [&](int, int64_t o, const Piece& p) {
+#pragma unroll
+      for (int k = 0; k < kDenseTile; k += 64) {
+        const double D = p.D[k / 64];
+        const uint8_t f = p.f[k / 64];
+        const bool in = f != 255 && D >= Tlo && D < Thi;
+        const double v = in ? level_weight(ix.cheb + i * kChebRow, sqrt(D) / ri) : 0.0;
+        acc += v;
+        na += v > 0.0 ? 1 : 0;
+        const uint64_t open = __ballot(v > 0.0);
+        if (open) hit |= 1ull << (i - 1);
+        if constexpr (LIST) {
+          dp.D[o + k] = v;
+          if (!(v > 0.0)) dp.F[o + k] = 255;
+          // lane l: the terms of table l, from the ballots of the tables' bits
+          uint64_t same = lane < ix.L ? open : 0ull;
+          for (int q = 0; q < lbits; ++q) {
+            const uint64_t ones = __ballot((f >> q) & 1);
+            same &= (lane >> q) & 1 ? ones : ~ones;
+          }
+          count += (uint32_t)__popcll(same);
+        }
+      }
+    });
+    if constexpr (LIST) {
+      uint32_t incl = count;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(incl, o);
+        if (lane >= o) incl += y;
+      }
+      count = incl - count;
+      if (lane == 63) dp.len[r * nct + c0] = (int32_t)incl;
+      const int64_t s0 = (int64_t)ix.seg_off[seg];
+      const int64_t out = r * dp.ncol + (int64_t)c0 * kDenseTile;
+      each_tile(c0, c1, [&](int ct, int64_t, const Piece& p) {
 #pragma unroll
         for (int k = 0; k < kDenseTile; k += 64) {
-          const double D = p.D[k / 64];
           const uint8_t f = p.f[k / 64];
-          const bool in = f != 255 && D >= Tlo && D < Thi;
-          const double v = in ? level_weight(ix.cheb + i * kChebRow, sqrt(D) / ri) : 0.0;
-          acc += v;
-          na += v > 0.0 ? 1 : 0;
-          const uint64_t open = __ballot(v > 0.0);
-          if (open) hit |= 1ull << (i - 1);
-          if constexpr (LIST) {
-            dp.D[o + k] = v;
-            if (!(v > 0.0)) dp.F[o + k] = 255;
-            // lane l: the terms of table l, from the ballots of the tables' bits
-            uint64_t same = lane < ix.L ? open : 0ull;
-            for (int q = 0; q < lbits; ++q) {
-              const uint64_t ones = __ballot((f >> q) & 1);
-              same &= (lane >> q) & 1 ? ones : ~ones;
-            }
-            count += (uint32_t)__popcll(same);
+          const uint64_t open = __ballot(f != 255);
+          uint64_t same = lane < ix.L ? open : 0ull, peers = open;  // terms of table `lane`; of this term's table
+          for (int q = 0; q < lbits; ++q) {
+            const uint64_t ones = __ballot((f >> q) & 1);
+            same &= (lane >> q) & 1 ? ones : ~ones;
+            peers &= (f >> q) & 1 ? ones : ~ones;
+          }
+          const uint32_t place = (uint32_t)__shfl((int)count, f & 63) + (uint32_t)__popcll(peers & below);
+          count += (uint32_t)__popcll(same);
+          if (f != 255) {
+            dp.V[out + place] = p.D[k / 64];
+            dp.J[out + place] = ix.members[s0 + (int64_t)(ct - c0) * kDenseTile + k + lane];
           }
         }
       });
-      if constexpr (LIST) {
-        uint32_t incl = count;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const uint32_t y = __shfl_up(incl, o);
-          if (lane >= o) incl += y;
-        }
-        count = incl - count;
-        if (lane == 63) dp.len[r * nct + c0] = (int32_t)incl;
-        const int64_t s0 = (int64_t)ix.seg_off[seg];
-        const int64_t out = r * dp.ncol + (int64_t)c0 * kDenseTile;
-        each_tile(c0, c1, [&](int ct, int64_t, const Piece& p) {
-#pragma unroll
-          for (int k = 0; k < kDenseTile; k += 64) {
-            const uint8_t f = p.f[k / 64];
-            const uint64_t open = __ballot(f != 255);
-            uint64_t same = lane < ix.L ? open : 0ull, peers = open;  // terms of table `lane`; of this term's table
-            for (int q = 0; q < lbits; ++q) {
-              const uint64_t ones = __ballot((f >> q) & 1);
-              same &= (lane >> q) & 1 ? ones : ~ones;
-              peers &= (f >> q) & 1 ? ones : ~ones;
-            }
-            const uint32_t place = (uint32_t)__shfl((int)count, f & 63) + (uint32_t)__popcll(peers & below);
-            count += (uint32_t)__popcll(same);
-            if (f != 255) {
-              dp.V[out + place] = p.D[k / 64];
-              dp.J[out + place] = ix.members[s0 + (int64_t)(ct - c0) * kDenseTile + k + lane];
-            }
-          }
-        });
-      }
     }
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-    if (lane == 0) {
-      Scopy[r * ix.K1 + t] += acc;
-      if (levels_out && hit) levels_out[(qrow0 + r) * ix.K1 + t] |= hit;
-    }
+  }
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+  if (lane == 0) {
+    Scopy[r * ix.K1 + t] += acc;
+    if (levels_out && hit) levels_out[(qrow0 + r) * ix.K1 + t] |= hit;
   }
   for (int o = 32; o > 0; o >>= 1) na += __shfl_xor(na, o);
   if (nacc && lane == 0 && na > 0)
