@@ -1890,8 +1890,14 @@ stag_status hash_query_batch(const stag_lsh_index* idx, const float* Q, int ldq,
   }
   const dim3 wide((unsigned)qb, (unsigned)ceil_div(idx->ntab, kHashTables));
   // fewer blocks than 4 a compute unit leave the chip waiting on the longer
-  // chains of a block (5,000 rows of 200: 190 us per table, 310 us in fours)
-  if (idx->dreg == 0 && K <= 8 && wide.y <= 65535 && (int64_t)wide.x * wide.y >= 1024) {
+  // chains of a block (5,000 rows of 200: 190 us per table, 310 us in fours),
+  // and rows that the caches hold between tables are read again at less than
+  // that costs (whole calls, an index of 5,000 rows of 200: 1 query 467 us per
+  // table, 557 in fours, 8,000 23.9 and 25.1 ms, 16,000 51.4 and 49.3; of 2,000
+  // rows of 784: 1 query 1.64 and 2.06 ms, 2,000 26.7 and 26.4, 16,000 266 and 200)
+  constexpr int64_t kCachedRows = 7000000;  // bytes
+  if (idx->dreg == 0 && K <= 8 && wide.y <= 65535 && (int64_t)wide.x * wide.y >= 1024 &&
+      cur * idx->d * (int64_t)sizeof(float) >= kCachedRows) {
     const bool vec = ldq % 4 == 0 && ((uintptr_t)Q & 15u) == 0;
     auto launch = [&](auto kern) {
       hipLaunchKernelGGL(kern, wide, dim3(256), 0, st, Q, (int64_t)ldq, q0, cur, idx->d, idx->dg, idx->G8, idx->B,
