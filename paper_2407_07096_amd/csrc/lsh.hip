@@ -2005,7 +2005,7 @@ stag_status alloc_dense(const stag_lsh_index* idx, int64_t rows, int64_t cur, bo
   dp->ncol = idx->dense_tiles * kDenseTile;
   STAG_TRY(ws.alloc(&dp->D, (size_t)rows * dp->ncol));
   STAG_TRY(ws.alloc(&dp->F, (size_t)rows * dp->ncol));
-  STAG_TRY(ws.alloc(&dp->any, (size_t)(rows / kDenseTile) * idx->dense_tiles));
+  STAG_TRY(ws.alloc(&dp->any, (size_t)(rows / 16) * idx->dense_tiles));
   if (draw) {
     STAG_TRY(ws.alloc(&dp->V, (size_t)rows * dp->ncol));
     STAG_TRY(ws.alloc(&dp->J, (size_t)rows * dp->ncol));
@@ -2023,7 +2023,7 @@ stag_status alloc_dense(const stag_lsh_index* idx, int64_t rows, int64_t cur, bo
 // time.
 stag_status walk_rows(const stag_lsh_index* idx, const float* Q, int ldq, int64_t q0, int64_t cur, int self_excl,
                       const uint64_t* qkeys, double* scopy, int64_t* ncand, int64_t* nacc, const DrawArgs* draw,
-                      const DensePairs& dp, double* qnorm, int64_t sub, hipStream_t st) {
+                      DensePairs dp, double* qnorm, int64_t sub, hipStream_t st) {
   const int K1 = idx->prm.shape.K1;
   const IndexView ix = make_view(idx);
   const LevelConst lc = make_levels(idx->prm);
@@ -2042,19 +2042,25 @@ stag_status walk_rows(const stag_lsh_index* idx, const float* Q, int ldq, int64_
       ScopedTimer tm("lsh_dense", st);
       hipLaunchKernelGGL(row_norms, dim3((unsigned)ceil_div(c, 4)), dim3(256), 0, st, Q + (q0 + p) * ldq, c, ldq,
                          qnorm);
-      const dim3 grid((unsigned)idx->dense_tiles, (unsigned)ceil_div(c, kDenseTile));
       // 16-byte query loads where every row starts at one (rows at ldq >= d
       // rounded up to 4 have the piece past d's last whole one too)
       const bool vec = ldq % 4 == 0 && ((uintptr_t)Q & 15u) == 0;
-      auto launch = [&](auto kern) {
+      // rows per workgroup: 16 NI, as many as fill the chip (two workgroups a
+      // compute unit) and the batch has.  One query of an index of 5,000 rows of
+      // 200: 92 us with 128 rows, 23 with 16; 200 queries of 3,000 rows of 150 in
+      // four copies, a whole call 222 and 170, of 30,000 rows of 256 520 and 455
+      auto launch = [&](auto NI) {
+        constexpr int ni = decltype(NI)::value;
+        dp.rows = 16 * ni;
+        const dim3 grid((unsigned)idx->dense_tiles, (unsigned)ceil_div(c, dp.rows));
+        const auto kern = vec ? dense_pairs<true, ni> : dense_pairs<false, ni>;
         hipLaunchKernelGGL(kern, grid, dim3(512), 0, st, ix, lc, Q, (int64_t)ldq, q0 + p, c, qkeys + p, cur, qnorm,
                            self_excl, dp, ncand);
       };
-      // tiles of few rows where there are few: one query of an index of 5,000
-      // rows of 200, 92 us with 128 rows, 23 with 16
-      if (c <= 16) launch(vec ? dense_pairs<true, 1> : dense_pairs<false, 1>);
-      else if (c <= 64) launch(vec ? dense_pairs<true, 4> : dense_pairs<false, 4>);
-      else launch(vec ? dense_pairs<true, 8> : dense_pairs<false, 8>);
+      auto fills = [&](int rows) { return c > rows / 2 && idx->dense_tiles * ceil_div(c, rows) >= 512; };
+      if (fills(kDenseTile)) launch(std::integral_constant<int, 8>());
+      else if (fills(64)) launch(std::integral_constant<int, 4>());
+      else launch(std::integral_constant<int, 1>());
       STAG_TRY(check_launch("dense_pairs"));
       auto terms = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(c, 4), (unsigned)K1), dim3(256), 0, st, ix, lc, q0 + p, c, dp,

@@ -44,7 +44,8 @@ struct DenseTile {
 
 // Pairs of one batch: D [rows][ncol] squared distances, then terms; F the
 // first table of the pair (255: no term); any [row tile][column tile] whether
-// a tile holds a pair at all (where not, D and F are not written).  For draws,
+// a tile, of `rows` queries, holds a pair at all (where not, D and F are not
+// written).  For draws,
 // V and J hold each (row, segment)'s positive terms and their points in the
 // walk's order (table, member ascending), from the segment's first column on,
 // and len their number at [row][first column tile].
@@ -55,6 +56,7 @@ struct DensePairs {
   double* V = nullptr;
   int32_t* J = nullptr;
   int32_t* len = nullptr;
+  int rows = kDenseTile;
   int ncol = 0;                    // columns, kDenseTile per column tile
   const DenseTile* tiles = nullptr;  // the column tiles, segments ascending
   const int32_t* first = nullptr;  // [nseg + 1] first column tile of each segment
@@ -117,7 +119,7 @@ static_assert(kDenseMembers == kDenseSamples * kMetTables && kDenseSamples == 64
 // by the fp64 rate (a subtraction and a fused product per coordinate and pair,
 // 4.65 cycles each: 14.9 ms of it).  8 x 8 chains per thread spilled.  A pair that the norm bounds of the walk put outside its level
 // needs no distance; a tile without a pair that does is left out whole.
-// NI < 8: batches of at most 16 NI queries, whose tile has no other rows.
+// 16 NI rows per workgroup (the figures are NI = 8's).
 template <bool QVEC, int NI>
 __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst lc, const float* __restrict__ Q,
                                                    int64_t ldq, int64_t qrow0, int64_t nq,
@@ -131,12 +133,12 @@ __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst l
   __shared__ int32_t mj[kDenseTile];
   const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
   const DenseTile ct = dp.tiles[blockIdx.x];
-  const int64_t r0 = (int64_t)blockIdx.y * kDenseTile;  // row of the batch
+  const int64_t r0 = (int64_t)blockIdx.y * 16 * NI;  // row of the batch
   const int L = ix.L, d = ix.d;
   const int lev = ct.seg % ix.J + 1;
   const int64_t s0 = (int64_t)ix.seg_off[ct.seg];
   const int mcnt = (int)min((int64_t)kDenseTile, (int64_t)ix.seg_off[ct.seg + 1] - s0 - ct.u0);
-  const int rcnt = (int)min((int64_t)kDenseTile, nq - r0);
+  const int rcnt = (int)min((int64_t)(16 * NI), nq - r0);
   if (tid < kDenseTile) mj[tid] = ix.members[s0 + ct.u0 + min(tid, mcnt - 1)];
 
   // first table of each pair: byte j of first[i] (255: none)
@@ -302,7 +304,7 @@ __global__ __launch_bounds__(256) void dense_terms(IndexView ix, LevelConst lc, 
   const int64_t r = (int64_t)blockIdx.x * 4 + wave;
   if (r >= nq) return;
   const int nct = dp.ncol / kDenseTile;
-  const uint8_t* any = dp.any + (r / kDenseTile) * nct;
+  const uint8_t* any = dp.any + (r / dp.rows) * nct;
   const uint64_t below = (1ull << lane) - 1ull;
   // the column tiles in [c0, c1) that hold a pair, the next one's values
   // loaded before this one's are used (a wave's loads one after the other

@@ -41,3 +41,27 @@ def test_small_batches_and_segments(n, d, kw):
     assert np.array_equal(st["n_cand"].cpu().numpy(), sr["n_cand"])
     assert np.array_equal(st["n_acc"].cpu().numpy(), sr["n_acc"])
     np.testing.assert_allclose(S.cpu().numpy(), R, rtol=1e-9, atol=0)
+
+
+# 16, 64 and 128 queries per workgroup, by the number of queries; rows on and
+# off 16-byte boundaries
+@pytest.mark.parametrize("n,d", [(1500, 132), (1100, 259)])
+def test_batches_of_every_tile_height(n, d):
+    kw = dict(k1=2, k2_constant=6, p_offset=0)
+    X, a = synth.sparse_uniform(n, d, 70 + n), 1e-3
+    sh = orc.lsh_derive(n, a, eps=0.5, **kw)
+    G0, B = synth.e2lsh_randomness(sh["K1"] * sh["J"] * sh["L"] * sh["K"], d, 71)
+    Q = np.concatenate([X[:20], synth.sparse_uniform(25, d, 72)])
+    announce(f"lsh dense tile heights n={n} d={d}")
+    idx = stag.LshIndex(to_dev(X), a, G0=to_dev(G0), b=to_dev(B), seed=3, eps=0.5, **kw)
+    R, sr = orc.lsh_kde(X, Q, a, G0, B, seed=3, return_stats=True, eps=0.5, **kw)
+    first = None
+    for m in (45, 400, 700, 1000, 1400, 2000, 2800, 4000, 5600, 9000, 20000):
+        S, st = idx.query(to_dev(np.resize(Q, (m, d))), stats=True)
+        torch.cuda.synchronize()
+        S, nc, na = (v.cpu().numpy() for v in (S, st["n_cand"], st["n_acc"]))
+        first = S[:45] if first is None else first
+        np.testing.assert_allclose(first, R, rtol=1e-9, atol=0)
+        rows = np.arange(m) % 45
+        assert np.array_equal(S, first[rows]), m
+        assert np.array_equal(nc, sr["n_cand"][rows]) and np.array_equal(na, sr["n_acc"][rows]), m
