@@ -117,9 +117,10 @@ static_assert(kDenseMembers == kDenseSamples * kMetTables && kDenseSamples == 64
 // coordinates, fed by 8 + 4 LDS reads of 16 bytes for two coordinates (one at a
 // time 22.4 ms, two 21.9 for 70,000 rows of 784 against 4,345 members).  Bound
 // by the fp64 rate (a subtraction and a fused product per coordinate and pair,
-// 4.65 cycles each: 14.9 ms of it).  8 x 8 chains per thread spilled.  A pair that the norm bounds of the walk put outside its level
-// needs no distance; a tile without a pair that does is left out whole.
-// 16 NI rows per workgroup (the figures are NI = 8's).
+// 4.65 cycles each: 14.9 ms of it).  8 x 8 chains per thread spilled.  A pair
+// that the norm bounds of the walk put outside its level needs no distance; a
+// tile without a pair that does is left out whole.  16 NI rows per workgroup
+// (the figures are NI = 8's; the rule is in walk_rows).
 template <bool QVEC, int NI>
 __global__ __launch_bounds__(512, 4) void dense_pairs(IndexView ix, LevelConst lc, const float* __restrict__ Q,
                                                    int64_t ldq, int64_t qrow0, int64_t nq,
@@ -308,8 +309,9 @@ __global__ __launch_bounds__(256) void dense_terms(IndexView ix, LevelConst lc, 
   const uint64_t below = (1ull << lane) - 1ull;
   // the column tiles in [c0, c1) that hold a pair, the next one's values
   // loaded before this one's are used (a wave's loads one after the other
-  // were what the terms waited for: 7.2 ms for 70,000 rows, then 6.7; 6.2 with the ranks below from ballots
-  // instead of a loop over the tables met)
+  // were what the terms waited for: 7.2 ms for 70,000 rows, then 6.7; 6.2 with
+  // the ranks below from ballots instead of a loop over the tables met; 5.2
+  // with a wave for every copy)
   struct Piece {
     double D[kDenseTile / 64];
     uint8_t f[kDenseTile / 64];
